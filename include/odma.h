@@ -281,9 +281,11 @@ int odma_append_kv(odma_pool_t* pool, int32_t layer, int32_t n,
  *   q        DEVICE [n][Hq][D] kv_dtype        out  DEVICE [n][Hq][D] out_dtype
  *   offsets  DEVICE int64[n]                   lengths DEVICE int32[n]
  *   block_table DEVICE int32[n][bt_stride] or NULL (contiguous slabs)
- * Launches a plan kernel (unless ODMA_REUSE_PLAN), the split-K attention kernel and
- * the cross-split reduction on `stream`, using the pool's workspace; calls on one
- * pool must therefore not overlap on different streams. */
+ * Plans (unless ODMA_REUSE_PLAN), attends and merges split requests on `stream`, using
+ * the pool's workspace; calls on one pool must therefore not overlap on different
+ * streams.  On the matrix-core kernel all of it is one launch for up to 1024 requests
+ * (beyond that the plan is a launch of its own); the workspace may hold any bytes when
+ * a planning call begins. */
 int odma_decode_attention(odma_pool_t* pool, int32_t layer, int32_t n,
                           const void* q, const int64_t* offsets, const int32_t* lengths,
                           const int32_t* block_table, int32_t bt_stride,
@@ -311,9 +313,8 @@ int odma_decode_step(odma_pool_t* pool, int32_t layer, int32_t n, const void* q,
  *            the array (up to 60 heads).  Beyond a limit: ODMA_INVALID_ARG with the reason in odma_last_error().
  *   flags    0 or ODMA_REUSE_PLAN (honoured only if the previous call on this GPU's array planned for this pool in
  *            its present state; otherwise the call plans again).
- *   Sharing  all pools and all calls on one GPU share that GPU's array, and it keeps the last call's contents; the
- *            plan kernel clears the counters that must start at zero.  Calls that overlap on one GPU (two streams,
- *            two threads) race: serialise them. */
+ *   Sharing  all pools and all calls on one GPU share that GPU's array, and it keeps the last call's contents.  Calls
+ *            that overlap on one GPU (two streams, two threads) race: serialise them. */
 #define ODMA_STATIC_SCRATCH_BYTES   (16u << 20)
 #define ODMA_STATIC_MAX_REQUESTS    1024
 #define ODMA_STATIC_MAX_WORKGROUPS  256

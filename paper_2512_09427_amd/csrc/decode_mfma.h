@@ -35,10 +35,9 @@ namespace {
 
 using odma_plan::StreamEntry;
 using odma_plan::WaveDesc;
-using odma_plan::ReqPos;
-using odma_plan::StreamHeader;
 using odma_plan::ReduceDesc;
 using odma_plan::STREAM_MAX_WG;
+using odma_plan::STREAM_MAX_LAUNCH_WG;
 
 struct StreamArgs {
   const char* k;             // layer base of the K pool
@@ -49,12 +48,14 @@ struct StreamArgs {
   const void* v_new;
   const int32_t* bt;
   int32_t bt_stride;
-  const StreamHeader* hdr;
-  const StreamEntry* entries;
-  const WaveDesc* waves;
-  const ReqPos* req_pos;
-  const ReduceDesc* red;     // [n_workgroups + 1], the last one empty
-  int32_t* arrive;           // [n_workgroups + 1] arrival counters of the in-kernel merge, zero between launches
+  StreamEntry* entries;      // the plan: read by the kernel, or written by it when it plans itself (plan_at >= 0)
+  WaveDesc* waves;
+  ReduceDesc* red;           // [n_workgroups + 1], the last one empty
+  const int32_t* lengths;
+  const int64_t* offsets;    // nullptr when paged
+  int32_t plan_at;           // -1: the plan is in memory; else float offset of the planning area in LDS
+  int32_t q_min, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (StreamShares)
+  unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
   int32_t fuse_reduce;       // 1: the last work-group to finish a cut segment merges it; 0: stream_reduce_kernel does
   float2* part_ml;           // [2 * n_workgroups][Hq]
   float* part_o;             // [2 * n_workgroups][Hq][128]
@@ -77,8 +78,7 @@ constexpr int STREAM_PLAN_LDS = 8192;
 __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
     const int32_t* __restrict__ lengths, const int64_t* __restrict__ offsets, int32_t n, int32_t Hkv,
     int32_t tile_tokens, int32_t n_waves, int32_t wpw, int32_t q_min, int32_t odd_xcd_weight, int32_t late_wave_weight,
-    StreamHeader* hdr, StreamEntry* entries,
-    WaveDesc* waves, ReqPos* req_pos, ReduceDesc* red, int32_t* arrive) {
+    StreamEntry* entries, WaveDesc* waves, ReduceDesc* red) {
   __shared__ int wave_tiles[STREAM_PLAN_THREADS / 64];
   __shared__ int wave_cnt[STREAM_PLAN_THREADS / 64];
   __shared__ int first_lds[STREAM_PLAN_LDS];
@@ -120,7 +120,6 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
   for (int r = r0; r < r1; ++r) {
     const int len = max(lengths[r], 0);
     const int tiles = (len + tile_tokens - 1) / tile_tokens;
-    req_pos[r] = ReqPos{run_tiles * Hkv, tiles};
     if (len > 0) {
       StreamEntry e;
       e.r = r;
@@ -140,7 +139,6 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
   const odma_plan::StreamShares shares = odma_plan::stream_shares(total, n_waves, wpw, q_min, odd_xcd_weight, late_wave_weight);
   const int used = shares.used;
   auto pos_of = [&](int W) -> int { return shares.start(W); };
-  if (tid == 0) *hdr = StreamHeader{total, n_entries, n_waves, used};
   const int n_wg = n_waves / wpw;
   for (int b = tid; b <= n_wg; b += STREAM_PLAN_THREADS) wg_pos[b] = pos_of(b * wpw);   // work-group starts
   __threadfence_block();
@@ -200,7 +198,205 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
       }
     }
     red[b] = rd;
-    arrive[b] = 0;
+  }
+}
+
+// ---------------------------------------------------------------------------------
+// The same plan, made by the attention launch itself: every work-group scans the lengths of the batch (a few KiB that
+// its XCD's L2 holds after the first reader) into an LDS table, finds its waves' ranges there, and leaves the records
+// in memory for later calls that reuse the plan.  The planning launch this replaces is one work-group on an empty chip
+// (6-8 us with three dependent round trips, plus the edge between two launches); the scan delays the first tile's loads
+// by a few microseconds instead.  A planning call, before and after: one request of 1 777 tokens 16.0 -> 12.9 us; 64
+// requests, 46 587 tokens 30.4 -> 26.3 us; 256 requests, 159 203 tokens 69.5 -> 64.2 us.  Beyond STREAM_INLINE_REQ requests
+// a thread would scan more than four of them and the table would pass 20 KiB of LDS: there the launch of its own stays.
+// ---------------------------------------------------------------------------------
+constexpr int STREAM_INLINE_REQ = 1024;
+constexpr int STREAM_INLINE_WG = 512;
+struct InlinePlan {          // LDS table: SoA over the non-empty requests, in batch order
+  int* wave_tot;             // [2 * waves]: tiles, entries per wave
+  int* info;                 // total tiles, entries, waves used
+  int* wg_pos;               // [n_wg + 1] first tile of every work-group
+  int* first;                // [n] first tile of the entry
+  int* r;
+  int* tiles;
+  int* len;
+  int* base_block;
+  int* wave_desc;            // [waves][12]: the waves' descriptors, stored at the end
+  __device__ InlinePlan(float* lds, int at, int wpw, int n_wg, int n) {
+    wave_tot = (int*)lds + at;
+    info = wave_tot + 2 * wpw;
+    wave_desc = info + 4;
+    wg_pos = wave_desc + 12 * wpw;
+    first = wg_pos + n_wg + 1;
+    r = first + n;
+    tiles = r + n;
+    len = tiles + n;
+    base_block = len + n;
+  }
+};
+__host__ __device__ inline int stream_inline_ints(int wpw, int n_wg, int n) { return 14 * wpw + 4 + n_wg + 1 + 5 * n; }
+
+// number of leading elements of the non-decreasing table tab[0 .. n) that are <= x (wave-uniform x)
+__device__ __forceinline__ int count_le(const int* tab, int n, int x) {
+  const int lane = threadIdx.x & 63;
+  int cnt = 0;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const bool le = i0 + lane < n && tab[min(i0 + lane, n - 1)] <= x;
+    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
+    cnt += c;
+    if (c < 64) break;
+  }
+  return cnt;
+}
+
+template <int WPW, int TT>
+__device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlinePlan& pl) {
+  constexpr int T = 64 * WPW, PER = STREAM_INLINE_REQ / T;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = a.n, n_wg = gridDim.x;
+  const int per = (n + T - 1) / T, r0 = min(tid * per, n), r1 = min(r0 + per, n);
+  int ln[PER], base[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const bool in = r0 + k < r1;
+    ln[k] = in ? a.lengths[r0 + k] : 0;
+    base[k] = in && a.offsets ? (int)(a.offsets[r0 + k] / BLK) : 0;
+  }
+  int loc_tiles = 0, loc_cnt = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    ln[k] = max(ln[k], 0);
+    loc_tiles += (ln[k] + TT - 1) / TT;
+    loc_cnt += ln[k] > 0;
+  }
+  int inc_tiles = loc_tiles, inc_cnt = loc_cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int yt = __shfl_up(inc_tiles, o), yc = __shfl_up(inc_cnt, o);
+    if (lane >= o) {
+      inc_tiles += yt;
+      inc_cnt += yc;
+    }
+  }
+  if (lane == 63) {
+    pl.wave_tot[2 * wv] = inc_tiles;
+    pl.wave_tot[2 * wv + 1] = inc_cnt;
+  }
+  __syncthreads();
+  int run_tiles = inc_tiles - loc_tiles, run_cnt = inc_cnt - loc_cnt, sum_tiles = 0, n_entries = 0;
+#pragma unroll
+  for (int i = 0; i < WPW; ++i) {
+    const int t = pl.wave_tot[2 * i], c = pl.wave_tot[2 * i + 1];
+    run_tiles += i < wv ? t : 0;
+    run_cnt += i < wv ? c : 0;
+    sum_tiles += t;
+    n_entries += c;
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (ln[k] > 0) {
+      const int tiles = (ln[k] + TT - 1) / TT;
+      pl.first[run_cnt] = run_tiles * a.Hkv;
+      pl.r[run_cnt] = r0 + k;
+      pl.tiles[run_cnt] = tiles;
+      pl.len[run_cnt] = ln[k];
+      pl.base_block[run_cnt] = base[k];
+      ++run_cnt;
+      run_tiles += tiles;
+    }
+  const int total = sum_tiles * a.Hkv;
+  const odma_plan::StreamShares shares =
+      odma_plan::stream_shares(total, n_wg * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
+  for (int b = tid; b <= n_wg; b += T) pl.wg_pos[b] = shares.start(b * WPW);
+  if (tid == 0) {
+    pl.info[0] = total;
+    pl.info[1] = n_entries;
+    pl.info[2] = shares.used;
+  }
+  __syncthreads();
+}
+
+// this wave's range and its first entry
+template <int WPW>
+__device__ __forceinline__ WaveDesc inline_wave_desc(const StreamArgs& a, const InlinePlan& pl) {
+  const int lane = threadIdx.x & 63, wv = rfl(threadIdx.x >> 6);
+  const int total = rfl(pl.info[0]), n_entries = rfl(pl.info[1]);
+  const odma_plan::StreamShares shares =
+      odma_plan::stream_shares(total, gridDim.x * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
+  const int at = shares.start(blockIdx.x * WPW + wv + (lane & 1));   // even lanes: the start, odd lanes: the end
+  WaveDesc wd;
+  wd.pos_start = __builtin_amdgcn_readlane(at, 0);
+  wd.pos_end = __builtin_amdgcn_readlane(at, 1);
+  wd.entry0 = 0;
+  wd.n_entries = n_entries;
+  wd.r = wd.tiles = wd.first_pos = wd.len = wd.base_block = wd.r_next = wd.pad1 = wd.pad2 = 0;
+  if (wd.pos_start < wd.pos_end) {
+    const int e = count_le(pl.first, n_entries, wd.pos_start) - 1;
+    wd.entry0 = e;
+    wd.r = rfl(pl.r[e]);
+    wd.tiles = rfl(pl.tiles[e]);
+    wd.first_pos = rfl(pl.first[e]);
+    wd.len = rfl(pl.len[e]);
+    wd.base_block = rfl(pl.base_block[e]);
+    wd.r_next = rfl(pl.r[min(e + 1, n_entries - 1)]);
+  }
+  if (lane == 0) {
+    int* o = pl.wave_desc + 12 * wv;
+    o[0] = wd.pos_start;
+    o[1] = wd.pos_end;
+    o[2] = wd.entry0;
+    o[3] = wd.n_entries;
+    o[4] = wd.r;
+    o[5] = wd.tiles;
+    o[6] = wd.first_pos;
+    o[7] = wd.len;
+    o[8] = wd.base_block;
+    o[9] = wd.r_next;
+    o[10] = o[11] = 0;
+  }
+  return wd;
+}
+
+// the segment cut by the boundary in front of work-group b (wave-uniform; the same rule as in stream_plan_kernel)
+template <int WPW>
+__device__ __forceinline__ ReduceDesc inline_cut(const InlinePlan& pl, int b, int n_wg) {
+  ReduceDesc rd = {0, 0, 0, 0};
+  const int total = rfl(pl.info[0]), n_entries = rfl(pl.info[1]), used_wg = rfl(pl.info[2]) / WPW;
+  const int bpos = rfl(pl.wg_pos[b]);
+  if (b > 0 && b < n_wg && bpos < total) {
+    const int e = count_le(pl.first, n_entries, bpos) - 1;
+    const int first = rfl(pl.first[e]), tiles = rfl(pl.tiles[e]);
+    const int g = (bpos - first) / tiles, start = first + g * tiles;
+    if (start < bpos) {
+      rd.b0 = count_le(pl.wg_pos, used_wg, start) - 1;
+      rd.n_parts = count_le(pl.wg_pos, used_wg, start + tiles - 1) - rd.b0;
+      rd.r = rfl(pl.r[e]);
+      rd.g = g;
+    }
+  }
+  return rd;
+}
+
+// the records that stream_plan_kernel would have left, for calls that reuse the plan
+template <int WPW>
+__device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const InlinePlan& pl, const ReduceDesc& rd) {
+  constexpr int T = 64 * WPW;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane < 12) ((int*)&a.waves[blockIdx.x * WPW + wv])[lane] = pl.wave_desc[12 * wv + lane];
+  if (threadIdx.x == 0) {
+    a.red[blockIdx.x] = rd;
+    if (blockIdx.x == gridDim.x - 1) a.red[gridDim.x] = ReduceDesc{0, 0, 0, 0};
+  }
+  const int n_entries = pl.info[1];
+  for (int i = blockIdx.x * T + threadIdx.x; i < n_entries; i += gridDim.x * T) {
+    StreamEntry e;
+    e.r = pl.r[i];
+    e.tiles = pl.tiles[i];
+    e.first_pos = pl.first[i];
+    e.len = pl.len[i];
+    e.base_block = pl.base_block[i];
+    e.pad0 = e.pad1 = e.pad2 = 0;
+    a.entries[i] = e;
   }
 }
 
@@ -234,6 +430,25 @@ __device__ __forceinline__ void store_pair_agent(float* p, float x, float y) {
 __device__ __forceinline__ float2 load_pair_agent(const float* p) {
   const unsigned long long v = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+
+// Arrival counter of a cut segment: {tag, count}, count 0 between launches.  The workspace is the caller's and may hold
+// anything when a launch begins (its first use, another pool's records, a caller who used it as scratch), and the launch
+// that plans itself has no earlier launch to clear counters in.  So the counter carries a tag: an arrival that finds other
+// bytes than the tag replaces them by {tag, 1} (compare-and-swap; whoever loses the swap adds to what the winner left).
+// The usual arrival is one atomic add, as with a counter known to be zero.  The tag is a NaN pattern, which no partial
+// state holds in the word that would have to hold it.  Returns the number of earlier arrivals.
+constexpr unsigned ARRIVE_TAG = 0x7fd15a3cu;
+__device__ __forceinline__ int count_in(unsigned long long* c) {
+  unsigned long long seen = __hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((unsigned)(seen >> 32) == ARRIVE_TAG) return (int)(unsigned)seen;
+  ++seen;                                                  // what the add left behind
+  while ((unsigned)(seen >> 32) != ARRIVE_TAG) {
+    if (__hip_atomic_compare_exchange_strong(c, &seen, ((unsigned long long)ARRIVE_TAG << 32) | 1ull, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return 0;
+  }
+  return (int)(unsigned)__hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Maximum over the four lanes that hold one column (lanes l, l ^ 16, l ^ 32, l ^ 48), in every one of them: two
@@ -313,17 +528,25 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
   constexpr int BLOCK_BYTES = BLK * HD * (FP8 ? 1 : 2);    // one pool block of K (or V)
 
   // the wave's range first: everything else waits for it
-  const WaveDesc wd = a.waves[blockIdx.x * WPW + rfl(wv)];
+  const bool planning = a.plan_at >= 0;
+  const InlinePlan pl(lds, a.plan_at, WPW, gridDim.x, a.n);
+  WaveDesc wd;
   // in-kernel merge: the segments cut at this work-group's two boundaries, requested now so that the
-  // epilogue does not wait for them
+  // epilogue does not wait for them (a launch that plans finds them in LDS while its last stores are under way)
   ReduceDesc rd_cut[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-  if (a.fuse_reduce) {
-    rd_cut[0] = a.red[blockIdx.x];
-    rd_cut[1] = a.red[blockIdx.x + 1];
+  if (planning) {
+    plan_in_block<WPW, TT>(a, pl);
+    wd = inline_wave_desc<WPW>(a, pl);
+  } else {
+    wd = a.waves[blockIdx.x * WPW + rfl(wv)];
+    if (a.fuse_reduce) {
+      rd_cut[0] = a.red[blockIdx.x];
+      rd_cut[1] = a.red[blockIdx.x + 1];
+    }
   }
   // requested early, needed last: whether the request this thread looks after is empty
   const int r_mine = blockIdx.x * (64 * WPW) + threadIdx.x;
-  const int tiles_mine = r_mine < a.n ? a.req_pos[r_mine].tiles : 1;
+  const int len_mine = r_mine < a.n ? a.lengths[r_mine] : 1;
   const int pos_start = rfl(wd.pos_start), pos_end = rfl(wd.pos_end), n_entries = rfl(wd.n_entries);
   const int n_my = pos_end - pos_start;
   TL_STAMP(1);
@@ -339,6 +562,14 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
 
     auto load_window = [&](Window& w, int e_base) {
       const int idx = min(e_base + lane, n_entries - 1);
+      if (planning) {
+        w.r = pl.r[idx];
+        w.tiles = pl.tiles[idx];
+        w.len = pl.len[idx];
+        w.base_block = pl.base_block[idx];
+        w.r_next = pl.r[min(idx + 1, n_entries - 1)];
+        return;
+      }
       const int4 lo = *(const int4*)&a.entries[idx];
       w.r = lo.x;
       w.tiles = lo.y;
@@ -1075,9 +1306,15 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
 #endif
   }
 
+  if (planning) {
+    rd_cut[0] = inline_cut<WPW>(pl, blockIdx.x, gridDim.x);
+    rd_cut[1] = inline_cut<WPW>(pl, blockIdx.x + 1, gridDim.x);
+    store_inline_plan<WPW>(a, pl, rd_cut[0]);
+  }
+
   // Outputs of empty requests are zeros: thread i of the grid looks after request i, i + grid size, ...
   for (int r = r_mine; r < a.n; r += gridDim.x * (64 * WPW)) {
-    if ((r == r_mine ? tiles_mine : a.req_pos[r].tiles) == 0) {
+    if ((r == r_mine ? len_mine : a.lengths[r]) <= 0) {
       const int64_t o = (int64_t)r * a.Hq * HD;
       if (a.out_bf16) {
         uint2v* p = (uint2v*)((unsigned short*)a.out + o);
@@ -1131,10 +1368,9 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     const bool in = second ? (rdb.n_parts > 0 && rdb.b0 == b) : rda.n_parts > 0;
     int last = 0;
     if (in) {
-      const int old = __hip_atomic_fetch_add(a.arrive + owner, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = old == n_parts - 1;
-      // the last arrival leaves the counter at zero for the next launch
-      if (last) __hip_atomic_store(a.arrive + owner, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = count_in(a.arrive + owner) == n_parts - 1;
+      // the last arrival leaves the count at zero for the next launch
+      if (last) __hip_atomic_store(a.arrive + owner, (unsigned long long)ARRIVE_TAG << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     merges_here[threadIdx.x] = last;
   }

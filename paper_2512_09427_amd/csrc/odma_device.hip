@@ -377,7 +377,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     while (qs > 1 && stream_lds_bytes(G, wpw, qs, aq) > 144 * 1024) --qs;
     if (stream_lds_bytes(G, wpw, qs, aq) > 160 * 1024) wpw = 4;
     int n_wg = pool->n_cu * wpc / wpw;
-    if (n_wg > STREAM_MAX_WG) n_wg = STREAM_MAX_WG;
+    if (n_wg > STREAM_MAX_LAUNCH_WG) n_wg = STREAM_MAX_LAUNCH_WG;
     if (n_wg < 1) n_wg = 1;
     if (scratch && n_wg > scratch->n_wg_cap) {
       odma::set_error(std::string(where) + ": the launch shape needs more work-groups than the static scratch holds");
@@ -392,12 +392,12 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     a.v_new = v_new;
     a.bt = block_table;
     a.bt_stride = bt_stride;
-    a.hdr = (const StreamHeader*)(ws + wl.header);
-    a.entries = (const StreamEntry*)(ws + wl.items);
-    a.waves = (const WaveDesc*)(ws + wl.waves);
-    a.req_pos = (const ReqPos*)(ws + wl.req_info);
-    a.red = (const ReduceDesc*)(ws + wl.red);
-    a.arrive = (int32_t*)(ws + wl.arrive);
+    a.entries = (StreamEntry*)(ws + wl.items);
+    a.waves = (WaveDesc*)(ws + wl.waves);
+    a.red = (ReduceDesc*)(ws + wl.red);
+    a.arrive = (unsigned long long*)(ws + wl.arrive);
+    a.lengths = lengths;
+    a.offsets = block_table ? nullptr : offsets;
     a.fuse_reduce = pool->fuse_reduce && !(flags & ODMA_SKIP_REDUCE);
     a.part_ml = (float2*)(ws + wl.part_ml);
     a.part_o = (float*)(ws + wl.part_o);
@@ -434,16 +434,24 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     const bool reuse = (flags & ODMA_REUSE_PLAN) && was.layout_gen == now.layout_gen && was.owner == now.owner && was.n == now.n &&
                        was.paged == now.paged && was.n_wg == now.n_wg && was.wpw == now.wpw && was.q_min == now.q_min &&
                        was.tile_tokens == now.tile_tokens && was.odd_w == now.odd_w && was.late_w == now.late_w;
+    // A call that plans does so inside the attention launch while the batch's table is small (STREAM_INLINE_REQ) and
+    // fits beside the wave's queues; larger batches take a planning launch of their own.
+    size_t lds_bytes = stream_lds_bytes(G, wpw, qs, aq);
+    a.plan_at = -1;
+    a.q_min = q_min;
+    a.odd_xcd_weight = now.odd_w;
+    a.late_wave_weight = now.late_w;
     if (!reuse) {
-      hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(STREAM_PLAN_THREADS), 0, s, lengths,
-                         block_table ? nullptr : offsets, n, c.n_kv_heads, tile_tokens, n_wg * wpw, wpw, q_min,
-                         now.odd_w, now.late_w, (StreamHeader*)(ws + wl.header),
-                         (StreamEntry*)(ws + wl.items), (WaveDesc*)(ws + wl.waves),
-                         (ReqPos*)(ws + wl.req_info), (ReduceDesc*)(ws + wl.red),
-                         (int32_t*)(ws + wl.arrive));
+      const size_t plan_bytes = (size_t)stream_inline_ints(wpw, n_wg, n) * 4;
+      if (n <= STREAM_INLINE_REQ && n_wg <= STREAM_INLINE_WG && lds_bytes + plan_bytes <= 160 * 1024) {
+        a.plan_at = (int32_t)(lds_bytes / 4);
+        lds_bytes += plan_bytes;
+      } else {
+        hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(STREAM_PLAN_THREADS), 0, s, lengths, a.offsets, n, c.n_kv_heads,
+                           tile_tokens, n_wg * wpw, wpw, q_min, now.odd_w, now.late_w, a.entries, a.waves, a.red);
+      }
       stamp = now;
     }
-    const size_t lds_bytes = stream_lds_bytes(G, wpw, qs, aq);
     const int nbuf = pool->pipeline_depth;
     const int fmt = d64 ? STREAM_BF16_D64 : fp8 ? STREAM_FP8_D128 : STREAM_BF16_D128;
     hipError_t e = launch_stream_kernel(fmt, fused, block_table != nullptr, nbuf, wpw, n_wg, lds_bytes, s, a);

@@ -39,18 +39,13 @@ struct WaveDesc {            // one wave's tile range, with its first entry inli
   int32_t r, tiles, first_pos, len;
   int32_t base_block, r_next, pad1, pad2;   // r_next: request of entry0 + 1
 };
-struct ReqPos {
-  int32_t first_pos, tiles;
-};
-struct StreamHeader {
-  int32_t total_tiles, n_entries, n_waves, waves_used;
-};
 struct ReduceDesc {          // the segment cut by the boundary in front of work-group b
   int32_t n_parts;           // work-groups the segment spans (0: no segment is cut here)
   int32_t r, g, b0;          // segment and the first work-group it touches; boundary b0 + 1 owns its merge
 };
 
 constexpr int STREAM_MAX_WG = 4096;  // work-groups the pool workspace is sized for
+constexpr int STREAM_MAX_LAUNCH_WG = 2048;   // most work-groups of one launch: eight waves per SIMD of 256 compute units
 
 // Shares of the tile stream.  Wave W of the `used` waves gets the tiles [start(W), start(W + 1)).
 //   * Fewer tiles than waves: the empty ranges are all on the LEFT (wave W gets tile total - (used - W)), never
@@ -79,6 +74,10 @@ struct StreamShares {
   ODMA_HD int start(int W) const {
     if (W >= used) return total;
     if (total < used) return total - (used - W) > 0 ? total - (used - W) : 0;
+    // Equal weights: floor(total * W / used).  The product is below 2^46 and exact in a double, and a quotient that is
+    // not whole lies at least 1 / used > 2^-15 under the next whole number, which rounding to 53 bits cannot reach: the
+    // division (which every wave waits for when it plans) need not be a 64-bit integer one.
+    if (w_even == w_odd && s_early == s_late) return (int)((double)((long long)total * W) / (double)used);
     return (int)((long long)total * cum(W) / cum_all);
   }
 };
@@ -107,17 +106,18 @@ ODMA_HD inline StreamShares stream_shares(int total, int n_waves, int wpw, int q
 // Byte offsets of the regions of a tile-stream workspace sized for max_requests requests, n_wg_cap attention
 // work-groups and n_q_heads query heads (partial states keep 128 channels per head).
 struct StreamLayout {
-  size_t header, req_info, items, waves, red, arrive, part_ml, part_o, end;
+  size_t header, req_info, items, waves, red, arrive, part_ml, part_o, end;   // (header and req_info: unused, kept so that the size stays)
 };
 ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int64_t n_wg_cap, int64_t n_q_heads) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   StreamLayout w;
   w.header = off;   off += 256;
-  w.req_info = off; off += up((size_t)max_requests * sizeof(ReqPos));
+  w.req_info = off; off += up((size_t)max_requests * 8);
   w.items = off;    off += up((size_t)max_requests * sizeof(StreamEntry));
   w.waves = off;    off += up((size_t)n_wg_cap * 8 * sizeof(WaveDesc));
   w.red = off;      off += up((size_t)(n_wg_cap + 1) * sizeof(ReduceDesc));
-  w.arrive = off;   off += up((size_t)(n_wg_cap + 1) * sizeof(int32_t));
+  w.arrive = off;   // one 64-bit counter per boundary of a launch
+  off += up((size_t)((n_wg_cap < STREAM_MAX_LAUNCH_WG ? n_wg_cap : STREAM_MAX_LAUNCH_WG) + 1) * sizeof(int64_t));
   w.part_ml = off;  off += up((size_t)2 * n_wg_cap * n_q_heads * 2 * sizeof(float));
   w.part_o = off;   off += up((size_t)2 * n_wg_cap * n_q_heads * 128 * sizeof(float));
   w.end = off;
