@@ -5,15 +5,18 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libodma.so")
 # development aids, built beside the library: a timing build whose waves stamp a clock (stream_timeline.py reads it;
-# only the bf16 / head_dim 128 kernels, no prefill) and a stand-alone read probe in the attention kernel's launch shape
+# only the bf16 / head_dim 128 decode kernels) and a stand-alone read probe in the attention kernel's launch shape
 TIMELINE_LIB = os.path.join(HERE, "libodma_timeline.so")
 DEPTH_PROBE = os.path.join(HERE, "read_depth_probe")
+# translation units with kernels (csrc/<name>.hip), the one that the timing build replaces first
+DEVICE_UNITS = ["odma_device", "odma_prefill"]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
@@ -38,14 +41,18 @@ def build(verbose: bool = True) -> str:
     obj_dir = os.path.join(HERE, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     host_o = os.path.join(obj_dir, "odma_host.o")
-    dev_o = os.path.join(obj_dir, "odma_device.o")
     _run([cxx, *HOST_FLAGS, *inc, "-c", os.path.join(CSRC, "odma_host.cpp"), "-o", host_o])
-    _run([hipcc, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, "odma_device.hip"), "-o", dev_o])
-    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", host_o, dev_o, "-pthread", "-o", LIB])
-    tl_o = os.path.join(obj_dir, "odma_device_timeline.o")
-    _run([hipcc, *HIP_FLAGS, "-DODMA_DEV_TIMELINE", "-DODMA_DEV_MINIMAL_VARIANTS", *inc, "-c",
-          os.path.join(CSRC, "odma_device.hip"), "-o", tl_o])
-    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", host_o, tl_o, "-pthread", "-o", TIMELINE_LIB])
+    # the device units are independent: compiled side by side
+    units = [(name, name, []) for name in DEVICE_UNITS]
+    units.append(("odma_device", "odma_device_timeline", ["-DODMA_DEV_TIMELINE", "-DODMA_DEV_MINIMAL_VARIANTS"]))
+    cmds = [[hipcc, *HIP_FLAGS, *defs, *inc, "-c", os.path.join(CSRC, src + ".hip"), "-o", os.path.join(obj_dir, obj + ".o")]
+            for src, obj, defs in units]
+    with ThreadPoolExecutor(max_workers=len(cmds)) as ex:
+        list(ex.map(_run, cmds))
+    objs = [os.path.join(obj_dir, name + ".o") for name in DEVICE_UNITS]
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", host_o, *objs, "-pthread", "-o", LIB])
+    timeline = [os.path.join(obj_dir, "odma_device_timeline.o")] + objs[1:]
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", host_o, *timeline, "-pthread", "-o", TIMELINE_LIB])
     _run([hipcc, *[f for f in HIP_FLAGS if f != "-fPIC"], os.path.join(CSRC, "read_depth_probe.hip"), "-o", DEPTH_PROBE])
     return LIB
 

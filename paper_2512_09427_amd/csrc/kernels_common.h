@@ -52,6 +52,13 @@ struct DecodeArgs {
   int32_t out_bf16;
 };
 
+struct RowArgs {
+  char* k;               // layer base
+  char* v;
+  int64_t head_stride;   // bytes
+  int32_t Hkv, D;
+};
+
 __device__ __forceinline__ int rfl(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 __device__ __forceinline__ float wave_max(float x) {

@@ -8,13 +8,6 @@ namespace {
 // ---------------------------------------------------------------------------------
 // append / export: row-major rows <-> pool block format
 // ---------------------------------------------------------------------------------
-struct RowArgs {
-  char* k;               // layer base
-  char* v;
-  int64_t head_stride;   // bytes
-  int32_t Hkv, D;
-};
-
 // element index inside a block
 __device__ __forceinline__ int k_index(int t, int d, int X) { return ((d / X) * BLK + t) * X + d % X; }
 __device__ __forceinline__ int v_index(int t, int d) {

@@ -1,0 +1,81 @@
+// Prompt (chunk) attention entry point of libodma for gfx950: launches the kernels in prefill_mfma.h.
+#include <hip/hip_runtime.h>
+
+#include <string>
+
+#include "odma_internal.h"
+#include "kernels_common.h"
+#include "prefill_mfma.h"
+#include "device_common.h"
+
+extern "C" {
+
+int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const void* q, int64_t total_q,
+                           const int64_t* q_start, const int32_t* n_q, const int64_t* offsets, const int32_t* lengths,
+                           const int32_t* block_table, int32_t bt_stride, void* out, void* stream) {
+  const char* where = "odma_prefill_attention";
+  int rc = device_ready(pool, where);
+  if (rc) return rc;
+  const odma_pool_config_t& c = pool->cfg;
+  if (pool->decode_kernel != ODMA_KERNEL_MFMA || c.head_dim != 128) {
+    odma::set_error(std::string(where) + ": needs a bf16 or fp8 pool with head_dim 128 (the matrix-core path)");
+    return ODMA_INVALID_ARG;
+  }
+  if (n == 0 || total_q == 0) return ODMA_OK;
+  if (!c.workspace) {
+    odma::set_error(std::string(where) + ": pool has no workspace");
+    return ODMA_INVALID_ARG;
+  }
+  if (layer < 0 || layer >= c.n_layers || n < 0 || n > c.max_requests || total_q < 0 || !q || !q_start || !n_q ||
+      !lengths || !out || (!block_table && !offsets) || (block_table && bt_stride <= 0)) {
+    odma::set_error(std::string(where) + ": invalid argument");
+    return ODMA_INVALID_ARG;
+  }
+  hipStream_t s = (hipStream_t)stream;
+  char* ws = (char*)c.workspace;
+  const RowArgs ra = row_args(pool, layer);
+  PrefillArgs a;
+  a.k = ra.k;
+  a.v = ra.v;
+  a.q = (const unsigned short*)q;
+  a.out = out;
+  a.q_start = q_start;
+  a.n_q = n_q;
+  a.offsets = offsets;
+  a.lengths = lengths;
+  a.bt = block_table;
+  a.bt_stride = bt_stride;
+  a.hdr = (PrefillHeader*)(ws + pool->ws.prefill);
+  a.item_start = (const int32_t*)(ws + pool->ws.prefill + 256);
+  a.n = n;
+  a.Hq = c.n_q_heads;
+  a.Hkv = c.n_kv_heads;
+  a.G = c.n_q_heads / c.n_kv_heads;
+  a.total_q = total_q;
+  a.head_stride = ra.head_stride;
+  const bool fp8 = pool->elem_bytes == 1;
+  a.scale_log2 = c.sm_scale * 1.4426950408889634f * (fp8 ? c.k_scale : 1.0f);
+  a.out_scale = fp8 ? c.v_scale : 1.0f;
+  a.out_bf16 = c.out_dtype == ODMA_BF16;
+  // column tiles per wave: 2 (128-column items, two work-groups per CU whose LDS and matrix phases overlap)
+  // measured faster than 4 (256-column items, one work-group per CU) on every prompt mix tried
+  const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
+  hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
+                     c.n_kv_heads, a.G, 64 * ct, a.hdr, (int32_t*)(ws + pool->ws.prefill + 256));
+  const dim3 grid(pool->n_cu * (ct == 2 ? 2 : 1));
+  switch ((fp8 ? 4 : 0) + (ct == 2 ? 2 : 0) + (block_table ? 1 : 0)) {
+    case 0: hipLaunchKernelGGL((prefill_kernel<false, 4, false>), grid, dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((prefill_kernel<true, 4, false>), grid, dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((prefill_kernel<false, 2, false>), grid, dim3(256), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((prefill_kernel<true, 2, false>), grid, dim3(256), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((prefill_kernel<false, 4, true>), grid, dim3(256), 0, s, a); break;
+    case 5: hipLaunchKernelGGL((prefill_kernel<true, 4, true>), grid, dim3(256), 0, s, a); break;
+    case 6: hipLaunchKernelGGL((prefill_kernel<false, 2, true>), grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((prefill_kernel<true, 2, true>), grid, dim3(256), 0, s, a); break;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(where, e);
+  return ODMA_OK;
+}
+
+}  // extern "C"

@@ -141,7 +141,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // loader role of this wave: waves 0, 1 bring the K tiles of a pair, waves 2, 3 the V tiles
   const bool loads_v = wv >= 2;
   const int which = wv & 1;                                            // first or second tile of the pair
-  const char* src_base = (loads_v ? a.v : a.k) + lane * 16;
+  const char* src_base = loads_v ? a.v : a.k;
+  const unsigned lane16 = lane * 16;
 
   // Work queue: one counter in memory, which answers about 14 M requests a second on this part -- with
   // thousands of small items that alone would bound the kernel.  A work-group therefore takes a run of
@@ -229,32 +230,33 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     const int64_t plane = (int64_t)g * a.head_stride;
     const const_i32* bt_row = as_constant(PAGED ? a.bt + (int64_t)r * a.bt_stride : nullptr);
     const int64_t base_block = PAGED ? 0 : a.offsets[r] / BLK;
-    // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  A
-    // second tile that does not exist is written as zeros; V slots at or past `len` (stale bytes, maybe
-    // NaN patterns) are zeroed too, so that a weight of 0 really removes them.  (K needs nothing: scores
-    // of tokens past a column's limit are replaced, not multiplied.)
-    auto tile_of = [&](int pr) { return 2 * pr + which; };
+    // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  Pairs past the
+    // end and a second tile that does not exist re-read the last tile: every step issues its loads, so the waits on
+    // them stay static counts (with conditional loads the wait before a stage was written covered the loads issued a
+    // moment ago as well, and the whole memory latency was exposed in every pair).  Tokens of such a tile lie at or past
+    // every column's limit, so their weights are zero.  V slots at or past `len` (stale bytes, maybe NaN patterns) are
+    // zeroed, so that a weight of 0 really removes them.  (K needs nothing: scores of tokens past a column's limit are
+    // replaced, not multiplied.)
+    auto tile_of = [&](int pr) { return min(2 * pr + which, n_tiles - 1); };
     int blk_next = 0;
     auto lookup = [&](int pr) {
-      if (PAGED) blk_next = bt_row[min(tile_of(pr), n_tiles - 1)];
+      if (PAGED) blk_next = bt_row[tile_of(pr)];
     };
     auto issue = [&](uint4v (&rg)[4], int pr) {
-      const int t = min(tile_of(pr), n_tiles - 1);
-      const int64_t off = plane + (PAGED ? (int64_t)blk_next : base_block + t) * TILE_BYTES;
+      const char* src = src_base + plane + (PAGED ? (int64_t)blk_next : base_block + tile_of(pr)) * TILE_BYTES;
 #pragma unroll
-      for (int s = 0; s < LOADS; ++s) rg[s] = *(const uint4v*)(src_base + off + s * 1024);
+      for (int s = 0; s < LOADS; ++s) rg[s] = *(const uint4v*)(src + s * 1024 + lane16);
     };
     auto write_stage = [&](uint4v (&rg)[4], int pr) {
       char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES;
       const int t = tile_of(pr);
-      const bool exists = t < n_tiles;
       if (FP8) {
         if (!loads_v) {
           // lane (t16, q) holds, per 64-channel half s, channels 64 s + 8 q .. +7 and 64 s + 32 + 8 q .. +7 of
           // token t16: two bf16 pieces, for channel octets 8 s + q and 8 s + 4 + q
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
-            const uint4v w = exists ? rg[s] : uint4v{0u, 0u, 0u, 0u};
+            const uint4v w = rg[s];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
               const uint4v o = {fp8x2_to_bf16x2<false>(w[2 * h]), fp8x2_to_bf16x2<true>(w[2 * h]),
@@ -265,13 +267,14 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         } else {
           // lane (c, q) holds, per half s, one word per channel group 4 s + i: channel c of tokens 4q .. 4q+3
           const int tok0 = t * BLK + 4 * g4;
+          const bool ragged = t * BLK + BLK > len;                      // (the same for the whole wave)
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
-            const uint4v w = exists ? rg[s] : uint4v{0u, 0u, 0u, 0u};
+            const uint4v w = rg[s];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               uint2v o = {fp8x2_to_bf16x2<false>(w[i]), fp8x2_to_bf16x2<true>(w[i])};
-              if (tok0 + 4 > len) {                                     // some of the four tokens are not there
+              if (ragged) {                                             // some of the tile's tokens are not there
                 if (tok0 + 0 >= len) o[0] &= 0xffff0000u;
                 if (tok0 + 1 >= len) o[0] &= 0x0000ffffu;
                 if (tok0 + 2 >= len) o[1] &= 0xffff0000u;
@@ -283,26 +286,27 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         }
       } else if (!loads_v) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-          *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = exists ? rg[s] : uint4v{0u, 0u, 0u, 0u};
+        for (int s = 0; s < 4; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
       } else {
         // lane (c, q) holds, per piece s, tokens 4q .. 4q+3 of channel groups 2s (low 8 bytes) and 2s+1
-        const int tok0 = t * BLK + 4 * g4;
+        if (t * BLK + BLK > len) {                                      // some of the tile's tokens are not there
+          const int tok0 = t * BLK + 4 * g4;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (tok0 + i >= len) {
+              const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+              for (int s = 0; s < 4; ++s) {
+                rg[s][i >> 1] &= keep;
+                rg[s][2 + (i >> 1)] &= keep;
+              }
+            }
+        }
+        char* dst = st + 8192 + lane * 16 + which * 8;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          uint4v w = exists ? rg[s] : uint4v{0u, 0u, 0u, 0u};
-          if (tok0 + 4 > len) {                                       // some of the four tokens are not there
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (tok0 + i >= len) {
-                const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
-                w[i >> 1] &= keep;
-                w[2 + (i >> 1)] &= keep;
-              }
-          }
-          char* dst = st + 8192 + lane * 16 + which * 8;
-          *(uint2v*)(dst + (2 * s) * 1024) = uint2v{w[0], w[1]};
-          *(uint2v*)(dst + (2 * s + 1) * 1024) = uint2v{w[2], w[3]};
+          *(uint2v*)(dst + (2 * s) * 1024) = uint2v{rg[s][0], rg[s][1]};
+          *(uint2v*)(dst + (2 * s + 1) * 1024) = uint2v{rg[s][2], rg[s][3]};
         }
       }
     };
@@ -444,27 +448,22 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       lookup(0);
       issue(ra, 0);
       lookup(1);
-      if (n_pairs > 1) issue(rb, 1);
+      issue(rb, 1);
       lookup(2);
       write_stage(ra, 0);
       __syncthreads();
-      for (int pr = 0; pr < n_pairs; pr += 2) {
-        if (pr + 2 < n_pairs) {
-          issue(ra, pr + 2);
-          lookup(pr + 3);
-        }
+      auto step = [&](uint4v (&near)[4], uint4v (&far)[4], int pr) {     // near: pair pr + 1, far: free for pair pr + 2
+        issue(far, pr + 2);
+        lookup(pr + 3);
         if (active) compute(pr);
-        if (pr + 1 < n_pairs) write_stage(rb, pr + 1);
+        write_stage(near, pr + 1);
         __syncthreads();
-        if (pr + 1 < n_pairs) {
-          if (pr + 3 < n_pairs) {
-            issue(rb, pr + 3);
-            lookup(pr + 4);
-          }
-          if (active) compute(pr + 1);
-          if (pr + 2 < n_pairs) write_stage(ra, pr + 2);
-          __syncthreads();
-        }
+      };
+      for (int pr = 0;;) {
+        step(rb, ra, pr);
+        if (++pr == n_pairs) break;
+        step(ra, rb, pr);
+        if (++pr == n_pairs) break;
       }
     };
     // each lane summed the weights of its own tokens: a column's total is the sum over g4
