@@ -46,7 +46,7 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   a.bt = block_table;
   a.bt_stride = bt_stride;
   a.hdr = (PrefillHeader*)(ws + pool->ws.prefill);
-  a.item_start = (const int32_t*)(ws + pool->ws.prefill + 256);
+  a.item_start = (int32_t*)(ws + pool->ws.prefill + 256);
   a.n = n;
   a.Hq = c.n_q_heads;
   a.Hkv = c.n_kv_heads;
@@ -61,7 +61,7 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // measured faster than 4 (256-column items, one work-group per CU) on every prompt mix tried
   const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
   hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
-                     c.n_kv_heads, a.G, 64 * ct, a.hdr, (int32_t*)(ws + pool->ws.prefill + 256));
+                     c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);
   const dim3 grid(pool->n_cu * (ct == 2 ? 2 : 1));
   switch ((fp8 ? 4 : 0) + (ct == 2 ? 2 : 0) + (block_table ? 1 : 0)) {
     case 0: hipLaunchKernelGGL((prefill_kernel<false, 4, false>), grid, dim3(256), 0, s, a); break;

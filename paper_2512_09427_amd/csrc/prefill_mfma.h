@@ -11,8 +11,12 @@
 // registers so that two work-groups share a CU and one's LDS reads and item start run under the other's
 // matrix instructions: +12 to +25 % on every prompt mix measured, and the default.
 //
-// Items are handed out through an atomic counter (persistent work-groups, heaviest columns of a
-// request first), because causal items differ in length by construction.
+// The items of a call, ordered by (request, KV head, column block from the heaviest down), are cut into eight queues
+// of equal cost, one per XCD (cost: the 32-token K/V pairs an item streams plus a constant for its start and end), and
+// handed out through atomic counters to persistent work-groups: causal items differ in length by construction.  The
+// work-groups of an XCD then read the same one or two K/V heads out of their L2 -- with one queue for the chip every XCD
+// fetched every K/V byte (16 x 4096 tokens: 60 M L2 misses of 128 bytes, 12 M with eight queues).  A work-group whose
+// queue is empty goes on with the fullest other one.
 #pragma once
 
 #include "kernels_common.h"
@@ -21,11 +25,13 @@ namespace {
 
 constexpr int PREFILL_PLAN_THREADS = 256;
 
+constexpr int PREFILL_XCDS = 8;
+constexpr double PREFILL_ITEM_COST = 5.0;   // start and end of an item, in K/V pairs
+
 struct PrefillHeader {
-  int32_t n_items;
-  int32_t next_item;       // work queue cursor, reset by the plan kernel
-  int32_t avg_pairs;       // mean number of 32-token K/V pairs an item streams (estimate of the plan)
-  int32_t pad1;
+  int32_t bound[PREFILL_XCDS + 1];          // items [bound[x], bound[x + 1]) are queue x
+  int32_t next[PREFILL_XCDS];               // queue cursors, reset by the plan kernel
+  int32_t avg_pairs;                        // mean cost of an item
 };
 
 struct PrefillArgs {
@@ -40,7 +46,7 @@ struct PrefillArgs {
   const int32_t* bt;
   int32_t bt_stride;
   PrefillHeader* hdr;
-  const int32_t* item_start; // [n + 1] exclusive prefix of items per request
+  int32_t* item_start;       // [n + 1] exclusive prefix of items per request
   int32_t n, Hq, Hkv, G;
   int64_t total_q;           // rows of q and out: rows at or past it are never touched
   int64_t head_stride;
@@ -60,54 +66,98 @@ __device__ __forceinline__ int prefill_rows(const int32_t* n_q, const int32_t* l
   return rows > 0 ? (int)rows : 0;
 }
 
-// one work-group: items per request -> exclusive prefix, total, queue cursor
+// Cost of the cb cheapest column blocks of one (request, KV head): block i streams about
+// (first_pos + (i + 1/2) * cols_item / G) / 32 pairs.  It only balances: any rule would give the same results.
+struct PrefillCost {
+  double base, slope;
+  __device__ __forceinline__ PrefillCost(int first_pos, int cols_item, int G)
+      : base(first_pos * (1.0 / 32) + PREFILL_ITEM_COST), slope((double)cols_item / (64.0 * G)) {}
+  __device__ __forceinline__ double upto(int cb) const { return cb * (base + cb * slope); }
+  __device__ __forceinline__ int block_at(double c) const {              // nearest block whose start costs c
+    return (int)(0.5 + (sqrt(base * base + 4.0 * slope * c) - base) / (2.0 * slope));
+  }
+};
+__device__ __forceinline__ int prefill_blocks(int rows, int G, int cols_item) {
+  return (int)(((int64_t)rows * G + cols_item - 1) / cols_item);
+}
+
+// one work-group: exclusive prefix of items per request, and the eight queues of equal cost
 __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(const int32_t* __restrict__ n_q,
                                                                            const int32_t* __restrict__ lengths,
                                                                            const int64_t* __restrict__ q_start,
                                                                            int64_t total_q, int32_t n, int32_t Hkv, int32_t G,
                                                                            int32_t cols_item, PrefillHeader* hdr,
                                                                            int32_t* item_start) {
-  __shared__ int part[PREFILL_PLAN_THREADS];
-  const int tid = threadIdx.x;
+  __shared__ double part_cost[PREFILL_PLAN_THREADS / 64];
+  __shared__ int part_items[PREFILL_PLAN_THREADS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (n + PREFILL_PLAN_THREADS - 1) / PREFILL_PLAN_THREADS;
   const int r0 = min(tid * per, n), r1 = min(r0 + per, n);
-  auto items_of = [&](int r) {
-    const int64_t cols = (int64_t)prefill_rows(n_q, lengths, q_start, total_q, r) * G;
-    return (int)((cols + cols_item - 1) / cols_item) * Hkv;
-  };
-  int sum = 0;
-  long long work = 0;                                      // pairs streamed by this thread's requests, all items together
-  for (int r = r0; r < r1; ++r) {
-    const int items = items_of(r);
-    sum += items;
-    // an item of request r sees on average len - rows / 2 keys
+  double cost = 0;
+  int items = 0;
+  auto add = [&](int r, auto&& at) {                        // at(cost and items before r, blocks of r, its cost rule)
     const int rows = prefill_rows(n_q, lengths, q_start, total_q, r);
-    work += (long long)items * ((lengths[r] - rows / 2 + 31) / 32);
+    const int nb = prefill_blocks(rows, G, cols_item);
+    const PrefillCost pc(lengths[r] - rows, cols_item, G);
+    at(nb, pc);
+    cost += Hkv * pc.upto(nb);
+    items += Hkv * nb;
+  };
+  for (int r = r0; r < r1; ++r) add(r, [](int, const PrefillCost&) {});
+  double inc_cost = cost;
+  int inc_items = items;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double yc = __shfl_up(inc_cost, o);
+    const int yi = __shfl_up(inc_items, o);
+    if (lane >= o) {
+      inc_cost += yc;
+      inc_items += yi;
+    }
   }
-  __shared__ long long work_all;
-  if (tid == 0) work_all = 0;
-  __syncthreads();
-  atomicAdd((unsigned long long*)&work_all, (unsigned long long)work);
-  part[tid] = sum;
-  __syncthreads();
-  for (int o = 1; o < PREFILL_PLAN_THREADS; o <<= 1) {
-    const int add = tid >= o ? part[tid - o] : 0;
-    __syncthreads();
-    part[tid] += add;
-    __syncthreads();
+  if (lane == 63) {
+    part_cost[wv] = inc_cost;
+    part_items[wv] = inc_items;
   }
-  int run = part[tid] - sum;
+  __syncthreads();
+  double all_cost = 0;
+  int all_items = 0;
+  cost = inc_cost - cost;
+  items = inc_items - items;
+  for (int i = 0; i < PREFILL_PLAN_THREADS / 64; ++i) {
+    if (i < wv) {
+      cost += part_cost[i];
+      items += part_items[i];
+    }
+    all_cost += part_cost[i];
+    all_items += part_items[i];
+  }
+  if (tid == 0) {
+    hdr->bound[0] = hdr->next[0] = 0;
+    hdr->bound[PREFILL_XCDS] = item_start[n] = all_items;
+    hdr->avg_pairs = (int)(all_cost / max(all_items, 1));
+  }
+  // boundary x lies at cost all_cost * x / 8, inside the request whose cost range holds it (the first request with items
+  // also takes boundaries that rounding leaves before it, the last one those behind it)
   for (int r = r0; r < r1; ++r) {
-    item_start[r] = run;
-    run += items_of(r);
+    item_start[r] = items;
+    const double before = cost;
+    const int first = items;
+    add(r, [&](int nb, const PrefillCost& pc) {
+      if (nb == 0) return;
+      const double per_head = pc.upto(nb);
+      for (int x = 1; x < PREFILL_XCDS; ++x) {
+        const double t = all_cost * x / PREFILL_XCDS - before;
+        const bool here = (t >= 0 || first == 0) && (t < Hkv * per_head || first + Hkv * nb == all_items);
+        if (!here) continue;
+        const int g = min(max((int)(t / per_head), 0), Hkv - 1);
+        // blocks run from the last one (the dearest) down: those that cost t come after those that cost the rest
+        const int left = min(max(pc.block_at(fmax(per_head - (t - g * per_head), 0.0)), 0), nb);
+        hdr->bound[x] = hdr->next[x] = first + g * nb + nb - left;
+      }
+    });
   }
-  if (tid == PREFILL_PLAN_THREADS - 1) {
-    item_start[n] = part[tid];
-    hdr->n_items = part[tid];
-    hdr->next_item = 0;
-    hdr->avg_pairs = (int)(work_all / max(part[tid], 1));
-    hdr->pad1 = 0;
-  }
+  if (all_items == 0 && tid < PREFILL_XCDS) hdr->bound[tid] = hdr->next[tid] = 0;
 }
 
 // LDS stage of one pair of tiles (32 tokens): K of both tiles as loaded (the 16x16x32 A operands of
@@ -116,6 +166,8 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
 // the second tile in one 16-byte piece.
 constexpr int PREFILL_STAGE_BYTES = 16384;
 constexpr int PREFILL_STAGES = 2;
+constexpr int PREFILL_LDS_REQ = 1024;        // requests whose item prefix a work-group keeps in LDS
+typedef const int64_t __attribute__((address_space(4))) const_i64;
 
 // two E4M3 bytes of a word -> two bf16 bit patterns in one word (exact: E4M3 values are bf16 values)
 template <bool HIGH_HALF>
@@ -133,7 +185,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   constexpr int LOADS = TILE_BYTES / 1024;                         // 16-byte loads per lane and tile
   constexpr int COLS_WAVE = 16 * CT, COLS_ITEM = 4 * COLS_WAVE;     // CT column tiles per wave, four waves per item
   __shared__ __attribute__((aligned(16))) char stage_mem[PREFILL_STAGES * PREFILL_STAGE_BYTES];
-  __shared__ int item_slot, redo_slot;
+  __shared__ int run_slot[2];
+  __shared__ int item_start_lds[PREFILL_LDS_REQ];
   const int lane = threadIdx.x & 63, wv = rfl(threadIdx.x >> 6);
   const int col16 = lane & 15, g4 = lane >> 4;
   const int G = a.G;
@@ -144,58 +197,88 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   const char* src_base = loads_v ? a.v : a.k;
   const unsigned lane16 = lane * 16;
 
-  // Work queue: one counter in memory, which answers about 14 M requests a second on this part -- with
-  // thousands of small items that alone would bound the kernel.  A work-group therefore takes a run of
-  // consecutive items per request, long enough to stream about 64 K/V pairs (some 40 us) but never more
-  // than an eighth of its share of the items, so that large items still balance one by one; and it asks
-  // one run ahead: the answer travels while the current run is computed.
-  const int n_items = a.hdr->n_items;
+  // Work queue: a counter in memory answers about 14 M requests a second on this part -- with thousands of small items
+  // that alone would bound the kernel.  A work-group therefore takes a run of consecutive items per request, long enough
+  // to stream about 64 K/V pairs (some 40 us) but never more than an eighth of its share of the items, so that large
+  // items still balance one by one; and it asks one run ahead: the answer travels while the current run is computed.
+  const int n_items = a.hdr->bound[PREFILL_XCDS];
   const int run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
+  int queue = blockIdx.x % PREFILL_XCDS;                               // (work-group b runs on XCD b % 8)
+  const int q_end = a.hdr->bound[min(lane, PREFILL_XCDS - 1) + 1];     // lane x: end of queue x
   int ahead = 0;
-  if (threadIdx.x == 0) ahead = atomicAdd(&a.hdr->next_item, run);
+  auto claim = [&]() {
+    if (threadIdx.x == 0) ahead = atomicAdd(&a.hdr->next[queue], run);
+  };
+  claim();
+  // wave 0: the next run of items, in run_slot (empty when the call is over)
+  auto settle = [&]() {
+    int start = rfl(ahead), end = __builtin_amdgcn_readlane(q_end, queue);
+    while (start >= end) {
+      int left = 0;
+      if (lane < PREFILL_XCDS)
+        left = q_end - __hip_atomic_load(&a.hdr->next[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int most = max(left, 0);
+#pragma unroll
+      for (int o = 1; o < PREFILL_XCDS; o <<= 1) most = max(most, __shfl_xor(most, o));
+      most = rfl(most);
+      if (most == 0) break;
+      queue = __builtin_ctzll(__builtin_amdgcn_ballot_w64(left == most));
+      claim();
+      start = rfl(ahead);
+      end = __builtin_amdgcn_readlane(q_end, queue);
+    }
+    if (lane == 0) {
+      run_slot[0] = start;
+      run_slot[1] = min(start + run, end);
+    }
+    if (start < end) claim();
+  };
+  const bool small = a.n <= PREFILL_LDS_REQ;
+  if (small)
+    for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
   int next = 0, run_end = 0;
   for (;;) {
     // ---- next item (every wave reaches the exit together)
     __syncthreads();                                       // the previous item's slot and stages are done with
     if (next == run_end) {
-      if (threadIdx.x == 0) item_slot = ahead;
+      if (wv == 0) settle();
       __syncthreads();
-      next = rfl(item_slot);
-      if (next >= n_items) break;
-      run_end = min(next + run, n_items);
-      if (threadIdx.x == 0) ahead = atomicAdd(&a.hdr->next_item, run);
+      next = rfl(run_slot[0]);
+      run_end = rfl(run_slot[1]);
+      if (next >= run_end) break;
     }
     const int item = next++;
-    // request of the item: largest r with item_start[r] <= item (item_start is non-decreasing; empty
-    // requests repeat a value, so take the last one that still has items).  Two wave-wide rounds.
-    int lo = 0, hi = a.n;                                  // answer in [lo, hi)
-    while (hi - lo > 1) {
-      const int span = hi - lo;
-      const int step = (span + 63) / 64;
-      const int idx = min(lo + lane * step, hi - 1);
-      const bool le = a.item_start[idx] <= item && lo + lane * step < hi;
-      const unsigned long long mask = __builtin_amdgcn_ballot_w64(le);
-      const int cnt = __builtin_popcountll(mask);          // lanes 0 .. cnt-1 satisfy it (cnt >= 1)
-      const int nlo = lo + (cnt - 1) * step;
-      hi = min(nlo + step, hi);
-      lo = nlo;
+    // Request of the item: largest r with item_start[r] <= item (item_start is non-decreasing; empty requests repeat
+    // a value, so it is the last one that still has items): the number of such entries, counted in LDS where they fit.
+    // Everything else an item needs is then one round of scalar loads, all in flight together: an item of a short prompt
+    // streams fewer than ten pairs, so each dependent round trip in front of it shows.
+    int cnt = 0;
+    for (int i0 = 0; i0 < a.n; i0 += 64) {
+      const int i = min(i0 + lane, a.n - 1);
+      const bool le = i0 + lane < a.n && (small ? item_start_lds[i] : a.item_start[i]) <= item;
+      const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
+      cnt += k;
+      if (k < 64) break;
     }
-    const int r = rfl(lo);
-    const int rows = prefill_rows(a.n_q, a.lengths, a.q_start, a.total_q, r);
-    const int len = a.lengths[r];
-    const int n_blocks_item = (int)(((int64_t)rows * G + COLS_ITEM - 1) / COLS_ITEM);
-    const int idx = item - a.item_start[r];
-    const int g = idx / n_blocks_item;
+    const int r = rfl(cnt - 1);
+    const int first_item = rfl(small ? item_start_lds[r] : a.item_start[r]);
+    const int len = as_constant(a.lengths)[r], asked = as_constant(a.n_q)[r];
+    const int64_t q_row0 = ((const const_i64*)(uintptr_t)a.q_start)[r];
+    const int64_t base_block = PAGED ? 0 : ((const const_i64*)(uintptr_t)a.offsets)[r] / BLK;
+    // (the request has items, so its rows exist: prefill_rows without its checks)
+    const int rows = (int)min((int64_t)min(asked, len), a.total_q - q_row0);
+    const int n_blocks_item = rfl((int)(((int64_t)rows * G + COLS_ITEM - 1) / COLS_ITEM));
+    const int idx = item - first_item;
+    const int g = rfl(idx / n_blocks_item);
     const int cb = n_blocks_item - 1 - (idx - g * n_blocks_item);    // heaviest (latest) columns first
     const int n_cols = rows * G;
     const int c0 = cb * COLS_ITEM + wv * COLS_WAVE;   // this wave's first column
     const bool active = c0 < n_cols;                                  // a wave without columns still helps to load
-    const int64_t q_row0 = a.q_start[r];
     const int first_pos = len - rows;                                // position of query token 0
 
     // ---- per-lane columns: tile ct holds column c0 + 16 ct + col16
     int lim[CT];                                                       // keys visible to the column (0: column absent)
-    const unsigned short* qptr[CT];
+    int64_t q_at[CT];                                                  // the column's row in q and out, in elements
     bf16x8 qreg[CT][4];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -203,13 +286,18 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       const bool ok = col < n_cols;
       const int j = ok ? col / G : 0, h = ok ? col - j * G : 0;
       lim[ct] = ok ? first_pos + j + 1 : 0;
-      qptr[ct] = a.q + ((q_row0 + j) * a.Hq + g * G + h) * 128;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-        qreg[ct][s] = ok ? *(const bf16x8*)(qptr[ct] + 32 * s + 8 * g4) : z;
-      }
+      q_at[ct] = ((q_row0 + j) * a.Hq + g * G + h) * 128;
     }
+    auto load_q = [&](bf16x8 (&qq)[CT][4]) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
+          qq[ct][s] = lim[ct] != 0 ? *(const bf16x8*)(a.q + q_at[ct] + 32 * s + 8 * g4) : z;
+        }
+    };
+    load_q(qreg);
     // keys the item streams: up to the limit of its last column; this wave's own columns end earlier
     const int item_last_col = min((cb + 1) * COLS_ITEM, n_cols) - 1;
     const int item_lim_max = first_pos + item_last_col / G + 1;
@@ -229,7 +317,6 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
 
     const int64_t plane = (int64_t)g * a.head_stride;
     const const_i32* bt_row = as_constant(PAGED ? a.bt + (int64_t)r * a.bt_stride : nullptr);
-    const int64_t base_block = PAGED ? 0 : a.offsets[r] / BLK;
     // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  Pairs past the
     // end and a second tile that does not exist re-read the last tile: every step issues its loads, so the waits on
     // them stay static counts (with conditional loads the wait before a stage was written covered the loads issued a
@@ -320,24 +407,25 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // exponent, and fp32 / bf16 weights have room for 2^127: the fast pass fixes m of a column to the
     // exact maximum over the first pair (every column sees token 0) and never moves it, so the steady
     // state holds no cross-lane maximum, no rescale of O and no second exponential.  Should later scores
-    // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), the item
-    // is redone by the slow pass below, the classic online softmax that moves its references.
-    auto scores = [&](float4v (&x)[CT][2], int pr) {
-      const char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES + lane * 16;
-      const int t0 = pr * 2 * BLK;
+    // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), the wave
+    // repeats its columns in the slow pass below, the classic online softmax that moves its references.
+    auto scores_of = [&](float4v (&x)[CT][2], const bf16x8 (&qq)[CT][4], auto&& kop) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         bf16x8 kk[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) kk[s] = *(const bf16x8*)(st + b * 4096 + s * 1024);
+        for (int s = 0; s < 4; ++s) kk[s] = kop(b, s);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
           float4v s4 = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int s = 0; s < 4; ++s) s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[s], qreg[ct][s], s4, 0, 0, 0);
+          for (int s = 0; s < 4; ++s) s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[s], qq[ct][s], s4, 0, 0, 0);
           x[ct][b] = s4;                                               // raw: the scale joins the exponent
         }
       }
+    };
+    auto mask = [&](float4v (&x)[CT][2], int pr) {
+      const int t0 = pr * 2 * BLK;
       if (t0 + 2 * BLK > lim_min) {                                    // some column cannot see the whole pair
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
@@ -387,7 +475,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       float4v x[CT][2];
       bf16x8 av[8];
       read_v(av, pr);
-      scores(x, pr);
+      const char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES + lane * 16;
+      scores_of(x, qreg, [&](int b, int s) { return *(const bf16x8*)(st + b * 4096 + s * 1024); });
+      mask(x, pr);
       if (pr == 0) {
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
@@ -399,51 +489,109 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       }
       weights(x, av);
     };
-    // slow pass: a reference moves whenever a score exceeds it by more than MAX_SLACK exponent units;
-    // the sums and O are rescaled then.  m = -inf until a column has seen a score.
+    // V slots at or past `len` hold stale bytes (maybe NaN patterns): zeroed in the operands, so that a weight of 0 really
+    // removes them.  (K needs nothing: scores of tokens past a column's limit are replaced, not multiplied.)
+    auto mask_v = [&](bf16x8 (&av)[8], int pr, int tiles, int len) {
+      const int ta = 2 * pr * BLK, tb = min(2 * pr + 1, tiles - 1) * BLK;
+      if (max(ta, tb) + BLK > len) {
+        uint4v keep;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int tok = (w < 2 ? ta : tb) + 4 * g4 + 2 * (w & 1);
+          keep[w] = (tok < len ? 0x0000ffffu : 0u) | (tok + 1 < len ? 0xffff0000u : 0u);
+        }
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) av[dt] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(uint4v, av[dt]) & keep);
+      }
+    };
+    auto join = [](uint2v lo, uint2v hi) { return __builtin_bit_cast(bf16x8, uint4v{lo[0], lo[1], hi[0], hi[1]}); };
+    // ---- slow pass of this wave's columns: operands straight from memory, no stage, no barrier.  A reference moves
+    // whenever a score exceeds it by more than MAX_SLACK exponent units; the sums and O are rescaled then.
     constexpr float MAX_SLACK = 12.0f;
-    auto compute_slow = [&](int pr) {
-      float4v x[CT][2];
-      scores(x, pr);
-      bool moved = false;
-      float local[CT];
+    auto slow_pass = [&]() {
+      bf16x8 qq[CT][4];
+      load_q(qq);
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        local[ct] = lane_max(x[ct]);
-        moved |= local[ct] > m[ct] + MAX_SLACK;                         // (m = -inf: any visible score moves it)
+        m[ct] = NEG_INF;
+        lsum[ct] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) O[ct][dt] = float4v{0.f, 0.f, 0.f, 0.f};
       }
-      if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+      for (int pr = 0; 2 * pr < n_tiles; ++pr) {
+        int64_t at[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int t = min(2 * pr + b, n_tiles - 1);
+          at[b] = plane + (int64_t)(PAGED ? a.bt[(int64_t)r * a.bt_stride + t] : base_block + t) * TILE_BYTES + lane * 16;
+        }
+        float4v x[CT][2];
+        scores_of(x, qq, [&](int b, int s) {
+          if (!FP8) return *(const bf16x8*)(a.k + at[b] + s * 1024);
+          const uint4v w = *(const uint4v*)(a.k + at[b] + (s >> 1) * 1024);
+          const unsigned w0 = w[2 * (s & 1)], w1 = w[2 * (s & 1) + 1];
+          return __builtin_bit_cast(bf16x8, uint4v{fp8x2_to_bf16x2<false>(w0), fp8x2_to_bf16x2<true>(w0),
+                                                   fp8x2_to_bf16x2<false>(w1), fp8x2_to_bf16x2<true>(w1)});
+        });
+        mask(x, pr);
+        bool moved = false;
+        float local[CT];
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          float tmax = local[ct];
-          tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-          tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-          const float m_new = fmaxf(m[ct], tmax);
-          // a column that has seen nothing yet keeps m = -inf; 0 stands in so that no inf - inf appears
-          const float alpha = __builtin_amdgcn_exp2f(m[ct] - (m_new == NEG_INF ? 0.f : m_new));
-          lsum[ct] *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 8; ++dt) O[ct][dt] *= alpha;
-          m[ct] = m_new;
+          local[ct] = lane_max(x[ct]);
+          moved |= local[ct] > m[ct] + MAX_SLACK;                          // (m = -inf: any visible score moves it)
         }
-      }
-      float keep[CT];
+        if (__builtin_amdgcn_ballot_w64(moved) != 0) {
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        keep[ct] = m[ct];
-        if (m[ct] == NEG_INF) m[ct] = 0.f;                              // stand-in while the weights are formed
-      }
-      bf16x8 av[8];
-      read_v(av, pr);
-      weights(x, av);
+          for (int ct = 0; ct < CT; ++ct) {
+            float tmax = local[ct];
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            const float m_new = fmaxf(m[ct], tmax);
+            // a column that has seen nothing yet keeps m = -inf; 0 stands in so that no inf - inf appears
+            const float alpha = __builtin_amdgcn_exp2f(m[ct] - (m_new == NEG_INF ? 0.f : m_new));
+            lsum[ct] *= alpha;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) m[ct] = keep[ct];
+            for (int dt = 0; dt < 8; ++dt) O[ct][dt] *= alpha;
+            m[ct] = m_new;
+          }
+        }
+        float keep[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          keep[ct] = m[ct];
+          if (m[ct] == NEG_INF) m[ct] = 0.f;                               // stand-in while the weights are formed
+        }
+        bf16x8 av[8];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          uint2v lo[2], hi[2];                                             // per tile: channel groups 2 s and 2 s + 1
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            uint4v w;
+            if (!FP8) w = *(const uint4v*)(a.v + at[b] + s * 1024);
+            else {
+              const uint4v f = *(const uint4v*)(a.v + at[b] + (s >> 1) * 1024);
+              const unsigned w0 = f[2 * (s & 1)], w1 = f[2 * (s & 1) + 1];
+              w = uint4v{fp8x2_to_bf16x2<false>(w0), fp8x2_to_bf16x2<true>(w0), fp8x2_to_bf16x2<false>(w1), fp8x2_to_bf16x2<true>(w1)};
+            }
+            lo[b] = uint2v{w[0], w[1]};
+            hi[b] = uint2v{w[2], w[3]};
+          }
+          av[2 * s] = join(lo[0], lo[1]);
+          av[2 * s + 1] = join(hi[0], hi[1]);
+        }
+        mask_v(av, pr, n_tiles, len);
+        weights(x, av);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) m[ct] = keep[ct];
+      }
     };
 
     // ---- pipeline: the loads of pair p + 2 are in flight while pair p is computed; pair p + 1 sits in
     // registers until the computation of pair p is over, is written into the other stage, and one
     // work-group barrier per pair makes it visible (and tells that the stage of pair p is free again).
-    auto stream = [&](auto&& compute) {
+    auto stream = [&]() {
       uint4v ra[4], rb[4];
       lookup(0);
       issue(ra, 0);
@@ -455,7 +603,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       auto step = [&](uint4v (&near)[4], uint4v (&far)[4], int pr) {     // near: pair pr + 1, far: free for pair pr + 2
         issue(far, pr + 2);
         lookup(pr + 3);
-        if (active) compute(pr);
+        if (active) compute_fast(pr);
         write_stage(near, pr + 1);
         __syncthreads();
       };
@@ -476,48 +624,45 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       }
     };
 
+    stream();
+    if (!active) continue;
     float l[CT];
-    stream(compute_fast);
     column_sums(l);
     bool redo = false;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) redo |= active && lim[ct] != 0 && !(l[ct] < 0x1p90f);
-    if (threadIdx.x == 0) redo_slot = 0;
-    __syncthreads();
-    if (__builtin_amdgcn_ballot_w64(redo) != 0 && lane == 0) redo_slot = 1;
-    __syncthreads();
-    if (redo_slot != 0) {                                              // the whole work-group: the barriers are shared
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        m[ct] = NEG_INF;
-        lsum[ct] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) O[ct][dt] = float4v{0.f, 0.f, 0.f, 0.f};
-      }
-      stream(compute_slow);
+    for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] != 0 && !(l[ct] < 0x1p90f);
+    if (__builtin_amdgcn_ballot_w64(redo) != 0) {                        // this wave's columns alone
+      slow_pass();
       column_sums(l);
     }
-    if (!active) continue;
 
     // ---- normalise and store: lane (col16, g4) holds channels 16 dt + 4 g4 .. +3 of its columns
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      if (lim[ct] == 0) continue;
       const float inv = a.out_scale / l[ct];
-      const int64_t o_base = (qptr[ct] - a.q) + 4 * g4;
       if (a.out_bf16) {
-        unsigned short* o = (unsigned short*)a.out + o_base;
+        // two channel groups at a time: the odd rows of 16 lanes swap their words of group dt for the even rows' words of
+        // group dt + 1, which leaves every lane eight consecutive channels of one group -- 16-byte stores, 64 bytes
+        // of a column together, half as many instructions
+        unsigned short* o = (unsigned short*)a.out + q_at[ct] + (g4 & 1) * 16 + (g4 >> 1) * 8;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-          uint2v pk;
-          pk[0] = (unsigned)float_to_bf16_bits(O[ct][dt][0] * inv) | ((unsigned)float_to_bf16_bits(O[ct][dt][1] * inv) << 16);
-          pk[1] = (unsigned)float_to_bf16_bits(O[ct][dt][2] * inv) | ((unsigned)float_to_bf16_bits(O[ct][dt][3] * inv) << 16);
-          *(uint2v*)(o + 16 * dt) = pk;
+        for (int dt = 0; dt < 8; dt += 2) {
+          uint4v pk;
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            const unsigned lo = (unsigned)float_to_bf16_bits(O[ct][dt][2 * w] * inv) | ((unsigned)float_to_bf16_bits(O[ct][dt][2 * w + 1] * inv) << 16);
+            const unsigned hi = (unsigned)float_to_bf16_bits(O[ct][dt + 1][2 * w] * inv) | ((unsigned)float_to_bf16_bits(O[ct][dt + 1][2 * w + 1] * inv) << 16);
+            const uint2v sw = __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+            pk[w] = sw[0];
+            pk[2 + w] = sw[1];
+          }
+          if (lim[ct] != 0) *(uint4v*)(o + 16 * dt) = pk;
         }
       } else {
-        float* o = (float*)a.out + o_base;
+        float* o = (float*)a.out + q_at[ct] + 4 * g4;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *(float4v*)(o + 16 * dt) = O[ct][dt] * inv;
+        for (int dt = 0; dt < 8; ++dt)
+          if (lim[ct] != 0) *(float4v*)(o + 16 * dt) = O[ct][dt] * inv;
       }
     }
   }
