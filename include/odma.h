@@ -82,7 +82,9 @@ extern "C" {
 #define ODMA_BLOCK_TOKENS  16    /* tokens per pool block == page size of the paged variant */
 
 /* decode kernel choice */
-#define ODMA_KERNEL_AUTO   0     /* MFMA kernel when the shape allows, else the VALU kernel */
+#define ODMA_KERNEL_AUTO   0     /* MFMA kernel when the shape allows; other shapes (fp32 storage, bf16 with a head_dim other
+                                    than 64 and 128) are reported as VALU and run on wide formats of the same tile-stream
+                                    kernel, at fp32 precision, unless max_splits sized the workspace too small for them */
 #define ODMA_KERNEL_VALU   1     /* fp32 vector-ALU kernel: any dtype, head_dim % 32 == 0 */
 #define ODMA_KERNEL_MFMA   2     /* matrix-core kernel: bf16 storage with head_dim 128 or 64, fp8 storage with head_dim 128; group <= 16 */
 

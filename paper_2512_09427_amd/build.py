@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libodma.so")
 TIMELINE_LIB = os.path.join(HERE, "libodma_timeline.so")
 DEPTH_PROBE = os.path.join(HERE, "read_depth_probe")
 # translation units with kernels (csrc/<name>.hip), the one that the timing build replaces first
-DEVICE_UNITS = ["odma_device", "odma_prefill"]
+DEVICE_UNITS = ["odma_device", "odma_prefill", "odma_wide_f32", "odma_wide_bf16"]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",

@@ -1,4 +1,5 @@
-// Matrix-core decode attention for bf16 storage (head_dim 128 or 64) and fp8 storage (head_dim 128), group size <= 16.
+// Matrix-core decode attention for bf16 storage (head_dim 128 or 64), fp8 storage (head_dim 128) and, as wide formats, fp32
+// storage and bf16 storage with any other head_dim; group size <= 16.
 //
 // Work decomposition ("tile stream").  A tile is one 16-token pool block of one KV head.
 // All tiles of the batch form one sequence ordered by (request, KV head, block); the plan
@@ -27,6 +28,7 @@
 // bf16 hi + lo parts so the P*V product keeps about 16 bits of P.
 #pragma once
 
+#include <atomic>
 #include <type_traits>
 
 #include "kernels_common.h"
@@ -42,9 +44,9 @@ using odma_plan::STREAM_MAX_LAUNCH_WG;
 struct StreamArgs {
   const char* k;             // layer base of the K pool
   const char* v;
-  const unsigned short* q;
+  const void* q;
   void* out;
-  const void* k_new;         // fused step only: [n][Hkv][head_dim] rows (bf16, or E4M3 bytes) appended at position len-1
+  const void* k_new;         // fused step only: [n][Hkv][head_dim] rows in storage type, appended at position len-1
   const void* v_new;
   const int32_t* bt;
   int32_t bt_stride;
@@ -58,13 +60,14 @@ struct StreamArgs {
   unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
   int32_t fuse_reduce;       // 1: the last work-group to finish a cut segment merges it; 0: stream_reduce_kernel does
   float2* part_ml;           // [2 * n_workgroups][Hq]
-  float* part_o;             // [2 * n_workgroups][Hq][128]
+  float* part_o;             // [2 * n_workgroups][Hq][ch]
   int32_t n, Hq, Hkv, G;
   int32_t wpw;               // waves per attention work-group (4 or 8)
   int32_t qs, aq;            // per-wave LDS queue depths: finished pieces, appended rows
   int64_t head_stride;       // bytes between KV-head planes of one layer
   float scale_log2;          // sm_scale * log2(e) (fp8 storage: times k_scale)
-  int32_t head_dim;          // 128, or 64 (bf16 only): stride of q and out rows
+  int32_t head_dim;          // stride of q and out rows
+  int32_t ch;                // channels a partial state keeps per head
   float out_scale;           // factor of the final normalisation: 1, or v_scale / 256 for fp8 storage (P is carried times 256)
   int32_t out_bf16;
 };
@@ -409,13 +412,15 @@ __device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const Inl
 // global memory (qs entries of slot + 8 ints) and of appended rows (aq records of STREAM_AQ_INTS).  The host sizes
 // the queues to the tiles a wave gets: a wave that runs out of queue has to write in mid-stream.
 constexpr int STREAM_MERGE_BATCH = 16;   // most partials whose loads are in flight together in the in-kernel merge
-__host__ __device__ inline int stream_slot_floats(int G) { return G * 128 + ((2 * G + 3) & ~3); }
-constexpr int STREAM_AQ_INTS = 8 + 128 + 256;   // appended-row record: 8 ints of header, 512 B of K pieces, 1 KiB of V pieces
-__host__ __device__ inline int stream_wave_queue_floats(int G, int qs, int aq) {
-  return qs * (stream_slot_floats(G) + 8) + aq * STREAM_AQ_INTS;
+// (ch: channels a state keeps per head; np: 1 KiB pieces of a K block)
+__host__ __device__ inline int stream_slot_floats(int G, int ch) { return G * ch + ((2 * G + 3) & ~3); }
+// appended-row record: 8 ints of header, 128 np bytes of K pieces, 256 np bytes of V pieces
+__host__ __device__ constexpr int stream_aq_ints(int np) { return 8 + 96 * np; }
+__host__ __device__ inline int stream_wave_queue_floats(int G, int ch, int np, int qs, int aq) {
+  return qs * (stream_slot_floats(G, ch) + 8) + aq * stream_aq_ints(np);
 }
-__host__ inline size_t stream_lds_bytes(int G, int wpw, int qs, int aq) {
-  return ((size_t)wpw * stream_slot_floats(G) + 2 * wpw + (size_t)wpw * stream_wave_queue_floats(G, qs, aq)) * 4;
+__host__ inline size_t stream_lds_bytes(int G, int ch, int np, int wpw, int qs, int aq) {
+  return ((size_t)wpw * stream_slot_floats(G, ch) + 2 * wpw + (size_t)wpw * stream_wave_queue_floats(G, ch, np, qs, aq)) * 4;
 }
 
 
@@ -498,22 +503,49 @@ struct Cursor {              // wave-uniform position in the tile stream
 
 // storage formats served by the tile stream
 constexpr int STREAM_BF16_D128 = 0, STREAM_FP8_D128 = 1, STREAM_BF16_D64 = 2;
+// every other head_dim D of bf16 pools, and every head_dim of fp32 pools: STREAM_BF16_WIDE + D / 32, STREAM_F32_WIDE + D / 32
+constexpr int STREAM_BF16_WIDE = 16, STREAM_F32_WIDE = 32;
+
+struct StreamFormat {        // what the kernel and its launch need to know of a format
+  int hd;                    // head_dim
+  int eb;                    // bytes of a K/V element
+  int np;                    // 1 KiB pieces of a K (or V) block
+  int blocks;                // pool blocks per tile
+  int ch;                    // channels a state keeps per head
+};
+__host__ __device__ constexpr StreamFormat stream_format(int fmt) {
+  if (fmt == STREAM_BF16_D128) return {128, 2, 4, 1, 128};
+  if (fmt == STREAM_FP8_D128) return {128, 1, 2, 2, 128};
+  if (fmt == STREAM_BF16_D64) return {64, 2, 2, 2, 128};
+  const bool f32 = fmt > STREAM_F32_WIDE;
+  const int hd = 32 * (fmt - (f32 ? STREAM_F32_WIDE : STREAM_BF16_WIDE)), eb = f32 ? 4 : 2;
+  return {hd, eb, hd * eb / 64, hd == 32 ? 2 : 1, hd};
+}
+// work-groups of one CU that the registers leave room for: a tile of eight pieces or more takes a SIMD for one wave
+__host__ __device__ constexpr int stream_min_waves(int fmt) {
+  return stream_format(fmt).np * stream_format(fmt).blocks >= 6 ? 1 : 2;
+}
 
 template <bool PAGED, int NBUF, int WPW, bool FUSED, int FMT>
-__global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a) {
+__global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream_kernel(StreamArgs a) {
   constexpr bool FP8 = FMT == STREAM_FP8_D128, D64 = FMT == STREAM_BF16_D64;
-  constexpr bool TWO = FMT != STREAM_BF16_D128;              // blocks of 2 KiB: a tile is two of them
-  constexpr int HD = D64 ? 64 : 128;                         // head_dim: stride of q and out rows
+  constexpr bool WIDE = FMT > STREAM_BF16_WIDE, F32 = FMT > STREAM_F32_WIDE;
+  constexpr StreamFormat F = stream_format(FMT);
+  constexpr bool TWO = F.blocks == 2;                        // small blocks: a tile is two of them
+  constexpr int HD = F.hd;                                   // head_dim: stride of q and out rows
+  constexpr int CH = F.ch, NP = F.np, NL = NP * F.blocks;    // NL: 16-byte loads per lane of a tile's K (or V)
+  constexpr int NQ = WIDE ? NP : 4;                          // 16-byte pieces of the query operand
   // A tile is what a wave requests per step: 4 KiB of K and 4 KiB of V.  bf16 with head_dim 128: one
   // 16-token pool block; fp8, or bf16 with head_dim 64: two of them (32 tokens), which need not be
-  // neighbours in the paged layout.  (Inside the kernel every state keeps 128 channels per head; with
-  // head_dim 64 the upper half stays zero and is not written out.)
+  // neighbours in the paged layout.  (Inside the kernel every state keeps CH channels per head; with
+  // bf16 head_dim 64 the upper half stays zero and is not written out.)  The wide formats -- fp32 pools, and bf16 pools
+  // with another head_dim -- take one block per tile whatever its size (two of head_dim 32).
   constexpr int TT = TWO ? 32 : BLK;
   extern __shared__ float lds[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int col = lane & 15, g4 = lane >> 4;
   const int G = a.G, Hkv = a.Hkv;
-  const int slot_floats = stream_slot_floats(G);
+  const int slot_floats = stream_slot_floats(G, CH);
   // [wave]{ready, to_end}; read and written with work-group-scope atomics (plain LDS instructions:
   // a volatile access would be compiled as a FLAT one, which also waits for the tile loads in flight)
   int* flags = (int*)(lds + WPW * slot_floats);
@@ -525,7 +557,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
   if (lane < TL_SLOTS) tl_lds[wv][lane] = 0;
   TL_STAMP(0);
 #endif
-  constexpr int BLOCK_BYTES = BLK * HD * (FP8 ? 1 : 2);    // one pool block of K (or V)
+  constexpr int BLOCK_BYTES = BLK * HD * F.eb;             // one pool block of K (or V)
 
   // the wave's range first: everything else waits for it
   const bool planning = a.plan_at >= 0;
@@ -558,7 +590,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
 
   if (n_my > 0) {
     const char* kbase = a.k + lane * 16;
-    const char* vbase = a.v + lane * 16;
+    const char* vbase = a.v + lane * (F32 ? 32 : 16);
 
     auto load_window = [&](Window& w, int e_base) {
       const int idx = min(e_base + lane, n_entries - 1);
@@ -646,39 +678,46 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     load_window(wc, cc.e_base);                            // needed only when a cursor leaves the first entry
     wp = wc;
 
-    bf16x8 kb[NBUF][4], vb[NBUF][4];
+    bf16x8 kb[NBUF][NL], vb[NBUF][NL];
     // Loads of the prefetch cursor's tile.  They are issued in every step, so that the waits stay
     // static counts; once the whole range has been requested the surplus loads all read the first
     // block of the layer's pools, which stays in the L2 instead of costing HBM traffic.
     int to_issue = n_my;
-    auto issue = [&](bf16x8 (&kk)[4], bf16x8 (&vv)[4]) {
+    auto issue = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int64_t off = to_issue > 0 ? tile_offset(pc) : 0;
-      // fp8: loads 0, 1 read the first block of the tile, loads 2, 3 the second one
-      const int64_t off2 = !TWO ? off + 2048 : (to_issue > 0 ? tile_offset2(pc) : 0);
+      // two blocks per tile: the first half of the loads reads the first block, the rest the second one
+      const int64_t off2 = !TWO ? 0 : (to_issue > 0 ? tile_offset2(pc) : 0);
       --to_issue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NL; ++j) {
         // streaming loads: K/V bytes are used once, and loads that do not allocate in the caches
         // read 9 % faster on this part (measured)
-        const int64_t o = j < 2 ? off + j * 1024 : off2 + (j - 2) * 1024;
+        const int64_t o = j < NP ? off + j * 1024 : off2 + (j - NP) * 1024;
         kk[j] = __builtin_nontemporal_load((const bf16x8*)(kbase + o));
-        vv[j] = __builtin_nontemporal_load((const bf16x8*)(vbase + o));
+        if (F32) {
+          // a lane's two fp32 pieces of 32 channels (c and 16 + c, four tokens each) are neighbours: the two loads that
+          // take them share their cache lines
+          const int64_t ov = j < NP ? off + (j >> 1) * 2048 + (j & 1) * 16 : off2 + ((j - NP) >> 1) * 2048 + (j & 1) * 16;
+          vv[j] = *(const bf16x8*)(vbase + ov);
+        } else {
+          vv[j] = __builtin_nontemporal_load((const bf16x8*)(vbase + o));
+        }
       }
     };
-    // Q^T operand of the segment at cursor c: lane (col, g4) holds q[head col][32 j + 8 g4 .. +8]
-    auto load_q = [&](bf16x8 (&qq)[4], int r, int g) {
-      const bf16x8* qp = (const bf16x8*)(a.q + ((int64_t)r * a.Hq + g * G + col) * HD + 8 * g4);
+    // Q^T operand of the segment at cursor c: lane (col, g4) holds q[head col][32 j + 8 g4 .. +8] (fp32: [16 j + 4 g4 .. +4])
+    auto load_q = [&](bf16x8 (&qq)[NQ], int r, int g) {
+      const char* qp = (const char*)a.q + ((int64_t)r * a.Hq + g * G + col) * HD * (F32 ? 4 : 2) + 16 * g4;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NQ; ++j) {
         bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-        qq[j] = (col < G && 32 * j < HD) ? qp[4 * j] : z;
+        qq[j] = (col < G && (WIDE || 32 * j < HD)) ? *(const bf16x8*)(qp + 64 * j) : z;
       }
     };
 
     // The first segment's queries are requested ahead of the first tiles and adopted inside the main loop, after
     // the second tile's loads have been issued: waiting for them here would hold those loads back by a whole
     // memory round trip.
-    bf16x8 qreg[4], qnext[4];
+    bf16x8 qreg[NQ], qnext[NQ];
     load_q(qnext, cc.r, cc.g);
 
     // prologue: NBUF-1 tiles in flight
@@ -697,12 +736,12 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     // low E4M3 part (together about 8 significant bits); the inverse scale joins the softmax scale.
     long qhi[4] = {0, 0, 0, 0}, qlo[4] = {0, 0, 0, 0};
     float qfac = a.scale_log2;
-    auto adopt_q = [&](const bf16x8 (&src)[4]) {
-      if (!FP8) {
+    auto adopt_q = [&](const bf16x8 (&src)[NQ]) {
+      if constexpr (!FP8) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) qreg[j] = src[j];
+        for (int j = 0; j < NQ; ++j) qreg[j] = src[j];
         return;
-      }
+      } else {
       float qf[4][8];
       float amax = 0.f;
 #pragma unroll
@@ -734,11 +773,12 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         qhi[j] = (long)(unsigned)hi[0] | ((long)hi[1] << 32);
         qlo[j] = (long)(unsigned)lo[0] | ((long)lo[1] << 32);
       }
+      }
     };
     float m = NEG_INF, lsum = 0.f;
-    float4v O[8];
+    float4v O[CH / 16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) O[i] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < CH / 16; ++i) O[i] = float4v{0.f, 0.f, 0.f, 0.f};
     bool from_start = cc.t == 0;
 
     // fused step: the token appended this step is the last token of its segment.  Its K/V row
@@ -747,9 +787,19 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     // The row is fetched with one wave-wide load (lanes 0..31 the K row, lanes 32..63 the V row,
     // 8 bytes each; 128-byte rows -- fp8 storage, or bf16 with head_dim 64: 4 bytes each) and handed to
     // the lanes that need its pieces through LDS: one entry in the load queue per segment instead of twelve.
+    // (Wide formats: 16 bytes of the K row and of the V row per lane, as many lanes as the row has.)
     uint2v newrow = {0u, 0u};
+    uint4v newrow_k = {0u, 0u, 0u, 0u}, newrow_v = {0u, 0u, 0u, 0u};
     bool new_ready = false;
     auto load_new = [&](int r, int g) {
+      if (WIDE) {
+        constexpr int ROW = HD * F.eb;
+        if (lane * 16 < ROW) {
+          newrow_k = *(const uint4v*)((const char*)a.k_new + ((int64_t)r * Hkv + g) * ROW + 16 * lane);
+          newrow_v = *(const uint4v*)((const char*)a.v_new + ((int64_t)r * Hkv + g) * ROW + 16 * lane);
+        }
+        return;
+      }
       const char* base = (const char*)(lane < 32 ? a.k_new : a.v_new);
       if (TWO) newrow[0] = *(const unsigned*)(base + ((int64_t)r * Hkv + g) * 128 + 4 * (lane & 31));
       else newrow = *(const uint2v*)(base + ((int64_t)r * Hkv + g) * 256 + 8 * (lane & 31));
@@ -762,39 +812,40 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     // 256-byte runs).  The neighbours' bytes go back unchanged; slots past the end may get stale
     // bytes again, as before.  fp8 storage: the same with the 2 KiB block that holds the token (two
     // 1 KiB pieces of K and of V instead of four).
-    constexpr int NP = TWO ? 2 : 4;                          // 1 KiB pieces per pool block
-    int* abase = (int*)(lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, a.qs, a.aq) +
+    int* abase = (int*)(lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq) +
                         a.qs * (slot_floats + 8));
+    constexpr int REC_V = 8 + 32 * NP;                       // where a record's V pieces begin
     int an = 0;
     // (Results leave with streaming stores: ordinary ones stay in the L2 as dirty lines that the end
     // of the kernel has to write back, which showed as 0.8 us per launch.)
     auto flush_appends = [&]() {
       for (int i = 0; i < an; ++i) {
-        const int* rec = abase + i * STREAM_AQ_INTS;
+        const int* rec = abase + i * stream_aq_ints(NP);
         const int64_t off = ((int64_t)rfl(rec[1]) << 32) | (unsigned)rfl(rec[0]);
         const int slot = rfl(rec[2]);
         const bf16x8* kq = (const bf16x8*)(rec + 8);
-        const bf16x8* vq = (const bf16x8*)(rec + 8 + 128);
+        const bf16x8* vq = (const bf16x8*)(rec + REC_V);
         if ((col >> 1) == (slot >> 1)) {
           char* kd = (char*)a.k + off + lane * 16;
 #pragma unroll
           for (int j = 0; j < NP; ++j) __builtin_nontemporal_store(kq[(j * 4 + g4) * 2 + (col & 1)], (bf16x8*)(kd + j * 1024));
         }
         if (g4 == (slot >> 2)) {
-          char* vd = (char*)a.v + off + lane * 16;
+          char* vd = (char*)a.v + off + lane * (F32 ? 32 : 16);
 #pragma unroll
-          for (int j = 0; j < NP; ++j) __builtin_nontemporal_store(vq[j * 16 + col], (bf16x8*)(vd + j * 1024));
+          for (int j = 0; j < NP; ++j)
+            __builtin_nontemporal_store(vq[j * 16 + col], (bf16x8*)(vd + (F32 ? (j >> 1) * 2048 + (j & 1) * 16 : j * 1024)));
         }
       }
       an = 0;
     };
     // Blocks of 2 KiB (fp8 storage, or bf16 with head_dim 64): the row's 128 K bytes and 128 V bytes are
-    // staged in the unused upper half of the record's K area; k0, k1 / v0, v1 are the register pieces of
+    // staged in the record's V area (overwritten by the patched pieces further down); k0, k1 / v0, v1 are the register pieces of
     // the block that holds the token.
     auto patch_two = [&](int* rec, int slot, bf16x8& k0, bf16x8& k1, bf16x8& v0, bf16x8& v1) {
       typedef unsigned uint4u __attribute__((ext_vector_type(4)));
       const int rr = slot & 3;
-      unsigned* stage = (unsigned*)(rec + 8 + 64);
+      unsigned* stage = (unsigned*)(rec + REC_V);
       stage[lane] = newrow[0];
       if (FP8) {
         const uint2v* krow = (const uint2v*)stage;          // K[0..128) as 16 pieces of 8 bytes
@@ -841,31 +892,72 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         kq[(4 + g4) * 2 + (col & 1)] = k1;
       }
       if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
-        bf16x8* vq = (bf16x8*)(rec + 8 + 128);
+        bf16x8* vq = (bf16x8*)(rec + REC_V);
         vq[col] = v0;
         vq[16 + col] = v1;
       }
     };
-    auto patch_and_store = [&](bf16x8 (&kk)[4], bf16x8 (&vv)[4]) {
+    // Wide formats: the same for blocks of NP pieces; blk: the tile's block that holds the token.
+    auto patch_wide = [&](int* rec, int slot, bf16x8 (&kk)[NL], bf16x8 (&vv)[NL], auto blk) {
+      constexpr int P0 = decltype(blk)::value * NP, ROW16 = HD * F.eb / 16;
+      const int rr = slot & 3;
+      uint4v* stage = (uint4v*)(rec + REC_V);
+      if (lane < ROW16) {
+        stage[lane] = newrow_k;
+        stage[ROW16 + lane] = newrow_v;
+      }
+      if (col == slot) {                                     // K: piece j of this lane is 16-byte chunk 4 j + g4 of the row
+#pragma unroll
+        for (int j = 0; j < NP; ++j) kk[P0 + j] = __builtin_bit_cast(bf16x8, stage[4 * j + g4]);
+      }
+      if (g4 == (slot >> 2)) {                               // V: this lane holds tokens 4*g4..+3 of HD / 16 channels
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt) {
+          if (F32) {
+            float4v w = __builtin_bit_cast(float4v, vv[P0 + dt % NP]);
+            const float vnew = ((const float*)(stage + ROW16))[16 * dt + col];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = i == rr ? vnew : w[i];
+            vv[P0 + dt % NP] = __builtin_bit_cast(bf16x8, w);
+          } else {
+            const __bf16 vnew = __builtin_bit_cast(__bf16, ((const unsigned short*)(stage + ROW16))[16 * dt + col]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (i == rr) vv[P0 + (dt >> 1) % NP][4 * (dt & 1) + i] = vnew;
+          }
+        }
+      }
+      if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
+#pragma unroll
+        for (int j = 0; j < NP; ++j) ((bf16x8*)(rec + 8))[(j * 4 + g4) * 2 + (col & 1)] = kk[P0 + j];
+      }
+      if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
+#pragma unroll
+        for (int j = 0; j < NP; ++j) ((bf16x8*)(rec + REC_V))[j * 16 + col] = vv[P0 + j];
+      }
+    };
+    auto patch_and_store = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int slot = (cc.len - 1) & (BLK - 1), rr = slot & 3;
       lookup_block(cc);                                      // the compute cursor looks its block up only here
       const bool second = TWO && (((cc.len - 1) / BLK) & 1);  // 32-token tiles: the token sits in the tile's second block
       const int64_t off = second ? tile_offset2(cc) : tile_offset(cc);
       if (an == a.aq) flush_appends();
-      int* rec = abase + an * STREAM_AQ_INTS;
+      int* rec = abase + an * stream_aq_ints(NP);
       if (lane == 0) {
         rec[0] = (int)(off & 0xffffffffll);
         rec[1] = (int)(off >> 32);
         rec[2] = slot;
       }
       ++an;
-      if (TWO) {
+      if constexpr (WIDE) {
+        if (second) patch_wide(rec, slot, kk, vv, std::integral_constant<int, F.blocks - 1>{});
+        else patch_wide(rec, slot, kk, vv, std::integral_constant<int, 0>{});
+      } else if constexpr (TWO) {
         if (second) patch_two(rec, slot, kk[2], kk[3], vv[2], vv[3]);
         else patch_two(rec, slot, kk[0], kk[1], vv[0], vv[1]);
-        return;
-      }
+      } else {
       // stage the row in the record's V area (overwritten by the patched pieces further down)
-      uint2v* stage = (uint2v*)(rec + 8 + 128);
+      uint2v* stage = (uint2v*)(rec + REC_V);
       stage[lane] = newrow;
       const bf16x8* krow = (const bf16x8*)stage;            // K[0..128) as 16 pieces of 8
       const unsigned short* vrow = (const unsigned short*)stage + 128;
@@ -888,9 +980,10 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         for (int j = 0; j < 4; ++j) kq[(j * 4 + g4) * 2 + (col & 1)] = kk[j];
       }
       if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
-        bf16x8* vq = (bf16x8*)(rec + 8 + 128);
+        bf16x8* vq = (bf16x8*)(rec + REC_V);
 #pragma unroll
         for (int j = 0; j < 4; ++j) vq[j * 16 + col] = vv[j];
+      }
       }
     };
 
@@ -899,7 +992,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     // low E4M3 part as well; O^T += V^T P^T contracts over all 32 tokens in one mfma per d-tile and
     // part, the operand of lane (., g4) holding tokens 4 g4 .. 4 g4 + 3 of block 0, then of block 1,
     // which is the order the pool's V block format and the S^T accumulator layout both give.
-    auto compute_fp8 = [&](bf16x8 (&kk)[4], bf16x8 (&vv)[4]) {
+    auto compute_fp8 = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       typedef long long2v __attribute__((ext_vector_type(2)));
       typedef unsigned uint4u __attribute__((ext_vector_type(4)));
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= 32: all)
@@ -977,7 +1070,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     // 128 with two channel steps; P V contracts over the 32 tokens in one 16x16x32 instruction per
     // channel group, the operand of lane (., g4) holding tokens 4 g4 .. +3 of the first block, then of
     // the second.  P is carried as a high plus a low bf16 part.
-    auto compute_d64 = [&](bf16x8 (&kk)[4], bf16x8 (&vv)[4]) {
+    auto compute_d64 = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= 32: all)
       const bool ragged = n_valid < TT;
       float x[2][4];
@@ -1040,15 +1133,116 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
       }
     };
 
-    auto compute = [&](bf16x8 (&kk)[4], bf16x8 (&vv)[4]) {
-      if (FP8) {
+    // Wide formats.  fp32: both products run on the fp32 matrix instruction (16x16x4), whose operands are single elements
+    // of the 16-byte pieces: element e of K piece j and of the query's is channel 16 j + 4 g4 + e, element e of V piece dt
+    // is token 4 g4 + e of channel 16 dt + col, and score row 4 g4 + e is where the accumulator holds it -- no data moves
+    // between lanes.  A 16-token tile of head_dim 128 takes 64 of them, 2048 cycles of the 6000 that its 16 KiB take to
+    // arrive.  bf16: as head_dim 128, but P is carried as three bf16 parts (24 bits), so that no weight has fewer bits than
+    // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
+    // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
+    // 4.5 TB/s); 4 requests of config 1, fused step, 23.1 -> 11.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
+    auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+      const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
+      const bool ragged = n_valid < TT;
+      float x[F.blocks][4];
+      float tmax = NEG_INF;
+#pragma unroll
+      for (int b = 0; b < F.blocks; ++b) {
+        float4v s[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};   // two chains: half the latency
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+          if (F32) {
+            const float4v kf = __builtin_bit_cast(float4v, kk[b * NP + j]), qf = __builtin_bit_cast(float4v, qreg[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[e], s[e & 1], 0, 0, 0);
+          } else {
+            s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[b * NP + j], qreg[j], s[j & 1], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float val = (s[0][i] + s[1][i]) * a.scale_log2;
+          if (ragged && 16 * b + 4 * g4 + i >= n_valid) val = NEG_INF;
+          x[b][i] = val;
+          tmax = fmaxf(tmax, val);
+        }
+      }
+      tmax = column_max(tmax);
+      if (__builtin_amdgcn_ballot_w64(tmax > m + LAZY_REF_LOG2) != 0) {   // lazy reference, as for head_dim 128
+        const float m_new = fmaxf(m, tmax);
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        lsum *= alpha;
+#pragma unroll
+        for (int i = 0; i < CH / 16; ++i) O[i] *= alpha;
+      }
+      float psum = 0.f;
+#pragma unroll
+      for (int b = 0; b < F.blocks; ++b) {
+        float pv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          pv[i] = __builtin_amdgcn_exp2f(x[b][i] - m);
+          psum += pv[i];
+        }
+        if (F32) {
+          if (ragged) {                                       // stale slots may hold anything: keep 0 * x == 0
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+              float4v w = __builtin_bit_cast(float4v, vv[b * NP + j]);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) w[i] = 16 * b + 4 * g4 + i >= n_valid ? 0.f : w[i];
+              vv[b * NP + j] = __builtin_bit_cast(bf16x8, w);
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int dt = 0; dt < CH / 16; ++dt)
+              O[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float4v, vv[b * NP + dt % NP])[e], pv[e], O[dt], 0, 0, 0);
+        } else {
+          bf16x4 part[3];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float rest = pv[i];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              part[k][i] = (__bf16)rest;
+              rest -= (float)part[k][i];
+            }
+          }
+          if (ragged) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (16 * b + 4 * g4 + i >= n_valid) {
+                  vv[b * NP + j][i] = (__bf16)0.f;
+                  vv[b * NP + j][4 + i] = (__bf16)0.f;
+                }
+          }
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int dt = 0; dt < CH / 16; ++dt) {
+              const bf16x8 w = vv[b * NP + (dt >> 1) % NP];
+              const bf16x4 half = (dt & 1) ? bf16x4{w[4], w[5], w[6], w[7]} : bf16x4{w[0], w[1], w[2], w[3]};
+              O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, half),
+                                                                __builtin_bit_cast(short4v, part[k]), O[dt], 0, 0, 0);
+            }
+        }
+      }
+      lsum += psum;
+    };
+
+    auto compute = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+      if constexpr (WIDE) {
+        compute_wide(kk, vv);
+      } else if constexpr (FP8) {
         compute_fp8(kk, vv);
-        return;
-      }
-      if (D64) {
+      } else if constexpr (D64) {
         compute_d64(kk, vv);
-        return;
-      }
+      } else {
       float4v s = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[j], qreg[j], s, 0, 0, 0);
@@ -1106,13 +1300,14 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bh, O[dt], 0, 0, 0);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bl, O[dt], 0, 0, 0);
       }
+      }
     };
 
     // Finished pieces are not stored to global memory right away: stores share the in-order
     // vmcnt queue with the tile loads, and a store in the middle of the stream makes the next
     // tile wait for the store's acknowledgement.  They are queued in LDS (a separate counter)
     // and written when the wave has streamed its whole range (or when the queue is full).
-    float* qbase = lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, a.qs, a.aq);
+    float* qbase = lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq);
     const int qstride = slot_floats + 8;
     int qn = 0;
     auto flush_outputs = [&]() {
@@ -1121,10 +1316,10 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         const int* meta = (const int*)(e + slot_floats);
         const int kind = rfl(meta[0]), r = rfl(meta[1]), g = rfl(meta[2]), gslot = rfl(meta[3]);
         if (col < G) {
-          float4v o4[8];
+          float4v o4[CH / 16];
 #pragma unroll
-          for (int dt = 0; dt < 8; ++dt) o4[dt] = *(const float4v*)(e + col * 128 + 16 * dt + 4 * g4);
-          const float m_e = e[G * 128 + col], l_e = e[G * 128 + G + col];
+          for (int dt = 0; dt < CH / 16; ++dt) o4[dt] = *(const float4v*)(e + col * CH + 16 * dt + 4 * g4);
+          const float m_e = e[G * CH + col], l_e = e[G * CH + G + col];
           if (kind == 0) {                                   // final: normalise and write to `out`
             const float inv = a.out_scale / l_e;
             const int64_t o_base = ((int64_t)r * a.Hq + g * G + col) * HD + 4 * g4;
@@ -1144,9 +1339,9 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
             }
           } else {                                           // un-normalised state to the HBM workspace
             const int64_t pi = (int64_t)gslot * a.Hq + g * G + col;
-            float* o = a.part_o + pi * 128 + 4 * g4;
+            float* o = a.part_o + pi * CH + 4 * g4;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
+            for (int dt = 0; dt < CH / 16; ++dt) {
               store_pair_agent(o + 16 * dt, o4[dt][0], o4[dt][1]);
               store_pair_agent(o + 16 * dt + 2, o4[dt][2], o4[dt][3]);
             }
@@ -1161,10 +1356,10 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
       float* e = qbase + qn * qstride;
       if (col < G) {
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *(float4v*)(e + col * 128 + 16 * dt + 4 * g4) = O[dt];
+        for (int dt = 0; dt < CH / 16; ++dt) *(float4v*)(e + col * CH + 16 * dt + 4 * g4) = O[dt];
         if (g4 == 0) {
-          e[G * 128 + col] = m;
-          e[G * 128 + G + col] = l_all;
+          e[G * CH + col] = m;
+          e[G * CH + G + col] = l_all;
         }
       }
       if (lane == 0) {
@@ -1182,10 +1377,10 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
       float* so = lds + wv * slot_floats;
       if (col < G) {
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *(float4v*)(so + col * 128 + 16 * dt + 4 * g4) = O[dt];
+        for (int dt = 0; dt < CH / 16; ++dt) *(float4v*)(so + col * CH + 16 * dt + 4 * g4) = O[dt];
         if (g4 == 0) {
-          so[G * 128 + col] = m;
-          so[G * 128 + G + col] = l_all;
+          so[G * CH + col] = m;
+          so[G * CH + G + col] = l_all;
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1208,12 +1403,12 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
         to_end = flag_get(2 * (wv + 1) + 1) != 0;
         const float* so = lds + (wv + 1) * slot_floats;
         const int c = col < G ? col : 0;
-        const float m2 = so[G * 128 + c], l2 = so[G * 128 + G + c];
+        const float m2 = so[G * CH + c], l2 = so[G * CH + G + c];
         const float m_new = fmaxf(m, m2);
         const float a1 = __builtin_amdgcn_exp2f(m - m_new), a2 = __builtin_amdgcn_exp2f(m2 - m_new);
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-          const float4v o2 = *(const float4v*)(so + c * 128 + 16 * dt + 4 * g4);
+        for (int dt = 0; dt < CH / 16; ++dt) {
+          const float4v o2 = *(const float4v*)(so + c * CH + 16 * dt + 4 * g4);
           O[dt] = O[dt] * a1 + o2 * a2;
         }
         m = m_new;
@@ -1289,7 +1484,7 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
               m = NEG_INF;
               lsum = 0.f;
 #pragma unroll
-              for (int k = 0; k < 8; ++k) O[k] = float4v{0.f, 0.f, 0.f, 0.f};
+              for (int k = 0; k < CH / 16; ++k) O[k] = float4v{0.f, 0.f, 0.f, 0.f};
               from_start = true;
             }
           }
@@ -1386,8 +1581,8 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
     const int n_parts = rd.n_parts, b0 = rd.b0;
     // thread -> (head, four channels); partial i of the segment sits in slot 2 (b0 + i), the first
     // one in its work-group's "starts here" slot 2 b0 + 1
-    for (int idx = threadIdx.x; idx < G * 32; idx += 64 * WPW) {
-      const int h = idx >> 5, d4 = idx & 31;
+    for (int idx = threadIdx.x; idx < G * (CH / 4); idx += 64 * WPW) {
+      const int h = idx / (CH / 4), d4 = idx - h * (CH / 4);
       auto part = [&](int i) -> int64_t { return (int64_t)(2 * (b0 + i) + (i == 0 ? 1 : 0)) * a.Hq + rd.g * G + h; };
       float m_run = -INFINITY, l_run = 0.f;
       float4v acc = float4v{0.f, 0.f, 0.f, 0.f};
@@ -1402,8 +1597,8 @@ __global__ __launch_bounds__(64 * WPW, 2) void decode_stream_kernel(StreamArgs a
           for (int u = 0; u < BATCH; ++u) {
             const int64_t pi = part(min(i0 + u, n_parts - 1));
             ml[u] = load_pair_agent((const float*)&a.part_ml[pi]);
-            const float2 lo = load_pair_agent(a.part_o + pi * 128 + 4 * d4);
-            const float2 hi = load_pair_agent(a.part_o + pi * 128 + 4 * d4 + 2);
+            const float2 lo = load_pair_agent(a.part_o + pi * CH + 4 * d4);
+            const float2 hi = load_pair_agent(a.part_o + pi * CH + 4 * d4 + 2);
             ov[u] = float4v{lo.x, lo.y, hi.x, hi.y};
           }
           float m_new = m_run;
@@ -1461,7 +1656,7 @@ __device__ __forceinline__ float merge_parts(const StreamArgs& a, PartFn part, i
     for (int u = 0; u < BATCH; ++u) {
       const int64_t pi = part(min(i0 + u, n_parts - 1));
       ml[u] = a.part_ml[pi];
-      ov[u] = a.part_o[pi * 128 + d];
+      ov[u] = a.part_o[pi * a.ch + d];
     }
     float m_new = m_run;
 #pragma unroll
@@ -1482,9 +1677,9 @@ __device__ __forceinline__ float merge_parts(const StreamArgs& a, PartFn part, i
   return acc * (a.out_scale / l_run);
 }
 
-// grid: n_wg * G work-groups (boundary, head) of 128 threads (one per channel); no LDS, no
+// grid: n_wg * G work-groups (boundary, head) of one thread per channel of a state; no LDS, no
 // barrier.  Used when the in-kernel merge of decode_stream_kernel is switched off.
-__global__ __launch_bounds__(128) void stream_reduce_kernel(StreamArgs a, int n_wg) {
+__global__ __launch_bounds__(256) void stream_reduce_kernel(StreamArgs a, int n_wg) {
   const int G = a.G, d = threadIdx.x;
   const int b = blockIdx.x / G, h = blockIdx.x - b * G;
   const ReduceDesc rd = a.red[b];
@@ -1501,4 +1696,25 @@ __global__ __launch_bounds__(128) void stream_reduce_kernel(StreamArgs a, int n_
   else __builtin_nontemporal_store(val, (float*)a.out + o);
 }
 
+// Launch with lds_bytes of dynamic LDS; `allowed`: the largest size enabled for the kernel so far (the default limit is
+// 64 KiB).  Racing callers may both set the attribute; the larger request wins in the end because each sets its own size
+// and then records the maximum.
+inline hipError_t launch_with_lds(void (*kernel)(StreamArgs), std::atomic<unsigned>& allowed, int n_wg, int wpw, size_t lds_bytes,
+                                  hipStream_t s, const StreamArgs& a) {
+  if (lds_bytes > 64 * 1024 && lds_bytes > allowed.load(std::memory_order_acquire)) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (e != hipSuccess) return e;
+    unsigned seen = allowed.load(std::memory_order_relaxed);
+    while (seen < lds_bytes && !allowed.compare_exchange_weak(seen, (unsigned)lds_bytes, std::memory_order_release)) {
+    }
+  }
+  hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(64 * wpw), lds_bytes, s, a);
+  return hipSuccess;
+}
+
 }  // namespace
+
+// The wide formats are compiled in units of their own (odma_wide_f32.hip, odma_wide_bf16.hip).  args: a StreamArgs, whose
+// type is local to every unit.
+hipError_t odma_launch_wide_f32(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args);
+hipError_t odma_launch_wide_bf16(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args);

@@ -122,7 +122,7 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
 
 namespace {
 
-// Every instantiation of the tile-stream attention kernel, indexed [format][fused][paged][3 - nbuf][wpw == 4],
+// Every instantiation of the tile-stream attention kernel but the wide formats (odma_wide_*.hip), indexed [format][fused][paged][3 - nbuf][wpw == 4],
 // and per instantiation the largest dynamic LDS size enabled so far (the default limit is 64 KiB).
 using StreamKernel = void (*)(StreamArgs);
 #ifdef ODMA_DEV_MINIMAL_VARIANTS
@@ -141,21 +141,12 @@ std::atomic<unsigned> stream_kernel_lds[3][2][2][2][2];   // zero-initialised: n
 
 hipError_t launch_stream_kernel(int fmt, bool fused, bool paged, int nbuf, int wpw, int n_wg, size_t lds_bytes,
                                 hipStream_t s, const StreamArgs& a) {
+  if (fmt > STREAM_F32_WIDE) return odma_launch_wide_f32(fmt, fused, paged, n_wg, lds_bytes, s, &a);
+  if (fmt > STREAM_BF16_WIDE) return odma_launch_wide_bf16(fmt, fused, paged, n_wg, lds_bytes, s, &a);
   if (fmt < 0 || fmt > 2 || (nbuf != 2 && nbuf != 3) || (wpw != 4 && wpw != 8)) return hipErrorInvalidValue;
   const StreamKernel kernel = stream_kernels[fmt][fused][paged][3 - nbuf][wpw == 4];
   if (!kernel) return hipErrorInvalidDeviceFunction;
-  std::atomic<unsigned>& allowed = stream_kernel_lds[fmt][fused][paged][3 - nbuf][wpw == 4];
-  if (lds_bytes > 64 * 1024 && lds_bytes > allowed.load(std::memory_order_acquire)) {
-    // racing callers may both set the attribute; the larger request wins in the end because each sets its own size
-    // and then records the maximum
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
-    unsigned seen = allowed.load(std::memory_order_relaxed);
-    while (seen < lds_bytes && !allowed.compare_exchange_weak(seen, (unsigned)lds_bytes, std::memory_order_release)) {
-    }
-  }
-  hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(64 * wpw), lds_bytes, s, a);
-  return hipSuccess;
+  return launch_with_lds(kernel, stream_kernel_lds[fmt][fused][paged][3 - nbuf][wpw == 4], n_wg, wpw, lds_bytes, s, a);
 }
 
 // Static scratch of odma_decode_attention_static: plan records, arrival counters and partial states of one decode
@@ -223,11 +214,13 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
   }
   hipStream_t s = (hipStream_t)stream;
   char* ws = scratch ? scratch->base : (char*)c.workspace;
-  const odma::WorkspaceLayout& wl = scratch ? scratch->layout : pool->ws;
+  const odma::WorkspaceLayout& wl = scratch ? scratch->layout : pool->wide_wg > 0 ? pool->wide : pool->ws;
   odma_pool::PlanStamp& stamp = scratch ? *scratch->stamp : pool->plan_stamp;
   const bool fp8 = pool->elem_bytes == 1;
   const bool d64 = pool->decode_kernel == ODMA_KERNEL_MFMA && c.head_dim == 64;
-  const bool fused = k_new != nullptr && pool->decode_kernel == ODMA_KERNEL_MFMA;
+  const bool wide = pool->wide_wg > 0 && !scratch;         // tile-stream kernel, wide formats
+  const bool stream_scheme = pool->decode_kernel == ODMA_KERNEL_MFMA || wide;
+  const bool fused = k_new != nullptr && stream_scheme;
   if (k_new && !fused) {
     // the vector-ALU path appends with the row kernel, then attends
     RowArgs wa = row_args(pool, layer);
@@ -249,19 +242,25 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
   const float scale_log2 = c.sm_scale * 1.4426950408889634f;
   const int G = c.n_q_heads / c.n_kv_heads;
 
-  if (pool->decode_kernel == ODMA_KERNEL_MFMA) {
+  if (stream_scheme) {
     // ---- tile-stream scheme: plan -> attention (one equal tile range per wave) -> reduce
     // Launch shape: one wave per SIMD (4 per CU, 4-wave work-groups) streams fastest, for both layouts.
-    int wpw = pool->waves_per_wg ? pool->waves_per_wg : 4;
+    // (The wide formats are compiled for that shape alone.)
+    const int fmt = wide ? (pool->elem_bytes == 4 ? STREAM_F32_WIDE : STREAM_BF16_WIDE) + c.head_dim / 32
+                         : d64 ? STREAM_BF16_D64 : fp8 ? STREAM_FP8_D128 : STREAM_BF16_D128;
+    const StreamFormat f = stream_format(fmt);
+    int wpw = pool->waves_per_wg && !wide ? pool->waves_per_wg : 4;
     const int wpc = pool->waves_per_cu ? pool->waves_per_cu : 4;
     // per-wave LDS queues: deep enough for the segments a wave of this launch shape typically finishes,
     // shallower (down to one entry) when a large GQA group makes the entries big
     int qs = 3, aq = wpw == 4 ? 6 : 3;
-    while (qs > 1 && stream_lds_bytes(G, wpw, qs, aq) > 144 * 1024) --qs;
-    if (stream_lds_bytes(G, wpw, qs, aq) > 160 * 1024) wpw = 4;
+    while (qs > 1 && stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq) > 144 * 1024) --qs;
+    if (stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq) > 160 * 1024) wpw = 4;
+    while (wide && aq > 1 && stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq) > 144 * 1024) --aq;
     int n_wg = pool->n_cu * wpc / wpw;
     if (n_wg > STREAM_MAX_LAUNCH_WG) n_wg = STREAM_MAX_LAUNCH_WG;
     if (n_wg < 1) n_wg = 1;
+    if (wide && n_wg > pool->wide_wg) n_wg = pool->wide_wg;
     if (scratch && n_wg > scratch->n_wg_cap) {
       odma::set_error(std::string(where) + ": the launch shape needs more work-groups than the static scratch holds");
       return ODMA_INVALID_ARG;
@@ -269,7 +268,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     StreamArgs a;
     a.k = ra.k;
     a.v = ra.v;
-    a.q = (const unsigned short*)q;
+    a.q = q;
     a.out = out;
     a.k_new = k_new;
     a.v_new = v_new;
@@ -297,8 +296,9 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     a.scale_log2 = fp8 ? scale_log2 * c.k_scale : scale_log2;
     a.out_scale = fp8 ? c.v_scale * (1.0f / 256.0f) : 1.0f;
     a.head_dim = c.head_dim;
+    a.ch = f.ch;
     a.out_bf16 = c.out_dtype == ODMA_BF16;
-    const int tile_tokens = (fp8 || d64) ? 2 * BLK : BLK;
+    const int tile_tokens = f.blocks * BLK;
     // A plan bakes in the slab bases and the launch shape, so ODMA_REUSE_PLAN is honoured only while the library
     // knows of nothing that changed them; otherwise the call plans again.
     const int q_min = pool->min_chunk ? (pool->min_chunk + tile_tokens - 1) / tile_tokens : 4;
@@ -319,7 +319,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
                        was.tile_tokens == now.tile_tokens && was.odd_w == now.odd_w && was.late_w == now.late_w;
     // A call that plans does so inside the attention launch while the batch's table is small (STREAM_INLINE_REQ) and
     // fits beside the wave's queues; larger batches take a planning launch of their own.
-    size_t lds_bytes = stream_lds_bytes(G, wpw, qs, aq);
+    size_t lds_bytes = stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq);
     a.plan_at = -1;
     a.q_min = q_min;
     a.odd_xcd_weight = now.odd_w;
@@ -336,11 +336,10 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
       stamp = now;
     }
     const int nbuf = pool->pipeline_depth;
-    const int fmt = d64 ? STREAM_BF16_D64 : fp8 ? STREAM_FP8_D128 : STREAM_BF16_D128;
     hipError_t e = launch_stream_kernel(fmt, fused, block_table != nullptr, nbuf, wpw, n_wg, lds_bytes, s, a);
     if (e != hipSuccess) return hip_fail(where, e);
     if (!pool->fuse_reduce && !(flags & ODMA_SKIP_REDUCE))
-      hipLaunchKernelGGL(stream_reduce_kernel, dim3(n_wg * G), dim3(128), 0, s, a, n_wg);
+      hipLaunchKernelGGL(stream_reduce_kernel, dim3(n_wg * G), dim3(f.ch), 0, s, a, n_wg);
   } else {
     // ---- chunked scheme: plan -> attention (one wave per (request, head, chunk)) -> reduce
     DecodeArgs a;

@@ -188,6 +188,23 @@ WorkspaceLayout workspace_layout(const odma_pool_config_t& c) {
   return w;
 }
 
+int wide_layout(const odma_pool_config_t& c, size_t bytes, WorkspaceLayout* out) {
+  constexpr int MOST = 256, LEAST = 16;    // work-groups: one per compute unit; with fewer than 16 the chunked kernel serves
+  for (int n_wg = MOST; n_wg >= LEAST; n_wg -= 16) {
+    const odma_plan::StreamLayout s = odma_plan::stream_layout(0, c.max_requests, n_wg, c.n_q_heads, c.head_dim);
+    if (s.end > bytes) continue;
+    out->items = s.items;
+    out->waves = s.waves;
+    out->red = s.red;
+    out->arrive = s.arrive;
+    out->part_ml = s.part_ml;
+    out->part_o = s.part_o;
+    out->total = s.end;
+    return n_wg;
+  }
+  return 0;
+}
+
 int resolve_decode_kernel(const odma_pool_config_t& c) {
   if (c.decode_kernel != ODMA_KERNEL_AUTO) return c.decode_kernel;
   const bool mfma = (c.kv_dtype == ODMA_BF16 && (c.head_dim == 128 || c.head_dim == 64)) || (c.kv_dtype == ODMA_FP8 && c.head_dim == 128);
@@ -323,6 +340,8 @@ int odma_pool_create(const odma_pool_config_t* cfg, odma_pool_t** out) {
   cal.hist.assign(cfg->large_cap / cfg->align_tokens, 0);
   p->ws = workspace_layout(*cfg);
   p->decode_kernel = resolve_decode_kernel(*cfg);
+  if (cfg->decode_kernel == ODMA_KERNEL_AUTO && p->decode_kernel == ODMA_KERNEL_VALU)
+    p->wide_wg = wide_layout(*cfg, p->ws.total, &p->wide);
   p->pool_blocks = (cfg->main_tokens + cfg->safety_tokens) / ODMA_BLOCK_TOKENS;
   p->elem_bytes = cfg->kv_dtype == ODMA_FP8 ? 1 : cfg->kv_dtype == ODMA_BF16 ? 2 : 4;
   if (p->cfg.k_scale == 0.0f) p->cfg.k_scale = 1.0f;

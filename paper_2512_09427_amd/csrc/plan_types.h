@@ -104,11 +104,12 @@ ODMA_HD inline StreamShares stream_shares(int total, int n_waves, int wpw, int q
 }
 
 // Byte offsets of the regions of a tile-stream workspace sized for max_requests requests, n_wg_cap attention
-// work-groups and n_q_heads query heads (partial states keep 128 channels per head).
+// work-groups and n_q_heads query heads (partial states keep `channels` channels per head).
 struct StreamLayout {
   size_t header, req_info, items, waves, red, arrive, part_ml, part_o, end;   // (header and req_info: unused, kept so that the size stays)
 };
-ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int64_t n_wg_cap, int64_t n_q_heads) {
+ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int64_t n_wg_cap, int64_t n_q_heads,
+                                          int64_t channels = 128) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   StreamLayout w;
   w.header = off;   off += 256;
@@ -119,7 +120,7 @@ ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int6
   w.arrive = off;   // one 64-bit counter per boundary of a launch
   off += up((size_t)((n_wg_cap < STREAM_MAX_LAUNCH_WG ? n_wg_cap : STREAM_MAX_LAUNCH_WG) + 1) * sizeof(int64_t));
   w.part_ml = off;  off += up((size_t)2 * n_wg_cap * n_q_heads * 2 * sizeof(float));
-  w.part_o = off;   off += up((size_t)2 * n_wg_cap * n_q_heads * 128 * sizeof(float));
+  w.part_o = off;   off += up((size_t)2 * n_wg_cap * n_q_heads * channels * sizeof(float));
   w.end = off;
   return w;
 }

@@ -1,0 +1,102 @@
+"""Decode of fp32 pools and of bf16 pools with a head_dim other than 64 and 128, every head_dim, on the tile-stream kernel
+(what ODMA_KERNEL_AUTO takes): attention, fused steps across block boundaries with the rows read back, both layouts, the
+largest group, the separate reduction, workspaces too small for it, and the vector-ALU kernel beside it.
+
+Bound: products and sums are fp32 (bf16 products are exact in it) and the weights keep 24 bits, so both kernels stay
+within 1e-5 + 1e-5 |oracle|, the bound the suite uses for fp32 pools."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from paper_2512_09427_amd import binding as B
+from tests import harness as H
+from tests.test_gpu_parity import small_workload
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = [("f32", d) for d in range(32, 257, 32)] + [("bf16", d) for d in (32, 96, 160, 192, 224, 256)]
+TOL = (1e-5, 1e-5)
+
+
+def make(lens, kvd, d, hq, hkv, extra=0, paged=False, sharp=True, **pool_args):
+    lens = np.asarray(lens, np.int64)
+    w = small_workload(lens, kv_dtype=kvd, hq=hq, hkv=hkv, d=d, seed=d, bounds=(96, 1024, 4096),
+                       main=65536)
+    dp = H.make_pool(w, out_dtype=B.F32, **pool_args)
+    kv = [wl.request_kv(w, 0, r, n_tokens=int(lens[r]) + extra, sharp=sharp) for r in range(len(lens))]
+    held = [(k[:n], v[:n]) for (k, v), n in zip(kv, lens)]
+    where = dict(block_table=wl.shuffled_block_table(lens + extra, w.pool_tokens // 16, 16, seed=5)) if paged else \
+        dict(offsets=H.assign_perfect(dp, np.maximum(lens + extra, 1))[0])
+    H.fill(dp, 0, held, **where)
+    return w, dp, lens, kv, held, where
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("kvd,d", FORMATS)
+def test_attention(kvd, d, paged):
+    w, dp, lens, _, kv, where = make([0, 1, 15, 16, 17, 31, 32, 33, 700, 2500, 48], kvd, d, 14, 2, paged=paged)
+    q = wl.queries(w, 0, sharp=True)
+    ref = H.oracle_out(w, q, kv)
+    ref[lens == 0] = 0.0
+    got = H.decode(dp, 0, q, lens, **where)
+    H.check(got, ref, *TOL, what=f"{kvd} {d}")
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, flags=B.REUSE_PLAN, **where), got)
+    dp.pool.odma_pool_tune(B.TUNE_FUSE_REDUCE, 0)
+    H.check(H.decode(dp, 0, q, lens, **where), ref, *TOL, what=f"{kvd} {d}, separate reduction")
+
+
+@pytest.mark.parametrize("kvd,d", FORMATS)
+def test_fused_steps(kvd, d):
+    steps = 18
+    lens0 = np.array([0, 1, 14, 15, 16, 30, 31, 600], np.int64)
+    for paged in (False, True):
+        w, dp, lens, kv, _, where = make(lens0, kvd, d, 3, 1, extra=steps, paged=paged)
+        lens = lens.copy()
+        for s in range(steps):
+            k_new = np.stack([kv[r][0][lens[r]] for r in range(len(lens))])
+            v_new = np.stack([kv[r][1][lens[r]] for r in range(len(lens))])
+            lens += 1
+            q = wl.queries(w, 0, step=s, sharp=True)
+            got = H.decode_step(dp, 0, q, k_new, v_new, lens, **where)
+            H.check(got, H.oracle_out(w, q, [(k[:n], v[:n]) for (k, v), n in zip(kv, lens)]), *TOL, what=f"{kvd} {d} step {s}")
+        for r in (0, 3, 5, 7):
+            at = dict(block_row=where["block_table"][r]) if paged else {}
+            gk, gv = H.gather(dp, 0, 0 if paged else int(where["offsets"][r]), int(lens[r]), **at)
+            np.testing.assert_array_equal(gk, kv[r][0][:lens[r]])
+            np.testing.assert_array_equal(gv, kv[r][1][:lens[r]])
+
+
+@pytest.mark.parametrize("kvd,d", [("f32", 256), ("f32", 64), ("bf16", 256), ("bf16", 32)])
+def test_largest_group_and_many_requests(kvd, d):
+    rng = np.random.default_rng(d)
+    w, dp, lens, _, kv, where = make(rng.integers(0, 90, 200), kvd, d, 16, 1)
+    q = wl.queries(w, 0, sharp=True)
+    ref = H.oracle_out(w, q, kv)
+    ref[lens == 0] = 0.0
+    H.check(H.decode(dp, 0, q, lens, **where), ref, *TOL, what=f"{kvd} {d}")
+
+
+@pytest.mark.parametrize("max_splits", [1, 40, 400, 0])
+def test_small_workspaces(max_splits):
+    """The workspace is sized by max_splits; whatever kernel it leaves room for must serve the call."""
+    w, dp, lens, _, kv, where = make([4000, 3, 900], "f32", 64, 4, 2, max_splits=max_splits)
+    q = wl.queries(w, 0, sharp=True)
+    dp.workspace.fill_(0xff)
+    H.check(H.decode(dp, 0, q, lens, **where), H.oracle_out(w, q, kv), *TOL, what=f"max_splits={max_splits}")
+
+
+@pytest.mark.parametrize("kvd,d", [("f32", 64), ("f32", 128), ("bf16", 96), ("bf16", 256)])
+def test_no_less_exact_than_the_vector_kernel(kvd, d):
+    """Scores of standard deviation one, as a model has them: near-uniform softmax over long requests, where the order of
+    the sums shows most."""
+    errs = []
+    for kernel in (B.KERNEL_VALU, B.KERNEL_AUTO):
+        w, dp, lens, _, kv, where = make([3000, 777, 64, 2048], kvd, d, 8, 2, decode_kernel=kernel)
+        assert dp.pool.odma_pool_decode_kernel() == B.KERNEL_VALU
+        q = wl.queries(w, 0, sharp=True)
+        ref = H.oracle_out(w, q, kv)
+        got = H.decode(dp, 0, q, lens, **where)
+        H.check(got, ref, *TOL, what=f"{kvd} {d} kernel {kernel}")
+        errs.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(f"{kvd} {d}: relative error vector kernel {errs[0]:.2e}, matrix cores {errs[1]:.2e}")
+    assert errs[1] <= 1.2 * errs[0] + 1e-8
