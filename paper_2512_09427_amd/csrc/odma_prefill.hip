@@ -62,7 +62,8 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
   hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
                      c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);
-  const dim3 grid(pool->n_cu * (ct == 2 ? 2 : 1));
+  const int slots = pool->n_cu * (ct == 2 ? 2 : 1);
+  const dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
   switch ((fp8 ? 4 : 0) + (ct == 2 ? 2 : 0) + (block_table ? 1 : 0)) {
     case 0: hipLaunchKernelGGL((prefill_kernel<false, 4, false>), grid, dim3(256), 0, s, a); break;
     case 1: hipLaunchKernelGGL((prefill_kernel<true, 4, false>), grid, dim3(256), 0, s, a); break;

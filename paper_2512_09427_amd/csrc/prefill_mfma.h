@@ -30,7 +30,7 @@ constexpr double PREFILL_ITEM_COST = 5.0;   // start and end of an item, in K/V 
 
 struct PrefillHeader {
   int32_t bound[PREFILL_XCDS + 1];          // items [bound[x], bound[x + 1]) are queue x
-  int32_t next[PREFILL_XCDS];               // queue cursors, reset by the plan kernel
+  int32_t next[PREFILL_XCDS];               // runs claimed of every queue beyond the first of each work-group, reset by the plan
   int32_t avg_pairs;                        // mean cost of an item
 };
 
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
     all_items += part_items[i];
   }
   if (tid == 0) {
-    hdr->bound[0] = hdr->next[0] = 0;
+    hdr->bound[0] = 0;
     hdr->bound[PREFILL_XCDS] = item_start[n] = all_items;
     hdr->avg_pairs = (int)(all_cost / max(all_items, 1));
   }
@@ -153,11 +153,12 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
         const int g = min(max((int)(t / per_head), 0), Hkv - 1);
         // blocks run from the last one (the dearest) down: those that cost t come after those that cost the rest
         const int left = min(max(pc.block_at(fmax(per_head - (t - g * per_head), 0.0)), 0), nb);
-        hdr->bound[x] = hdr->next[x] = first + g * nb + nb - left;
+        hdr->bound[x] = first + g * nb + nb - left;
       }
     });
   }
-  if (all_items == 0 && tid < PREFILL_XCDS) hdr->bound[tid] = hdr->next[tid] = 0;
+  if (all_items == 0 && tid < PREFILL_XCDS) hdr->bound[tid] = 0;
+  if (tid < PREFILL_XCDS) hdr->next[tid] = 0;
 }
 
 // LDS stage of one pair of tiles (32 tokens): K of both tiles as loaded (the 16x16x32 A operands of
@@ -197,26 +198,34 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   const char* src_base = loads_v ? a.v : a.k;
   const unsigned lane16 = lane * 16;
 
-  // Work queue: a counter in memory answers about 14 M requests a second on this part -- with thousands of small items
-  // that alone would bound the kernel.  A work-group therefore takes a run of consecutive items per request, long enough
-  // to stream about 64 K/V pairs (some 40 us) but never more than an eighth of its share of the items, so that large
-  // items still balance one by one; and it asks one run ahead: the answer travels while the current run is computed.
+  // Work queues.  A counter in memory answers about 14 M requests a second on this part -- with thousands of small items
+  // that alone would bound the kernel.  A work-group therefore takes runs of consecutive items, long enough to stream
+  // about 64 K/V pairs (some 40 us) but never more than an eighth of its share of the items, so that large items still
+  // balance one by one; its first run is its turn's (no counter is touched when that is all there is), and it asks for the
+  // next one a run ahead: the answer travels while the current run is computed.
   const int n_items = a.hdr->bound[PREFILL_XCDS];
   const int run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
+  const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
+  const int q_at = a.hdr->bound[min(lane, PREFILL_XCDS - 1)], q_end = a.hdr->bound[min(lane, PREFILL_XCDS - 1) + 1];   // lane x: queue x
+  const unsigned long long longer = __builtin_amdgcn_ballot_w64(lane < PREFILL_XCDS && q_end - q_at > turns * run);
   int queue = blockIdx.x % PREFILL_XCDS;                               // (work-group b runs on XCD b % 8)
-  const int q_end = a.hdr->bound[min(lane, PREFILL_XCDS - 1) + 1];     // lane x: end of queue x
   int ahead = 0;
   auto claim = [&]() {
-    if (threadIdx.x == 0) ahead = atomicAdd(&a.hdr->next[queue], run);
+    if (threadIdx.x == 0) ahead = atomicAdd(&a.hdr->next[queue], 1);
   };
-  claim();
-  // wave 0: the next run of items, in run_slot (empty when the call is over)
+  // wave 0: the run after the present one, in run_slot (empty when the call is over).  With its own queue empty a
+  // work-group goes on with the fullest one that was longer than its work-groups' first runs.
+  bool claimed = false;
   auto settle = [&]() {
-    int start = rfl(ahead), end = __builtin_amdgcn_readlane(q_end, queue);
-    while (start >= end) {
+    int start = 0, end = 0;
+    if (claimed) {
+      end = __builtin_amdgcn_readlane(q_end, queue);
+      start = min(__builtin_amdgcn_readlane(q_at, queue) + (turns + rfl(ahead)) * run, end);
+    }
+    while (start >= end && longer != 0) {
       int left = 0;
       if (lane < PREFILL_XCDS)
-        left = q_end - __hip_atomic_load(&a.hdr->next[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        left = q_end - q_at - (turns + __hip_atomic_load(&a.hdr->next[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) * run;
       int most = max(left, 0);
 #pragma unroll
       for (int o = 1; o < PREFILL_XCDS; o <<= 1) most = max(most, __shfl_xor(most, o));
@@ -224,23 +233,29 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       if (most == 0) break;
       queue = __builtin_ctzll(__builtin_amdgcn_ballot_w64(left == most));
       claim();
-      start = rfl(ahead);
       end = __builtin_amdgcn_readlane(q_end, queue);
+      start = min(__builtin_amdgcn_readlane(q_at, queue) + (turns + rfl(ahead)) * run, end);
     }
     if (lane == 0) {
       run_slot[0] = start;
       run_slot[1] = min(start + run, end);
     }
-    if (start < end) claim();
+    claimed = start < end && ((longer >> queue) & 1) != 0;
+    if (claimed) claim();
   };
+  int next = __builtin_amdgcn_readlane(q_at, queue) + (int)(blockIdx.x / PREFILL_XCDS) * run;
+  int run_end = min(next + run, __builtin_amdgcn_readlane(q_end, queue));
+  if (wv == 0 && next < run_end && ((longer >> queue) & 1) != 0) {
+    claimed = true;
+    claim();
+  }
   const bool small = a.n <= PREFILL_LDS_REQ;
   if (small)
     for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
-  int next = 0, run_end = 0;
   for (;;) {
     // ---- next item (every wave reaches the exit together)
     __syncthreads();                                       // the previous item's slot and stages are done with
-    if (next == run_end) {
+    if (next >= run_end) {
       if (wv == 0) settle();
       __syncthreads();
       next = rfl(run_slot[0]);
