@@ -69,7 +69,8 @@ int odma_gather_kv(odma_pool_t* pool, int32_t layer, int64_t offset, int32_t len
     return ODMA_INVALID_ARG;
   }
   RowArgs a = row_args(pool, layer);
-  dim3 grid(length < 4096 ? length : 4096);
+  const int groups = (length + BLK - 1) / BLK;
+  const dim3 grid(pool->elem_bytes == 1 ? (length < 4096 ? length : 4096) : (groups < 4096 ? groups : 4096));
   hipStream_t s = (hipStream_t)stream;
   if (pool->elem_bytes == 1)
     hipLaunchKernelGGL(gather_fp8_kernel, grid, dim3(256), 0, s, a, offset, length, block_row, (unsigned char*)k_out,
