@@ -389,7 +389,8 @@ int odma_pool_tune(odma_pool_t* pool, int32_t knob, int32_t value);
  * waves_per_wg = 4 or 8) streams [start[w], start[w + 1]).  min_tiles: fewest tiles per wave before fewer waves
  * are used; weights as for ODMA_TUNE_ODD_XCD_WEIGHT / _LATE_WAVE_WEIGHT.  start: host int32[n_waves + 1];
  * waves_used: nullable.  Guarantee that the attention kernel depends on: among the used waves the empty ranges
- * come first (no empty range lies between two ranges that hold tiles). */
+ * come first (no empty range lies between two ranges that hold tiles).  (A small batch may be cut at its segments
+ * instead, one work-group each: then every work-group's ranges follow the same guarantee.) */
 int odma_stream_plan_ranges(int32_t total_tiles, int32_t n_waves, int32_t waves_per_wg, int32_t min_tiles,
                             int32_t odd_xcd_weight, int32_t late_wave_weight, int32_t* start, int32_t* waves_used);
 

@@ -57,6 +57,7 @@ struct StreamArgs {
   const int64_t* offsets;    // nullptr when paged
   int32_t plan_at;           // -1: the plan is in memory; else float offset of the planning area in LDS
   int32_t q_min, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (StreamShares)
+  int32_t whole_extra;       // tiles beyond an equal share that a wave may get in order that no segment is cut (-1: never)
   unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
   int32_t fuse_reduce;       // 1: the last work-group to finish a cut segment merges it; 0: stream_reduce_kernel does
   float2* part_ml;           // [2 * n_workgroups][Hq]
@@ -215,9 +216,16 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
 // ---------------------------------------------------------------------------------
 constexpr int STREAM_INLINE_REQ = 1024;
 constexpr int STREAM_INLINE_WG = 512;
+// A batch with no more (request, KV head) segments than work-groups is cut at its segments instead -- one work-group each,
+// whose waves heal the cuts between them in LDS -- if that gives no wave more than STREAM_MERGE_TILES tiles beyond an equal
+// share: nothing is left to merge through memory then (store, acknowledgement, counter, partial loads, all behind the last
+// tile), which is worth about that many tiles.  Bf16, 4 KV heads, equal shares -> whole segments: 16 requests of 100 to 133
+// tokens 13.3 -> 9.9 us, 60 of them 14.0 -> 10.4, 60 of 400 to 533 tokens 20.5 -> 16.2; but one of 900 tokens, where the
+// equal shares are a sixth of a segment's, 13.5 -> 16.0: it keeps equal shares.
+constexpr int STREAM_MERGE_TILES = 5;
 struct InlinePlan {          // LDS table: SoA over the non-empty requests, in batch order
-  int* wave_tot;             // [2 * waves]: tiles, entries per wave
-  int* info;                 // total tiles, entries, waves used
+  int* wave_tot;             // [3 * waves]: tiles, entries, longest request per wave
+  int* info;                 // total tiles, entries, waves used, whether work-groups take whole segments
   int* wg_pos;               // [n_wg + 1] first tile of every work-group
   int* first;                // [n] first tile of the entry
   int* r;
@@ -227,7 +235,7 @@ struct InlinePlan {          // LDS table: SoA over the non-empty requests, in b
   int* wave_desc;            // [waves][12]: the waves' descriptors, stored at the end
   __device__ InlinePlan(float* lds, int at, int wpw, int n_wg, int n) {
     wave_tot = (int*)lds + at;
-    info = wave_tot + 2 * wpw;
+    info = wave_tot + 3 * wpw;
     wave_desc = info + 4;
     wg_pos = wave_desc + 12 * wpw;
     first = wg_pos + n_wg + 1;
@@ -237,7 +245,7 @@ struct InlinePlan {          // LDS table: SoA over the non-empty requests, in b
     base_block = len + n;
   }
 };
-__host__ __device__ inline int stream_inline_ints(int wpw, int n_wg, int n) { return 14 * wpw + 4 + n_wg + 1 + 5 * n; }
+__host__ __device__ inline int stream_inline_ints(int wpw, int n_wg, int n) { return 15 * wpw + 4 + n_wg + 1 + 5 * n; }
 
 // number of leading elements of the non-decreasing table tab[0 .. n) that are <= x (wave-uniform x)
 __device__ __forceinline__ int count_le(const int* tab, int n, int x) {
@@ -265,12 +273,13 @@ __device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlineP
     ln[k] = in ? a.lengths[r0 + k] : 0;
     base[k] = in && a.offsets ? (int)(a.offsets[r0 + k] / BLK) : 0;
   }
-  int loc_tiles = 0, loc_cnt = 0;
+  int loc_tiles = 0, loc_cnt = 0, longest = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     ln[k] = max(ln[k], 0);
     loc_tiles += (ln[k] + TT - 1) / TT;
     loc_cnt += ln[k] > 0;
+    longest = max(longest, (ln[k] + TT - 1) / TT);
   }
   int inc_tiles = loc_tiles, inc_cnt = loc_cnt;
 #pragma unroll
@@ -280,16 +289,19 @@ __device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlineP
       inc_tiles += yt;
       inc_cnt += yc;
     }
+    longest = max(longest, __shfl_xor(longest, o));
   }
   if (lane == 63) {
-    pl.wave_tot[2 * wv] = inc_tiles;
-    pl.wave_tot[2 * wv + 1] = inc_cnt;
+    pl.wave_tot[3 * wv] = inc_tiles;
+    pl.wave_tot[3 * wv + 1] = inc_cnt;
+    pl.wave_tot[3 * wv + 2] = longest;
   }
   __syncthreads();
   int run_tiles = inc_tiles - loc_tiles, run_cnt = inc_cnt - loc_cnt, sum_tiles = 0, n_entries = 0;
 #pragma unroll
   for (int i = 0; i < WPW; ++i) {
-    const int t = pl.wave_tot[2 * i], c = pl.wave_tot[2 * i + 1];
+    const int t = pl.wave_tot[3 * i], c = pl.wave_tot[3 * i + 1];
+    longest = max(longest, pl.wave_tot[3 * i + 2]);
     run_tiles += i < wv ? t : 0;
     run_cnt += i < wv ? c : 0;
     sum_tiles += t;
@@ -310,13 +322,23 @@ __device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlineP
   const int total = sum_tiles * a.Hkv;
   const odma_plan::StreamShares shares =
       odma_plan::stream_shares(total, n_wg * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
-  for (int b = tid; b <= n_wg; b += T) pl.wg_pos[b] = shares.start(b * WPW);
+  const int n_seg = n_entries * a.Hkv;
+  const bool whole = a.whole_extra >= 0 && n_seg <= n_wg &&
+                     (long long)longest * shares.used <= WPW * (total + (long long)a.whole_extra * shares.used);
+  if (!whole)
+    for (int b = tid; b <= n_wg; b += T) pl.wg_pos[b] = shares.start(b * WPW);
   if (tid == 0) {
     pl.info[0] = total;
     pl.info[1] = n_entries;
-    pl.info[2] = shares.used;
+    pl.info[2] = whole ? n_seg * WPW : shares.used;
+    pl.info[3] = whole;
   }
   __syncthreads();
+  if (whole)                                               // (read in the epilogue, behind the next barrier)
+    for (int b = tid; b <= n_wg; b += T) {
+      const int e = b / a.Hkv;
+      pl.wg_pos[b] = b < n_seg ? pl.first[e] + (b - e * a.Hkv) * pl.tiles[e] : total;
+    }
 }
 
 // this wave's range and its first entry
@@ -324,17 +346,30 @@ template <int WPW>
 __device__ __forceinline__ WaveDesc inline_wave_desc(const StreamArgs& a, const InlinePlan& pl) {
   const int lane = threadIdx.x & 63, wv = rfl(threadIdx.x >> 6);
   const int total = rfl(pl.info[0]), n_entries = rfl(pl.info[1]);
-  const odma_plan::StreamShares shares =
-      odma_plan::stream_shares(total, gridDim.x * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
-  const int at = shares.start(blockIdx.x * WPW + wv + (lane & 1));   // even lanes: the start, odd lanes: the end
   WaveDesc wd;
-  wd.pos_start = __builtin_amdgcn_readlane(at, 0);
-  wd.pos_end = __builtin_amdgcn_readlane(at, 1);
   wd.entry0 = 0;
   wd.n_entries = n_entries;
   wd.r = wd.tiles = wd.first_pos = wd.len = wd.base_block = wd.r_next = wd.pad1 = wd.pad2 = 0;
+  int e = 0;
+  if (rfl(pl.info[3])) {
+    // segment b, its tiles in equal parts; with fewer tiles than waves the empty parts on the left (see StreamShares)
+    const int seg = blockIdx.x;
+    wd.pos_start = wd.pos_end = total;
+    if (seg < n_entries * a.Hkv) {
+      e = seg / a.Hkv;
+      const int t = rfl(pl.tiles[e]), at = rfl(pl.first[e]) + (seg - e * a.Hkv) * t;
+      wd.pos_start = at + (t < WPW ? max(t - (WPW - wv), 0) : t * wv / WPW);
+      wd.pos_end = at + (t < WPW ? max(t - (WPW - wv - 1), 0) : t * (wv + 1) / WPW);
+    }
+  } else {
+    const odma_plan::StreamShares shares =
+        odma_plan::stream_shares(total, gridDim.x * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
+    const int at = shares.start(blockIdx.x * WPW + wv + (lane & 1));   // even lanes: the start, odd lanes: the end
+    wd.pos_start = __builtin_amdgcn_readlane(at, 0);
+    wd.pos_end = __builtin_amdgcn_readlane(at, 1);
+    if (wd.pos_start < wd.pos_end) e = count_le(pl.first, n_entries, wd.pos_start) - 1;
+  }
   if (wd.pos_start < wd.pos_end) {
-    const int e = count_le(pl.first, n_entries, wd.pos_start) - 1;
     wd.entry0 = e;
     wd.r = rfl(pl.r[e]);
     wd.tiles = rfl(pl.tiles[e]);

@@ -323,6 +323,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     size_t lds_bytes = stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq);
     a.plan_at = -1;
     a.q_min = q_min;
+    a.whole_extra = pool->min_chunk ? -1 : STREAM_MERGE_TILES;   // (a pool with a tuned minimum keeps equal shares)
     a.odd_xcd_weight = now.odd_w;
     a.late_wave_weight = now.late_w;
     if (!reuse) {

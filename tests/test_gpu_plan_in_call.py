@@ -107,3 +107,20 @@ def test_planning_call_in_a_replayed_graph():
         torch.cuda.synchronize()
         got = out.cpu().numpy().copy()
         np.testing.assert_array_equal(got, H.decode(dp, 0, q, now, offsets=off))
+
+
+@pytest.mark.parametrize("wpw", [4, 8])
+@pytest.mark.parametrize("lens", [
+    [1], [16], [17, 33, 49, 64],                             # fewer tiles than waves: empty parts on the left
+    list(range(1, 65)),                                      # 128 segments of one to four tiles
+    [300] * 60, [575, 576, 577],                             # near the longest segment that one work-group takes
+    [5] * 128, [5] * 129,                                    # as many segments as work-groups, and two more
+    [0, 40, 0, 0, 2000, 16],                                 # one long request: equal shares
+])
+def test_small_batches_cut_at_their_segments_or_not(lens, wpw):
+    dp, q, lens, off, ref = make(lens, seed=77, main=65536)
+    dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_WG, wpw)
+    dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_CU, wpw)         # one work-group per compute unit
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    H.check(got, ref, *TIGHT_F32, what=str(lens[:6]))
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
