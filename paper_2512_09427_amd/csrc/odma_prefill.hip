@@ -60,20 +60,21 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // column tiles per wave: 2 (128-column items, two work-groups per CU whose LDS and matrix phases overlap)
   // measured faster than 4 (256-column items, one work-group per CU) on every prompt mix tried
   const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
-  hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
-                     c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);
   const int slots = pool->n_cu * (ct == 2 ? 2 : 1);
   const dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
-  switch ((fp8 ? 4 : 0) + (ct == 2 ? 2 : 0) + (block_table ? 1 : 0)) {
-    case 0: hipLaunchKernelGGL((prefill_kernel<false, 4, false>), grid, dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL((prefill_kernel<true, 4, false>), grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((prefill_kernel<false, 2, false>), grid, dim3(256), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((prefill_kernel<true, 2, false>), grid, dim3(256), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((prefill_kernel<false, 4, true>), grid, dim3(256), 0, s, a); break;
-    case 5: hipLaunchKernelGGL((prefill_kernel<true, 4, true>), grid, dim3(256), 0, s, a); break;
-    case 6: hipLaunchKernelGGL((prefill_kernel<false, 2, true>), grid, dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((prefill_kernel<true, 2, true>), grid, dim3(256), 0, s, a); break;
-  }
+  // Few items -- no more than work-groups, counted from the rows of q (rows that several requests share only make more of
+  // them): planned in the attention launch.  With more, the work-groups balance through counters, which a planning launch
+  // clears.
+  const int64_t items = (total_q * a.G + 64 * ct - 1) / (64 * ct) * a.Hkv + (int64_t)n * a.Hkv;
+  const bool here = n <= PREFILL_LDS_REQ && items <= (int64_t)grid.x;
+  if (!here)
+    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
+                       c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);
+  // [fp8][two column tiles][paged][planned here]
+#define ODMA_PREFILL(P, CT, F) {prefill_kernel<P, CT, F, false>, prefill_kernel<P, CT, F, true>}
+#define ODMA_PREFILL_F(F) {{ODMA_PREFILL(false, 4, F), ODMA_PREFILL(true, 4, F)}, {ODMA_PREFILL(false, 2, F), ODMA_PREFILL(true, 2, F)}}
+  static void (*const kernels[2][2][2][2])(PrefillArgs) = {ODMA_PREFILL_F(false), ODMA_PREFILL_F(true)};
+  hipLaunchKernelGGL(kernels[fp8][ct == 2][block_table != nullptr][here], grid, dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(where, e);
   return ODMA_OK;

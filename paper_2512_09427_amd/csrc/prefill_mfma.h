@@ -46,7 +46,7 @@ struct PrefillArgs {
   const int32_t* bt;
   int32_t bt_stride;
   PrefillHeader* hdr;
-  int32_t* item_start;       // [n + 1] exclusive prefix of items per request
+  int32_t* item_start;       // [n] exclusive prefix of items per request
   int32_t n, Hq, Hkv, G;
   int64_t total_q;           // rows of q and out: rows at or past it are never touched
   int64_t head_stride;
@@ -81,21 +81,22 @@ __device__ __forceinline__ int prefill_blocks(int rows, int G, int cols_item) {
   return (int)(((int64_t)rows * G + cols_item - 1) / cols_item);
 }
 
-// one work-group: exclusive prefix of items per request, and the eight queues of equal cost
-__global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(const int32_t* __restrict__ n_q,
-                                                                           const int32_t* __restrict__ lengths,
-                                                                           const int64_t* __restrict__ q_start,
-                                                                           int64_t total_q, int32_t n, int32_t Hkv, int32_t G,
-                                                                           int32_t cols_item, PrefillHeader* hdr,
-                                                                           int32_t* item_start) {
-  __shared__ double part_cost[PREFILL_PLAN_THREADS / 64];
-  __shared__ int part_items[PREFILL_PLAN_THREADS / 64];
+// One work-group of PREFILL_PLAN_THREADS: exclusive prefix of items per request (item_start[0 .. n)), and in `pl` the bounds of
+// the eight queues of equal cost.  Ends with a barrier.
+struct PrefillPlan {
+  double part_cost[PREFILL_PLAN_THREADS / 64];
+  int part_items[PREFILL_PLAN_THREADS / 64];
+  int bound[PREFILL_XCDS + 1], avg_pairs;
+};
+__device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* lengths, const int64_t* q_start, int64_t total_q,
+                                             int32_t n, int32_t Hkv, int32_t G, int32_t cols_item, PrefillPlan& pl,
+                                             int32_t* item_start) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (n + PREFILL_PLAN_THREADS - 1) / PREFILL_PLAN_THREADS;
   const int r0 = min(tid * per, n), r1 = min(r0 + per, n);
   double cost = 0;
   int items = 0;
-  auto add = [&](int r, auto&& at) {                        // at(cost and items before r, blocks of r, its cost rule)
+  auto add = [&](int r, auto&& at) {                        // at(blocks of r, its cost rule), then past r
     const int rows = prefill_rows(n_q, lengths, q_start, total_q, r);
     const int nb = prefill_blocks(rows, G, cols_item);
     const PrefillCost pc(lengths[r] - rows, cols_item, G);
@@ -116,8 +117,8 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
     }
   }
   if (lane == 63) {
-    part_cost[wv] = inc_cost;
-    part_items[wv] = inc_items;
+    pl.part_cost[wv] = inc_cost;
+    pl.part_items[wv] = inc_items;
   }
   __syncthreads();
   double all_cost = 0;
@@ -126,19 +127,17 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
   items = inc_items - items;
   for (int i = 0; i < PREFILL_PLAN_THREADS / 64; ++i) {
     if (i < wv) {
-      cost += part_cost[i];
-      items += part_items[i];
+      cost += pl.part_cost[i];
+      items += pl.part_items[i];
     }
-    all_cost += part_cost[i];
-    all_items += part_items[i];
+    all_cost += pl.part_cost[i];
+    all_items += pl.part_items[i];
   }
-  if (tid == 0) {
-    hdr->bound[0] = 0;
-    hdr->bound[PREFILL_XCDS] = item_start[n] = all_items;
-    hdr->avg_pairs = (int)(all_cost / max(all_items, 1));
-  }
-  // boundary x lies at cost all_cost * x / 8, inside the request whose cost range holds it (the first request with items
-  // also takes boundaries that rounding leaves before it, the last one those behind it)
+  // a boundary that rounding leaves to no thread keeps its share of the items
+  if (tid <= PREFILL_XCDS) pl.bound[tid] = (int)((long long)all_items * tid / PREFILL_XCDS);
+  if (tid == 0) pl.avg_pairs = (int)(all_cost / max(all_items, 1));
+  __syncthreads();
+  // boundary x lies at cost all_cost * x / 8, inside the request whose cost range holds it
   for (int r = r0; r < r1; ++r) {
     item_start[r] = items;
     const double before = cost;
@@ -148,17 +147,33 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
       const double per_head = pc.upto(nb);
       for (int x = 1; x < PREFILL_XCDS; ++x) {
         const double t = all_cost * x / PREFILL_XCDS - before;
-        const bool here = (t >= 0 || first == 0) && (t < Hkv * per_head || first + Hkv * nb == all_items);
-        if (!here) continue;
-        const int g = min(max((int)(t / per_head), 0), Hkv - 1);
+        if (t < 0 || t >= Hkv * per_head) continue;
+        const int g = min((int)(t / per_head), Hkv - 1);
         // blocks run from the last one (the dearest) down: those that cost t come after those that cost the rest
         const int left = min(max(pc.block_at(fmax(per_head - (t - g * per_head), 0.0)), 0), nb);
-        hdr->bound[x] = first + g * nb + nb - left;
+        pl.bound[x] = first + g * nb + nb - left;
       }
     });
   }
-  if (all_items == 0 && tid < PREFILL_XCDS) hdr->bound[tid] = 0;
+  __syncthreads();
+  if (tid == 0)                                             // (two threads' ranges may meet an ulp apart)
+    for (int x = 1; x <= PREFILL_XCDS; ++x) pl.bound[x] = min(max(pl.bound[x], pl.bound[x - 1]), all_items);
+  __syncthreads();
+}
+
+// the plan as a launch of its own: for calls with many items or requests
+__global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(const int32_t* __restrict__ n_q,
+                                                                           const int32_t* __restrict__ lengths,
+                                                                           const int64_t* __restrict__ q_start,
+                                                                           int64_t total_q, int32_t n, int32_t Hkv, int32_t G,
+                                                                           int32_t cols_item, PrefillHeader* hdr,
+                                                                           int32_t* item_start) {
+  __shared__ PrefillPlan pl;
+  prefill_plan(n_q, lengths, q_start, total_q, n, Hkv, G, cols_item, pl, item_start);
+  const int tid = threadIdx.x;
+  if (tid <= PREFILL_XCDS) hdr->bound[tid] = pl.bound[tid];
   if (tid < PREFILL_XCDS) hdr->next[tid] = 0;
+  if (tid == 0) hdr->avg_pairs = pl.avg_pairs;
 }
 
 // LDS stage of one pair of tiles (32 tokens): K of both tiles as loaded (the 16x16x32 A operands of
@@ -180,7 +195,9 @@ __device__ __forceinline__ unsigned fp8x2_to_bf16x2(unsigned w) {
 
 // FP8: the pools hold E4M3 bytes (2 KiB blocks in the fp8 operand order of the decode kernel); the loader waves
 // widen them to bf16 on the way into LDS and store them in the bf16 layout, everything after that is shared.
-template <bool PAGED, int CT, bool FP8>
+// HERE: the kernel plans for itself (a variant of its own: inside the other one the plan cost the pair loop registers, 254
+// for 242, and 2 to 7 % of every long call).
+template <bool PAGED, int CT, bool FP8, bool HERE>
 __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillArgs a) {
   constexpr int TILE_BYTES = BLK * 128 * (FP8 ? 1 : 2);
   constexpr int LOADS = TILE_BYTES / 1024;                         // 16-byte loads per lane and tile
@@ -203,11 +220,22 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // about 64 K/V pairs (some 40 us) but never more than an eighth of its share of the items, so that large items still
   // balance one by one; its first run is its turn's (no counter is touched when that is all there is), and it asks for the
   // next one a run ahead: the answer travels while the current run is computed.
-  const int n_items = a.hdr->bound[PREFILL_XCDS];
-  const int run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
+  //
+  // A call whose items are few (the launch's rule) plans here instead of in a launch in front -- six microseconds of one
+  // work-group's round trips and the edge between two launches -- and its work-groups take every `turns`-th item of their
+  // queue: no counter has to be clear before the launch.  7 prompts of 21 to
+  // 58 tokens 11.2 -> 8.9 us, 28 of 91 to 546 tokens 20.0 -> 18.3.
+  const int* bound = a.hdr->bound;
+  if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
+    __shared__ PrefillPlan plan;
+    prefill_plan(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
+    bound = plan.bound;
+  }
+  const int n_items = bound[PREFILL_XCDS];
+  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
-  const int q_at = a.hdr->bound[min(lane, PREFILL_XCDS - 1)], q_end = a.hdr->bound[min(lane, PREFILL_XCDS - 1) + 1];   // lane x: queue x
-  const unsigned long long longer = __builtin_amdgcn_ballot_w64(lane < PREFILL_XCDS && q_end - q_at > turns * run);
+  const int q_at = bound[min(lane, PREFILL_XCDS - 1)], q_end = bound[min(lane, PREFILL_XCDS - 1) + 1];   // lane x: queue x
+  const unsigned long long longer = HERE ? 0 : __builtin_amdgcn_ballot_w64(lane < PREFILL_XCDS && q_end - q_at > turns * run);
   int queue = blockIdx.x % PREFILL_XCDS;                               // (work-group b runs on XCD b % 8)
   int ahead = 0;
   auto claim = [&]() {
@@ -250,12 +278,18 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     claim();
   }
   const bool small = a.n <= PREFILL_LDS_REQ;
-  if (small)
+  if (small && !HERE)
     for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
+  int at = next;                                                       // first item of the present run
   for (;;) {
     // ---- next item (every wave reaches the exit together)
     __syncthreads();                                       // the previous item's slot and stages are done with
-    if (next >= run_end) {
+    if (HERE && next >= run_end) {
+      at += turns;
+      next = at;
+      run_end = at + 1;
+      if (next >= __builtin_amdgcn_readlane(q_end, queue)) break;
+    } else if (next >= run_end) {
       if (wv == 0) settle();
       __syncthreads();
       next = rfl(run_slot[0]);
