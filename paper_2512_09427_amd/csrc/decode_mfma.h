@@ -17,7 +17,8 @@
 // it reaches the end of its range, folds that state into its own registers and writes the
 // result.  Waves only ever wait for their right-hand neighbour, so the chain cannot
 // deadlock and needs no barrier.  Only pieces cut by a work-group boundary go to the HBM
-// workspace (at most two per work-group) and are merged by stream_reduce_kernel.
+// workspace (at most two per work-group) and are merged by the last work-group to arrive
+// at the segment, or by stream_reduce_kernel when the pool asks for a launch of its own.
 //
 // Per tile:  S^T[16 tok x 16 heads] = K_blk[16 x 128] * Q^T[128 x 16]     4 x mfma 16x16x32 bf16
 //            O^T[128 x 16 heads]   += V_blk^T[128 x 16 tok] * P^T[16 x 16] 8 x mfma 16x16x16 bf16
@@ -1175,7 +1176,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // arrive.  bf16: as head_dim 128, but P is carried as three bf16 parts (24 bits), so that no weight has fewer bits than
     // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
     // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
-    // 4.5 TB/s); 4 requests of config 1, fused step, 23.1 -> 11.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
+    // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 9.1 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
     auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
       const bool ragged = n_valid < TT;
