@@ -261,6 +261,23 @@ __device__ __forceinline__ int count_le(const int* tab, int n, int x) {
   return cnt;
 }
 
+// x of the lane CTRL away, 0 where that lane does not exist (all lanes active)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+// one step of a wave's inclusive scans of two sums and a maximum (>= 0): row shifts inside 16 lanes, then the last lane of
+// a row (0x142) or of two (0x143) to the rows behind it.  Six steps of vector arithmetic; through LDS permutes
+// (__shfl_up) each step is a dependent round trip, and the scan stands in front of the first tile of every launch: 0.3 us
+// of each (4 fp32 requests of 16 to 128 tokens 9.2 -> 8.9 us, one of 1777 tokens in bf16 13.3 -> 13.05, 60 of up to 500
+// 16.25 -> 15.9).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void scan_step(int& sum, int& cnt, int& top) {
+  sum += dpp_or_zero<CTRL, ROWS>(sum);
+  cnt += dpp_or_zero<CTRL, ROWS>(cnt);
+  top = max(top, dpp_or_zero<CTRL, ROWS>(top));
+}
+
 template <int WPW, int TT>
 __device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlinePlan& pl) {
   constexpr int T = 64 * WPW, PER = STREAM_INLINE_REQ / T;
@@ -283,16 +300,13 @@ __device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlineP
     longest = max(longest, (ln[k] + TT - 1) / TT);
   }
   int inc_tiles = loc_tiles, inc_cnt = loc_cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int yt = __shfl_up(inc_tiles, o), yc = __shfl_up(inc_cnt, o);
-    if (lane >= o) {
-      inc_tiles += yt;
-      inc_cnt += yc;
-    }
-    longest = max(longest, __shfl_xor(longest, o));
-  }
-  if (lane == 63) {
+  scan_step<0x111, 0xf>(inc_tiles, inc_cnt, longest);
+  scan_step<0x112, 0xf>(inc_tiles, inc_cnt, longest);
+  scan_step<0x114, 0xf>(inc_tiles, inc_cnt, longest);
+  scan_step<0x118, 0xf>(inc_tiles, inc_cnt, longest);
+  scan_step<0x142, 0xa>(inc_tiles, inc_cnt, longest);
+  scan_step<0x143, 0xc>(inc_tiles, inc_cnt, longest);
+  if (lane == 63) {                                        // (the wave's sums and maximum)
     pl.wave_tot[3 * wv] = inc_tiles;
     pl.wave_tot[3 * wv + 1] = inc_cnt;
     pl.wave_tot[3 * wv + 2] = longest;
@@ -1176,7 +1190,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // arrive.  bf16: as head_dim 128, but P is carried as three bf16 parts (24 bits), so that no weight has fewer bits than
     // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
     // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
-    // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 9.1 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
+    // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 8.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
     auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
       const bool ragged = n_valid < TT;
