@@ -444,7 +444,7 @@ def time_prefill(torch, B, wl, reps: int = 10, check: bool = True):
     res = {"workload": "whole prompts, 16 x 4096 + 1 x 333 tokens, 28 q heads / 4 KV heads, head_dim 128, bf16, one layer",
            "ms": round(ms, 4), "tflops": round(tflops, 1), "prompt_tokens_per_s_per_layer": round(total / (ms * 1e-3), 1),
            "bound": "mfma", "peak_tflops": MFMA_BF16_PEAK_TFLOPS, "frac": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4),
-           "kernel": "prefill_kernel<false, 2>", "oracle_check": None}
+           "kernel": "prefill_kernel<false, 2, false, false>", "oracle_check": None}
     log(f"prefill: {ms:.3f} ms for {total} prompt tokens -> {tflops:.1f} TFLOP/s ({100 * tflops / MFMA_BF16_PEAK_TFLOPS:.1f} % of the "
         f"dense bf16 MFMA peak)")
     if check:
@@ -884,7 +884,7 @@ def main():
                              "achieved": round(c4["bytes_per_launch"] / (c4["kernel_us_per_layer"] * 1e-6) / 1e9, 1),
                              "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                              "frac": round(c4["bytes_per_launch"] / (c4["kernel_us_per_layer"] * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-                             "timing": "step time / 28: includes the plan kernel of the step and the gaps between eager launches"},
+                             "timing": "step time / 28: includes the planning of the step and the gaps between eager launches"},
                 "migration": None if big is None else {
                     "launches": len(copies), "requests": sum(m["requests"] for m in copies),
                     "largest": {"step": big["step"], "requests": big["requests"], "tokens": big["tokens"], "ms": round(big["ms"], 4),
@@ -906,7 +906,7 @@ def main():
             c5["workload"] = ("configs[4]: 1000 decode steps, up to 256 slots, one layer, lengths sliding from log-normal "
                               "(median 256) to Pareto(1.2, min 128) clipped at 65536, recalibration every 100 steps over a "
                               "window of 2048; sustained KV GB/s = bytes attended / time of the decode launches (events "
-                              "around every eager odma_decode_step, plan kernel included)")
+                              "around every eager odma_decode_step, planning included)")
             config5 = c5
 
     host = None if args.profile_only else time_host_allocator(B, wl, w, lengths)
