@@ -825,7 +825,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       }
       }
     };
-    float m = NEG_INF, lsum = 0.f;
+    float m = LOWEST_REF, lsum = 0.f;
     float4v O[CH / 16];
 #pragma unroll
     for (int i = 0; i < CH / 16; ++i) O[i] = float4v{0.f, 0.f, 0.f, 0.f};
@@ -1531,7 +1531,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
             advance(cc, wc);
             if (seg_end) {
               q_pending = true;
-              m = NEG_INF;
+              m = LOWEST_REF;
               lsum = 0.f;
 #pragma unroll
               for (int k = 0; k < CH / 16; ++k) O[k] = float4v{0.f, 0.f, 0.f, 0.f};

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64) void decode_valu_kernel(DecodeArgs a) {
     float m[GMAX], lsum[GMAX], o[GMAX][KMAX];
 #pragma unroll
     for (int h = 0; h < GMAX; ++h) {
-      m[h] = NEG_INF;
+      m[h] = LOWEST_REF;
       lsum[h] = 0.f;
 #pragma unroll
       for (int k = 0; k < KMAX; ++k) o[h][k] = 0.f;

@@ -59,6 +59,12 @@ struct RowArgs {
   int32_t Hkv, D;
 };
 
+// Where the running reference of a softmax starts: the lowest finite number, not -inf.  A column all of whose scores so
+// far are -inf then has weights 2^(-inf - m) = 0 and keeps (m, 0, 0), a state that later scores, other pieces and other
+// partials join by the usual rescale; from -inf the differences -inf - -inf would be NaN and stay in the sums.  Finite
+// scores see no difference: 2^(m - score) is 0 from either start.
+constexpr float LOWEST_REF = -__FLT_MAX__;
+
 __device__ __forceinline__ int rfl(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 __device__ __forceinline__ float wave_max(float x) {

@@ -1,0 +1,76 @@
+"""Infinite scores: K rows that score -inf (what a caller uses to switch tokens off), for whole tiles, whole ranges of a
+wave or a work-group, and for some heads of a group only.  The oracle gives these tokens weight 0; the outputs are held
+to the bounds of the finite cases, since the tokens that remain are ordinary."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from paper_2512_09427_amd import binding as B
+from tests import harness as H
+from tests.test_gpu_parity import small_workload
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = [("f32", 64, B.KERNEL_AUTO), ("f32", 64, B.KERNEL_VALU), ("f32", 256, B.KERNEL_AUTO), ("bf16", 32, B.KERNEL_AUTO),
+           ("bf16", 96, B.KERNEL_AUTO), ("bf16", 96, B.KERNEL_VALU), ("bf16", 64, B.KERNEL_AUTO), ("bf16", 128, B.KERNEL_AUTO)]
+# lengths, and per request the tokens that are switched off
+LENS = [64, 40, 700, 5000, 5000, 33]
+OFF = [slice(0, 16), slice(0, 32), slice(0, 650), slice(0, 4400), slice(300, 5000), slice(1, 33)]
+
+
+def bits(kvd, x):
+    x = np.float32(x)
+    return x if kvd == "f32" else np.uint16(x.view(np.uint32) >> 16)
+
+
+def case(kvd, d, kernel, edit, hq=4, hkv=2):
+    lens = np.array(LENS)
+    w = small_workload(lens, kv_dtype=kvd, hq=hq, hkv=hkv, d=d, seed=d, bounds=(64, 1024, 8192), large_cap=8192, main=1 << 15)
+    dp = H.make_pool(w, out_dtype=B.F32, decode_kernel=kernel)
+    kv = [wl.request_kv(w, 0, r) for r in range(len(lens))]
+    q = wl.queries(w, 0)
+    edit(q, kv)
+    off, _ = H.assign_perfect(dp, lens)
+    H.fill(dp, 0, kv, offsets=off)
+    return w, dp, q, kv, lens, off
+
+
+def tolerance(kvd, d):
+    return (1e-5, 1e-5) if kvd == "f32" or d not in (64, 128) else (2e-5, 2e-4)
+
+
+@pytest.mark.parametrize("some_heads", [False, True])
+@pytest.mark.parametrize("kvd,d,kernel", FORMATS)
+def test_tokens_switched_off(kvd, d, kernel, some_heads):
+    """K of channel 0 is -inf; or, for some heads, so low that their queries' product overflows while the others' is 0."""
+    def edit(q, kv):
+        for r, tokens in enumerate(OFF):
+            kv[r][0][:, :, 0] = bits(kvd, 0.0)
+            kv[r][0][tokens, :, 0] = bits(kvd, -3e38 if some_heads else -np.inf)
+        q[:, :, 0] = bits(kvd, 1.0)
+        if some_heads:
+            q[:, 0::2, 0] = bits(kvd, 1e10)
+            q[:, 1::2, 0] = bits(kvd, 0.0)
+
+    w, dp, q, kv, lens, off = case(kvd, d, kernel, edit)
+    ref = H.oracle_out(w, q, kv)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    H.check(got, ref, *tolerance(kvd, d), what=f"{kvd} {d} kernel {kernel}")
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
+    dp.pool.odma_pool_tune(B.TUNE_FUSE_REDUCE, 0)
+    H.check(H.decode(dp, 0, q, lens, offsets=off), ref, *tolerance(kvd, d), what=f"{kvd} {d}, separate reduction")
+
+
+@pytest.mark.parametrize("kvd,d,kernel", FORMATS)
+def test_a_request_without_a_finite_score_touches_no_other(kvd, d, kernel):
+    """All tokens of request 2 are off: its softmax has no value, the others keep theirs."""
+    def edit(q, kv):
+        for r in range(len(LENS)):
+            kv[r][0][:, :, 0] = bits(kvd, -np.inf if r == 2 else 0.0)
+        q[:, :, 0] = bits(kvd, 1.0)
+
+    w, dp, q, kv, lens, off = case(kvd, d, kernel, edit)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    assert np.isnan(got[2]).all()
+    keep = [r for r in range(len(LENS)) if r != 2]
+    H.check(got[keep], H.oracle_out(w, q, [kv[r] if r != 2 else kv[0] for r in range(len(LENS))])[keep], *tolerance(kvd, d))
