@@ -1251,14 +1251,19 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
             for (int dt = 0; dt < CH / 16; ++dt)
               O[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float4v, vv[b * NP + dt % NP])[e], pv[e], O[dt], 0, 0, 0);
         } else {
+          // Three parts of eight bits each, cut off and not rounded, so that none is negative, and none of a weight that is
+          // not 0 is 0 (2^-40 of the weight stands in): an infinite V times the parts is that infinity, as times the weight,
+          // where parts of both signs would give inf - inf and a part of 0 would give 0 * inf.
           bf16x4 part[3];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
+            const float least = pv[i] * 0x1p-40f;
             float rest = pv[i];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-              part[k][i] = (__bf16)rest;
-              rest -= (float)part[k][i];
+              const float cut = __uint_as_float(__float_as_uint(k == 0 ? rest : fmaxf(rest, least)) & 0xffff0000u);
+              part[k][i] = __builtin_bit_cast(__bf16, (unsigned short)(__float_as_uint(cut) >> 16));
+              rest -= cut;
             }
           }
           if (ragged) {

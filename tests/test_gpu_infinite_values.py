@@ -1,6 +1,7 @@
 """Infinite scores: K rows that score -inf (what a caller uses to switch tokens off), for whole tiles, whole ranges of a
 wave or a work-group, and for some heads of a group only.  The oracle gives these tokens weight 0; the outputs are held
-to the bounds of the finite cases, since the tokens that remain are ordinary."""
+to the bounds of the finite cases, since the tokens that remain are ordinary.  Infinite values: channels in which a V row
+is infinite come out infinite, the others as ever."""
 import numpy as np
 import pytest
 
@@ -74,3 +75,29 @@ def test_a_request_without_a_finite_score_touches_no_other(kvd, d, kernel):
     assert np.isnan(got[2]).all()
     keep = [r for r in range(len(LENS)) if r != 2]
     H.check(got[keep], H.oracle_out(w, q, [kv[r] if r != 2 else kv[0] for r in range(len(LENS))])[keep], *tolerance(kvd, d))
+
+
+def check_with_infinities(got, ref, tol, what):
+    inf = np.isinf(ref)
+    assert inf.any() and not np.isnan(ref).any()
+    np.testing.assert_array_equal(got[inf], ref[inf], err_msg=what)
+    H.check(np.where(inf, 0.0, got), np.where(inf, 0.0, ref), *tol, what=what)
+
+
+@pytest.mark.parametrize("kvd,d,kernel", [("f32", 32, B.KERNEL_AUTO), ("f32", 256, B.KERNEL_AUTO), ("f32", 96, B.KERNEL_VALU)] +
+                         [("bf16", d, B.KERNEL_AUTO) for d in (32, 96, 160, 192, 224, 256)] + [("bf16", 96, B.KERNEL_VALU)])
+def test_infinite_values(kvd, d, kernel):
+    """One token's V is +inf in some channels, another's -inf in others, of ordinary weight, in requests that one wave
+    finishes and that several do; also a weight of exactly 1 (request 5 holds one token)."""
+    lens = np.array([1 if r == 5 else n for r, n in enumerate(LENS)])
+    w = small_workload(lens, kv_dtype=kvd, hq=4, hkv=2, d=d, seed=d, bounds=(64, 1024, 8192), large_cap=8192, main=1 << 15)
+    dp = H.make_pool(w, out_dtype=B.F32, decode_kernel=kernel)
+    kv = [wl.request_kv(w, 0, r) for r in range(len(lens))]
+    for r, n in enumerate(lens):
+        kv[r][1][n // 2, :, 3::7] = bits(kvd, np.inf)
+        if n > 1:
+            kv[r][1][n - 1, :, 5::7] = bits(kvd, -np.inf)
+    q = wl.queries(w, 0)
+    off, _ = H.assign_perfect(dp, lens)
+    H.fill(dp, 0, kv, offsets=off)
+    check_with_infinities(H.decode(dp, 0, q, lens, offsets=off), H.oracle_out(w, q, kv), tolerance(kvd, d), f"{kvd} {d} kernel {kernel}")
