@@ -369,11 +369,14 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  Pairs past the
     // end and a second tile that does not exist re-read the last tile: every step issues its loads, so the waits on
     // them stay static counts (with conditional loads the wait before a stage was written covered the loads issued a
-    // moment ago as well, and the whole memory latency was exposed in every pair).  Tokens of such a tile lie at or past
-    // every column's limit, so their weights are zero.  V slots at or past `len` (stale bytes, maybe NaN patterns) are
-    // zeroed, so that a weight of 0 really removes them.  (K needs nothing: scores of tokens past a column's limit are
-    // replaced, not multiplied.)
+    // moment ago as well, and the whole memory latency was exposed in every pair).  V slots at or past `len` (stale bytes,
+    // maybe NaN patterns) are zeroed, and so is the V of a tile that does not exist (the last tile's may be infinite), so
+    // that a weight of 0 really removes them.  (K needs nothing: scores of tokens past a column's limit are replaced, not
+    // multiplied, and the tokens of such a tile lie past every column's limit.)
     auto tile_of = [&](int pr) { return min(2 * pr + which, n_tiles - 1); };
+    // tokens below it have a V: with an odd number of tiles the wave of the second tiles meets the last tile only where its
+    // own does not exist (one number for the whole item: decided pair by pair it cost fp8 pools 8 %)
+    const int held = (which & n_tiles & 1) ? (n_tiles - 1) * BLK : len;
     int blk_next = 0;
     auto lookup = [&](int pr) {
       if (PAGED) blk_next = bt_row[tile_of(pr)];
@@ -403,7 +406,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         } else {
           // lane (c, q) holds, per half s, one word per channel group 4 s + i: channel c of tokens 4q .. 4q+3
           const int tok0 = t * BLK + 4 * g4;
-          const bool ragged = t * BLK + BLK > len;                      // (the same for the whole wave)
+          const bool ragged = t * BLK + BLK > held;                      // (the same for the whole wave)
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
             const uint4v w = rg[s];
@@ -411,10 +414,10 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
             for (int i = 0; i < 4; ++i) {
               uint2v o = {fp8x2_to_bf16x2<false>(w[i]), fp8x2_to_bf16x2<true>(w[i])};
               if (ragged) {                                             // some of the tile's tokens are not there
-                if (tok0 + 0 >= len) o[0] &= 0xffff0000u;
-                if (tok0 + 1 >= len) o[0] &= 0x0000ffffu;
-                if (tok0 + 2 >= len) o[1] &= 0xffff0000u;
-                if (tok0 + 3 >= len) o[1] &= 0x0000ffffu;
+                if (tok0 + 0 >= held) o[0] &= 0xffff0000u;
+                if (tok0 + 1 >= held) o[0] &= 0x0000ffffu;
+                if (tok0 + 2 >= held) o[1] &= 0xffff0000u;
+                if (tok0 + 3 >= held) o[1] &= 0x0000ffffu;
               }
               *(uint2v*)(st + 8192 + (4 * s + i) * 1024 + lane * 16 + which * 8) = o;
             }
@@ -425,11 +428,11 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         for (int s = 0; s < 4; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
       } else {
         // lane (c, q) holds, per piece s, tokens 4q .. 4q+3 of channel groups 2s (low 8 bytes) and 2s+1
-        if (t * BLK + BLK > len) {                                      // some of the tile's tokens are not there
+        if (t * BLK + BLK > held) {                                      // some of the tile's tokens are not there
           const int tok0 = t * BLK + 4 * g4;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (tok0 + i >= len) {
+            if (tok0 + i >= held) {
               const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
 #pragma unroll
               for (int s = 0; s < 4; ++s) {
@@ -538,16 +541,15 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       }
       weights(x, av);
     };
-    // V slots at or past `len` hold stale bytes (maybe NaN patterns): zeroed in the operands, so that a weight of 0 really
-    // removes them.  (K needs nothing: scores of tokens past a column's limit are replaced, not multiplied.)
-    auto mask_v = [&](bf16x8 (&av)[8], int pr, int tiles, int len) {
-      const int ta = 2 * pr * BLK, tb = min(2 * pr + 1, tiles - 1) * BLK;
-      if (max(ta, tb) + BLK > len) {
+    // the same zeroing in the operands
+    auto mask_v = [&](bf16x8 (&av)[8], int pr) {
+      const int ta = 2 * pr * BLK, held = 2 * pr + 1 < n_tiles ? len : min(len, ta + BLK);
+      if (ta + 2 * BLK > held) {
         uint4v keep;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const int tok = (w < 2 ? ta : tb) + 4 * g4 + 2 * (w & 1);
-          keep[w] = (tok < len ? 0x0000ffffu : 0u) | (tok + 1 < len ? 0xffff0000u : 0u);
+          const int tok = ta + (w < 2 ? 0 : BLK) + 4 * g4 + 2 * (w & 1);
+          keep[w] = (tok < held ? 0x0000ffffu : 0u) | (tok + 1 < held ? 0xffff0000u : 0u);
         }
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) av[dt] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(uint4v, av[dt]) & keep);
@@ -630,7 +632,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
           av[2 * s] = join(lo[0], lo[1]);
           av[2 * s + 1] = join(hi[0], hi[1]);
         }
-        mask_v(av, pr, n_tiles, len);
+        mask_v(av, pr);
         weights(x, av);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) m[ct] = keep[ct];

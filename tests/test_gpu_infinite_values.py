@@ -101,3 +101,32 @@ def test_infinite_values(kvd, d, kernel):
     off, _ = H.assign_perfect(dp, lens)
     H.fill(dp, 0, kv, offsets=off)
     check_with_infinities(H.decode(dp, 0, q, lens, offsets=off), H.oracle_out(w, q, kv), tolerance(kvd, d), f"{kvd} {d} kernel {kernel}")
+
+
+@pytest.mark.parametrize("grow", [False, True])
+@pytest.mark.parametrize("paged", [False, True])
+def test_infinite_values_of_a_prompt_with_an_odd_number_of_tiles(paged, grow):
+    """The last query sees the infinite V of its own token; the tile after the last one does not exist.  With `grow` the
+    scores outgrow the first pair's reference, so the columns are repeated."""
+    lens, n_q = np.array([48, 20, 5, 16, 300]), np.array([48, 4, 5, 1, 20])
+    w = small_workload(lens, hq=7, hkv=1, seed=6)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    kv = [wl.request_kv(w, 0, r) for r in range(len(lens))]
+    rng = np.random.default_rng(6)
+    q, _ = wl.draw_values(rng, (int(n_q.sum()), 7, 128), w.data_scale, "bf16")
+    q[:, :, 0] = bits("bf16", 1.0)
+    for r, n in enumerate(lens):
+        kv[r][0][:, :, 0] = bits("bf16", 0.0)
+        if grow:
+            kv[r][0][-1, :, 0] = bits("bf16", 2048.0)
+        kv[r][1][-1, :, 3::7] = bits("bf16", np.inf)
+    where = dict(block_table=wl.shuffled_block_table(lens, w.pool_tokens // 16, 16, seed=5)) if paged else \
+        dict(offsets=H.assign_perfect(dp, lens)[0])
+    H.fill(dp, 0, kv, **where)
+    q_start = np.concatenate([[0], np.cumsum(n_q)[:-1]])
+    got = H.prefill(dp, 0, q, q_start, n_q, lens, **where)
+    for r, n in enumerate(lens):
+        last = q_start[r] + n_q[r] - 1
+        ref = H.oracle_out(w, q[last:last + 1], [kv[r]])
+        # (the weights of a prompt are bf16: 2^-8 of the values they average)
+        check_with_infinities(got[last:last + 1], ref, (2.0 ** -8 * w.data_scale * 4, 2e-2), f"request {r}")
