@@ -459,8 +459,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // exponent, and fp32 / bf16 weights have room for 2^127: the fast pass fixes m of a column to the
     // exact maximum over the first pair (every column sees token 0) and never moves it, so the steady
     // state holds no cross-lane maximum, no rescale of O and no second exponential.  Should later scores
-    // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), the wave
-    // repeats its columns in the slow pass below, the classic online softmax that moves its references.
+    // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), or lie so far below the
+    // stand-in reference of a column whose first pair scored -inf that the sum stays under 2^-60, the wave repeats its
+    // columns in the slow pass below, the classic online softmax that moves its references.
     auto scores_of = [&](float4v (&x)[CT][2], const bf16x8 (&qq)[CT][4], auto&& kop) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
@@ -681,7 +682,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     column_sums(l);
     bool redo = false;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] != 0 && !(l[ct] < 0x1p90f);
+    for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] != 0 && !(l[ct] > 0x1p-60f && l[ct] < 0x1p90f);
     if (__builtin_amdgcn_ballot_w64(redo) != 0) {                        // this wave's columns alone
       slow_pass();
       column_sums(l);

@@ -130,3 +130,27 @@ def test_infinite_values_of_a_prompt_with_an_odd_number_of_tiles(paged, grow):
         ref = H.oracle_out(w, q[last:last + 1], [kv[r]])
         # (the weights of a prompt are bf16: 2^-8 of the values they average)
         check_with_infinities(got[last:last + 1], ref, (2.0 ** -8 * w.data_scale * 4, 2e-2), f"request {r}")
+
+
+@pytest.mark.parametrize("score", [-300.0, -3.0, 200.0])
+def test_prompt_whose_first_tokens_are_switched_off(score):
+    """The first pair of tiles, and more, scores -inf; what follows lies far below, near and far above zero."""
+    lens, n_q, off = np.array([64, 200, 333]), np.array([20, 1, 200]), np.array([40, 64, 100])
+    w = small_workload(lens, hq=7, hkv=1, seed=8)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    kv = [wl.request_kv(w, 0, r) for r in range(len(lens))]
+    q, _ = wl.draw_values(np.random.default_rng(8), (int(n_q.sum()), 7, 128), w.data_scale, "bf16")
+    q[:, :, 0] = bits("bf16", 1.0)
+    for r in range(len(lens)):
+        kv[r][0][:, :, 0] = bits("bf16", score * np.log(2.0) * np.sqrt(128.0))
+        kv[r][0][:off[r], :, 0] = bits("bf16", -np.inf)
+    where = dict(offsets=H.assign_perfect(dp, lens)[0])
+    H.fill(dp, 0, kv, **where)
+    q_start = np.concatenate([[0], np.cumsum(n_q)[:-1]])
+    got = H.prefill(dp, 0, q, q_start, n_q, lens, **where)
+    for r, n in enumerate(lens):
+        for j in range(max(0, int(off[r] - (n - n_q[r]))), n_q[r]):       # queries that see a token that is on
+            seen = int(n - n_q[r] + j + 1)
+            ref = H.oracle_out(w, q[q_start[r] + j:q_start[r] + j + 1], [(kv[r][0][:seen], kv[r][1][:seen])])
+            # (the weights of a prompt are bf16: 2^-8 of the values they average)
+            H.check(got[q_start[r] + j:q_start[r] + j + 1], ref, 2.0 ** -8 * w.data_scale * 4, 2e-2, what=f"request {r} query {j}")
