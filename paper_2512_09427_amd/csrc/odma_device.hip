@@ -335,13 +335,21 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
         hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(STREAM_PLAN_THREADS), 0, s, lengths, a.offsets, n, c.n_kv_heads,
                            tile_tokens, n_wg * wpw, wpw, q_min, now.odd_w, now.late_w, a.entries, a.waves, a.red);
       }
-      stamp = now;
+      // no plan until the launch that writes it has been accepted: a failed call must not leave one to reuse
+      stamp = odma_pool::PlanStamp();
     }
     const int nbuf = pool->pipeline_depth;
     hipError_t e = launch_stream_kernel(fmt, fused, block_table != nullptr, nbuf, wpw, n_wg, lds_bytes, s, a);
-    if (e != hipSuccess) return hip_fail(where, e);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();                               // reported here, not by the next call as well
+      return hip_fail(where, e);
+    }
     if (!pool->fuse_reduce && !(flags & ODMA_SKIP_REDUCE))
       hipLaunchKernelGGL(stream_reduce_kernel, dim3(n_wg * G), dim3(f.ch), 0, s, a, n_wg);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(where, e);
+    stamp = now;
+    return ODMA_OK;
   } else {
     // ---- chunked scheme: plan -> attention (one wave per (request, head, chunk)) -> reduce
     DecodeArgs a;

@@ -1,0 +1,75 @@
+"""The host side of the device calls, on a stand-in HIP runtime (no GPU): what a planning call leaves behind when its launch
+fails, and the dynamic LDS size when two threads raise it.  Each case runs in a process of its own (tests/fake_runtime.py)."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++")
+pytestmark = pytest.mark.skipif(CXX is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    d = tmp_path_factory.mktemp("fake_hip")
+    (d / "map").write_text("hip_4.2 { global: hip*; __hip*; fake_*; local: *; };\n")
+    so = str(d / "libamdhip64.so.7")
+    subprocess.run([CXX, "-O1", "-std=c++17", "-shared", "-fPIC", "-pthread", "-Wl,-soname,libamdhip64.so.7",
+                    f"-Wl,--version-script={d / 'map'}", os.path.join(ROOT, "tests", "native", "fake_hip.cpp"), "-o", so],
+                   check=True, capture_output=True, text=True, timeout=120)
+    return so
+
+
+def run(runtime, code):
+    env = dict(os.environ, FAKE_HIP=runtime, PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", "from tests.fake_runtime import *\n" + textwrap.dedent(code)], cwd=ROOT, env=env,
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+
+
+POOLS = [
+    ("make_pool()", 5, False),                               # planned in the attention launch
+    ("make_pool()", 1500, False),                            # by a launch in front of it
+    ("make_pool()", 5, True),                                # static scratch
+    ("make_pool(kv_dtype=B.F32)", 5, False),                 # wide format
+    ("make_pool(kv_dtype=B.FP8)", 5, False),
+]
+
+
+@pytest.mark.parametrize("first", [False, True])
+@pytest.mark.parametrize("pool,n,static", POOLS)
+def test_a_planning_launch_that_failed_left_no_plan(runtime, pool, n, static, first):
+    """`first`: the pool's first call fails; otherwise one that replaces the plan of another batch."""
+    run(runtime, f"""
+        n = {n}
+        call = lambda p, m, flags=0: decode(p, m, flags, static={static})
+        other = {pool}
+        planning = launched(lambda: call(other, n))
+        reusing = launched(lambda: call(other, n, B.REUSE_PLAN))
+        assert planning != reusing and len(reusing) == 1, (planning, reusing)
+        p = {pool}
+        if not {first}:
+            call(p, n - 1)
+        hip.fake_fail_launch(len(planning) - 1)              # the attention launch
+        assert fails(lambda: call(p, n))
+        assert launched(lambda: call(p, n, B.REUSE_PLAN)) == planning
+        assert launched(lambda: call(p, n, B.REUSE_PLAN)) == reusing
+    """)
+
+
+@pytest.mark.parametrize("pool,static", [(p, s) for p, n, s in POOLS if n == 5])
+def test_a_planning_call_refused_its_lds_left_no_plan(runtime, pool, static):
+    run(runtime, f"""
+        call = lambda n, flags=0: decode(p, n, flags, static={static})
+        p = {pool}
+        call(3)
+        hip.fake_fail_attribute(0)
+        assert fails(lambda: call(1000))                     # (a longer planning table: more LDS)
+        again = launched(lambda: call(1000, B.REUSE_PLAN))
+        assert again == launched(lambda: call(1000))
+        assert again != launched(lambda: call(1000, B.REUSE_PLAN))
+    """)
