@@ -30,6 +30,7 @@
 #pragma once
 
 #include <atomic>
+#include <mutex>
 #include <type_traits>
 
 #include "kernels_common.h"
@@ -1752,15 +1753,17 @@ __global__ __launch_bounds__(256) void stream_reduce_kernel(StreamArgs a, int n_
 }
 
 // Launch with lds_bytes of dynamic LDS; `allowed`: the largest size enabled for the kernel so far (the default limit is
-// 64 KiB).  Racing callers may both set the attribute; the larger request wins in the end because each sets its own size
-// and then records the maximum.
+// 64 KiB).  Checking, setting and recording a larger size are one step: of two callers that raise it at once, the smaller
+// size must not be the one set last.
 inline hipError_t launch_with_lds(void (*kernel)(StreamArgs), std::atomic<unsigned>& allowed, int n_wg, int wpw, size_t lds_bytes,
                                   hipStream_t s, const StreamArgs& a) {
   if (lds_bytes > 64 * 1024 && lds_bytes > allowed.load(std::memory_order_acquire)) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
-    unsigned seen = allowed.load(std::memory_order_relaxed);
-    while (seen < lds_bytes && !allowed.compare_exchange_weak(seen, (unsigned)lds_bytes, std::memory_order_release)) {
+    static std::mutex raising;
+    std::lock_guard<std::mutex> lock(raising);
+    if (lds_bytes > allowed.load(std::memory_order_relaxed)) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+      if (e != hipSuccess) return e;
+      allowed.store((unsigned)lds_bytes, std::memory_order_release);
     }
   }
   hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(64 * wpw), lds_bytes, s, a);

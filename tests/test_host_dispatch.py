@@ -73,3 +73,22 @@ def test_a_planning_call_refused_its_lds_left_no_plan(runtime, pool, static):
         assert again == launched(lambda: call(1000))
         assert again != launched(lambda: call(1000, B.REUSE_PLAN))
     """)
+
+
+@pytest.mark.parametrize("pool", ["make_pool(hq=32)", "make_pool(hq=32, kv_dtype=B.F32)", "make_pool(hq=32, kv_dtype=B.FP8)"])
+def test_two_threads_raise_the_lds_size(runtime, pool):
+    """A call that asked for the smaller size is overtaken by one that asks for a larger: the larger stays allowed."""
+    run(runtime, f"""
+        import threading, time
+        p, p2 = {pool}, {pool}
+        hip.fake_hold_first_attribute()
+        slow = threading.Thread(target=lambda: decode(p, 300))
+        slow.start()
+        while hip.fake_attribute_calls() < 1:
+            time.sleep(0.001)
+        decode(p2, 1000)
+        slow.join()
+        assert hip.fake_attribute_calls() == 2
+        decode(p, 900)
+        decode(p2, 1000)
+    """)
