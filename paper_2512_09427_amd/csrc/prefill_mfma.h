@@ -298,18 +298,33 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     }
     const int item = next++;
     // Request of the item: largest r with item_start[r] <= item (item_start is non-decreasing; empty requests repeat
-    // a value, so it is the last one that still has items): the number of such entries, counted in LDS where they fit.
+    // a value, so it is the last one that still has items).  In LDS, where the table fits: the number of such entries, 64 a
+    // round.  In memory every round is a dependent round trip, so there the 64 lanes probe evenly spaced entries of the
+    // range that is left, which is two rounds up to 4096 requests (counted 64 by 64, 4096 requests of 8 to 40 tokens took
+    // 795 us instead of 429).
     // Everything else an item needs is then one round of scalar loads, all in flight together: an item of a short prompt
     // streams fewer than ten pairs, so each dependent round trip in front of it shows.
-    int cnt = 0;
-    for (int i0 = 0; i0 < a.n; i0 += 64) {
-      const int i = min(i0 + lane, a.n - 1);
-      const bool le = i0 + lane < a.n && (small ? item_start_lds[i] : a.item_start[i]) <= item;
-      const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
-      cnt += k;
-      if (k < 64) break;
+    int found = 0;
+    if (small) {
+      int cnt = 0;
+      for (int i0 = 0; i0 < a.n; i0 += 64) {
+        const bool le = i0 + lane < a.n && item_start_lds[min(i0 + lane, a.n - 1)] <= item;
+        const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
+        cnt += k;
+        if (k < 64) break;
+      }
+      found = cnt - 1;
+    } else {
+      int hi = a.n;                                                    // the request is in [found, hi)
+      while (hi - found > 1) {
+        const int span = (hi - found + 63) / 64, i = found + lane * span;
+        const bool le = i < hi && a.item_start[min(i, hi - 1)] <= item;
+        const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));   // (at least the first)
+        found += (k - 1) * span;
+        hi = min(found + span, hi);
+      }
     }
-    const int r = rfl(cnt - 1);
+    const int r = rfl(found);
     const int first_item = rfl(small ? item_start_lds[r] : a.item_start[r]);
     const int len = as_constant(a.lengths)[r], asked = as_constant(a.n_q)[r];
     const int64_t q_row0 = ((const const_i64*)(uintptr_t)a.q_start)[r];

@@ -30,3 +30,15 @@ def test_requests_around_the_size_of_the_item_table(n):
     lens = rng.integers(0, 24, n)
     lens[n // 2] = 900
     chunk_case(lens, lens, hq=2, hkv=1, sharp=True, seed=92, bounds=(64, 512, 1024), large_cap=1024, main=1 << 17)
+
+
+@pytest.mark.parametrize("n", [1500, 4096, 4097])
+def test_requests_found_in_memory(n):
+    """The 64-way search: one whole round and a part, two rounds, and one request more; a third of the requests empty,
+    at both ends too, so that values repeat across the probes."""
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 12, n)
+    lens[rng.random(n) < 1 / 3] = 0
+    lens[:70] = lens[-70:] = 0
+    lens[n // 3] = 300
+    chunk_case(lens, lens, hq=2, hkv=1, sharp=True, seed=93, bounds=(64, 512, 1024), large_cap=1024, main=n * 64 + 4096)
