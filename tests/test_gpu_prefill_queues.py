@@ -4,8 +4,12 @@ wave has columns of some lanes only.  Bounds of tests/test_gpu_prefill.py."""
 import numpy as np
 import pytest
 
+import workloads as wl
+from oracle import attention as oa
 from paper_2512_09427_amd import binding as B
-from tests.test_gpu_prefill import chunk_case
+from tests import harness as H
+from tests.test_gpu_parity import small_workload
+from tests.test_gpu_prefill import P_ROUNDING, TIGHT, chunk_case
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +46,29 @@ def test_requests_found_in_memory(n):
     lens[:70] = lens[-70:] = 0
     lens[n // 3] = 300
     chunk_case(lens, lens, hq=2, hkv=1, sharp=True, seed=93, bounds=(64, 512, 1024), large_cap=1024, main=n * 64 + 4096)
+
+
+@pytest.mark.parametrize("column_tiles", [2, 4])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("kvd", ["bf16", "fp8"])
+def test_columns_that_are_repeated(kvd, paged, column_tiles):
+    """Scores of standard deviation 64: most columns outgrow their first pair's reference and are repeated; requests of one
+    tile, odd and even numbers of tiles, whole prompts and late chunks."""
+    lens, n_q = np.array([16, 37, 48, 64, 700, 333]), np.array([16, 37, 1, 64, 90, 333])
+    w = small_workload(lens, kv_dtype=kvd, hq=7, hkv=1, seed=95)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    dp.pool.odma_pool_tune(B.TUNE_PREFILL_COLUMN_TILES, column_tiles)
+    f, sign_off = (wl.FP8_SCALE, 0x7f) if kvd == "fp8" else (1.0, 0x7fff)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    q, _ = wl.draw_values(np.random.default_rng(95), (int(n_q.sum()), 7, 128), 64.0, "bf16")
+    q_start = np.concatenate([[0], np.cumsum(n_q)[:-1]])
+    where = dict(block_table=wl.shuffled_block_table(lens, w.pool_tokens // 16, 16, seed=79)) if paged else \
+        dict(offsets=H.assign_perfect(dp, lens)[0])
+    H.fill(dp, 0, kv, **where)
+    got = H.prefill(dp, 0, q, q_start, n_q, lens, **where)
+    for r in range(len(lens)):
+        rows = slice(q_start[r], q_start[r] + n_q[r])
+        ref = oa.attend_chunk(q[rows], kv[r][0], kv[r][1], f / np.sqrt(128.0)) * f
+        ref_abs = oa.attend_chunk(q[rows], kv[r][0], kv[r][1] & sign_off, f / np.sqrt(128.0)) * f
+        # scores up to 400, summed in fp32 over 128 channels: an error of 400 * 2^-24 * 8 in the exponent, twice over |V|
+        H.check(got[rows], ref, TIGHT[0] + (P_ROUNDING + 4e-4) * ref_abs, TIGHT[1], what=f"request {r}")
