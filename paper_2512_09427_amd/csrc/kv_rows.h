@@ -190,55 +190,51 @@ __global__ __launch_bounds__(256) void append_bf16_d128_kernel(RowArgs a, int32_
   }
 }
 
-// Export: one 16-token group of the request per work-group and round, ROW_CHUNK bytes of the rows at a time, the other way
-// round: V pieces are read whole and turned into rows in LDS (one longest request of 7 801 tokens x 4 heads x 128 in bf16:
-// 18.4 -> 9.2 us; before, 256 threads read one token's V in 2-byte elements).
+// Export: a work-group takes GATHER_CHUNK bytes of the rows of one 16-token group, one K piece and one or two V pieces per
+// thread; V pieces are read whole and turned into rows in LDS.  Bound by its round trips (block id, pieces, rows), so every
+// chunk has a work-group of its own: with 1 KiB chunks taken in turn by one work-group, a short export of rows of several
+// KiB took up to ten times what reading token by token had (16 tokens of 8 heads x 256 in fp32: 3.3 -> 15.6 us, now 2.9; of
+// 32 x 128 in bf16: 4.4 -> 18.6, now 2.9; 8000 tokens of 4 x 128 in bf16: 18.3 -> 8.2, now 7.3).
+constexpr int GATHER_CHUNK = 256;
 template <typename T>
 __global__ __launch_bounds__(256) void gather_kernel(RowArgs a, int64_t offset, int32_t length,
                                                      const int32_t* __restrict__ block_row,
                                                      T* __restrict__ k_out, T* __restrict__ v_out) {
   constexpr int X = 16 / sizeof(T);
-  constexpr int CE = ROW_CHUNK / sizeof(T), STRIDE = CE + X;
-  constexpr int LOADS = BLK * ROW_CHUNK / 16 / 256;
+  constexpr int CE = GATHER_CHUNK / sizeof(T), STRIDE = CE + X;
   __shared__ __attribute__((aligned(16))) T rows[BLK * STRIDE];
   const int row_elems = a.Hkv * a.D;
   const int64_t block_elems = (int64_t)BLK * a.D;
+  const int e0 = blockIdx.y * CE, pieces = min(CE, row_elems - e0) / X;
+  // K: thread -> (piece c, token t); V: thread -> (32-channel group, token quad, channel of its first half)
+  const int t = threadIdx.x & 15, c = threadIdx.x >> 4;
+  const int ek = e0 + c * X, gk = ek / a.D, dk = ek - gk * a.D;
+  const int cv = threadIdx.x & 15, tq = (threadIdx.x >> 4) & 3, gr = threadIdx.x >> 6;
+  const int ev = e0 + gr * 32, gv = ev / a.D, dv = ev - gv * a.D;
+  const bool has_k = c < pieces, has_v = gr * 32 < pieces * X;
+  const T* kd = (const T*)(a.k + (int64_t)gk * a.head_stride) + k_index(t, dk, X);
+  const T* vd = (const T*)(a.v + (int64_t)gv * a.head_stride) + v_index(4 * tq, dv + cv);
   for (int64_t p0 = (int64_t)blockIdx.x * BLK; p0 < length; p0 += (int64_t)gridDim.x * BLK) {
     const int have = (int)min((int64_t)BLK, length - p0);
-    const int64_t blk = block_row ? (int64_t)block_row[p0 / BLK] : offset / BLK + p0 / BLK;
-    for (int e0 = 0; e0 < row_elems; e0 += CE) {
-      const int pieces = min(CE, row_elems - e0) / X;
-      __syncthreads();                                                // the previous chunk's rows have left
-      for (int i = threadIdx.x; i < pieces * X * 2; i += 256) {       // V: 64 threads per group of 32 channels
-        const int c = i & 15, tq = (i >> 4) & 3, gr = i >> 6;
-        const int e = e0 + gr * 32, g = e / a.D, d0 = e - g * a.D;
-        const T* vd = (const T*)(a.v + (int64_t)g * a.head_stride) + blk * block_elems + v_index(4 * tq, d0 + c);
-        alignas(16) T piece[8];
+    const int64_t at = (block_row ? (int64_t)block_row[p0 / BLK] : offset / BLK + p0 / BLK) * block_elems;
+    uint4v kp = {0u, 0u, 0u, 0u};
+    alignas(16) T piece[8];
+    if (has_v)
 #pragma unroll
-        for (int k = 0; k < (int)sizeof(piece) / 16; ++k) ((uint4v*)piece)[k] = ((const uint4v*)vd)[k];
+      for (int k = 0; k < (int)sizeof(piece) / 16; ++k) ((uint4v*)piece)[k] = ((const uint4v*)(vd + at))[k];
+    if (has_k) kp = *(const uint4v*)(kd + at);
+    __syncthreads();                                                  // the previous group's rows have left
+    if (has_v)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          rows[(4 * tq + k) * STRIDE + gr * 32 + c] = piece[k];
-          rows[(4 * tq + k) * STRIDE + gr * 32 + 16 + c] = piece[4 + k];
-        }
+      for (int k = 0; k < 4; ++k) {
+        rows[(4 * tq + k) * STRIDE + gr * 32 + cv] = piece[k];
+        rows[(4 * tq + k) * STRIDE + gr * 32 + 16 + cv] = piece[4 + k];
       }
-      uint4v kp[LOADS];
-#pragma unroll
-      for (int l = 0; l < LOADS; ++l) {
-        const int i = threadIdx.x + 256 * l, t = i & 15, c = i >> 4;
-        const int e = e0 + min(c, pieces - 1) * X, g = e / a.D, d0 = e - g * a.D;
-        kp[l] = *(const uint4v*)((const T*)(a.k + (int64_t)g * a.head_stride) + blk * block_elems + k_index(t, d0, X));
-      }
-      __syncthreads();
-#pragma unroll
-      for (int l = 0; l < LOADS; ++l) {
-        const int i = threadIdx.x + 256 * l, t = i & 15, c = i >> 4;
-        if (c < pieces && t < have) {
-          const int64_t dst = (p0 + t) * row_elems + e0 + c * X;
-          *(uint4v*)(k_out + dst) = kp[l];
-          *(uint4v*)(v_out + dst) = *(const uint4v*)(rows + t * STRIDE + c * X);
-        }
-      }
+    __syncthreads();
+    if (has_k && t < have) {
+      const int64_t dst = (p0 + t) * row_elems + ek;
+      *(uint4v*)(k_out + dst) = kp;
+      *(uint4v*)(v_out + dst) = *(const uint4v*)(rows + t * STRIDE + c * X);
     }
   }
 }

@@ -70,7 +70,9 @@ int odma_gather_kv(odma_pool_t* pool, int32_t layer, int64_t offset, int32_t len
   }
   RowArgs a = row_args(pool, layer);
   const int groups = (length + BLK - 1) / BLK;
-  const dim3 grid(pool->elem_bytes == 1 ? (length < 4096 ? length : 4096) : (groups < 4096 ? groups : 4096));
+  const int row_bytes = (int)(a.Hkv * a.D * pool->elem_bytes);
+  const dim3 grid = pool->elem_bytes == 1 ? dim3(length < 4096 ? length : 4096)
+                                          : dim3(groups < 4096 ? groups : 4096, (row_bytes + GATHER_CHUNK - 1) / GATHER_CHUNK);
   hipStream_t s = (hipStream_t)stream;
   if (pool->elem_bytes == 1)
     hipLaunchKernelGGL(gather_fp8_kernel, grid, dim3(256), 0, s, a, offset, length, block_row, (unsigned char*)k_out,

@@ -48,3 +48,19 @@ def test_rewriting_the_first_rows_of_a_block_keeps_the_others(kvd, d, rows):
     gk, gv = H.gather(dp, 0, int(off[0]), 48)
     np.testing.assert_array_equal(gk, k)
     np.testing.assert_array_equal(gv, v)
+
+
+@pytest.mark.parametrize("kvd,d,hkv,n_tok", [("f32", 128, 32, 33), ("bf16", 128, 20, 18), ("bf16", 96, 11, 40), ("f32", 32, 1, 70001),
+                                             ("bf16", 32, 3, 66000)])
+def test_rows_of_many_chunks_and_more_groups_than_the_grid(kvd, d, hkv, n_tok):
+    """Rows of up to 16 KiB, the last chunk partial; exports and appends of more 16-token groups than work-groups in a grid row."""
+    lens = np.array([n_tok])
+    w = small_workload(lens, kv_dtype=kvd, hq=hkv, hkv=hkv, d=d, seed=11, bounds=(64, 1 << 17), large_cap=1 << 17, main=1 << 17,
+                       safety=1 << 17)
+    dp = H.make_pool(w)
+    kv = wl.request_kv(w, 0, 0)
+    off, _ = H.assign_perfect(dp, lens)
+    H.fill(dp, 0, [kv], offsets=off)
+    gk, gv = H.gather(dp, 0, int(off[0]), n_tok)
+    np.testing.assert_array_equal(gk, kv[0])
+    np.testing.assert_array_equal(gv, kv[1])
