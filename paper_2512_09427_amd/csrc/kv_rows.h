@@ -15,14 +15,19 @@ __device__ __forceinline__ int v_index(int t, int d) {
 }
 
 constexpr int APPEND_GRID_X = 512;  // most work-groups per request in a bulk append (each takes every 512th group of 16 rows)
+constexpr int APPEND_FILL = 1024;   // work-groups up to which append_kernel deals out the chunks of its rows (beyond, four per
+                                    // compute unit, the launch is bound by memory: with 4096, 256 prompts of 100 rows took 10 % more)
 
 // Any storage type of 2 or 4 bytes, any head_dim.  A 16-token group that starts on a block boundary is written block-wise,
 // ROW_CHUNK bytes of the rows at a time: a K piece is 16 contiguous source bytes, and goes straight through a register; V
 // is staged in LDS, so that a thread writes four tokens of two channels at once (16 or 32 bytes) instead of 2- or 4-byte
 // elements all over the block.  Slots past the appended rows keep what they hold.  Bound by memory: the scattered stores
 // it replaces cost a partial sector each (164 prompts of 218 138 tokens x 4 heads x 64 in bf16, two layers with migrations
-// and export, 1.07 GB: 760 -> 231 us, 4.6 TB/s).  Groups that start inside a block (the one-row append of a decode
-// step) go row by row.
+// and export, 1.07 GB: 760 -> 231 us, 4.6 TB/s).  A small launch is bound by round trips instead, which chunks taken in turn
+// pile up, so there the third grid dimension deals them out (one prompt of 16 rows of 8 x 256 in fp32: 20.0 us row by row,
+// 19.7 in turn, 4.8 dealt out; 64 of 6 rows of 32 x 64 in bf16: 9.7, 12.8, 5.5).  Groups that start inside a block, or hold
+// one or two rows (the append of a decode step), go row by row (64 single rows of 8 x 128 in fp32: 3.7 us, 10.0 by the
+// block; from three rows on the block wins or is within a microsecond).
 constexpr int ROW_CHUNK = 1024;
 template <typename T>
 __global__ __launch_bounds__(256) void append_kernel(RowArgs a, int32_t n, const int64_t* __restrict__ offsets,
@@ -47,10 +52,10 @@ __global__ __launch_bounds__(256) void append_kernel(RowArgs a, int32_t n, const
   // APPEND_GRID_X wide, however long the longest append of the batch is
   for (int j0 = blockIdx.x * BLK; j0 < cnt; j0 += gridDim.x * BLK) {
     const int have = min(BLK, cnt - j0);
-    if ((pos0 + j0) % BLK == 0) {
+    if ((pos0 + j0) % BLK == 0 && have > 2) {
       const int pos = pos0 + j0;
       const int64_t blk = bt ? (int64_t)bt[(int64_t)r * bt_stride + pos / BLK] : offsets[r] / BLK + pos / BLK;
-      for (int e0 = 0; e0 < row_elems; e0 += CE) {                   // (a chunk is whole groups of 32 channels)
+      for (int e0 = blockIdx.z * CE; e0 < row_elems; e0 += CE * gridDim.z) {   // (a chunk is whole groups of 32 channels)
         const int pieces = min(CE, row_elems - e0) / X;               // 16-byte pieces of a row in this chunk
         uint4v kp[LOADS], vp[LOADS];
 #pragma unroll
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(256) void append_kernel(RowArgs a, int32_t n, const
       const int t = pos % BLK;
       const T* ks = k_new + (src0 + j) * row_elems;
       const T* vs = v_new + (src0 + j) * row_elems;
-      for (int c = threadIdx.x; c < chunks; c += blockDim.x) {
+      for (int c = blockIdx.z * blockDim.x + threadIdx.x; c < chunks; c += blockDim.x * gridDim.z) {
         const int e0 = c * X, g = e0 / a.D, d0 = e0 % a.D;
         T* kd = (T*)(a.k + (int64_t)g * a.head_stride) + blk * block_elems;
         T* vd = (T*)(a.v + (int64_t)g * a.head_stride) + blk * block_elems;

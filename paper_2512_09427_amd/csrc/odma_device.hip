@@ -21,6 +21,16 @@
 #include "kv_rows.h"
 #include "device_common.h"
 
+namespace {
+// Work-groups that share a 16-token group in append_kernel: up to one per chunk of its rows while the launch stays at
+// APPEND_FILL work-groups.
+int append_splits(const odma_pool* pool, int64_t work_groups) {
+  const int64_t row_bytes = (int64_t)pool->cfg.n_kv_heads * pool->cfg.head_dim * (int64_t)pool->elem_bytes;
+  const int64_t chunks = (row_bytes + ROW_CHUNK - 1) / ROW_CHUNK, room = APPEND_FILL / work_groups;
+  return (int)(room < 1 ? 1 : room < chunks ? room : chunks);
+}
+}  // namespace
+
 extern "C" {
 
 int odma_append_kv(odma_pool_t* pool, int32_t layer, int32_t n, const int64_t* offsets,
@@ -39,6 +49,7 @@ int odma_append_kv(odma_pool_t* pool, int32_t layer, int32_t n, const int64_t* o
   RowArgs a = row_args(pool, layer);
   const int groups = (max_new + BLK - 1) / BLK;
   dim3 grid(groups < APPEND_GRID_X ? groups : APPEND_GRID_X, n);
+  const dim3 split(grid.x, n, append_splits(pool, (int64_t)grid.x * n));
   hipStream_t s = (hipStream_t)stream;
   if (pool->elem_bytes == 1)
     hipLaunchKernelGGL(append_fp8_kernel, grid, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
@@ -47,10 +58,10 @@ int odma_append_kv(odma_pool_t* pool, int32_t layer, int32_t n, const int64_t* o
     hipLaunchKernelGGL(append_bf16_d128_kernel, grid, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
                        block_table, bt_stride, (const unsigned short*)k_new, (const unsigned short*)v_new);
   else if (pool->elem_bytes == 2)
-    hipLaunchKernelGGL(append_kernel<unsigned short>, grid, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
+    hipLaunchKernelGGL(append_kernel<unsigned short>, split, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
                        block_table, bt_stride, (const unsigned short*)k_new, (const unsigned short*)v_new);
   else
-    hipLaunchKernelGGL(append_kernel<float>, grid, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
+    hipLaunchKernelGGL(append_kernel<float>, split, dim3(256), 0, s, a, n, offsets, positions, 0, n_new, src_start,
                        block_table, bt_stride, (const float*)k_new, (const float*)v_new);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail("odma_append_kv", e);
