@@ -1633,7 +1633,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
   }
   for (int which = 0; which < 2; ++which) {
     if (!(which == 0 ? do_a : do_b)) continue;
-    const ReduceDesc rd = rd_cut[which];
+    const ReduceDesc rd = which == 0 ? rd_cut[0] : rd_cut[1];   // (indexed by a variable the pair would live in scratch)
     const int n_parts = rd.n_parts, b0 = rd.b0;
     // thread -> (head, four channels); partial i of the segment sits in slot 2 (b0 + i), the first
     // one in its work-group's "starts here" slot 2 b0 + 1
