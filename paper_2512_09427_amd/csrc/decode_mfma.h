@@ -572,9 +572,10 @@ __host__ __device__ constexpr StreamFormat stream_format(int fmt) {
   const int hd = 32 * (fmt - (f32 ? STREAM_F32_WIDE : STREAM_BF16_WIDE)), eb = f32 ? 4 : 2;
   return {hd, eb, hd * eb / 64, hd == 32 ? 2 : 1, hd};
 }
-// work-groups of one CU that the registers leave room for: a tile of eight pieces or more takes a SIMD for one wave
+// work-groups of one CU that the registers leave room for: a tile of five pieces or more takes a SIMD for one wave (with room
+// for two, bf16 with head_dim 160 spilled 5 registers, fused 38: 256 fused requests of 4 heads 118 -> 95 us)
 __host__ __device__ constexpr int stream_min_waves(int fmt) {
-  return stream_format(fmt).np * stream_format(fmt).blocks >= 6 ? 1 : 2;
+  return stream_format(fmt).np * stream_format(fmt).blocks >= 5 ? 1 : 2;
 }
 
 template <bool PAGED, int NBUF, int WPW, bool FUSED, int FMT>
