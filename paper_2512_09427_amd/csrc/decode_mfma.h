@@ -587,6 +587,8 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
   constexpr int HD = F.hd;                                   // head_dim: stride of q and out rows
   constexpr int CH = F.ch, NP = F.np, NL = NP * F.blocks;    // NL: 16-byte loads per lane of a tile's K (or V)
   constexpr int NQ = WIDE ? NP : 4;                          // 16-byte pieces of the query operand
+  // Two tile buffers and the output of the widest formats leave room for one query operand, not for the next one beside it
+  constexpr bool LATE_Q = NQ >= 14;
   // A tile is what a wave requests per step: 4 KiB of K and 4 KiB of V.  bf16 with head_dim 128: one
   // 16-token pool block; fp8, or bf16 with head_dim 64: two of them (32 tokens), which need not be
   // neighbours in the paged layout.  (Inside the kernel every state keeps CH channels per head; with
@@ -769,8 +771,9 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // The first segment's queries are requested ahead of the first tiles and adopted inside the main loop, after
     // the second tile's loads have been issued: waiting for them here would hold those loads back by a whole
     // memory round trip.
-    bf16x8 qreg[NQ], qnext[NQ];
-    load_q(qnext, cc.r, cc.g);
+    bf16x8 qreg[NQ], qnext[LATE_Q ? 1 : NQ];
+    if constexpr (LATE_Q) load_q(qreg, cc.r, cc.g);
+    else load_q(qnext, cc.r, cc.g);
 
     // prologue: NBUF-1 tiles in flight
     int p_left = n_my - 1;                                 // prefetch cursor may still advance this often
@@ -1484,7 +1487,10 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // Order inside a step matters because vmcnt retires in order: the queries of the next
     // segment are requested BEFORE this step's tile loads and adopted one step later AFTER
     // that step's tile loads, so waiting for them never drains the tile pipeline.
-    bool q_pending = true;                                   // the first segment's queries wait in qnext
+    // (LATE_Q: they are requested right behind the last tile of the segment before, and the next tile waits for them;
+    // fp32 with head_dim 256 spilled 98 registers, fused 314, with the second operand.  64 requests of 4 heads 184 -> 102 us,
+    // fused 141 -> 110; one of 300 tokens 55 -> 33, as long as on the vector kernel)
+    bool q_pending = !LATE_Q;                                // the first segment's queries wait in qnext
     for (int i = 0; i < n_my; i += NBUF) {
 #pragma unroll
       for (int u = 0; u < NBUF; ++u) {
@@ -1494,13 +1500,13 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         if (q_pending && seg_end && more) {
           // a one-tile segment: its successor's queries are requested below, so the ones waiting
           // in qnext must be adopted first (this wait can stall; the common case is further down)
-          adopt_q(qnext);
+          if constexpr (!LATE_Q) adopt_q(qnext);
           q_pending = false;
         }
-        if (seg_end && more) {
+        if (!LATE_Q && seg_end && more) {
           const int ng = cc.g + 1 == Hkv ? 0 : cc.g + 1;
           const int nr = cc.g + 1 == Hkv ? cc.r_next : cc.r;
-          load_q(qnext, nr, ng);
+          if constexpr (!LATE_Q) load_q(qnext, nr, ng);
         }
         if (FUSED && active) {
           // fetch the appended row one tile before it is needed when the segment allows it
@@ -1518,7 +1524,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         if (q_pending) {
           // adopted after this step's tile loads were issued: waiting for the queries (requested a
           // step ago) then costs no more than waiting for the tile computed next
-          adopt_q(qnext);
+          if constexpr (!LATE_Q) adopt_q(qnext);
           q_pending = false;
         }
         if (active) {
@@ -1537,7 +1543,8 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
           if (more) {
             advance(cc, wc);
             if (seg_end) {
-              q_pending = true;
+              if constexpr (LATE_Q) load_q(qreg, cc.r, cc.g);
+              else q_pending = true;
               m = LOWEST_REF;
               lsum = 0.f;
 #pragma unroll
