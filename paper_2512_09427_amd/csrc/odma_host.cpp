@@ -188,11 +188,11 @@ WorkspaceLayout workspace_layout(const odma_pool_config_t& c) {
   return w;
 }
 
-int wide_layout(const odma_pool_config_t& c, size_t bytes, WorkspaceLayout* out) {
-  constexpr int MOST = 256, LEAST = 16;    // work-groups: one per compute unit; with fewer than 16 the chunked kernel serves
-  for (int n_wg = MOST; n_wg >= LEAST; n_wg -= 16) {
+int wide_layout(const odma_pool_config_t& c, size_t bytes, int64_t max_pairs, WorkspaceLayout* out) {
+  for (int n_wg = odma_plan::STREAM_WIDE_WG; n_wg >= odma_plan::STREAM_WIDE_LEAST_WG; n_wg -= 16) {
     const odma_plan::StreamLayout s = odma_plan::stream_layout(0, c.max_requests, n_wg, c.n_q_heads, c.head_dim);
     if (s.end > bytes) continue;
+    if (odma_plan::chunked_is_wider(max_pairs, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, n_wg)) return 0;
     out->items = s.items;
     out->waves = s.waves;
     out->red = s.red;
@@ -341,7 +341,7 @@ int odma_pool_create(const odma_pool_config_t* cfg, odma_pool_t** out) {
   p->ws = workspace_layout(*cfg);
   p->decode_kernel = resolve_decode_kernel(*cfg);
   if (cfg->decode_kernel == ODMA_KERNEL_AUTO && p->decode_kernel == ODMA_KERNEL_VALU)
-    p->wide_wg = wide_layout(*cfg, p->ws.total, &p->wide);
+    p->wide_wg = wide_layout(*cfg, p->ws.total, p->ws.max_pairs, &p->wide);
   p->pool_blocks = (cfg->main_tokens + cfg->safety_tokens) / ODMA_BLOCK_TOKENS;
   p->elem_bytes = cfg->kv_dtype == ODMA_FP8 ? 1 : cfg->kv_dtype == ODMA_BF16 ? 2 : 4;
   if (p->cfg.k_scale == 0.0f) p->cfg.k_scale = 1.0f;

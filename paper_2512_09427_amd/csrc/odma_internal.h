@@ -77,7 +77,8 @@ struct WorkspaceLayout {
 };
 
 WorkspaceLayout workspace_layout(const odma_pool_config_t& cfg);
-int wide_layout(const odma_pool_config_t& cfg, size_t bytes, WorkspaceLayout* out);   // work-groups that fit `bytes`
+// work-groups of the wide formats in `bytes`; 0: the chunked kernel, whose work list has max_pairs entries, serves the pool
+int wide_layout(const odma_pool_config_t& cfg, size_t bytes, int64_t max_pairs, WorkspaceLayout* out);
 bool validate_config(const odma_pool_config_t& cfg, std::string* why);
 int resolve_decode_kernel(const odma_pool_config_t& cfg);
 void set_error(const std::string& msg);
@@ -107,7 +108,8 @@ struct odma_pool {
   int decode_kernel = ODMA_KERNEL_VALU;
   // Pools that resolve to the chunked kernel by themselves (fp32 storage, or bf16 with a head_dim other than 64 and 128)
   // are decoded by the tile-stream kernel's wide formats, in the workspace the chunked scheme sizes: `wide` is the carve-up
-  // with as many work-groups (at most STREAM_WIDE_WG) as fit it; wide_wg 0: too small, the chunked kernel serves the pool.
+  // with as many work-groups (at most STREAM_WIDE_WG) as fit it; wide_wg 0: the chunked kernel serves the pool, because too
+  // few fit or because it spreads much further in so small a workspace (plan_types.h).
   odma::WorkspaceLayout wide;
   int wide_wg = 0;
   int n_cu = 0;                            // filled on first device call

@@ -46,6 +46,18 @@ struct ReduceDesc {          // the segment cut by the boundary in front of work
 
 constexpr int STREAM_MAX_WG = 4096;  // work-groups the pool workspace is sized for
 constexpr int STREAM_MAX_LAUNCH_WG = 2048;   // most work-groups of one launch: eight waves per SIMD of 256 compute units
+// Work-groups of a pool served by the wide formats, whose partial states live in the workspace that the chunked scheme
+// sizes: one per compute unit, as many as fit.  In a small workspace the chunked kernel may spread further, one wave per
+// (chunk, KV head), up to eight per compute unit; it does G heads' arithmetic on the vector ALU, though, where the matrix
+// cores do not care.  It serves the pool if it has more than 1 + 2 G times the waves (chunked_is_wider), or if less than
+// STREAM_WIDE_LEAST_WG work-groups fit.  Measured both ways over 743 calls with max_splits of 24 to 520, 1 to 32 KV heads and
+// G of 1 to 8: none is slower than on the chunked kernel, the mean takes 0.66 of its time.  Without the rule 129 were
+// slower, 32 heads with G = 1 up to six times (8 requests, 16 500 tokens, bf16, head_dim 32: 206 us against 34).
+constexpr int STREAM_WIDE_WG = 256, STREAM_WIDE_LEAST_WG = 16;
+inline bool chunked_is_wider(int64_t pairs, int64_t n_kv_heads, int64_t group, int64_t n_wg) {
+  const int64_t most = 8 * STREAM_WIDE_WG, waves = pairs * n_kv_heads < most ? pairs * n_kv_heads : most;
+  return waves > (1 + 2 * group) * 4 * n_wg;
+}
 
 // Shares of the tile stream.  Wave W of the `used` waves gets the tiles [start(W), start(W + 1)).
 //   * Fewer tiles than waves: the empty ranges are all on the LEFT (wave W gets tile total - (used - W)), never

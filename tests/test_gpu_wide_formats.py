@@ -100,3 +100,37 @@ def test_no_less_exact_than_the_vector_kernel(kvd, d):
         errs.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     print(f"{kvd} {d}: relative error vector kernel {errs[0]:.2e}, matrix cores {errs[1]:.2e}")
     assert errs[1] <= 1.2 * errs[0] + 1e-8
+
+
+@pytest.mark.parametrize("step", [False, True])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("kernel", [B.KERNEL_AUTO, B.KERNEL_VALU])
+@pytest.mark.parametrize("kvd,d", [("f32", 64), ("f32", 160), ("bf16", 96), ("bf16", 128), ("bf16", 256)])
+def test_both_kernels_in_both_layouts(kvd, d, kernel, paged, step):
+    """The tile stream (AUTO) and the chunked kernel (VALU: a step appends, then attends)."""
+    w, dp, lens, kv, held, where = make([1, 15, 16, 17, 700, 2500, 48, 333], kvd, d, 6, 2, extra=1, paged=paged, decode_kernel=kernel)
+    tol = TOL if kernel == B.KERNEL_VALU or (kvd, d) != ("bf16", 128) else (2e-5, 2e-4)
+    q = wl.queries(w, 0, sharp=True)
+    if not step:
+        H.check(H.decode(dp, 0, q, lens, **where), H.oracle_out(w, q, held), *tol, what=f"{kvd} {d}")
+        return
+    k_new, v_new = (np.stack([kv[r][i][lens[r]] for r in range(len(lens))]) for i in (0, 1))
+    H.check(H.decode_step(dp, 0, q, k_new, v_new, lens + 1, **where), H.oracle_out(w, q, kv), *tol, what=f"{kvd} {d}")
+    for r in range(len(lens)):
+        at = dict(block_row=where["block_table"][r]) if paged else {}
+        gk, gv = H.gather(dp, 0, 0 if paged else int(where["offsets"][r]), int(lens[r]) + 1, **at)
+        np.testing.assert_array_equal(gk, kv[r][0])
+        np.testing.assert_array_equal(gv, kv[r][1])
+
+
+@pytest.mark.parametrize("max_splits", [24, 72, 200, 520])
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (8, 8), (16, 4)])
+def test_small_workspaces_by_either_kernel(hq, hkv, max_splits):
+    """Which kernel a small workspace is served by depends on the heads (tests/test_host_dispatch.py): either serves it, attention
+    and fused step, whatever the workspace holds."""
+    w, dp, lens, kv, held, where = make([4000, 3, 900], "f32", 64, hq, hkv, extra=1, max_splits=max_splits)
+    q = wl.queries(w, 0, sharp=True)
+    dp.workspace.fill_(0xff)
+    H.check(H.decode(dp, 0, q, lens, **where), H.oracle_out(w, q, held), *TOL, what=f"max_splits={max_splits}")
+    k_new, v_new = (np.stack([kv[r][i][lens[r]] for r in range(3)]) for i in (0, 1))
+    H.check(H.decode_step(dp, 0, q, k_new, v_new, lens + 1, **where), H.oracle_out(w, q, kv), *TOL, what=f"max_splits={max_splits}")

@@ -92,3 +92,54 @@ def test_two_threads_raise_the_lds_size(runtime, pool):
         decode(p, 900)
         decode(p2, 1000)
     """)
+
+
+def test_kernels_that_serve_a_pool(runtime):
+    """AUTO: the tile stream, in its wide formats where head_dim or storage ask for them; VALU: the chunked kernel.  A fused
+    step is one launch on the tile stream, an append and three launches on the chunked kernel."""
+    run(runtime, """
+        stream, chunked = ["decode_stream_kernel"], ["plan_kernel", "decode_valu_kernel", "reduce_kernel"]
+        names = lambda call: [k for k, *_ in launched(call)]
+        formats = [(B.F32, d) for d in range(32, 257, 32)] + [(B.BF16, d) for d in range(32, 257, 32)] + [(B.FP8, 128)]
+        for kv, d in formats:
+            for paged in (False, True):
+                p = make_pool(kv_dtype=kv, head_dim=d)
+                assert names(lambda: decode(p, 6, paged=paged)) == stream
+                assert names(lambda: step(p, 6, paged=paged)) == stream
+                assert names(lambda: step(p, 6, B.REUSE_PLAN, paged=paged)) == stream
+                if kv == B.FP8:
+                    continue
+                p = make_pool(kv_dtype=kv, head_dim=d, decode_kernel=B.KERNEL_VALU)
+                assert p.odma_pool_decode_kernel() == B.KERNEL_VALU
+                assert names(lambda: decode(p, 6, paged=paged)) == chunked
+                assert names(lambda: step(p, 6, paged=paged)) == ["append_kernel"] + chunked
+        p = make_pool(kv_dtype=B.F32)
+        assert names(lambda: decode(p, 1024)) == stream
+        assert names(lambda: decode(p, 1025)) == ["stream_plan_kernel"] + stream
+    """)
+
+
+def test_kernels_that_serve_a_pool_with_a_small_workspace(runtime):
+    """max_splits sizes the workspace: the wide formats take as many work-groups as fit, from 16 up, unless the chunked kernel
+    has more than 1 + 2 G times their waves there."""
+    run(runtime, """
+        seen = set()
+        for kv, d, hq, hkv in [(B.F32, 64, 4, 2), (B.F32, 128, 28, 4), (B.F32, 128, 8, 8), (B.F32, 128, 32, 32), (B.F32, 256, 16, 8),
+                               (B.BF16, 96, 16, 4), (B.BF16, 32, 32, 32), (B.BF16, 32, 16, 1)]:
+            served = []
+            for max_splits in [1, 8, 24, 32, 40, 56, 72, 100, 136, 200, 264, 400, 520, 700, 1032, 8192]:
+                p = make_pool(kv_dtype=kv, head_dim=d, hq=hq, hkv=hkv, max_requests=8, max_splits=max_splits)
+                got = launched(lambda: decode(p, 6))
+                if got[0][0] == "plan_kernel":
+                    assert [k for k, *_ in got] == ["plan_kernel", "decode_valu_kernel", "reduce_kernel"]
+                    served.append(0)
+                    continue
+                assert len(got) == 1
+                n_wg = got[0][1][0]
+                assert 16 <= n_wg <= 256 and min((8 + max_splits) * hkv, 2048) <= (1 + 2 * hq // hkv) * 4 * n_wg, got
+                served.append(n_wg)
+            assert served[0] == 0 and served[-2:] == [256, 256], served
+            seen.add(tuple(served))
+        # many KV heads, one query head each: chunked as long as the workspace is small
+        assert any(s[8] == 0 for s in seen) and any(s[3] > 0 for s in seen), seen
+    """)
