@@ -1196,6 +1196,9 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
     // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
     // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 8.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
+    // The reference is the running maximum, as the vector kernel's was, and not a lazy one: weights of up to 2^LAZY_REF_LOG2
+    // would take values past 1e36 out of the range of fp32 (lazy took 0.9 % less time at head_dim 128 in fp32, with the same
+    // error; a reference 2^LAZY_REF_LOG2 above the maximum keeps the range, but its exponents are larger, and so was the error: 3.5e-7).
     auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
       const bool ragged = n_valid < TT;
@@ -1223,7 +1226,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         }
       }
       tmax = column_max(tmax);
-      if (__builtin_amdgcn_ballot_w64(tmax > m + LAZY_REF_LOG2) != 0) {   // lazy reference, as for head_dim 128
+      if (__builtin_amdgcn_ballot_w64(tmax > m) != 0) {
         const float m_new = fmaxf(m, tmax);
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         m = m_new;

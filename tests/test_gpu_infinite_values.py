@@ -154,3 +154,27 @@ def test_prompt_whose_first_tokens_are_switched_off(score):
             ref = H.oracle_out(w, q[q_start[r] + j:q_start[r] + j + 1], [(kv[r][0][:seen], kv[r][1][:seen])])
             # (the weights of a prompt are bf16: 2^-8 of the values they average)
             H.check(got[q_start[r] + j:q_start[r] + j + 1], ref, 2.0 ** -8 * w.data_scale * 4, 2e-2, what=f"request {r} query {j}")
+
+
+@pytest.mark.parametrize("size", [1e-37, 1e37])
+@pytest.mark.parametrize("kvd,d,kernel", [("f32", 64, B.KERNEL_AUTO), ("f32", 128, B.KERNEL_AUTO), ("f32", 64, B.KERNEL_VALU),
+                                          ("bf16", 32, B.KERNEL_AUTO), ("bf16", 96, B.KERNEL_AUTO), ("bf16", 256, B.KERNEL_AUTO)])
+def test_values_near_the_ends_of_the_range(kvd, d, kernel, size):
+    """Values of 1e37 and 1e-37: the weights that multiply them are at most 1, the largest of a request is 1.  (Few tokens of
+    like weight, so that their sum stays in range.)"""
+    lens = np.array([1, 2, 17, 40, 300])
+    w = small_workload(lens, kv_dtype=kvd, hq=4, hkv=2, d=d, seed=d, bounds=(64, 1024), large_cap=1024, main=1 << 13)
+    dp = H.make_pool(w, out_dtype=B.F32, decode_kernel=kernel)
+    kv = []
+    for r in range(len(lens)):
+        k, _ = wl.request_kv(w, 0, r, sharp=True)
+        v, _ = wl.draw_values(np.random.default_rng([7, r]), k.shape, size, kvd)
+        kv.append((k, v))
+    q, _ = wl.draw_values(np.random.default_rng(7), (len(lens), 4, d), 4.0, kvd)
+    off, _ = H.assign_perfect(dp, lens)
+    H.fill(dp, 0, kv, offsets=off)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    assert np.isfinite(got).all()
+    # (values of 1e-37 sit at the bottom of the normal range, where sums lose up to eight bits)
+    tol = (1e-5, 1e-5) if size > 1 else (1e-4, 1e-4)
+    H.check(got.astype(np.float64) / size, H.oracle_out(w, q, kv) / size, *tol, what=f"{kvd} {d}")
