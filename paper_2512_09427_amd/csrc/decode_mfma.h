@@ -1781,6 +1781,25 @@ inline hipError_t launch_with_lds(void (*kernel)(StreamArgs), std::atomic<unsign
   return hipSuccess;
 }
 
+// The wide formats of one storage type, in the launch shape of four waves and two buffers: BASE + D32 for every D32 given
+// (head_dim 32 D32).  Instantiated in a unit of its own per storage type.
+template <int BASE, int... D32>
+hipError_t launch_wide(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args) {
+  struct Entry {
+    int fmt;
+    void (*kernel[2][2])(StreamArgs);                        // [fused][paged]
+  };
+  static const Entry entries[] = {
+      {BASE + D32,
+       {{decode_stream_kernel<false, 2, 4, false, BASE + D32>, decode_stream_kernel<true, 2, 4, false, BASE + D32>},
+        {decode_stream_kernel<false, 2, 4, true, BASE + D32>, decode_stream_kernel<true, 2, 4, true, BASE + D32>}}}...};
+  static std::atomic<unsigned> allowed[sizeof...(D32)][2][2];   // dynamic LDS enabled so far (nothing: zero-initialised)
+  for (size_t i = 0; i < sizeof...(D32); ++i)
+    if (entries[i].fmt == fmt)
+      return launch_with_lds(entries[i].kernel[fused][paged], allowed[i][fused][paged], n_wg, 4, lds_bytes, s, *(const StreamArgs*)args);
+  return hipErrorInvalidDeviceFunction;
+}
+
 }  // namespace
 
 // The wide formats are compiled in units of their own (odma_wide_f32.hip, odma_wide_bf16.hip).  args: a StreamArgs, whose

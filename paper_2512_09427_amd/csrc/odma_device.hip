@@ -463,8 +463,6 @@ int odma_decode_attention_static(odma_pool_t* pool, int32_t layer, int32_t n, co
   if (rc) return rc;
   DecodeScratch sc;
   sc.base = dev->ptr;
-  sc.layout.header = sl.header;
-  sc.layout.req_info = sl.req_info;
   sc.layout.items = sl.items;
   sc.layout.waves = sl.waves;
   sc.layout.red = sl.red;
@@ -522,6 +520,3 @@ int launch_migrate_copy(odma_pool* pool, int32_t n, const int64_t* src_byte, con
 }
 const bool migrate_copy_installed = (odma::migrate_copy = &launch_migrate_copy, true);
 }  // namespace
-
-extern "C" {
-}  // extern "C"

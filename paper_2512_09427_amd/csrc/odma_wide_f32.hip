@@ -3,33 +3,6 @@
 
 #include "decode_mfma.h"
 
-namespace {
-
-using StreamKernel = void (*)(StreamArgs);
-// [fused][paged], launch shape of four waves and two buffers
-#define ODMA_WIDE(D32) {{decode_stream_kernel<false, 2, 4, false, STREAM_F32_WIDE + D32>, decode_stream_kernel<true, 2, 4, false, STREAM_F32_WIDE + D32>}, \
-                        {decode_stream_kernel<false, 2, 4, true, STREAM_F32_WIDE + D32>, decode_stream_kernel<true, 2, 4, true, STREAM_F32_WIDE + D32>}}
-struct WideKernels {
-  int head_dim;
-  StreamKernel kernel[2][2];
-};
-const WideKernels wide_kernels[] = {
-    {32, ODMA_WIDE(1)},
-    {64, ODMA_WIDE(2)},
-    {96, ODMA_WIDE(3)},
-    {128, ODMA_WIDE(4)},
-    {160, ODMA_WIDE(5)},
-    {192, ODMA_WIDE(6)},
-    {224, ODMA_WIDE(7)},
-    {256, ODMA_WIDE(8)}};
-std::atomic<unsigned> wide_lds[sizeof(wide_kernels) / sizeof(wide_kernels[0])][2][2];   // dynamic LDS enabled so far
-
-}  // namespace
-
 hipError_t odma_launch_wide_f32(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args) {
-  for (size_t i = 0; i < sizeof(wide_kernels) / sizeof(wide_kernels[0]); ++i)
-    if (wide_kernels[i].head_dim == 32 * (fmt - STREAM_F32_WIDE))
-      return launch_with_lds(wide_kernels[i].kernel[fused][paged], wide_lds[i][fused][paged], n_wg, 4, lds_bytes, s,
-                             *(const StreamArgs*)args);
-  return hipErrorInvalidDeviceFunction;
+  return launch_wide<STREAM_F32_WIDE, 1, 2, 3, 4, 5, 6, 7, 8>(fmt, fused, paged, n_wg, lds_bytes, s, args);
 }
