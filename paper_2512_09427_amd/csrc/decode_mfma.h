@@ -526,6 +526,7 @@ __device__ __forceinline__ float column_sum(float x) {
   return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 constexpr float LAZY_REF_LOG2 = 8.0f;
+constexpr float WIDE_LAZY_REF_LOG2 = 4.0f, WIDE_WEIGHT_SCALE = 0x1p-4f;   // wide formats: slack, and the factor 2^-slack of their weights
 
 // Development builds only (-DODMA_DEV_TIMELINE): wall-clock stamps (100 MHz) per wave, read back with
 // odma_dev_timeline().  Slots: 0 kernel entry, 1 range descriptor in registers, 2 stream end, 3 queued results written,
@@ -1196,9 +1197,10 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
     // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
     // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 8.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
-    // The reference is the running maximum, as the vector kernel's was, and not a lazy one: weights of up to 2^LAZY_REF_LOG2
-    // would take values past 1e36 out of the range of fp32 (lazy took 0.9 % less time at head_dim 128 in fp32, with the same
-    // error; a reference 2^LAZY_REF_LOG2 above the maximum keeps the range, but its exponents are larger, and so was the error: 3.5e-7).
+    // Weights are carried times 2^-4, the state's l and O with them, and the lazy reference may lag by 2^4: no weight exceeds
+    // 1, as none did in the vector kernel, and values past 1e36 stay in the range of fp32 (at the other end, values under
+    // 1e-36 lose up to four bits of it).  The factor is exact, so results are those of the unscaled weights.  (The running
+    // maximum as reference, rescaled whenever it moves, cost up to 5 %; the factor inside the exponent cost accuracy, 3.2e-7 -> 3.5e-7.)
     auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
       const bool ragged = n_valid < TT;
@@ -1226,7 +1228,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         }
       }
       tmax = column_max(tmax);
-      if (__builtin_amdgcn_ballot_w64(tmax > m) != 0) {
+      if (__builtin_amdgcn_ballot_w64(tmax > m + WIDE_LAZY_REF_LOG2) != 0) {   // lazy reference, as for head_dim 128
         const float m_new = fmaxf(m, tmax);
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         m = m_new;
@@ -1240,7 +1242,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         float pv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          pv[i] = __builtin_amdgcn_exp2f(x[b][i] - m);
+          pv[i] = __builtin_amdgcn_exp2f(x[b][i] - m) * WIDE_WEIGHT_SCALE;
           psum += pv[i];
         }
         if (F32) {
