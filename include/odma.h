@@ -84,18 +84,20 @@ extern "C" {
 /* decode kernel choice */
 #define ODMA_KERNEL_AUTO   0     /* MFMA kernel when the shape allows; other shapes (fp32 storage, bf16 with a head_dim other
                                     than 64 and 128) are reported as VALU and run on wide formats of the same tile-stream
-                                    kernel, at fp32 precision, unless max_splits sized the workspace too small for them */
+                                    kernel, at fp32 precision, unless max_splits sized the workspace so small that the VALU
+                                    kernel has many more waves there (it then serves them) */
 #define ODMA_KERNEL_VALU   1     /* fp32 vector-ALU kernel: any dtype, head_dim % 32 == 0 */
 #define ODMA_KERNEL_MFMA   2     /* matrix-core kernel: bf16 storage with head_dim 128 or 64, fp8 storage with head_dim 128; group <= 16 */
 
 /* odma_decode_attention flags */
 #define ODMA_REUSE_PLAN    1     /* caller asserts that n, lengths, offsets and the choice between offsets and a block
                                     table are what the previous planning call on this pool saw (the 28 layers of one
-                                    step): skip re-planning.  The matrix-core plan bakes the slab bases in, so the
+                                    step): skip re-planning.  The tile-stream plan (matrix-core kernel and wide
+                                    formats) bakes the slab bases in, so the
                                     library drops the flag by itself, and plans again, whenever it knows the assertion
                                     cannot hold: n differs, contiguous/paged differs, a request was assigned, released
-                                    or migrated since, or a launch-shape knob changed.  Changed lengths, or offsets
-                                    edited by the caller, it cannot see. */
+                                    or migrated since, a launch-shape knob changed, or the call that planned
+                                    failed.  Changed lengths, or offsets edited by the caller, it cannot see. */
 #define ODMA_SKIP_REDUCE   2     /* kernel timing only: no cross-split reduction (neither the launch nor the in-kernel
                                     merge), so outputs of requests split over several chunks are NOT valid */
 
@@ -285,9 +287,9 @@ int odma_append_kv(odma_pool_t* pool, int32_t layer, int32_t n,
  *   block_table DEVICE int32[n][bt_stride] or NULL (contiguous slabs)
  * Plans (unless ODMA_REUSE_PLAN), attends and merges split requests on `stream`, using
  * the pool's workspace; calls on one pool must therefore not overlap on different
- * streams.  On the matrix-core kernel all of it is one launch for up to 1024 requests
- * (beyond that the plan is a launch of its own); the workspace may hold any bytes when
- * a planning call begins. */
+ * streams.  On the matrix-core kernel and the wide formats all of it is one launch for up
+ * to 1024 requests (beyond that the plan is a launch of its own); the workspace may hold
+ * any bytes when a planning call begins. */
 int odma_decode_attention(odma_pool_t* pool, int32_t layer, int32_t n,
                           const void* q, const int64_t* offsets, const int32_t* lengths,
                           const int32_t* block_table, int32_t bt_stride,
@@ -298,8 +300,9 @@ int odma_decode_attention(odma_pool_t* pool, int32_t layer, int32_t n,
  * streams a request's last block patches the new row in and writes it to the pool).
  * lengths are the lengths AFTER the append and must be >= 1 (a request with length 0 is
  * skipped and yields zeros).  k_new, v_new: DEVICE [n][Hkv][D] kv_dtype.  Other arguments as
- * for odma_decode_attention.  One launch on the matrix-core kernel; on the vector-ALU kernel the
- * row append and the attention are launched one after the other.  Capacity is the caller's business (odma_advance / odma_migrate). */
+ * for odma_decode_attention.  One launch on the matrix-core kernel and the wide formats (which write the
+ * token's neighbours in its block, same request, back unchanged); on the vector-ALU kernel the row append and
+ * the attention are launched one after the other.  Capacity is the caller's business (odma_advance / odma_migrate). */
 int odma_decode_step(odma_pool_t* pool, int32_t layer, int32_t n, const void* q, const void* k_new,
                      const void* v_new, const int64_t* offsets, const int32_t* lengths,
                      const int32_t* block_table, int32_t bt_stride, void* out, uint32_t flags,
@@ -367,8 +370,11 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
 
 /* Launch-shape knobs for experiments and benchmarks; defaults suit MI355X.  Returns
  * ODMA_INVALID_ARG for an unknown knob or a value outside its range. */
+/* (The wide formats run in work-groups of four waves with two tile buffers, at most one work-group per compute unit: they
+ * honour MIN_CHUNK, ODD_XCD_WEIGHT and FUSE_REDUCE, WAVES_PER_CU up to 4, and ignore the others.) */
 #define ODMA_TUNE_WAVES_PER_CU     1   /* decode waves launched per compute unit, 1..64; 0 = default (MFMA kernel: 4 = one per
-                                          SIMD; VALU kernel: 8) */
+                                          SIMD; VALU kernel: 8).  The MFMA kernel launches at most 2048 work-groups, which
+                                          is 32 waves per compute unit in work-groups of four */
 #define ODMA_TUNE_ITEMS_PER_WAVE   2   /* VALU kernel: work items aimed at per wave, in sixteenths, 4..256 (default 32 = 2.0) */
 #define ODMA_TUNE_MIN_CHUNK        3   /* smallest range a wave is given, in tokens, multiple of 64 (default 64) */
 #define ODMA_TUNE_PIPELINE_DEPTH   4   /* register tile buffers per wave in the MFMA kernel: 2 or 3 (default 2) */
@@ -394,7 +400,8 @@ int odma_pool_tune(odma_pool_t* pool, int32_t knob, int32_t value);
 int odma_stream_plan_ranges(int32_t total_tiles, int32_t n_waves, int32_t waves_per_wg, int32_t min_tiles,
                             int32_t odd_xcd_weight, int32_t late_wave_weight, int32_t* start, int32_t* waves_used);
 
-/* Names the decode kernel the pool resolved to (ODMA_KERNEL_VALU or _MFMA). */
+/* Names the decode kernel the pool resolved to (ODMA_KERNEL_VALU or _MFMA; VALU also for pools that the wide formats of the
+ * tile-stream kernel serve, see ODMA_KERNEL_AUTO). */
 int odma_pool_decode_kernel(const odma_pool_t* pool);
 
 const char* odma_last_error(void);

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // A call whose items are few (the launch's rule) plans here instead of in a launch in front -- six microseconds of one
   // work-group's round trips and the edge between two launches -- and its work-groups take every `turns`-th item of their
   // queue: no counter has to be clear before the launch.  7 prompts of 21 to
-  // 58 tokens 11.2 -> 8.9 us, 28 of 91 to 546 tokens 20.0 -> 18.3.
+  // 58 tokens 11.2 -> 8.3 us, 28 of 91 to 546 tokens 20.0 -> 17.5.
   const int* bound = a.hdr->bound;
   if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
     __shared__ PrefillPlan plan;

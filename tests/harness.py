@@ -215,7 +215,7 @@ def assign_perfect(dp: DevicePool, lengths: np.ndarray, extra: int = 0):
 
 def run_smoke():
     assert torch.cuda.is_available(), "smoke() needs a GPU"
-    # Tiny configuration (fp32, VALU kernel): assign -> append -> decode, against the oracle
+    # Tiny configuration (fp32, wide format of the tile stream): assign -> append -> decode, against the oracle
     w = wl.tiny()
     dp = make_pool(w)
     off, _ = assign_perfect(dp, w.lengths)
@@ -224,7 +224,7 @@ def run_smoke():
     q = wl.queries(w, 0)
     got = decode(dp, 0, q, w.lengths, offsets=off)
     rel = check(got, oracle_out(w, q, kv), 1e-5, 1e-5, "tiny")
-    print(f"smoke tiny (fp32, VALU kernel): max err / max|ref| = {rel:.2e}")
+    print(f"smoke tiny (fp32, tile-stream kernel): max err / max|ref| = {rel:.2e}")
     # a few Qwen-shaped bf16 requests through the MFMA kernel, one of them split over chunks
     w2 = wl.qwen_b64()
     w2.lengths = np.array([1, 17, 300, 2500, 64, 1023], dtype=np.int64)
