@@ -57,7 +57,7 @@ struct StreamArgs {
   ReduceDesc* red;           // [n_workgroups + 1], the last one empty
   const int32_t* lengths;
   const int64_t* offsets;    // nullptr when paged
-  int32_t plan_at;           // -1: the plan is in memory; else float offset of the planning area in LDS
+  int32_t plan_at;           // a launch that plans: float offset of the planning area in LDS
   int32_t q_min, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (StreamShares)
   int32_t whole_extra;       // tiles beyond an equal share that a wave may get in order that no segment is cut (-1: never)
   unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
@@ -579,7 +579,9 @@ __host__ __device__ constexpr int stream_min_waves(int fmt) {
   return stream_format(fmt).np * stream_format(fmt).blocks >= 5 ? 1 : 2;
 }
 
-template <bool PAGED, int NBUF, int WPW, bool FUSED, int FMT>
+// PLAN: the launch makes its plan (a variant of its own: with the planning code behind a run-time branch every launch that
+// reuses a plan, all layers of a step but the first, was 0.3 to 0.7 us longer, and fused bf16 steps of head_dim 64 up to 7 %)
+template <bool PAGED, int NBUF, int WPW, bool FUSED, int FMT, bool PLAN>
 __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream_kernel(StreamArgs a) {
   constexpr bool FP8 = FMT == STREAM_FP8_D128, D64 = FMT == STREAM_BF16_D64;
   constexpr bool WIDE = FMT > STREAM_BF16_WIDE, F32 = FMT > STREAM_F32_WIDE;
@@ -615,13 +617,12 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
   constexpr int BLOCK_BYTES = BLK * HD * F.eb;             // one pool block of K (or V)
 
   // the wave's range first: everything else waits for it
-  const bool planning = a.plan_at >= 0;
   const InlinePlan pl(lds, a.plan_at, WPW, gridDim.x, a.n);
   WaveDesc wd;
   // in-kernel merge: the segments cut at this work-group's two boundaries, requested now so that the
   // epilogue does not wait for them (a launch that plans finds them in LDS while its last stores are under way)
   ReduceDesc rd_cut[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-  if (planning) {
+  if constexpr (PLAN) {
     plan_in_block<WPW, TT>(a, pl);
     wd = inline_wave_desc<WPW>(a, pl);
   } else {
@@ -649,7 +650,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
 
     auto load_window = [&](Window& w, int e_base) {
       const int idx = min(e_base + lane, n_entries - 1);
-      if (planning) {
+      if constexpr (PLAN) {
         w.r = pl.r[idx];
         w.tiles = pl.tiles[idx];
         w.len = pl.len[idx];
@@ -1570,7 +1571,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
 #endif
   }
 
-  if (planning) {
+  if constexpr (PLAN) {
     rd_cut[0] = inline_cut<WPW>(pl, blockIdx.x, gridDim.x);
     rd_cut[1] = inline_cut<WPW>(pl, blockIdx.x + 1, gridDim.x);
     store_inline_plan<WPW>(a, pl, rd_cut[0]);
@@ -1783,9 +1784,29 @@ inline hipError_t launch_with_lds(void (*kernel)(StreamArgs), std::atomic<unsign
   return hipSuccess;
 }
 
+// Every launch shape of a format: register buffers per wave (3 or 2), waves per work-group (8 or 4).
+template <int FMT, bool PLAN>
+hipError_t launch_shapes(bool fused, bool paged, int nbuf, int wpw, int n_wg, size_t lds_bytes, hipStream_t s, const void* args) {
+  // [fused][paged][3 - nbuf][wpw == 4]
+#ifdef ODMA_DEV_MINIMAL_VARIANTS
+  // development builds: only the default shape is compiled; the launch of another fails with an error
+#define ODMA_SHAPES(U, P) {{nullptr, nullptr}, {nullptr, decode_stream_kernel<P, 2, 4, U, FMT, PLAN>}}
+#else
+#define ODMA_SHAPES(U, P) {{decode_stream_kernel<P, 3, 8, U, FMT, PLAN>, decode_stream_kernel<P, 3, 4, U, FMT, PLAN>}, \
+                           {decode_stream_kernel<P, 2, 8, U, FMT, PLAN>, decode_stream_kernel<P, 2, 4, U, FMT, PLAN>}}
+#endif
+  static void (*const kernels[2][2][2][2])(StreamArgs) = {{ODMA_SHAPES(false, false), ODMA_SHAPES(false, true)},
+                                                          {ODMA_SHAPES(true, false), ODMA_SHAPES(true, true)}};
+#undef ODMA_SHAPES
+  static std::atomic<unsigned> allowed[2][2][2][2];          // dynamic LDS enabled so far (nothing: zero-initialised)
+  const auto kernel = kernels[fused][paged][3 - nbuf][wpw == 4];
+  if (!kernel) return hipErrorInvalidDeviceFunction;
+  return launch_with_lds(kernel, allowed[fused][paged][3 - nbuf][wpw == 4], n_wg, wpw, lds_bytes, s, *(const StreamArgs*)args);
+}
+
 // The wide formats of one storage type, in the launch shape of four waves and two buffers: BASE + D32 for every D32 given
 // (head_dim 32 D32).  Instantiated in a unit of its own per storage type.
-template <int BASE, int... D32>
+template <bool PLAN, int BASE, int... D32>
 hipError_t launch_wide(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args) {
   struct Entry {
     int fmt;
@@ -1793,8 +1814,8 @@ hipError_t launch_wide(int fmt, bool fused, bool paged, int n_wg, size_t lds_byt
   };
   static const Entry entries[] = {
       {BASE + D32,
-       {{decode_stream_kernel<false, 2, 4, false, BASE + D32>, decode_stream_kernel<true, 2, 4, false, BASE + D32>},
-        {decode_stream_kernel<false, 2, 4, true, BASE + D32>, decode_stream_kernel<true, 2, 4, true, BASE + D32>}}}...};
+       {{decode_stream_kernel<false, 2, 4, false, BASE + D32, PLAN>, decode_stream_kernel<true, 2, 4, false, BASE + D32, PLAN>},
+        {decode_stream_kernel<false, 2, 4, true, BASE + D32, PLAN>, decode_stream_kernel<true, 2, 4, true, BASE + D32, PLAN>}}}...};
   static std::atomic<unsigned> allowed[sizeof...(D32)][2][2];   // dynamic LDS enabled so far (nothing: zero-initialised)
   for (size_t i = 0; i < sizeof...(D32); ++i)
     if (entries[i].fmt == fmt)
@@ -1804,7 +1825,22 @@ hipError_t launch_wide(int fmt, bool fused, bool paged, int n_wg, size_t lds_byt
 
 }  // namespace
 
-// The wide formats are compiled in units of their own (odma_wide_f32.hip, odma_wide_bf16.hip).  args: a StreamArgs, whose
-// type is local to every unit.
+// The kernels are compiled in units of their own, one per format (or family of wide formats) and PLAN: odma_stream.hip,
+// odma_wide_f32.hip and odma_wide_bf16.hip.  args: a StreamArgs, whose type is local to every unit.
+template <int FMT, bool PLAN>
+hipError_t odma_launch_stream(bool fused, bool paged, int nbuf, int wpw, int n_wg, size_t lds_bytes, hipStream_t s, const void* args);
+template <bool PLAN>
 hipError_t odma_launch_wide_f32(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args);
+template <bool PLAN>
 hipError_t odma_launch_wide_bf16(int fmt, bool fused, bool paged, int n_wg, size_t lds_bytes, hipStream_t s, const void* args);
+#define ODMA_STREAM_UNIT(FMT, PLAN) \
+  template <> hipError_t odma_launch_stream<FMT, PLAN>(bool, bool, int, int, int, size_t, hipStream_t, const void*);
+#define ODMA_WIDE_UNITS(PLAN) \
+  template <> hipError_t odma_launch_wide_f32<PLAN>(int, bool, bool, int, size_t, hipStream_t, const void*); \
+  template <> hipError_t odma_launch_wide_bf16<PLAN>(int, bool, bool, int, size_t, hipStream_t, const void*);
+ODMA_STREAM_UNIT(STREAM_BF16_D128, false) ODMA_STREAM_UNIT(STREAM_BF16_D128, true)
+ODMA_STREAM_UNIT(STREAM_FP8_D128, false) ODMA_STREAM_UNIT(STREAM_FP8_D128, true)
+ODMA_STREAM_UNIT(STREAM_BF16_D64, false) ODMA_STREAM_UNIT(STREAM_BF16_D64, true)
+ODMA_WIDE_UNITS(false) ODMA_WIDE_UNITS(true)
+#undef ODMA_STREAM_UNIT
+#undef ODMA_WIDE_UNITS

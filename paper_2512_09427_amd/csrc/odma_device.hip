@@ -136,31 +136,20 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
 
 namespace {
 
-// Every instantiation of the tile-stream attention kernel but the wide formats (odma_wide_*.hip), indexed [format][fused][paged][3 - nbuf][wpw == 4],
-// and per instantiation the largest dynamic LDS size enabled so far (the default limit is 64 KiB).
-using StreamKernel = void (*)(StreamArgs);
-#ifdef ODMA_DEV_MINIMAL_VARIANTS
-// development builds: only the default launch shape of the bf16 / head_dim 128 format is compiled; every other entry
-// is null and its launch fails with an error
-#define ODMA_SK_W(F, U, P, N) {nullptr, (F == STREAM_BF16_D128 && N == 2) ? decode_stream_kernel<P, 2, 4, U, STREAM_BF16_D128> : nullptr}
-#else
-#define ODMA_SK_W(F, U, P, N) {decode_stream_kernel<P, N, 8, U, F>, decode_stream_kernel<P, N, 4, U, F>}
-#endif
-#define ODMA_SK_N(F, U, P) {ODMA_SK_W(F, U, P, 3), ODMA_SK_W(F, U, P, 2)}
-#define ODMA_SK_P(F, U) {ODMA_SK_N(F, U, false), ODMA_SK_N(F, U, true)}
-#define ODMA_SK_U(F) {ODMA_SK_P(F, false), ODMA_SK_P(F, true)}
-const StreamKernel stream_kernels[3][2][2][2][2] = {ODMA_SK_U(STREAM_BF16_D128), ODMA_SK_U(STREAM_FP8_D128),
-                                                    ODMA_SK_U(STREAM_BF16_D64)};
-std::atomic<unsigned> stream_kernel_lds[3][2][2][2][2];   // zero-initialised: nothing enabled beyond the default
-
-hipError_t launch_stream_kernel(int fmt, bool fused, bool paged, int nbuf, int wpw, int n_wg, size_t lds_bytes,
+// plan: the launch makes its plan
+hipError_t launch_stream_kernel(int fmt, bool plan, bool fused, bool paged, int nbuf, int wpw, int n_wg, size_t lds_bytes,
                                 hipStream_t s, const StreamArgs& a) {
-  if (fmt > STREAM_F32_WIDE) return odma_launch_wide_f32(fmt, fused, paged, n_wg, lds_bytes, s, &a);
-  if (fmt > STREAM_BF16_WIDE) return odma_launch_wide_bf16(fmt, fused, paged, n_wg, lds_bytes, s, &a);
-  if (fmt < 0 || fmt > 2 || (nbuf != 2 && nbuf != 3) || (wpw != 4 && wpw != 8)) return hipErrorInvalidValue;
-  const StreamKernel kernel = stream_kernels[fmt][fused][paged][3 - nbuf][wpw == 4];
-  if (!kernel) return hipErrorInvalidDeviceFunction;
-  return launch_with_lds(kernel, stream_kernel_lds[fmt][fused][paged][3 - nbuf][wpw == 4], n_wg, wpw, lds_bytes, s, a);
+  if (fmt > STREAM_F32_WIDE)
+    return (plan ? odma_launch_wide_f32<true> : odma_launch_wide_f32<false>)(fmt, fused, paged, n_wg, lds_bytes, s, &a);
+  if (fmt > STREAM_BF16_WIDE)
+    return (plan ? odma_launch_wide_bf16<true> : odma_launch_wide_bf16<false>)(fmt, fused, paged, n_wg, lds_bytes, s, &a);
+  if ((nbuf != 2 && nbuf != 3) || (wpw != 4 && wpw != 8)) return hipErrorInvalidValue;
+  const auto launch = fmt == STREAM_BF16_D128  ? (plan ? odma_launch_stream<STREAM_BF16_D128, true> : odma_launch_stream<STREAM_BF16_D128, false>)
+                      : fmt == STREAM_FP8_D128 ? (plan ? odma_launch_stream<STREAM_FP8_D128, true> : odma_launch_stream<STREAM_FP8_D128, false>)
+                      : fmt == STREAM_BF16_D64 ? (plan ? odma_launch_stream<STREAM_BF16_D64, true> : odma_launch_stream<STREAM_BF16_D64, false>)
+                                               : nullptr;
+  if (!launch) return hipErrorInvalidValue;
+  return launch(fused, paged, nbuf, wpw, n_wg, lds_bytes, s, &a);
 }
 
 // Static scratch of odma_decode_attention_static: plan records, arrival counters and partial states of one decode
@@ -352,7 +341,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
       stamp = odma_pool::PlanStamp();
     }
     const int nbuf = pool->pipeline_depth;
-    hipError_t e = launch_stream_kernel(fmt, fused, block_table != nullptr, nbuf, wpw, n_wg, lds_bytes, s, a);
+    hipError_t e = launch_stream_kernel(fmt, a.plan_at >= 0, fused, block_table != nullptr, nbuf, wpw, n_wg, lds_bytes, s, a);
     if (e != hipSuccess) {
       (void)hipGetLastError();                               // reported here, not by the next call as well
       return hip_fail(where, e);
@@ -475,14 +464,6 @@ int odma_decode_attention_static(odma_pool_t* pool, int32_t layer, int32_t n, co
   return decode_impl(where, pool, layer, n, q, nullptr, nullptr, offsets, lengths, block_table, bt_stride, out, flags,
                      stream, &sc);
 }
-
-#ifdef ODMA_DEV_TIMELINE
-int odma_dev_timeline(long long* host_dst, size_t n_values) {
-  hipError_t e = hipDeviceSynchronize();
-  if (e == hipSuccess) e = hipMemcpyFromSymbol(host_dst, HIP_SYMBOL(odma_dev_timeline_buf), n_values * sizeof(long long));
-  return e == hipSuccess ? ODMA_OK : hip_fail("odma_dev_timeline", e);
-}
-#endif
 
 }  // extern "C"
 
