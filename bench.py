@@ -681,12 +681,12 @@ def main():
     if one_launch:
         dom_us, bytes_per_launch = time_step_kernel(torch, B, runner, reps=10, graph=use_graph)
         dom_eager_us, _ = time_step_kernel(torch, B, runner, reps=10, graph=False)
-        dom_name = f"decode_stream_kernel<false,2,4,true,{fmt}>"
+        dom_name = f"decode_stream_kernel<false,2,4,true,{fmt},false>"
         dom_what = "fused decode step of one layer: append of the new token, attention, merge of cut segments"
     else:
         dom_us, bytes_per_launch = time_attention_kernel(torch, B, runner, reps=10, with_reduce=True, graph=use_graph)
         dom_eager_us, _ = time_attention_kernel(torch, B, runner, reps=10, with_reduce=True, graph=False)
-        dom_name = f"decode_stream_kernel<false,2,4,false,{fmt}>" if mfma else "decode_valu_kernel<unsigned short,false>"
+        dom_name = f"decode_stream_kernel<false,2,4,false,{fmt},false>" if mfma else "decode_valu_kernel<unsigned short,false>"
         dom_what = "attention of one layer with the cross-split reduction (the append is a launch of its own)"
     achieved = bytes_per_launch / (dom_us * 1e-6) / 1e9
     log(f"dominant kernel of the step ({dom_what}): {dom_us:.2f} us per launch in a graph of 28 ({dom_eager_us:.2f} us "
@@ -733,7 +733,7 @@ def main():
                 "timing": "two events around 10 replays of a HIP graph of 28 launches (one per layer pool)" if use_graph
                           else "two events around 280 eager launches",
                 "bytes_per_launch": int(bytes_per_launch),
-                "attention_only": {"kernel": f"decode_stream_kernel<false,2,4,false,{fmt}>" if mfma
+                "attention_only": {"kernel": f"decode_stream_kernel<false,2,4,false,{fmt},false>" if mfma
                                    else "decode_valu_kernel<unsigned short,false>",
                                    "avg_us": round(attn_us, 2), "bytes_per_launch": int(attn_bytes),
                                    "GBps": round(attn_rate, 1), "frac": round(attn_rate / HBM_PEAK_GBPS, 4),
@@ -851,7 +851,7 @@ def main():
                "oracle_check": chk8, "oracle_check_after_timed_steps": chk8_after}
         if r8.fused:
             sus8, sbytes8 = time_step_kernel(torch, B, r8, reps=10, graph=use_graph)
-            fp8["step_kernel"] = {"kernel": "decode_stream_kernel<false,2,4,true,1>", "avg_us": round(sus8, 2),
+            fp8["step_kernel"] = {"kernel": "decode_stream_kernel<false,2,4,true,1,false>", "avg_us": round(sus8, 2),
                                   "bytes_per_launch": int(sbytes8),
                                   "achieved_GBps": round(sbytes8 / (sus8 * 1e-6) / 1e9, 1)}
         log(f"fp8 pools: {fp8['ms_per_step']:.3f} ms/step ({fp8['step_time_vs_bf16']:.3f} x the bf16 step), {v8:.1f} GB/s KV; "
@@ -879,7 +879,7 @@ def main():
                 "workload": "configs[3]: 28 layers, batch 128, log-normal lengths (median 1024, clip 8192), 64 steps, 6 seeded "
                             "overflows migrated in mid-run by odma_migrate_batch; step = advance + 28 x fused odma_decode_step "
                             "(eager launches, events around the 28 launches)",
-                "roofline": {"bound": "hbm", "kernel": "decode_stream_kernel<false,2,4,true,0>",
+                "roofline": {"bound": "hbm", "kernel": "decode_stream_kernel<false,2,4,true,0,false>",
                              "avg_us": round(c4["kernel_us_per_layer"], 2), "bytes_per_launch": c4["bytes_per_launch"],
                              "achieved": round(c4["bytes_per_launch"] / (c4["kernel_us_per_layer"] * 1e-6) / 1e9, 1),
                              "peak": HBM_PEAK_GBPS, "unit": "GB/s",
