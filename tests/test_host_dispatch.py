@@ -143,3 +143,23 @@ def test_kernels_that_serve_a_pool_with_a_small_workspace(runtime):
         # many KV heads, one query head each: chunked as long as the workspace is small
         assert any(s[8] == 0 for s in seen) and any(s[3] > 0 for s in seen), seen
     """)
+
+
+@pytest.mark.parametrize("kv,d", [("BF16", 128), ("BF16", 64), ("FP8", 128), ("F32", 128), ("BF16", 96)])
+def test_launches_that_plan_are_kernels_of_their_own(runtime, kv, d):
+    """One kernel per (planning, fused, paged); a batch planned by a launch in front runs the one that reuses a plan."""
+    run(runtime, f"""
+        def kernel(call):
+            at = hip.fake_launches()
+            call()
+            return [hip.fake_name(i) for i in range(at, hip.fake_launches()) if b"decode_stream_kernel" in hip.fake_name(i)]
+        p = make_pool(kv_dtype=B.{kv}, head_dim={d})
+        seen = {{}}
+        for paged in (False, True):
+            for f in (decode, step):
+                plans, = kernel(lambda: f(p, 9, paged=paged))
+                reuses, = kernel(lambda: f(p, 9, B.REUSE_PLAN, paged=paged))
+                seen[f, paged, True], seen[f, paged, False] = plans, reuses
+                assert kernel(lambda: f(p, 1200, paged=paged)) == [reuses]
+        assert len(set(seen.values())) == 8, seen
+    """)
