@@ -212,8 +212,8 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
 // its XCD's L2 holds after the first reader) into an LDS table, finds its waves' ranges there, and leaves the records
 // in memory for later calls that reuse the plan.  The planning launch this replaces is one work-group on an empty chip
 // (6-8 us with three dependent round trips, plus the edge between two launches); the scan delays the first tile's loads
-// by a few microseconds instead.  A planning call, before and after: one request of 1 777 tokens 16.0 -> 12.9 us; 64
-// requests, 46 587 tokens 30.4 -> 26.3 us; 256 requests, 159 203 tokens 69.5 -> 64.2 us.  Beyond STREAM_INLINE_REQ requests
+// by a few microseconds instead.  A planning call, before and after: one request of 1 777 tokens 16.0 -> 12.7 us; 64
+// requests, 46 587 tokens 30.4 -> 25.9 us; 256 requests, 159 203 tokens 69.5 -> 64.6 us.  Beyond STREAM_INLINE_REQ requests
 // a thread would scan more than four of them and the table would pass 20 KiB of LDS: there the launch of its own stays.
 // ---------------------------------------------------------------------------------
 constexpr int STREAM_INLINE_REQ = 1024;
@@ -1196,8 +1196,8 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // between lanes.  A 16-token tile of head_dim 128 takes 64 of them, 2048 cycles of the 6000 that its 16 KiB take to
     // arrive.  bf16: as head_dim 128, but P is carried as three bf16 parts (24 bits), so that no weight has fewer bits than
     // the vector-ALU kernel gave it.  That kernel was bound by its lane arithmetic (2048 operations per token and KV head):
-    // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 42.2 us with plan and merge in the launch (191 MB,
-    // 4.5 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 8.9 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
+    // batch 64, 46 587 tokens of 28 / 4 heads x 128 in fp32, 116.4 -> 41.6 us with plan and merge in the launch (193 MB,
+    // 4.6 TB/s); fused step of 4 requests of 16 to 128 tokens, 23.1 -> 8.8 us.  Error against 64 bits 4.1e-7 -> 3.2e-7.
     // Weights are carried times 2^-4, the state's l and O with them, and the lazy reference may lag by 2^4: no weight exceeds
     // 1, as none did in the vector kernel, and values past 1e36 stay in the range of fp32 (at the other end, values under
     // 1e-36 lose up to four bits of it).  The factor is exact, so results are those of the unscaled weights.  (The running
