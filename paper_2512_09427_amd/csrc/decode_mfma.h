@@ -734,12 +734,15 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     load_window(wc, cc.e_base);                            // needed only when a cursor leaves the first entry
     wp = wc;
 
-    bf16x8 kb[NBUF][NL], vb[NBUF][NL];
+    // The tiles' registers are words, not vectors of bf16: where a branch changes 16-bit elements (the mask of a ragged tail,
+    // the appended row), the compiler takes whole vectors apart over every branch they live across, the ones whose loads
+    // are in flight too, and waits for those in every tile (bf16 with head_dim 96, 10 600 tokens: 18 us or 33, by luck).
+    uint4v kb[NBUF][NL], vb[NBUF][NL];
     // Loads of the prefetch cursor's tile.  They are issued in every step, so that the waits stay
     // static counts; once the whole range has been requested the surplus loads all read the first
     // block of the layer's pools, which stays in the L2 instead of costing HBM traffic.
     int to_issue = n_my;
-    auto issue = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto issue = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       const int64_t off = to_issue > 0 ? tile_offset(pc) : 0;
       // two blocks per tile: the first half of the loads reads the first block, the rest the second one
       const int64_t off2 = !TWO ? 0 : (to_issue > 0 ? tile_offset2(pc) : 0);
@@ -749,31 +752,31 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         // streaming loads: K/V bytes are used once, and loads that do not allocate in the caches
         // read 9 % faster on this part (measured)
         const int64_t o = j < NP ? off + j * 1024 : off2 + (j - NP) * 1024;
-        kk[j] = __builtin_nontemporal_load((const bf16x8*)(kbase + o));
+        kk[j] = __builtin_nontemporal_load((const uint4v*)(kbase + o));
         if (F32) {
           // a lane's two fp32 pieces of 32 channels (c and 16 + c, four tokens each) are neighbours: the two loads that
           // take them share their cache lines
           const int64_t ov = j < NP ? off + (j >> 1) * 2048 + (j & 1) * 16 : off2 + ((j - NP) >> 1) * 2048 + (j & 1) * 16;
-          vv[j] = *(const bf16x8*)(vbase + ov);
+          vv[j] = *(const uint4v*)(vbase + ov);
         } else {
-          vv[j] = __builtin_nontemporal_load((const bf16x8*)(vbase + o));
+          vv[j] = __builtin_nontemporal_load((const uint4v*)(vbase + o));
         }
       }
     };
     // Q^T operand of the segment at cursor c: lane (col, g4) holds q[head col][32 j + 8 g4 .. +8] (fp32: [16 j + 4 g4 .. +4])
-    auto load_q = [&](bf16x8 (&qq)[NQ], int r, int g) {
+    auto load_q = [&](uint4v (&qq)[NQ], int r, int g) {
       const char* qp = (const char*)a.q + ((int64_t)r * a.Hq + g * G + col) * HD * (F32 ? 4 : 2) + 16 * g4;
 #pragma unroll
       for (int j = 0; j < NQ; ++j) {
-        bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-        qq[j] = (col < G && (WIDE || 32 * j < HD)) ? *(const bf16x8*)(qp + 64 * j) : z;
+        const uint4v z = {0u, 0u, 0u, 0u};
+        qq[j] = (col < G && (WIDE || 32 * j < HD)) ? *(const uint4v*)(qp + 64 * j) : z;
       }
     };
 
     // The first segment's queries are requested ahead of the first tiles and adopted inside the main loop, after
     // the second tile's loads have been issued: waiting for them here would hold those loads back by a whole
     // memory round trip.
-    bf16x8 qreg[NQ], qnext[LATE_Q ? 1 : NQ];
+    uint4v qreg[NQ], qnext[LATE_Q ? 1 : NQ];
     if constexpr (LATE_Q) load_q(qreg, cc.r, cc.g);
     else load_q(qnext, cc.r, cc.g);
 
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // low E4M3 part (together about 8 significant bits); the inverse scale joins the softmax scale.
     long qhi[4] = {0, 0, 0, 0}, qlo[4] = {0, 0, 0, 0};
     float qfac = a.scale_log2;
-    auto adopt_q = [&](const bf16x8 (&src)[NQ]) {
+    auto adopt_q = [&](const uint4v (&src)[NQ]) {
       if constexpr (!FP8) {
 #pragma unroll
         for (int j = 0; j < NQ; ++j) qreg[j] = src[j];
@@ -805,7 +808,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          qf[j][i] = (float)src[j][i];
+          qf[j][i] = __uint_as_float((i & 1) ? src[j][i >> 1] & 0xffff0000u : src[j][i >> 1] << 16);
           amax = fmaxf(amax, fabsf(qf[j][i]));
         }
       amax = column_max(amax);
@@ -880,27 +883,42 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         const int* rec = abase + i * stream_aq_ints(NP);
         const int64_t off = ((int64_t)rfl(rec[1]) << 32) | (unsigned)rfl(rec[0]);
         const int slot = rfl(rec[2]);
-        const bf16x8* kq = (const bf16x8*)(rec + 8);
-        const bf16x8* vq = (const bf16x8*)(rec + REC_V);
+        const uint4v* kq = (const uint4v*)(rec + 8);
+        const uint4v* vq = (const uint4v*)(rec + REC_V);
         if ((col >> 1) == (slot >> 1)) {
           char* kd = (char*)a.k + off + lane * 16;
 #pragma unroll
-          for (int j = 0; j < NP; ++j) __builtin_nontemporal_store(kq[(j * 4 + g4) * 2 + (col & 1)], (bf16x8*)(kd + j * 1024));
+          for (int j = 0; j < NP; ++j) __builtin_nontemporal_store(kq[(j * 4 + g4) * 2 + (col & 1)], (uint4v*)(kd + j * 1024));
         }
         if (g4 == (slot >> 2)) {
           char* vd = (char*)a.v + off + lane * (F32 ? 32 : 16);
 #pragma unroll
           for (int j = 0; j < NP; ++j)
-            __builtin_nontemporal_store(vq[j * 16 + col], (bf16x8*)(vd + (F32 ? (j >> 1) * 2048 + (j & 1) * 16 : j * 1024)));
+            __builtin_nontemporal_store(vq[j * 16 + col], (uint4v*)(vd + (F32 ? (j >> 1) * 2048 + (j & 1) * 16 : j * 1024)));
         }
       }
       an = 0;
     };
+    // Token rr of the four that V words lo (tokens 0, 1) and hi (2, 3) hold of a channel becomes x (bf16).
+    auto insert_v = [](unsigned& lo, unsigned& hi, int rr, unsigned short x) {
+      const unsigned keep = (rr & 1) ? 0x0000ffffu : 0xffff0000u, put = (unsigned)x << (16 * (rr & 1));
+      lo = rr < 2 ? (lo & keep) | put : lo;
+      hi = rr < 2 ? hi : (hi & keep) | put;
+    };
+    auto insert_v_group = [&](uint4v& w, int half, int rr, unsigned short x) {   // half: which of the piece's two channel groups
+      unsigned lo = w[2 * half], hi = w[2 * half + 1];
+      insert_v(lo, hi, rr, x);
+      w[2 * half] = lo;
+      w[2 * half + 1] = hi;
+    };
     // Blocks of 2 KiB (fp8 storage, or bf16 with head_dim 64): the row's 128 K bytes and 128 V bytes are
-    // staged in the record's V area (overwritten by the patched pieces further down); k0, k1 / v0, v1 are the register pieces of
-    // the block that holds the token.
-    auto patch_two = [&](int* rec, int slot, bf16x8& k0, bf16x8& k1, bf16x8& v0, bf16x8& v1) {
-      typedef unsigned uint4u __attribute__((ext_vector_type(4)));
+    // staged in the record's V area (overwritten by the patched pieces further down).  The pieces of the block that holds the
+    // token, the tile's first or second, are selected by value: through a reference chosen at run time the tile's registers
+    // live in scratch memory, in every tile (fused steps of 256 requests, 28 / 4 heads x 64 in bf16, config 3's lengths: 49 us
+    // a layer, now 33).
+    auto patch_two = [&](int* rec, int slot, auto second, uint4v (&kk)[NL], uint4v (&vv)[NL]) {
+      uint4v k0 = second ? kk[NL / 2] : kk[0], k1 = second ? kk[NL / 2 + 1] : kk[1];
+      uint4v v0 = second ? vv[NL / 2] : vv[0], v1 = second ? vv[NL / 2 + 1] : vv[1];
       const int rr = slot & 3;
       unsigned* stage = (unsigned*)(rec + REC_V);
       stage[lane] = newrow[0];
@@ -909,22 +927,19 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         const unsigned char* vrow = (const unsigned char*)(stage + 32);
         if (col == slot) {                                   // K: per 64-channel half, 8 channels of each of its two k-steps
           const uint2v a0 = krow[g4], b0 = krow[4 + g4], a1 = krow[8 + g4], b1 = krow[12 + g4];
-          k0 = __builtin_bit_cast(bf16x8, uint4u{a0[0], a0[1], b0[0], b0[1]});
-          k1 = __builtin_bit_cast(bf16x8, uint4u{a1[0], a1[1], b1[0], b1[1]});
+          k0 = uint4v{a0[0], a0[1], b0[0], b0[1]};
+          k1 = uint4v{a1[0], a1[1], b1[0], b1[1]};
         }
         if (g4 == (slot >> 2)) {                             // V: byte rr of every word is the new token's channel
-          uint4u w0 = __builtin_bit_cast(uint4u, v0), w1 = __builtin_bit_cast(uint4u, v1);
           const unsigned keep = ~(0xffu << (8 * rr));
 #pragma unroll
           for (int w = 0; w < 4; ++w) {
-            w0[w] = (w0[w] & keep) | ((unsigned)vrow[16 * w + col] << (8 * rr));
-            w1[w] = (w1[w] & keep) | ((unsigned)vrow[64 + 16 * w + col] << (8 * rr));
+            v0[w] = (v0[w] & keep) | ((unsigned)vrow[16 * w + col] << (8 * rr));
+            v1[w] = (v1[w] & keep) | ((unsigned)vrow[64 + 16 * w + col] << (8 * rr));
           }
-          v0 = __builtin_bit_cast(bf16x8, w0);
-          v1 = __builtin_bit_cast(bf16x8, w1);
         }
       } else {
-        const bf16x8* krow = (const bf16x8*)stage;          // K[0..64) as 8 pieces of 8 channels
+        const uint4v* krow = (const uint4v*)stage;          // K[0..64) as 8 pieces of 8 channels
         const unsigned short* vrow = (const unsigned short*)(stage + 32);
         if (col == slot) {                                   // K: 8 channels of the new token per k-step
           k0 = krow[g4];
@@ -932,31 +947,31 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         }
         if (g4 == (slot >> 2)) {                             // V: this lane holds tokens 4*g4..+3 of 4 channels
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const __bf16 vnew = __builtin_bit_cast(__bf16, vrow[16 * k + col]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (i == rr) {
-                if (k < 2) v0[4 * (k & 1) + i] = vnew;
-                else v1[4 * (k & 1) + i] = vnew;
-              }
-          }
+          for (int k = 0; k < 4; ++k) insert_v_group(k < 2 ? v0 : v1, k & 1, rr, vrow[16 * k + col]);
         }
       }
       if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
-        bf16x8* kq = (bf16x8*)(rec + 8);
+        uint4v* kq = (uint4v*)(rec + 8);
         kq[g4 * 2 + (col & 1)] = k0;
         kq[(4 + g4) * 2 + (col & 1)] = k1;
       }
       if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
-        bf16x8* vq = (bf16x8*)(rec + REC_V);
+        uint4v* vq = (uint4v*)(rec + REC_V);
         vq[col] = v0;
         vq[16 + col] = v1;
       }
+      kk[0] = second ? kk[0] : k0;
+      kk[1] = second ? kk[1] : k1;
+      vv[0] = second ? vv[0] : v0;
+      vv[1] = second ? vv[1] : v1;
+      kk[NL / 2] = second ? k0 : kk[NL / 2];
+      kk[NL / 2 + 1] = second ? k1 : kk[NL / 2 + 1];
+      vv[NL / 2] = second ? v0 : vv[NL / 2];
+      vv[NL / 2 + 1] = second ? v1 : vv[NL / 2 + 1];
     };
-    // Wide formats: the same for blocks of NP pieces; blk: the tile's block that holds the token.
-    auto patch_wide = [&](int* rec, int slot, bf16x8 (&kk)[NL], bf16x8 (&vv)[NL], auto blk) {
-      constexpr int P0 = decltype(blk)::value * NP, ROW16 = HD * F.eb / 16;
+    // Wide formats: the same for a block of NP pieces.
+    auto patch_wide = [&](int* rec, int slot, uint4v* kk, uint4v* vv) {
+      constexpr int ROW16 = HD * F.eb / 16;
       const int rr = slot & 3;
       uint4v* stage = (uint4v*)(rec + REC_V);
       if (lane < ROW16) {
@@ -965,35 +980,30 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       }
       if (col == slot) {                                     // K: piece j of this lane is 16-byte chunk 4 j + g4 of the row
 #pragma unroll
-        for (int j = 0; j < NP; ++j) kk[P0 + j] = __builtin_bit_cast(bf16x8, stage[4 * j + g4]);
+        for (int j = 0; j < NP; ++j) kk[j] = stage[4 * j + g4];
       }
       if (g4 == (slot >> 2)) {                               // V: this lane holds tokens 4*g4..+3 of HD / 16 channels
 #pragma unroll
         for (int dt = 0; dt < HD / 16; ++dt) {
           if (F32) {
-            float4v w = __builtin_bit_cast(float4v, vv[P0 + dt % NP]);
-            const float vnew = ((const float*)(stage + ROW16))[16 * dt + col];
+            const unsigned vnew = ((const unsigned*)(stage + ROW16))[16 * dt + col];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = i == rr ? vnew : w[i];
-            vv[P0 + dt % NP] = __builtin_bit_cast(bf16x8, w);
+            for (int i = 0; i < 4; ++i) vv[dt % NP][i] = i == rr ? vnew : vv[dt % NP][i];
           } else {
-            const __bf16 vnew = __builtin_bit_cast(__bf16, ((const unsigned short*)(stage + ROW16))[16 * dt + col]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (i == rr) vv[P0 + (dt >> 1) % NP][4 * (dt & 1) + i] = vnew;
+            insert_v_group(vv[(dt >> 1) % NP], dt & 1, rr, ((const unsigned short*)(stage + ROW16))[16 * dt + col]);
           }
         }
       }
       if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
 #pragma unroll
-        for (int j = 0; j < NP; ++j) ((bf16x8*)(rec + 8))[(j * 4 + g4) * 2 + (col & 1)] = kk[P0 + j];
+        for (int j = 0; j < NP; ++j) ((uint4v*)(rec + 8))[(j * 4 + g4) * 2 + (col & 1)] = kk[j];
       }
       if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
 #pragma unroll
-        for (int j = 0; j < NP; ++j) ((bf16x8*)(rec + REC_V))[j * 16 + col] = vv[P0 + j];
+        for (int j = 0; j < NP; ++j) ((uint4v*)(rec + REC_V))[j * 16 + col] = vv[j];
       }
     };
-    auto patch_and_store = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto patch_and_store = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       const int slot = (cc.len - 1) & (BLK - 1), rr = slot & 3;
       lookup_block(cc);                                      // the compute cursor looks its block up only here
       const bool second = TWO && (((cc.len - 1) / BLK) & 1);  // 32-token tiles: the token sits in the tile's second block
@@ -1007,16 +1017,31 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       }
       ++an;
       if constexpr (WIDE) {
-        if (second) patch_wide(rec, slot, kk, vv, std::integral_constant<int, F.blocks - 1>{});
-        else patch_wide(rec, slot, kk, vv, std::integral_constant<int, 0>{});
+        if constexpr (TWO) {
+          uint4v k[NP], v[NP];
+#pragma unroll
+          for (int j = 0; j < NP; ++j) {
+            k[j] = second ? kk[NP + j] : kk[j];
+            v[j] = second ? vv[NP + j] : vv[j];
+          }
+          patch_wide(rec, slot, k, v);
+#pragma unroll
+          for (int j = 0; j < NP; ++j) {
+            kk[j] = second ? kk[j] : k[j];
+            vv[j] = second ? vv[j] : v[j];
+            kk[NP + j] = second ? k[j] : kk[NP + j];
+            vv[NP + j] = second ? v[j] : vv[NP + j];
+          }
+        } else {
+          patch_wide(rec, slot, kk, vv);
+        }
       } else if constexpr (TWO) {
-        if (second) patch_two(rec, slot, kk[2], kk[3], vv[2], vv[3]);
-        else patch_two(rec, slot, kk[0], kk[1], vv[0], vv[1]);
+        patch_two(rec, slot, second, kk, vv);
       } else {
       // stage the row in the record's V area (overwritten by the patched pieces further down)
       uint2v* stage = (uint2v*)(rec + REC_V);
       stage[lane] = newrow;
-      const bf16x8* krow = (const bf16x8*)stage;            // K[0..128) as 16 pieces of 8
+      const uint4v* krow = (const uint4v*)stage;            // K[0..128) as 16 pieces of 8
       const unsigned short* vrow = (const unsigned short*)stage + 128;
       if (col == slot) {                                     // K: this lane holds 8 channels of the new token per k-step
 #pragma unroll
@@ -1024,20 +1049,15 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       }
       if (g4 == (slot >> 2)) {                               // V: this lane holds tokens 4*g4..+3 of 8 channels
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const __bf16 vnew = __builtin_bit_cast(__bf16, vrow[16 * k + col]);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (i == rr) vv[k >> 1][4 * (k & 1) + i] = vnew;
-        }
+        for (int k = 0; k < 8; ++k) insert_v_group(vv[k >> 1], k & 1, rr, vrow[16 * k + col]);
       }
       if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
-        bf16x8* kq = (bf16x8*)(rec + 8);
+        uint4v* kq = (uint4v*)(rec + 8);
 #pragma unroll
         for (int j = 0; j < 4; ++j) kq[(j * 4 + g4) * 2 + (col & 1)] = kk[j];
       }
       if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
-        bf16x8* vq = (bf16x8*)(rec + REC_V);
+        uint4v* vq = (uint4v*)(rec + REC_V);
 #pragma unroll
         for (int j = 0; j < 4; ++j) vq[j * 16 + col] = vv[j];
       }
@@ -1049,9 +1069,8 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // low E4M3 part as well; O^T += V^T P^T contracts over all 32 tokens in one mfma per d-tile and
     // part, the operand of lane (., g4) holding tokens 4 g4 .. 4 g4 + 3 of block 0, then of block 1,
     // which is the order the pool's V block format and the S^T accumulator layout both give.
-    auto compute_fp8 = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto compute_fp8 = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       typedef long long2v __attribute__((ext_vector_type(2)));
-      typedef unsigned uint4u __attribute__((ext_vector_type(4)));
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= 32: all)
       const bool ragged = n_valid < TT;
       float x[2][4];
@@ -1114,20 +1133,31 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       }
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) {
-        const unsigned w0 = __builtin_bit_cast(uint4u, vv[dt >> 2])[dt & 3] & keep0;
-        const unsigned w1 = __builtin_bit_cast(uint4u, vv[2 + (dt >> 2)])[dt & 3] & keep1;
+        const unsigned w0 = vv[dt >> 2][dt & 3] & keep0;
+        const unsigned w1 = vv[2 + (dt >> 2)][dt & 3] & keep1;
         const long av = (long)w0 | ((long)w1 << 32);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(av, phi, O[dt], 0, 0, 0);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(av, plo, O[dt], 0, 0, 0);
       }
     };
 
+    // bf16 V pieces (tokens 4 g4 .. + 3 of two channel groups each): slots past the end may hold stale bytes (even NaN
+    // patterns), zero them so 0 * x stays 0.  left: tokens from the piece's block on that are in range.
+    auto zero_past = [&](uint4v* w, int pieces, int left) {
+      const int t = 4 * g4;
+      const unsigned k01 = (t < left ? 0x0000ffffu : 0u) | (t + 1 < left ? 0xffff0000u : 0u);
+      const unsigned k23 = (t + 2 < left ? 0x0000ffffu : 0u) | (t + 3 < left ? 0xffff0000u : 0u);
+#pragma unroll
+      for (int j = 0; j < pieces; ++j) w[j] &= uint4v{k01, k23, k01, k23};
+    };
+    auto as_bf16 = [](uint4v w) { return __builtin_bit_cast(bf16x8, w); };
+
     // bf16, head_dim 64: the tile is two pool blocks of 2 KiB (32 tokens), kk / vv [0], [1] the two
     // 1 KiB pieces of the first block, [2], [3] those of the second.  Scores per block as for head_dim
     // 128 with two channel steps; P V contracts over the 32 tokens in one 16x16x32 instruction per
     // channel group, the operand of lane (., g4) holding tokens 4 g4 .. +3 of the first block, then of
     // the second.  P is carried as a high plus a low bf16 part.
-    auto compute_d64 = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto compute_d64 = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= 32: all)
       const bool ragged = n_valid < TT;
       float x[2][4];
@@ -1136,7 +1166,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       for (int b = 0; b < 2; ++b) {
         float4v s = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 2; ++j) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[2 * b + j], qreg[j], s, 0, 0, 0);
+        for (int j = 0; j < 2; ++j) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16(kk[2 * b + j]), as_bf16(qreg[j]), s, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           float val = s[i] * a.scale_log2;
@@ -1168,23 +1198,13 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         }
       lsum += psum;
       if (ragged) {
-        // slots past the end may hold stale bytes (even NaN patterns): zero them so 0 * x stays 0
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (16 * b + 4 * g4 + i >= n_valid) {
-                vv[2 * b + j][i] = (__bf16)0.f;
-                vv[2 * b + j][4 + i] = (__bf16)0.f;
-              }
+        zero_past(vv, 2, n_valid);
+        zero_past(vv + 2, 2, n_valid - BLK);
       }
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
-        const bf16x8 wa = vv[dt >> 1], wb = vv[2 + (dt >> 1)];
-        const bf16x8 av = (dt & 1) ? bf16x8{wa[4], wa[5], wa[6], wa[7], wb[4], wb[5], wb[6], wb[7]}
-                                   : bf16x8{wa[0], wa[1], wa[2], wa[3], wb[0], wb[1], wb[2], wb[3]};
+        const uint4v wa = vv[dt >> 1], wb = vv[2 + (dt >> 1)];
+        const bf16x8 av = as_bf16((dt & 1) ? uint4v{wa[2], wa[3], wb[2], wb[3]} : uint4v{wa[0], wa[1], wb[0], wb[1]});
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phi, O[dt], 0, 0, 0);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plo, O[dt], 0, 0, 0);
       }
@@ -1202,7 +1222,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     // 1, as none did in the vector kernel, and values past 1e36 stay in the range of fp32 (at the other end, values under
     // 1e-36 lose up to four bits of it).  The factor is exact, so results are those of the unscaled weights.  (The running
     // maximum as reference, rescaled whenever it moves, cost up to 5 %; the factor inside the exponent cost accuracy, 3.2e-7 -> 3.5e-7.)
-    auto compute_wide = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto compute_wide = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= TT: all)
       const bool ragged = n_valid < TT;
       float x[F.blocks][4];
@@ -1217,7 +1237,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[e], s[e & 1], 0, 0, 0);
           } else {
-            s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[b * NP + j], qreg[j], s[j & 1], 0, 0, 0);
+            s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16(kk[b * NP + j]), as_bf16(qreg[j]), s[j & 1], 0, 0, 0);
           }
         }
 #pragma unroll
@@ -1249,12 +1269,9 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         if (F32) {
           if (ragged) {                                       // stale slots may hold anything: keep 0 * x == 0
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-              float4v w = __builtin_bit_cast(float4v, vv[b * NP + j]);
+            for (int j = 0; j < NP; ++j)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) w[i] = 16 * b + 4 * g4 + i >= n_valid ? 0.f : w[i];
-              vv[b * NP + j] = __builtin_bit_cast(bf16x8, w);
-            }
+              for (int i = 0; i < 4; ++i) vv[b * NP + j][i] = 16 * b + 4 * g4 + i >= n_valid ? 0u : vv[b * NP + j][i];
           }
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -1277,22 +1294,13 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
               rest -= cut;
             }
           }
-          if (ragged) {
-#pragma unroll
-            for (int j = 0; j < NP; ++j)
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                if (16 * b + 4 * g4 + i >= n_valid) {
-                  vv[b * NP + j][i] = (__bf16)0.f;
-                  vv[b * NP + j][4 + i] = (__bf16)0.f;
-                }
-          }
+          if (ragged) zero_past(vv + b * NP, NP, n_valid - BLK * b);
 #pragma unroll
           for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int dt = 0; dt < CH / 16; ++dt) {
-              const bf16x8 w = vv[b * NP + (dt >> 1) % NP];
-              const bf16x4 half = (dt & 1) ? bf16x4{w[4], w[5], w[6], w[7]} : bf16x4{w[0], w[1], w[2], w[3]};
+              const uint4v w = vv[b * NP + (dt >> 1) % NP];
+              const uint2v half = (dt & 1) ? uint2v{w[2], w[3]} : uint2v{w[0], w[1]};
               O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, half),
                                                                 __builtin_bit_cast(short4v, part[k]), O[dt], 0, 0, 0);
             }
@@ -1301,7 +1309,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       lsum += psum;
     };
 
-    auto compute = [&](bf16x8 (&kk)[NL], bf16x8 (&vv)[NL]) {
+    auto compute = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
       if constexpr (WIDE) {
         compute_wide(kk, vv);
       } else if constexpr (FP8) {
@@ -1311,7 +1319,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
       } else {
       float4v s = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[j], qreg[j], s, 0, 0, 0);
+      for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16(kk[j]), as_bf16(qreg[j]), s, 0, 0, 0);
       const int n_valid = cc.len - cc.t * BLK;              // tokens of this block in range (>= 16: all)
       const bool ragged = n_valid < BLK;
       float x[4];
@@ -1345,23 +1353,13 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
         plo[i] = (__bf16)(pv - (float)hi);
       }
       lsum += psum;
-      if (ragged) {
-        // slots past the end may hold stale bytes (even NaN patterns): zero them so 0 * x stays 0
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (4 * g4 + i >= n_valid) {
-              vv[j][i] = (__bf16)0.f;
-              vv[j][4 + i] = (__bf16)0.f;
-            }
-      }
+      if (ragged) zero_past(vv, NL, n_valid);
       const short4v bh = __builtin_bit_cast(short4v, phi);
       const short4v bl = __builtin_bit_cast(short4v, plo);
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) {
-        const bf16x8 w = vv[dt >> 1];
-        const bf16x4 half = (dt & 1) ? bf16x4{w[4], w[5], w[6], w[7]} : bf16x4{w[0], w[1], w[2], w[3]};
+        const uint4v w = vv[(dt >> 1) % NL];
+        const uint2v half = (dt & 1) ? uint2v{w[2], w[3]} : uint2v{w[0], w[1]};
         const short4v av = __builtin_bit_cast(short4v, half);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bh, O[dt], 0, 0, 0);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bl, O[dt], 0, 0, 0);
