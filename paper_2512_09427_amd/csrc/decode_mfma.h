@@ -573,16 +573,19 @@ __host__ __device__ constexpr StreamFormat stream_format(int fmt) {
   const int hd = 32 * (fmt - (f32 ? STREAM_F32_WIDE : STREAM_BF16_WIDE)), eb = f32 ? 4 : 2;
   return {hd, eb, hd * eb / 64, hd == 32 ? 2 : 1, hd};
 }
-// work-groups of one CU that the registers leave room for: a tile of five pieces or more takes a SIMD for one wave (with room
-// for two, bf16 with head_dim 160 spilled 5 registers, fused 38: 256 fused requests of 4 heads 118 -> 95 us)
-__host__ __device__ constexpr int stream_min_waves(int fmt) {
+// Waves of one SIMD that the registers leave room for: a tile of five pieces or more takes a SIMD for one wave (with room
+// for two, bf16 with head_dim 160 spilled 5 registers, fused 38: 256 fused requests of 4 heads 118 -> 95 us).  It bounds the
+// compiler from above as well: one wave is what the launch has for a SIMD, and in the hope of a third that would fit, the
+// registers for the merge's loads were saved by waiting for them one by one.
+__host__ __device__ constexpr int stream_waves(int fmt) {
   return stream_format(fmt).np * stream_format(fmt).blocks >= 5 ? 1 : 2;
 }
 
 // PLAN: the launch makes its plan (a variant of its own: with the planning code behind a run-time branch every launch that
 // reuses a plan, all layers of a step but the first, was 0.3 to 0.7 us longer, and fused bf16 steps of head_dim 64 up to 7 %)
 template <bool PAGED, int NBUF, int WPW, bool FUSED, int FMT, bool PLAN>
-__global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream_kernel(StreamArgs a) {
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * WPW, 64 * WPW), amdgpu_waves_per_eu(stream_waves(FMT), stream_waves(FMT)))) void
+decode_stream_kernel(StreamArgs a) {
   constexpr bool FP8 = FMT == STREAM_FP8_D128, D64 = FMT == STREAM_BF16_D64;
   constexpr bool WIDE = FMT > STREAM_BF16_WIDE, F32 = FMT > STREAM_F32_WIDE;
   constexpr StreamFormat F = stream_format(FMT);
@@ -1643,6 +1646,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
     tl_flush();
     return;
   }
+#pragma nounroll
   for (int which = 0; which < 2; ++which) {
     if (!(which == 0 ? do_a : do_b)) continue;
     const ReduceDesc rd = which == 0 ? rd_cut[0] : rd_cut[1];   // (indexed by a variable the pair would live in scratch)
@@ -1669,6 +1673,7 @@ __global__ __launch_bounds__(64 * WPW, stream_min_waves(FMT)) void decode_stream
             const float2 hi = load_pair_agent(a.part_o + pi * CH + 4 * d4 + 2);
             ov[u] = float4v{lo.x, lo.y, hi.x, hi.y};
           }
+          asm volatile("" ::: "memory");                     // every load of the batch is issued before the first is waited for
           float m_new = m_run;
 #pragma unroll
           for (int u = 0; u < BATCH; ++u)
