@@ -19,6 +19,8 @@
 // queue is empty goes on with the fullest other one.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels_common.h"
 
 namespace {
@@ -26,12 +28,21 @@ namespace {
 constexpr int PREFILL_PLAN_THREADS = 256;
 
 constexpr int PREFILL_XCDS = 8;
+// A queue's last items go out one by one, this many per work-group: a work-group holds the run it is on and the one after
+// it, and with runs of four items to the end the last work-group of a call was busy 23 % longer than the mean one.  256
+// prompts around 256 tokens 715 -> 670 us, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 -> 632 (two singles: 677,
+// 664; eight: 675, 664).
+constexpr int PREFILL_SINGLES = 4;
 constexpr double PREFILL_ITEM_COST = 5.0;   // start and end of an item, in K/V pairs
 
 struct PrefillHeader {
   int32_t bound[PREFILL_XCDS + 1];          // items [bound[x], bound[x + 1]) are queue x
   int32_t next[PREFILL_XCDS];               // runs claimed of every queue beyond the first of each work-group, reset by the plan
   int32_t avg_pairs;                        // mean cost of an item
+};
+
+struct PrefillBounds {
+  int bound[PREFILL_XCDS + 1];
 };
 
 struct PrefillArgs {
@@ -218,24 +229,32 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // Work queues.  A counter in memory answers about 14 M requests a second on this part -- with thousands of small items
   // that alone would bound the kernel.  A work-group therefore takes runs of consecutive items, long enough to stream
   // about 64 K/V pairs (some 40 us) but never more than an eighth of its share of the items, so that large items still
-  // balance one by one; its first run is its turn's (no counter is touched when that is all there is), and it asks for the
-  // next one a run ahead: the answer travels while the current run is computed.
+  // balance one by one, as do the last items of a queue; its first run is its turn's (no counter is touched when that is all
+  // there is), and it asks for the next one a run ahead: the answer travels while the current run is computed.
   //
   // A call whose items are few (the launch's rule) plans here instead of in a launch in front -- six microseconds of one
   // work-group's round trips and the edge between two launches -- and its work-groups take every `turns`-th item of their
   // queue: no counter has to be clear before the launch.  7 prompts of 21 to
   // 58 tokens 11.2 -> 8.3 us, 28 of 91 to 546 tokens 20.0 -> 17.5.
-  const int* bound = a.hdr->bound;
+  __shared__ typename std::conditional<HERE, PrefillPlan, PrefillBounds>::type plan;   // (in LDS: read between runs only)
+  int (&bound)[PREFILL_XCDS + 1] = plan.bound;
+  const bool small = a.n <= PREFILL_LDS_REQ;
   if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
-    __shared__ PrefillPlan plan;
     prefill_plan(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
-    bound = plan.bound;
+  } else {
+    if (threadIdx.x <= PREFILL_XCDS) bound[threadIdx.x] = a.hdr->bound[threadIdx.x];
+    if (small)
+      for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
+    __syncthreads();
   }
-  const int n_items = bound[PREFILL_XCDS];
-  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
+  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(rfl(bound[PREFILL_XCDS]) / ((int)gridDim.x * 8), 1));
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
-  const int q_at = bound[min(lane, PREFILL_XCDS - 1)], q_end = bound[min(lane, PREFILL_XCDS - 1) + 1];   // lane x: queue x
-  const unsigned long long longer = HERE ? 0 : __builtin_amdgcn_ballot_w64(lane < PREFILL_XCDS && q_end - q_at > turns * run);
+  // Run j of a queue of len items begins at its item run_at(len, j) and ends where the next one begins: the last
+  // PREFILL_SINGLES items per work-group are runs of their own.
+  auto run_at = [&](int len, int j) {
+    const int whole = max(len - PREFILL_SINGLES * turns, 0) / run;
+    return min(min(j, whole) * run + max(j - whole, 0), len);
+  };
   int queue = blockIdx.x % PREFILL_XCDS;                               // (work-group b runs on XCD b % 8)
   int ahead = 0;
   auto claim = [&]() {
@@ -245,41 +264,45 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // work-group goes on with the fullest one that was longer than its work-groups' first runs.
   bool claimed = false;
   auto settle = [&]() {
+    const int x = lane % PREFILL_XCDS, at = bound[x], len = bound[x + 1] - at;   // lane x: queue x
+    const bool more = run_at(len, turns) < len;
+    const unsigned longer = (unsigned)__builtin_amdgcn_ballot_w64(more);
     int start = 0, end = 0;
-    if (claimed) {
-      end = __builtin_amdgcn_readlane(q_end, queue);
-      start = min(__builtin_amdgcn_readlane(q_at, queue) + (turns + rfl(ahead)) * run, end);
-    }
+    auto take = [&]() {                                                // the run that `ahead` names
+      const int j = turns + rfl(ahead);
+      start = __builtin_amdgcn_readlane(at + run_at(len, j), queue);
+      end = __builtin_amdgcn_readlane(at + run_at(len, j + 1), queue);
+    };
+    if (claimed) take();
     while (start >= end && longer != 0) {
-      int left = 0;
-      if (lane < PREFILL_XCDS)
-        left = q_end - q_at - (turns + __hip_atomic_load(&a.hdr->next[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) * run;
-      int most = max(left, 0);
+      const int taken = __hip_atomic_load(&a.hdr->next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int left = more ? len - run_at(len, turns + taken) : 0;
+      int most = left;
 #pragma unroll
       for (int o = 1; o < PREFILL_XCDS; o <<= 1) most = max(most, __shfl_xor(most, o));
       most = rfl(most);
       if (most == 0) break;
       queue = __builtin_ctzll(__builtin_amdgcn_ballot_w64(left == most));
       claim();
-      end = __builtin_amdgcn_readlane(q_end, queue);
-      start = min(__builtin_amdgcn_readlane(q_at, queue) + (turns + rfl(ahead)) * run, end);
+      take();
     }
     if (lane == 0) {
       run_slot[0] = start;
-      run_slot[1] = min(start + run, end);
+      run_slot[1] = end;
     }
     claimed = start < end && ((longer >> queue) & 1) != 0;
     if (claimed) claim();
   };
-  int next = __builtin_amdgcn_readlane(q_at, queue) + (int)(blockIdx.x / PREFILL_XCDS) * run;
-  int run_end = min(next + run, __builtin_amdgcn_readlane(q_end, queue));
-  if (wv == 0 && next < run_end && ((longer >> queue) & 1) != 0) {
-    claimed = true;
-    claim();
+  int next, run_end;                                                   // the present run: what is left of it
+  {
+    const int at = rfl(bound[queue]), len = rfl(bound[queue + 1]) - at, turn = blockIdx.x / PREFILL_XCDS;
+    next = at + run_at(len, turn);
+    run_end = at + run_at(len, turn + 1);
+    if (!HERE && wv == 0 && next < run_end && run_at(len, turns) < len) {
+      claimed = true;
+      claim();
+    }
   }
-  const bool small = a.n <= PREFILL_LDS_REQ;
-  if (small && !HERE)
-    for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
   int at = next;                                                       // first item of the present run
   for (;;) {
     // ---- next item (every wave reaches the exit together)
@@ -288,7 +311,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       at += turns;
       next = at;
       run_end = at + 1;
-      if (next >= __builtin_amdgcn_readlane(q_end, queue)) break;
+      if (next >= rfl(bound[queue + 1])) break;
     } else if (next >= run_end) {
       if (wv == 0) settle();
       __syncthreads();

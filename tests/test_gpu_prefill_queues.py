@@ -48,6 +48,16 @@ def test_requests_found_in_memory(n):
     chunk_case(lens, lens, hq=2, hkv=1, sharp=True, seed=93, bounds=(64, 512, 1024), large_cap=1024, main=n * 64 + 4096)
 
 
+@pytest.mark.parametrize("n", [800, 1030, 2100])
+def test_runs_of_items_and_single_ones(n):
+    """More items than eight per work-group, so that they go out in runs of one to four, the last of every queue alone; one
+    request has a queue's share by itself."""
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 12, n)
+    lens[n // 5] = 700
+    chunk_case(lens, lens, hq=8, hkv=8, sharp=True, seed=94, bounds=(64, 512, 1024), large_cap=1024, main=n * 64 + 4096)
+
+
 @pytest.mark.parametrize("column_tiles", [2, 4])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("kvd", ["bf16", "fp8"])
