@@ -340,7 +340,8 @@ int odma_decode_attention_static(odma_pool_t* pool, int32_t layer, int32_t n,
  *   total_q    host: rows of q and out; rows at or past it are never read or written
  *   q_start    DEVICE int64[n]        n_q  DEVICE int32[n] (0: nothing to do; clamped to lengths[r])
  *   offsets, lengths, block_table, bt_stride as for odma_decode_attention (lengths include the chunk)
- * Launches the attention kernel on `stream`, for calls with many work items after a plan kernel, using the pool's workspace. */
+ * Launches the attention kernel on `stream`, for calls with many work items after a plan kernel, using the pool's workspace
+ * (plan, and for few long items the states of their parts): prompt calls on one pool must not overlap on different streams. */
 int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const void* q, int64_t total_q,
                            const int64_t* q_start, const int32_t* n_q, const int64_t* offsets,
                            const int32_t* lengths, const int32_t* block_table, int32_t bt_stride,

@@ -474,39 +474,6 @@ __host__ inline size_t stream_lds_bytes(int G, int ch, int np, int wpw, int qs, 
   return ((size_t)wpw * stream_slot_floats(G, ch) + 2 * wpw + (size_t)wpw * stream_wave_queue_floats(G, ch, np, qs, aq)) * 4;
 }
 
-
-// Partial states cross from one XCD's L2 to another's inside one launch.  They are written and
-// read with agent-scope accesses (write-through / coherent reads, 8 bytes at a time), which keeps
-// the exchange coherent without flushing or invalidating a whole L2 -- a release or acquire fence
-// at agent scope does exactly that on this part and costs tens of microseconds per launch.
-__device__ __forceinline__ void store_pair_agent(float* p, float x, float y) {
-  const unsigned long long v = (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
-  __hip_atomic_store((unsigned long long*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float2 load_pair_agent(const float* p) {
-  const unsigned long long v = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
-}
-
-// Arrival counter of a cut segment: {tag, count}, count 0 between launches.  The workspace is the caller's and may hold
-// anything when a launch begins (its first use, another pool's records, a caller who used it as scratch), and the launch
-// that plans itself has no earlier launch to clear counters in.  So the counter carries a tag: an arrival that finds other
-// bytes than the tag replaces them by {tag, 1} (compare-and-swap; whoever loses the swap adds to what the winner left).
-// The usual arrival is one atomic add, as with a counter known to be zero.  The tag is a NaN pattern, which no partial
-// state holds in the word that would have to hold it.  Returns the number of earlier arrivals.
-constexpr unsigned ARRIVE_TAG = 0x7fd15a3cu;
-__device__ __forceinline__ int count_in(unsigned long long* c) {
-  unsigned long long seen = __hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((unsigned)(seen >> 32) == ARRIVE_TAG) return (int)(unsigned)seen;
-  ++seen;                                                  // what the add left behind
-  while ((unsigned)(seen >> 32) != ARRIVE_TAG) {
-    if (__hip_atomic_compare_exchange_strong(c, &seen, ((unsigned long long)ARRIVE_TAG << 32) | 1ull, __ATOMIC_RELAXED,
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      return 0;
-  }
-  return (int)(unsigned)__hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Maximum over the four lanes that hold one column (lanes l, l ^ 16, l ^ 32, l ^ 48), in every one of them: two
 // register swaps between rows of 16 lanes and between halves of the wave, no trip through the LDS crossbar.
 __device__ __forceinline__ float column_max(float x) {

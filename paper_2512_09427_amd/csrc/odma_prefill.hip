@@ -1,6 +1,7 @@
 // Prompt (chunk) attention entry point of libodma for gfx950: launches the kernels in prefill_mfma.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "odma_internal.h"
@@ -61,12 +62,28 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // measured faster than 4 (256-column items, one work-group per CU) on every prompt mix tried
   const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
   const int slots = pool->n_cu * (ct == 2 ? 2 : 1);
-  const dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
+  dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
+  // States of parts of items live where no decode launch reaches: its regions are sized for STREAM_MAX_WG work-groups, of
+  // which a launch has at most STREAM_MAX_LAUNCH_WG.
+  constexpr int64_t spare = odma_plan::STREAM_MAX_WG - odma_plan::STREAM_MAX_LAUNCH_WG;
+  static_assert(spare > 0 && spare * 8 * sizeof(odma_plan::WaveDesc) >= 4096 * sizeof(int64_t), "room for the counters");
+  a.part_slots = (int32_t)std::min<int64_t>(2 * spare * a.Hq / (64 * ct), 4096);
+  a.arrive = (unsigned long long*)(ws + pool->ws.waves + odma_plan::STREAM_MAX_LAUNCH_WG * 8 * sizeof(odma_plan::WaveDesc));
+  a.part_ml = (float2*)(ws + pool->ws.part_ml) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq;
+  a.part_o = (float*)(ws + pool->ws.part_o) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq * 128;
   // Few items -- no more than work-groups, counted from the rows of q (rows that several requests share only make more of
   // them): planned in the attention launch.  With more, the work-groups balance through counters, which a planning launch
   // clears.
   const int64_t items = (total_q * a.G + 64 * ct - 1) / (64 * ct) * a.Hkv + (int64_t)n * a.Hkv;
   const bool here = n <= PREFILL_LDS_REQ && items <= (int64_t)grid.x;
+  // Such a launch has a work-group for every part that an item can have, counted from the longest request there can be, and
+  // none beyond: they would each scan the batch and hold up the end of the launch (a queue's first parts go to its first
+  // work-groups, which start first).
+  if (here) {
+    const int64_t longest = block_table ? (int64_t)bt_stride * BLK : std::max<int64_t>(c.large_cap, pool->boundaries.back());
+    const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
+    grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
+  }
   if (!here)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
                        c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);

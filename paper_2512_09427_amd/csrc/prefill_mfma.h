@@ -16,7 +16,7 @@
 // handed out through atomic counters to persistent work-groups: causal items differ in length by construction.  The
 // work-groups of an XCD then read the same one or two K/V heads out of their L2 -- with one queue for the chip every XCD
 // fetched every K/V byte (16 x 4096 tokens: 60 M L2 misses of 128 bytes, 12 M with eight queues).  A work-group whose
-// queue is empty goes on with the fullest other one.
+// queue is empty goes on with the fullest other one.  A call with few items cuts their keys into parts instead (prefill_parts).
 #pragma once
 
 #include <type_traits>
@@ -33,6 +33,19 @@ constexpr int PREFILL_XCDS = 8;
 // prompts around 256 tokens 715 -> 670 us, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 -> 632 (two singles: 677,
 // 664; eight: 675, 664).
 constexpr int PREFILL_SINGLES = 4;
+// A call of few items (one chunk of a long prompt: a hundred, or eight) leaves most of the chip idle while each streams its
+// keys in one serial chain.  Such a call cuts the keys of its items into parts, one per work-group, whose states the last one to
+// arrive merges.  A pair costs a lone work-group about 0.55 us and a merged state 1.2, so the best number of parts grows
+// with the square root of the pairs; at 16 pairs cutting is worth its fixed cost of 2.5 us.  One chunk of 128 tokens, 28 / 4 heads
+// (28 items): ending at 512 tokens 18.4 us both ways (at 384 16.2 whole, 17.0 cut), at 640 20.5 -> 18.8; two at 1024 28.0 ->
+// 23.5; chunks of 512 (112 items) at 2048 48.2 -> 37.9, at 8192 161 -> 86, at 32 768 612 -> 268; one of 128 at 5090 with 8 / 8
+// heads 102 -> 32.5.  With sqrt(0.75 pairs) parts two chunks at 1024 take 24.4, a whole prompt of 700 26.7 (whole 24.0, so 21.6).
+constexpr int PREFILL_PARTS = 32;
+__host__ __device__ inline int prefill_parts(int pairs) {
+  if (pairs < 16) return 1;
+  const int p = (int)sqrtf(0.4f * (float)pairs);
+  return p < PREFILL_PARTS ? p : PREFILL_PARTS;
+}
 constexpr double PREFILL_ITEM_COST = 5.0;   // start and end of an item, in K/V pairs
 
 struct PrefillHeader {
@@ -64,6 +77,10 @@ struct PrefillArgs {
   float scale_log2;          // sm_scale * log2(e) (fp8 pools: times k_scale)
   float out_scale;           // 1, or v_scale for fp8 pools
   int32_t out_bf16;
+  int32_t part_slots;        // parts of cut items whose states the workspace holds
+  unsigned long long* arrive;   // [part_slots] arrival counters of cut items (count_in)
+  float2* part_ml;           // [part_slots][columns of an item]: reference and sum
+  float* part_o;             // [part_slots][columns of an item * 128]: outputs, lane by lane
 };
 
 // query tokens of request r that are really there: never more than the tokens it holds, never
@@ -247,6 +264,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
     __syncthreads();
   }
+  // Most parts that an item is cut into; one that is too short for so many leaves its last ones empty.
+  const int parts = HERE ? max(min(PREFILL_PARTS, min(a.part_slots, (int)gridDim.x) / max(rfl(bound[PREFILL_XCDS]), 1)), 1) : 1;
   const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(rfl(bound[PREFILL_XCDS]) / ((int)gridDim.x * 8), 1));
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
   // Run j of a queue of len items begins at its item run_at(len, j) and ends where the next one begins: the last
@@ -295,7 +314,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   };
   int next, run_end;                                                   // the present run: what is left of it
   {
-    const int at = rfl(bound[queue]), len = rfl(bound[queue + 1]) - at, turn = blockIdx.x / PREFILL_XCDS;
+    const int at = HERE ? 0 : rfl(bound[queue]), turn = blockIdx.x / PREFILL_XCDS;
+    const int len = HERE ? (rfl(bound[queue + 1]) - rfl(bound[queue])) * parts : rfl(bound[queue + 1]) - at;
     next = at + run_at(len, turn);
     run_end = at + run_at(len, turn + 1);
     if (!HERE && wv == 0 && next < run_end && run_at(len, turns) < len) {
@@ -311,7 +331,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       at += turns;
       next = at;
       run_end = at + 1;
-      if (next >= rfl(bound[queue + 1])) break;
+      if (next >= (rfl(bound[queue + 1]) - rfl(bound[queue])) * parts) break;
     } else if (next >= run_end) {
       if (wv == 0) settle();
       __syncthreads();
@@ -319,7 +339,12 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       run_end = rfl(run_slot[1]);
       if (next >= run_end) break;
     }
-    const int item = next++;
+    int item = next++, part = 0;
+    if constexpr (HERE) {                                  // the first parts of a queue's items, then the second ones, ...
+      const int first = rfl(bound[queue]), len = rfl(bound[queue + 1]) - first;
+      part = rfl(item / len);
+      item = first + item - part * len;
+    }
     // Request of the item: largest r with item_start[r] <= item (item_start is non-decreasing; empty requests repeat
     // a value, so it is the last one that still has items).  In LDS, where the table fits: the number of such entries, 64 a
     // round.  In memory every round is a dependent round trip, so there the 64 lanes probe evenly spaced entries of the
@@ -349,7 +374,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     }
     const int r = rfl(found);
     const int first_item = rfl(small ? item_start_lds[r] : a.item_start[r]);
-    const int len = as_constant(a.lengths)[r], asked = as_constant(a.n_q)[r];
+    int len = as_constant(a.lengths)[r];
+    const int asked = as_constant(a.n_q)[r];
     const int64_t q_row0 = ((const const_i64*)(uintptr_t)a.q_start)[r];
     const int64_t base_block = PAGED ? 0 : ((const const_i64*)(uintptr_t)a.offsets)[r] / BLK;
     // (the request has items, so its rows exist: prefill_rows without its checks)
@@ -364,7 +390,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     const int first_pos = len - rows;                                // position of query token 0
 
     // ---- per-lane columns: tile ct holds column c0 + 16 ct + col16
-    int lim[CT];                                                       // keys visible to the column (0: column absent)
+    // keys visible to the column (of a part: from its first one on, which may be less than none)
+    constexpr int ABSENT = HERE ? -(1 << 30) : 0;                      // (or less)
+    int lim[CT];
     int64_t q_at[CT];                                                  // the column's row in q and out, in elements
     bf16x8 qreg[CT][4];
 #pragma unroll
@@ -372,7 +400,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       const int col = c0 + 16 * ct + col16;
       const bool ok = col < n_cols;
       const int j = ok ? col / G : 0, h = ok ? col - j * G : 0;
-      lim[ct] = ok ? first_pos + j + 1 : 0;
+      lim[ct] = ok ? first_pos + j + 1 : ABSENT;
       q_at[ct] = ((q_row0 + j) * a.Hq + g * G + h) * 128;
     }
     auto load_q = [&](bf16x8 (&qq)[CT][4]) {
@@ -381,16 +409,30 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-          qq[ct][s] = lim[ct] != 0 ? *(const bf16x8*)(a.q + q_at[ct] + 32 * s + 8 * g4) : z;
+          qq[ct][s] = lim[ct] > ABSENT ? *(const bf16x8*)(a.q + q_at[ct] + 32 * s + 8 * g4) : z;
         }
     };
     load_q(qreg);
     // keys the item streams: up to the limit of its last column; this wave's own columns end earlier
     const int item_last_col = min((cb + 1) * COLS_ITEM, n_cols) - 1;
     const int item_lim_max = first_pos + item_last_col / G + 1;
-    const int lim_min = first_pos + c0 / G + 1;                       // pairs below it need no mask in this wave
-    const int n_tiles = (item_lim_max + BLK - 1) / BLK;
-    const int n_pairs = (n_tiles + 1) / 2;
+    int lim_min = first_pos + c0 / G + 1;                             // pairs below it need no mask in this wave
+    int n_tiles = (item_lim_max + BLK - 1) / BLK, skipped = 0;         // skipped: tiles in front of the part
+    const int all_pairs = (n_tiles + 1) / 2;
+    int n_pairs = all_pairs, n_parts = 1;
+    if (HERE && parts > 1) {
+      n_parts = min(prefill_parts(all_pairs), parts);
+      if (part >= n_parts) continue;
+      // from here on the part's first token is token 0
+      const int before = all_pairs * part / n_parts;
+      n_pairs = all_pairs * (part + 1) / n_parts - before;
+      n_tiles -= 2 * before;
+      len -= 2 * BLK * before;
+      skipped = 2 * before;
+      lim_min -= 2 * BLK * before;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) lim[ct] -= 2 * BLK * before;
+    }
 
     float m[CT], lsum[CT];
     float4v O[CT][8];
@@ -402,8 +444,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       for (int dt = 0; dt < 8; ++dt) O[ct][dt] = float4v{0.f, 0.f, 0.f, 0.f};
     }
 
-    const int64_t plane = (int64_t)g * a.head_stride;
-    const const_i32* bt_row = as_constant(PAGED ? a.bt + (int64_t)r * a.bt_stride : nullptr);
+    const int64_t plane = (int64_t)g * a.head_stride + (PAGED ? 0 : (int64_t)skipped * TILE_BYTES);
+    const const_i32* bt_row = as_constant(PAGED ? a.bt + (int64_t)r * a.bt_stride + skipped : nullptr);
     // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  Pairs past the
     // end and a second tile that does not exist re-read the last tile: every step issues its loads, so the waits on
     // them stay static counts (with conditional loads the wait before a stage was written covered the loads issued a
@@ -495,7 +537,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     //
     // Softmax reference.  Softmax is invariant under the choice of the reference m subtracted in the
     // exponent, and fp32 / bf16 weights have room for 2^127: the fast pass fixes m of a column to the
-    // exact maximum over the first pair (every column sees token 0) and never moves it, so the steady
+    // exact maximum over the item's (or part's) first pair and never moves it, so the steady
     // state holds no cross-lane maximum, no rescale of O and no second exponential.  Should later scores
     // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), or lie so far below the
     // stand-in reference of a column whose first pair scored -inf that the sum stays under 2^-60, the wave repeats its
@@ -636,7 +678,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       };
       look_up(0);
       if (FP8) load(kr, a.k, next_at);
-      for (int pr = 0; 2 * pr < n_tiles; ++pr) {
+      for (int pr = 0; HERE ? pr < n_pairs : 2 * pr < n_tiles; ++pr) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) at[b] = next_at[b];
         look_up(pr + 1);
@@ -725,16 +767,81 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     };
 
     stream();
-    if (!active) continue;
+    if (!HERE && !active) continue;
     float l[CT];
-    column_sums(l);
-    bool redo = false;
+    if (HERE)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] != 0 && !(l[ct] > 0x1p-60f && l[ct] < 0x1p90f);
-    if (__builtin_amdgcn_ballot_w64(redo) != 0) {                        // this wave's columns alone
-      slow_pass();
+      for (int ct = 0; ct < CT; ++ct) l[ct] = 0.f;
+    if (!HERE || active) {
       column_sums(l);
+      bool redo = false;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] > 0 && !(l[ct] > 0x1p-60f && l[ct] < 0x1p90f);
+      if (__builtin_amdgcn_ballot_w64(redo) != 0) {                      // this wave's columns alone
+        slow_pass();
+        column_sums(l);
+      }
     }
+    if (HERE && n_parts > 1) {
+      // ---- merge of the parts: each leaves its state (m, l, O) in the workspace, the last to arrive keeps its own in registers
+      // and takes in the others'.  Nobody waits for anybody; order as in the decode kernel's merge: the stores are
+      // acknowledged before the barrier, the arrival is counted behind it, the loads follow the full count.
+      const int slot0 = item * parts, slot = slot0 + part;
+      auto ml_at = [&](int of, int ct) { return (float*)(a.part_ml + (int64_t)of * COLS_ITEM + wv * COLS_WAVE + 16 * ct + col16); };
+      auto o_at = [&](int of, int ct, int dt) {
+        return a.part_o + ((((int64_t)of * 4 + wv) * CT + ct) * 8 + dt) * 256 + lane * 4;
+      };
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        if (!(l[ct] != 0.f)) m[ct] = NEG_INF;                            // a column that saw nothing here has no reference
+      if (active) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          if (g4 == 0) store_pair_agent(ml_at(slot, ct), m[ct], l[ct]);
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt) {
+            store_pair_agent(o_at(slot, ct, dt), O[ct][dt][0], O[ct][dt][1]);
+            store_pair_agent(o_at(slot, ct, dt) + 2, O[ct][dt][2], O[ct][dt][3]);
+          }
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const bool last = count_in(a.arrive + item) == n_parts - 1;
+        // the last arrival leaves the count at zero for the next launch
+        if (last) __hip_atomic_store(a.arrive + item, (unsigned long long)ARRIVE_TAG << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        run_slot[0] = last;
+      }
+      __syncthreads();
+      if (!run_slot[0]) continue;
+      if (active) {
+        for (int i = 0; i < n_parts - 1; ++i) {
+          const int of = slot0 + i + (i >= part ? 1 : 0);
+          float2 ml[CT];
+          float4v ov[CT][8];
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            ml[ct] = load_pair_agent(ml_at(of, ct));
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) {
+              const float2 lo = load_pair_agent(o_at(of, ct, dt)), hi = load_pair_agent(o_at(of, ct, dt) + 2);
+              ov[ct][dt] = float4v{lo.x, lo.y, hi.x, hi.y};
+            }
+          }
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const float m_new = fmaxf(m[ct], ml[ct].x), ref = m_new == NEG_INF ? 0.f : m_new;
+            const float keep = __builtin_amdgcn_exp2f(m[ct] - ref), add = __builtin_amdgcn_exp2f(ml[ct].x - ref);
+            l[ct] = l[ct] * keep + ml[ct].y * add;
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) O[ct][dt] = O[ct][dt] * keep + ov[ct][dt] * add;
+            m[ct] = m_new;
+          }
+        }
+      }
+    }
+    if (!active) continue;
 
     // ---- normalise and store: lane (col16, g4) holds channels 16 dt + 4 g4 .. +3 of its columns
 #pragma unroll
@@ -756,13 +863,13 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
             pk[w] = sw[0];
             pk[2 + w] = sw[1];
           }
-          if (lim[ct] != 0) *(uint4v*)(o + 16 * dt) = pk;
+          if (lim[ct] > ABSENT) *(uint4v*)(o + 16 * dt) = pk;
         }
       } else {
         float* o = (float*)a.out + q_at[ct] + 4 * g4;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt)
-          if (lim[ct] != 0) *(float4v*)(o + 16 * dt) = O[ct][dt] * inv;
+          if (lim[ct] > ABSENT) *(float4v*)(o + 16 * dt) = O[ct][dt] * inv;
       }
     }
   }

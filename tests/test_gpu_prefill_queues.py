@@ -3,6 +3,7 @@ empty requests around the boundaries, more requests than the item table in LDS h
 wave has columns of some lanes only.  Bounds of tests/test_gpu_prefill.py."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as wl
 from oracle import attention as oa
@@ -56,6 +57,53 @@ def test_runs_of_items_and_single_ones(n):
     lens = rng.integers(1, 12, n)
     lens[n // 5] = 700
     chunk_case(lens, lens, hq=8, hkv=8, sharp=True, seed=94, bounds=(64, 512, 1024), large_cap=1024, main=n * 64 + 4096)
+
+
+@pytest.mark.parametrize("column_tiles", [2, 4])
+@pytest.mark.parametrize("kvd,paged", [("bf16", False), ("bf16", True), ("fp8", False), ("fp8", True)])
+@pytest.mark.parametrize("lens,n_q,hq,hkv", [
+    ([480, 481, 512, 513], [5, 37, 64, 1], 8, 8),            # 15 pairs (whole) and 16 (two parts), odd and even numbers of tiles
+    ([5090], [128], 8, 8),                                   # one chunk, eight parts
+    ([1000, 31], [1000, 31], 7, 1),                          # late parts that some columns see nothing of; short items whole
+    ([4000, 0, 2500, 17], [19, 0, 18, 17], 7, 1),            # empty request, a block that is just full, one column more
+    ([9000, 3000], [20, 300], 1, 1),                         # fewer states than parts in the workspace
+])
+def test_items_cut_into_parts(lens, n_q, hq, hkv, kvd, paged, column_tiles):
+    for out_dtype in (B.F32, B.BF16):
+        chunk_case(lens, n_q, hq=hq, hkv=hkv, sharp=True, seed=96, column_tiles=column_tiles, out_dtype=out_dtype, kv_dtype=kvd,
+                   paged=paged, bounds=(512, 16384), large_cap=16384, main=1 << 17)
+
+
+def test_parts_whatever_the_workspace_holds():
+    """Arrival counters and states in a workspace of arbitrary bytes, and again in what the call before left there; a graph's
+    replays beside them."""
+    lens, n_q = np.array([3000, 700]), np.array([40, 700])
+    w = small_workload(lens, hq=8, hkv=8, seed=97, bounds=(512, 4096), large_cap=4096, main=1 << 14)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    q, _ = wl.draw_values(np.random.default_rng(97), (int(n_q.sum()), 8, 128), 1.0, "bf16")
+    q_start = np.array([0, 40])
+    off = H.assign_perfect(dp, lens)[0]
+    H.fill(dp, 0, kv, offsets=off)
+    ref = np.concatenate([oa.attend_chunk(q[a:a + m], kv[r][0], kv[r][1], 1.0 / np.sqrt(128.0)) for r, (a, m) in enumerate(zip(q_start, n_q))])
+    ref_abs = np.concatenate([oa.attend_chunk(q[a:a + m], kv[r][0], kv[r][1] & 0x7fff, 1.0 / np.sqrt(128.0))
+                              for r, (a, m) in enumerate(zip(q_start, n_q))])
+    for fill in (0, 0xff, 0x7f, None, None):                 # None: as the last call left it
+        if fill is not None:
+            dp.workspace.fill_(fill)
+        got = H.prefill(dp, 0, q, q_start, n_q, lens, offsets=off)
+        H.check(got, ref, TIGHT[0] + P_ROUNDING * ref_abs, TIGHT[1], what=f"workspace of {fill}")
+    args = [H.to_dev(x) for x in (q, q_start.astype(np.int64), n_q.astype(np.int32), np.asarray(off, np.int64), lens.astype(np.int32))]
+    out = torch.zeros(q.shape, dtype=torch.float32, device=H.DEV)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dp.pool.odma_prefill_attention(0, 2, args[0], len(q), args[1], args[2], args[3], args[4], None, 0, out,
+                                       torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        H.check(out.cpu().numpy(), ref, TIGHT[0] + P_ROUNDING * ref_abs, TIGHT[1], what="replay")
 
 
 @pytest.mark.parametrize("column_tiles", [2, 4])
