@@ -783,9 +783,10 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       }
     }
     if (HERE && n_parts > 1) {
-      // ---- merge of the parts: each leaves its state (m, l, O) in the workspace, the last to arrive keeps its own in registers
-      // and takes in the others'.  Nobody waits for anybody; order as in the decode kernel's merge: the stores are
-      // acknowledged before the barrier, the arrival is counted behind it, the loads follow the full count.
+      // ---- merge of the parts: each leaves its state (m, l, O) in the workspace, the last to arrive reads them all, its own
+      // too, from the first part to the last, so that a call repeats bit for bit whatever the order of arrival.  Nobody waits
+      // for anybody; order as in the decode kernel's merge: the stores are acknowledged before the barrier, the arrival is
+      // counted behind it, the loads follow the full count.
       const int slot0 = item * parts, slot = slot0 + part;
       auto ml_at = [&](int of, int ct) { return (float*)(a.part_ml + (int64_t)of * COLS_ITEM + wv * COLS_WAVE + 16 * ct + col16); };
       auto o_at = [&](int of, int ct, int dt) {
@@ -816,8 +817,14 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       __syncthreads();
       if (!run_slot[0]) continue;
       if (active) {
-        for (int i = 0; i < n_parts - 1; ++i) {
-          const int of = slot0 + i + (i >= part ? 1 : 0);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          m[ct] = NEG_INF;
+          l[ct] = 0.f;
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt) O[ct][dt] = float4v{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int of = slot0; of < slot0 + n_parts; ++of) {
           float2 ml[CT];
           float4v ov[CT][8];
 #pragma unroll

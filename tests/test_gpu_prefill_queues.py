@@ -106,6 +106,20 @@ def test_parts_whatever_the_workspace_holds():
         H.check(out.cpu().numpy(), ref, TIGHT[0] + P_ROUNDING * ref_abs, TIGHT[1], what="replay")
 
 
+def test_items_cut_into_parts_repeat_bit_for_bit():
+    """The states of an item are merged in the order of its keys, whichever work-group comes last."""
+    lens, n_q = np.array([5090, 3000]), np.array([128, 40])
+    w = small_workload(lens, hq=8, hkv=8, seed=98, bounds=(512, 8192), large_cap=8192, main=1 << 14)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    q, _ = wl.draw_values(np.random.default_rng(98), (int(n_q.sum()), 8, 128), 1.0, "bf16")
+    off = H.assign_perfect(dp, lens)[0]
+    H.fill(dp, 0, kv, offsets=off)
+    first = H.prefill(dp, 0, q, np.array([0, 128]), n_q, lens, offsets=off)
+    for _ in range(20):
+        np.testing.assert_array_equal(H.prefill(dp, 0, q, np.array([0, 128]), n_q, lens, offsets=off), first)
+
+
 @pytest.mark.parametrize("column_tiles", [2, 4])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("kvd", ["bf16", "fp8"])
