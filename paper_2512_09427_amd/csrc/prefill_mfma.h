@@ -540,8 +540,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // exact maximum over the item's (or part's) first pair and never moves it, so the steady
     // state holds no cross-lane maximum, no rescale of O and no second exponential.  Should later scores
     // exceed that reference so far that a column's weight sum passes 2^90 (or turns inf / NaN), or lie so far below the
-    // stand-in reference of a column whose first pair scored -inf that the sum stays under 2^-60, the wave repeats its
-    // columns in the slow pass below, the classic online softmax that moves its references.
+    // stand-in reference of a column whose first pair scored -inf that the sum stays under 2^-60 (in a part: 1/2), the wave
+    // repeats its columns in the slow pass below, the classic online softmax that moves its references.
     auto scores_of = [&](float4v (&x)[CT][2], const bf16x8 (&qq)[CT][4], auto&& kop) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
@@ -774,9 +774,12 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       for (int ct = 0; ct < CT; ++ct) l[ct] = 0.f;
     if (!HERE || active) {
       column_sums(l);
+      // Parts: a stand-in may not lie above its state's largest score either.  In the merge it would push the others' references
+      // out of the exponent's range: 0, with scores of -60, beside one of -150 whose scores grew to -61.
+      const float least = HERE && n_parts > 1 ? 0.5f : 0x1p-60f;
       bool redo = false;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] > 0 && !(l[ct] > 0x1p-60f && l[ct] < 0x1p90f);
+      for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] > 0 && !(l[ct] > least && l[ct] < 0x1p90f);
       if (__builtin_amdgcn_ballot_w64(redo) != 0) {                      // this wave's columns alone
         slow_pass();
         column_sums(l);

@@ -178,3 +178,44 @@ def test_values_near_the_ends_of_the_range(kvd, d, kernel, size):
     # (values of 1e-37 sit at the bottom of the normal range, where sums lose up to eight bits)
     tol = (1e-5, 1e-5) if size > 1 else (1e-4, 1e-4)
     H.check(got.astype(np.float64) / size, H.oracle_out(w, q, kv) / size, *tol, what=f"{kvd} {d}")
+
+
+# One request of 32 pairs of tiles, cut behind pairs 10 and 21: per case its scores, as (first token, token behind the last,
+# score), later entries over earlier ones, and the tokens whose V is infinite.
+PARTS = {
+    # the middle part begins with tokens that are switched off and goes on far below zero (2^-59.5 in all); one token of the
+    # first part holds a tenth of that, 89 powers of two above those it began with
+    "low behind tokens that are off": ([(0, 320, -152), (100, 101, -62.7), (320, 352, -np.inf), (352, 672, -67.8), (672, 1024, -np.inf)], []),
+    "a part that is off": ([(320, 672, -np.inf)], []),
+    "all but the last part off": ([(0, 700, -np.inf)], []),
+    "infinite values of ordinary weight": ([], [40, 500, 1000]),
+}
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("name", list(PARTS))
+def test_prompt_whose_keys_are_cut_into_parts(name, paged):
+    scores, infinite = PARTS[name]
+    n, n_q = 1024, 4
+    w = small_workload([n], hq=7, hkv=1, seed=9, main=1 << 14)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    k, v = wl.request_kv(w, 0, 0)
+    q = np.zeros((n_q, 7, 128), np.uint16)                     # (scores as they are given, nothing beside them)
+    q[:, :, 0] = bits("bf16", 1.0)
+    k[:, :, 0] = bits("bf16", 0.0)
+    for a, b, score in scores:
+        k[a:b, :, 0] = bits("bf16", score * np.log(2.0) * np.sqrt(128.0))
+    v[infinite, :, 3::7] = bits("bf16", np.inf)
+    where = dict(block_table=wl.shuffled_block_table([n], w.pool_tokens // 16, 16, seed=5)) if paged else \
+        dict(offsets=H.assign_perfect(dp, np.array([n]))[0])
+    H.fill(dp, 0, [(k, v)], **where)
+    got = H.prefill(dp, 0, q, np.array([0]), np.array([n_q]), np.array([n]), **where)
+    for j in range(n_q):
+        seen = n - n_q + j + 1
+        ref = H.oracle_out(w, q[j:j + 1], [(k[:seen], v[:seen])])
+        # (the weights of a prompt are bf16: 2^-8 of the values they average)
+        tol = (2.0 ** -8 * w.data_scale * 4, 2e-2)
+        if infinite:
+            check_with_infinities(got[j:j + 1], ref, tol, f"{name}, query {j}")
+        else:
+            H.check(got[j:j + 1], ref, *tol, what=f"{name}, query {j}")
