@@ -842,7 +842,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct) {
             const float m_new = fmaxf(m[ct], ml[ct].x), ref = m_new == NEG_INF ? 0.f : m_new;
-            const float keep = __builtin_amdgcn_exp2f(m[ct] - ref), add = __builtin_amdgcn_exp2f(ml[ct].x - ref);
+            // (factors of at least the smallest number: 0 would make an infinite value NaN that is one in the whole item)
+            const float keep = fmaxf(__builtin_amdgcn_exp2f(m[ct] - ref), 0x1p-149f);
+            const float add = fmaxf(__builtin_amdgcn_exp2f(ml[ct].x - ref), 0x1p-149f);
             l[ct] = l[ct] * keep + ml[ct].y * add;
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt) O[ct][dt] = O[ct][dt] * keep + ov[ct][dt] * add;

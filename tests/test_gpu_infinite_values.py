@@ -189,6 +189,8 @@ PARTS = {
     "a part that is off": ([(320, 672, -np.inf)], []),
     "all but the last part off": ([(0, 700, -np.inf)], []),
     "infinite values of ordinary weight": ([], [40, 500, 1000]),
+    # 2^-90 of the weight that the sums began with, 2^-140 of the largest
+    "an infinite value of little weight": ([(320, 672, -100), (500, 501, -90), (672, 1024, 50)], [500]),
 }
 
 
