@@ -340,8 +340,12 @@ int odma_decode_attention_static(odma_pool_t* pool, int32_t layer, int32_t n,
  *   total_q    host: rows of q and out; rows at or past it are never read or written
  *   q_start    DEVICE int64[n]        n_q  DEVICE int32[n] (0: nothing to do; clamped to lengths[r])
  *   offsets, lengths, block_table, bt_stride as for odma_decode_attention (lengths include the chunk)
- * Launches the attention kernel on `stream`, for calls with many work items after a plan kernel, using the pool's workspace
- * (plan, and for few long items the states of their parts): prompt calls on one pool must not overlap on different streams. */
+ * Launches the attention kernel on `stream`, for calls with many work items after a plan kernel, using the pool's workspace.
+ * A work item is up to 128 (query token, head) columns of one request and KV head.  Calls with more items than two per compute
+ * unit, or with more than 1024 requests, keep their plan in the workspace and must not overlap with each other on different
+ * streams of one pool; calls of fewer are independent.  On the null stream the latter divide long requests among the compute
+ * units, with partial results in the workspace (no decode call reads or writes them); on other streams every item is one
+ * work-group's, so its rows may differ in rounding. */
 int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const void* q, int64_t total_q,
                            const int64_t* q_start, const int32_t* n_q, const int64_t* offsets,
                            const int32_t* lengths, const int32_t* block_table, int32_t bt_stride,

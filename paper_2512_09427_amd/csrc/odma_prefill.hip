@@ -64,10 +64,12 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   const int slots = pool->n_cu * (ct == 2 ? 2 : 1);
   dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
   // States of parts of items live where no decode launch reaches: its regions are sized for STREAM_MAX_WG work-groups, of
-  // which a launch has at most STREAM_MAX_LAUNCH_WG.
+  // which a launch has at most STREAM_MAX_LAUNCH_WG.  There is one set of them, for the null stream: its calls are ordered,
+  // whoever makes them.  A call on another stream, captured ones among them, may run beside it or beside its like, so it cuts
+  // nothing and keeps nothing in the workspace.
   constexpr int64_t spare = odma_plan::STREAM_MAX_WG - odma_plan::STREAM_MAX_LAUNCH_WG;
   static_assert(spare > 0 && spare * 8 * sizeof(odma_plan::WaveDesc) >= 4096 * sizeof(int64_t), "room for the counters");
-  a.part_slots = (int32_t)std::min<int64_t>(2 * spare * a.Hq / (64 * ct), 4096);
+  a.part_slots = s ? 0 : (int32_t)std::min<int64_t>(2 * spare * a.Hq / (64 * ct), 4096);
   a.arrive = (unsigned long long*)(ws + pool->ws.waves + odma_plan::STREAM_MAX_LAUNCH_WG * 8 * sizeof(odma_plan::WaveDesc));
   a.part_ml = (float2*)(ws + pool->ws.part_ml) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq;
   a.part_o = (float*)(ws + pool->ws.part_o) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq * 128;
@@ -76,10 +78,10 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // clears.
   const int64_t items = (total_q * a.G + 64 * ct - 1) / (64 * ct) * a.Hkv + (int64_t)n * a.Hkv;
   const bool here = n <= PREFILL_LDS_REQ && items <= (int64_t)grid.x;
-  // Such a launch has a work-group for every part that an item can have, counted from the longest request there can be, and
-  // none beyond: they would each scan the batch and hold up the end of the launch (a queue's first parts go to its first
+  // A launch that cuts has a work-group for every part that an item can have, counted from the longest request there can be,
+  // and none beyond: they would each scan the batch and hold up the end of the launch (a queue's first parts go to its first
   // work-groups, which start first).
-  if (here) {
+  if (here && a.part_slots) {
     const int64_t longest = block_table ? (int64_t)bt_stride * BLK : std::max<int64_t>(c.large_cap, pool->boundaries.back());
     const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
     grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);

@@ -16,7 +16,7 @@
 // handed out through atomic counters to persistent work-groups: causal items differ in length by construction.  The
 // work-groups of an XCD then read the same one or two K/V heads out of their L2 -- with one queue for the chip every XCD
 // fetched every K/V byte (16 x 4096 tokens: 60 M L2 misses of 128 bytes, 12 M with eight queues).  A work-group whose
-// queue is empty goes on with the fullest other one.  A call with few items cuts their keys into parts instead (prefill_parts).
+// queue is empty goes on with the fullest other one.  A call with few items may cut their keys into parts instead (prefill_parts).
 #pragma once
 
 #include <type_traits>
@@ -34,8 +34,8 @@ constexpr int PREFILL_XCDS = 8;
 // 664; eight: 675, 664).
 constexpr int PREFILL_SINGLES = 4;
 // A call of few items (one chunk of a long prompt: a hundred, or eight) leaves most of the chip idle while each streams its
-// keys in one serial chain.  Such a call cuts the keys of its items into parts, one per work-group, whose states the last one to
-// arrive merges.  A pair costs a lone work-group about 0.55 us and a merged state 1.2, so the best number of parts grows
+// keys in one serial chain.  Such a call on the null stream cuts the keys of its items into parts, one per work-group, whose
+// states the last one to arrive merges.  A pair costs a lone work-group about 0.55 us and a merged state 1.2, so the best number of parts grows
 // with the square root of the pairs; at 16 pairs cutting is worth its fixed cost of 2.5 us.  One chunk of 128 tokens, 28 / 4 heads
 // (28 items): ending at 512 tokens 18.4 us both ways (at 384 16.2 whole, 17.0 cut), at 640 20.5 -> 18.8; two at 1024 28.0 ->
 // 23.5; chunks of 512 (112 items) at 2048 48.2 -> 37.9, at 8192 161 -> 86, at 32 768 612 -> 268; one of 128 at 5090 with 8 / 8
@@ -77,7 +77,7 @@ struct PrefillArgs {
   float scale_log2;          // sm_scale * log2(e) (fp8 pools: times k_scale)
   float out_scale;           // 1, or v_scale for fp8 pools
   int32_t out_bf16;
-  int32_t part_slots;        // parts of cut items whose states the workspace holds
+  int32_t part_slots;        // parts of cut items whose states the workspace holds (0: items stay whole)
   unsigned long long* arrive;   // [part_slots] arrival counters of cut items (count_in)
   float2* part_ml;           // [part_slots][columns of an item]: reference and sum
   float* part_o;             // [part_slots][columns of an item * 128]: outputs, lane by lane

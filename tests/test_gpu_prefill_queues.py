@@ -120,6 +120,48 @@ def test_items_cut_into_parts_repeat_bit_for_bit():
         np.testing.assert_array_equal(H.prefill(dp, 0, q, np.array([0, 128]), n_q, lens, offsets=off), first)
 
 
+def test_calls_on_other_streams_are_independent():
+    """Calls of few items on streams of their own leave the workspace alone, so they may overlap."""
+    lens, n_q = np.array([5090, 3000]), np.array([128, 40])
+    w = small_workload(lens, hq=8, hkv=8, seed=99, bounds=(512, 8192), large_cap=8192, main=1 << 14)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    q_start = np.array([0, 128])
+    off = H.assign_perfect(dp, lens)[0]
+    H.fill(dp, 0, kv, offsets=off)
+    where = [H.to_dev(x) for x in (q_start.astype(np.int64), n_q.astype(np.int32), np.asarray(off, np.int64), lens.astype(np.int32))]
+    qs = [wl.draw_values(np.random.default_rng(seed), (int(n_q.sum()), 8, 128), 1.0, "bf16")[0] for seed in (99, 100)]
+    sides = [torch.cuda.Stream() for _ in qs]
+    dev = [H.to_dev(q) for q in qs]
+    outs = [torch.zeros(q.shape, dtype=torch.float32, device=H.DEV) for q in qs]
+
+    def call(i):
+        dp.pool.odma_prefill_attention(0, 2, dev[i], len(qs[i]), where[0], where[1], where[2], where[3], None, 0, outs[i], sides[i])
+
+    dp.workspace.fill_(0x5a)
+    alone = []
+    for i, q in enumerate(qs):
+        torch.cuda.synchronize()
+        call(i)
+        torch.cuda.synchronize()
+        alone.append(outs[i].clone())
+        for r, (a, m) in enumerate(zip(q_start, n_q)):
+            rows = slice(a, a + m)
+            ref = oa.attend_chunk(q[rows], kv[r][0], kv[r][1], 1.0 / np.sqrt(128.0))
+            ref_abs = oa.attend_chunk(q[rows], kv[r][0], kv[r][1] & 0x7fff, 1.0 / np.sqrt(128.0))
+            H.check(alone[i][rows].cpu().numpy(), ref, TIGHT[0] + P_ROUNDING * ref_abs, TIGHT[1], what=f"request {r}")
+    assert bool((dp.workspace == 0x5a).all())
+    for _ in range(10):
+        for o in outs:
+            o.zero_()
+        torch.cuda.synchronize()
+        for _ in range(4):
+            call(0)
+            call(1)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], alone[0]) and torch.equal(outs[1], alone[1])
+
+
 @pytest.mark.parametrize("column_tiles", [2, 4])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("kvd", ["bf16", "fp8"])
