@@ -265,8 +265,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     __syncthreads();
   }
   // Most parts that an item is cut into; one that is too short for so many leaves its last ones empty.
-  const int parts = HERE ? max(min(PREFILL_PARTS, min(a.part_slots, (int)gridDim.x) / max(rfl(bound[PREFILL_XCDS]), 1)), 1) : 1;
-  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(rfl(bound[PREFILL_XCDS]) / ((int)gridDim.x * 8), 1));
+  const int n_items = rfl(bound[PREFILL_XCDS]);
+  const int parts = HERE ? max(min(PREFILL_PARTS, min(a.part_slots, (int)gridDim.x) / max(n_items, 1)), 1) : 1;
+  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
   // Run j of a queue of len items begins at its item run_at(len, j) and ends where the next one begins: the last
   // PREFILL_SINGLES items per work-group are runs of their own.
@@ -312,38 +313,48 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     claimed = start < end && ((longer >> queue) & 1) != 0;
     if (claimed) claim();
   };
-  int next, run_end;                                                   // the present run: what is left of it
-  {
-    const int at = HERE ? 0 : rfl(bound[queue]), turn = blockIdx.x / PREFILL_XCDS;
-    const int len = HERE ? (rfl(bound[queue + 1]) - rfl(bound[queue])) * parts : rfl(bound[queue + 1]) - at;
+  int next = 0, run_end = 0;                                           // the present run: what is left of it
+  // HERE: the work-group's next part, the end of its XCD's, and the items they belong to, [first_of, first_of + n_of): all first
+  // parts, then the second ones, ...  An XCD has its queue's items.  With fewer items than queues all XCDs share them: some
+  // queues would be empty, and one item's parts an eighth of the work-groups' (one chunk of 128 tokens at 32 768, 4 / 1 heads,
+  // 99 -> 65 us; of 16, 8 / 1 heads, 136 -> 63).
+  int unit = blockIdx.x / PREFILL_XCDS, unit_end = 0, first_of = 0, n_of = n_items;
+  if constexpr (HERE) {
+    if (n_items < PREFILL_XCDS) {
+      unit += n_items * parts * queue / PREFILL_XCDS;
+      unit_end = n_items * parts * (queue + 1) / PREFILL_XCDS;
+    } else {
+      first_of = rfl(bound[queue]);
+      n_of = rfl(bound[queue + 1]) - first_of;
+      unit_end = n_of * parts;
+    }
+  } else {
+    const int at = rfl(bound[queue]), len = rfl(bound[queue + 1]) - at, turn = blockIdx.x / PREFILL_XCDS;
     next = at + run_at(len, turn);
     run_end = at + run_at(len, turn + 1);
-    if (!HERE && wv == 0 && next < run_end && run_at(len, turns) < len) {
+    if (wv == 0 && next < run_end && run_at(len, turns) < len) {
       claimed = true;
       claim();
     }
   }
-  int at = next;                                                       // first item of the present run
   for (;;) {
     // ---- next item (every wave reaches the exit together)
     __syncthreads();                                       // the previous item's slot and stages are done with
-    if (HERE && next >= run_end) {
-      at += turns;
-      next = at;
-      run_end = at + 1;
-      if (next >= (rfl(bound[queue + 1]) - rfl(bound[queue])) * parts) break;
-    } else if (next >= run_end) {
-      if (wv == 0) settle();
-      __syncthreads();
-      next = rfl(run_slot[0]);
-      run_end = rfl(run_slot[1]);
-      if (next >= run_end) break;
-    }
-    int item = next++, part = 0;
-    if constexpr (HERE) {                                  // the first parts of a queue's items, then the second ones, ...
-      const int first = rfl(bound[queue]), len = rfl(bound[queue + 1]) - first;
-      part = rfl(item / len);
-      item = first + item - part * len;
+    int item, part = 0;
+    if constexpr (HERE) {
+      if (unit >= unit_end) break;
+      part = rfl(unit / n_of);
+      item = first_of + unit - part * n_of;
+      unit += turns;
+    } else {
+      if (next >= run_end) {
+        if (wv == 0) settle();
+        __syncthreads();
+        next = rfl(run_slot[0]);
+        run_end = rfl(run_slot[1]);
+        if (next >= run_end) break;
+      }
+      item = next++;
     }
     // Request of the item: largest r with item_start[r] <= item (item_start is non-decreasing; empty requests repeat
     // a value, so it is the last one that still has items).  In LDS, where the table fits: the number of such entries, 64 a

@@ -74,6 +74,16 @@ def test_items_cut_into_parts(lens, n_q, hq, hkv, kvd, paged, column_tiles):
                    paged=paged, bounds=(512, 16384), large_cap=16384, main=1 << 17)
 
 
+@pytest.mark.parametrize("lens,n_q,hq,hkv", [
+    ([6000], [16], 8, 1),                                    # one item, eight parts for eight XCDs
+    ([700, 3000], [30, 20], 4, 1),                           # two, of two and six parts
+    ([2500], [70], 7, 7),                                    # seven: one fewer than queues
+    ([2500], [130], 8, 4),                                   # twelve: queues again
+])
+def test_fewer_items_than_queues(lens, n_q, hq, hkv):
+    chunk_case(lens, n_q, hq=hq, hkv=hkv, sharp=True, seed=101, bounds=(512, 8192), large_cap=8192, main=1 << 14)
+
+
 def test_parts_whatever_the_workspace_holds():
     """Arrival counters and states in a workspace of arbitrary bytes, and again in what the call before left there; a graph's
     replays beside them."""
