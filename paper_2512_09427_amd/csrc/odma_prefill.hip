@@ -78,22 +78,21 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // clears.
   const int64_t items = (total_q * a.G + 64 * ct - 1) / (64 * ct) * a.Hkv + (int64_t)n * a.Hkv;
   const bool here = n <= PREFILL_LDS_REQ && items <= (int64_t)grid.x;
-  // A launch that cuts has a work-group for every part that an item can have, counted from the longest request there can be,
-  // and none beyond: they would each scan the batch and hold up the end of the launch (a queue's first parts go to its first
-  // work-groups, which start first).
-  if (here && a.part_slots) {
-    const int64_t longest = block_table ? (int64_t)bt_stride * BLK : std::max<int64_t>(c.large_cap, pool->boundaries.back());
-    const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
-    grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
-  }
+  // Items are cut on the null stream, and where a request can be long enough.  Such a launch has a work-group for every part that
+  // an item can have, counted from the longest request there can be, and none beyond: they would each scan the batch and hold
+  // up the end of the launch (a queue's first parts go to its first work-groups, which start first).
+  const int64_t longest = block_table ? (int64_t)bt_stride * BLK : std::max<int64_t>(c.large_cap, pool->boundaries.back());
+  const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
+  const bool cut = here && a.part_slots && parts > 1;
+  if (cut) grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
   if (!here)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
                        c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start);
-  // [fp8][two column tiles][paged][planned here]
-#define ODMA_PREFILL(P, CT, F) {prefill_kernel<P, CT, F, false>, prefill_kernel<P, CT, F, true>}
+  // [fp8][two column tiles][paged][planned in front, here, here and cut]
+#define ODMA_PREFILL(P, CT, F) {prefill_kernel<P, CT, F, false, false>, prefill_kernel<P, CT, F, true, false>, prefill_kernel<P, CT, F, true, true>}
 #define ODMA_PREFILL_F(F) {{ODMA_PREFILL(false, 4, F), ODMA_PREFILL(true, 4, F)}, {ODMA_PREFILL(false, 2, F), ODMA_PREFILL(true, 2, F)}}
-  static void (*const kernels[2][2][2][2])(PrefillArgs) = {ODMA_PREFILL_F(false), ODMA_PREFILL_F(true)};
-  hipLaunchKernelGGL(kernels[fp8][ct == 2][block_table != nullptr][here], grid, dim3(256), 0, s, a);
+  static void (*const kernels[2][2][2][3])(PrefillArgs) = {ODMA_PREFILL_F(false), ODMA_PREFILL_F(true)};
+  hipLaunchKernelGGL(kernels[fp8][ct == 2][block_table != nullptr][here + cut], grid, dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(where, e);
   return ODMA_OK;

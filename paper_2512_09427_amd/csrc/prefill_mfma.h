@@ -225,7 +225,9 @@ __device__ __forceinline__ unsigned fp8x2_to_bf16x2(unsigned w) {
 // widen them to bf16 on the way into LDS and store them in the bf16 layout, everything after that is shared.
 // HERE: the kernel plans for itself (a variant of its own: inside the other one the plan cost the pair loop registers, 254
 // for 242, and 2 to 7 % of every long call).
-template <bool PAGED, int CT, bool FP8, bool HERE>
+// CUT: it cuts items into parts as well, where they are few and long (again a variant of its own, for calls that may: with the
+// code in them calls of few items took 0.3 to 0.4 us more, 41 prompts of 1 to 250 tokens 12.05 -> 12.45).
+template <bool PAGED, int CT, bool FP8, bool HERE, bool CUT>
 __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillArgs a) {
   constexpr int TILE_BYTES = BLK * 128 * (FP8 ? 1 : 2);
   constexpr int LOADS = TILE_BYTES / 1024;                         // 16-byte loads per lane and tile
@@ -266,7 +268,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   }
   // Most parts that an item is cut into; one that is too short for so many leaves its last ones empty.
   const int n_items = rfl(bound[PREFILL_XCDS]);
-  const int parts = HERE ? max(min(PREFILL_PARTS, min(a.part_slots, (int)gridDim.x) / max(n_items, 1)), 1) : 1;
+  // (fractions with a denominator of at most 512 are 1/512 apart or more; beyond 512 items the result is at most 1 all the same)
+  const float part_room = (float)min(a.part_slots, (int)gridDim.x) * __builtin_amdgcn_rcpf((float)max(n_items, 1)) + 0x1p-10f;
+  const int parts = CUT ? rfl(max(min((int)part_room, PREFILL_PARTS), 1)) : 1;
   const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
   // Run j of a queue of len items begins at its item run_at(len, j) and ends where the next one begins: the last
@@ -343,7 +347,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     int item, part = 0;
     if constexpr (HERE) {
       if (unit >= unit_end) break;
-      part = rfl(unit / n_of);
+      if (CUT) part = rfl((int)(((float)unit + 0.5f) * __builtin_amdgcn_rcpf((float)n_of)));   // (half an n_of-th or more from whole numbers)
       item = first_of + unit - part * n_of;
       unit += turns;
     } else {
@@ -402,7 +406,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
 
     // ---- per-lane columns: tile ct holds column c0 + 16 ct + col16
     // keys visible to the column (of a part: from its first one on, which may be less than none)
-    constexpr int ABSENT = HERE ? -(1 << 30) : 0;                      // (or less)
+    constexpr int ABSENT = CUT ? -(1 << 30) : 0;                      // (or less)
     int lim[CT];
     int64_t q_at[CT];                                                  // the column's row in q and out, in elements
     bf16x8 qreg[CT][4];
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     int n_tiles = (item_lim_max + BLK - 1) / BLK, skipped = 0;         // skipped: tiles in front of the part
     const int all_pairs = (n_tiles + 1) / 2;
     int n_pairs = all_pairs, n_parts = 1;
-    if (HERE && parts > 1) {
+    if (CUT && parts > 1) {
       n_parts = min(prefill_parts(all_pairs), parts);
       if (part >= n_parts) continue;
       // from here on the part's first token is token 0
@@ -689,7 +693,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       };
       look_up(0);
       if (FP8) load(kr, a.k, next_at);
-      for (int pr = 0; HERE ? pr < n_pairs : 2 * pr < n_tiles; ++pr) {
+      for (int pr = 0; CUT ? pr < n_pairs : 2 * pr < n_tiles; ++pr) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) at[b] = next_at[b];
         look_up(pr + 1);
@@ -778,16 +782,16 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     };
 
     stream();
-    if (!HERE && !active) continue;
+    if (!CUT && !active) continue;
     float l[CT];
-    if (HERE)
+    if (CUT)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) l[ct] = 0.f;
-    if (!HERE || active) {
+    if (!CUT || active) {
       column_sums(l);
       // Parts: a stand-in may not lie above its state's largest score either.  In the merge it would push the others' references
       // out of the exponent's range: 0, with scores of -60, beside one of -150 whose scores grew to -61.
-      const float least = HERE && n_parts > 1 ? 0.5f : 0x1p-60f;
+      const float least = CUT && n_parts > 1 ? 0.5f : 0x1p-60f;
       bool redo = false;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) redo |= lim[ct] > 0 && !(l[ct] > least && l[ct] < 0x1p90f);
@@ -796,7 +800,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         column_sums(l);
       }
     }
-    if (HERE && n_parts > 1) {
+    if (CUT && __builtin_expect(n_parts > 1, 0)) {         // (the merge's code stands behind the whole items')
       // ---- merge of the parts: each leaves its state (m, l, O) in the workspace, the last to arrive reads them all, its own
       // too, from the first part to the last, so that a call repeats bit for bit whatever the order of arrival.  Nobody waits
       // for anybody; order as in the decode kernel's merge: the stores are acknowledged before the barrier, the arrival is

@@ -163,3 +163,30 @@ def test_launches_that_plan_are_kernels_of_their_own(runtime, kv, d):
                 assert kernel(lambda: f(p, 1200, paged=paged)) == [reuses]
         assert len(set(seen.values())) == 8, seen
     """)
+
+
+def test_prompt_calls_that_may_be_cut(runtime):
+    """The variant that cuts items into parts: calls of few items on the null stream, of pools (or block tables) whose requests can
+    hold 16 pairs of tiles.  It has a work-group for every part there can be; the others of such calls have all of them."""
+    run(runtime, """
+        def prompt(p, n=1, rows=16, stream=0, paged=None):
+            at = hip.fake_launches()
+            p.odma_prefill_attention(0, n, Q, rows, OFFS, NEW, None if paged else OFFS, LENS, TABLE if paged else None, paged or 0, OUT,
+                                     stream)
+            return [(hip.fake_name(i).decode(), hip.fake_grid(i, 0)) for i in range(at, hip.fake_launches())]
+
+        variant = lambda paged, here, cut: f"prefill_kernelILb{int(paged)}ELi2ELb0ELb{int(here)}ELb{int(cut)}E"
+        def check(got, paged, here, cut, grid=512):
+            assert len(got) == (1 if here else 2) and variant(paged, here, cut) in got[-1][0] and got[-1][1] == grid, got
+
+        p = make_pool()                                      # requests of up to 4096 tokens: up to 7 parts
+        check(prompt(p), False, True, True, 32)              # 2 + 2 items at most, 28 parts
+        check(prompt(p, stream=77), False, True, False)
+        check(prompt(p, paged=32), True, True, True, 8)      # 512 tokens: 2 parts
+        check(prompt(p, paged=31), True, True, False)
+        check(prompt(p, paged=1 << 30), True, True, True, 128)
+        check(prompt(p, n=200), False, True, True)
+        check(prompt(p, n=300), False, False, False)
+        check(prompt(p, rows=1 << 20), False, False, False)
+        check(prompt(p, rows=1 << 20, stream=77), False, False, False)
+    """)
