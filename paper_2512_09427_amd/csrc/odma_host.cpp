@@ -170,6 +170,10 @@ WorkspaceLayout workspace_layout(const odma_pool_config_t& c) {
     w.arrive = s.arrive;
     w.part_ml = s.part_ml;
     w.part_o = s.part_o;
+    w.prompt_arrive = s.prompt_arrive;
+    w.prompt_ml = s.prompt_ml;
+    w.prompt_o = s.prompt_o;
+    w.prompt_columns = s.prompt_columns;
     off = s.end;
     // prefill attention: queue header and the exclusive prefix of work items per request
     w.prefill = off;  off += 256 + up((size_t)(c.max_requests + 1) * sizeof(int32_t));

@@ -73,6 +73,8 @@ struct Recalibrator {
 // Device workspace carve-up (byte offsets from cfg.workspace); the record types it sizes are in plan_types.h.
 struct WorkspaceLayout {
   size_t header = 0, req_info = 0, items = 0, waves = 0, red = 0, arrive = 0, part_ml = 0, part_o = 0, prefill = 0, total = 0;
+  size_t prompt_arrive = 0, prompt_ml = 0, prompt_o = 0;   // prompt attention's states of parts
+  int64_t prompt_columns = 0;
   int64_t max_pairs = 0;
 };
 

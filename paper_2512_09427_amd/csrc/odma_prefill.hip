@@ -63,16 +63,13 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   const int ct = pool->prefill_ct ? pool->prefill_ct : 2;
   const int slots = pool->n_cu * (ct == 2 ? 2 : 1);
   dim3 grid((slots + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);   // every queue has as many work-groups
-  // States of parts of items live where no decode launch reaches: its regions are sized for STREAM_MAX_WG work-groups, of
-  // which a launch has at most STREAM_MAX_LAUNCH_WG.  There is one set of them, for the null stream: its calls are ordered,
-  // whoever makes them.  A call on another stream, captured ones among them, may run beside it or beside its like, so it cuts
-  // nothing and keeps nothing in the workspace.
-  constexpr int64_t spare = odma_plan::STREAM_MAX_WG - odma_plan::STREAM_MAX_LAUNCH_WG;
-  static_assert(spare > 0 && spare * 8 * sizeof(odma_plan::WaveDesc) >= 4096 * sizeof(int64_t), "room for the counters");
-  a.part_slots = s ? 0 : (int32_t)std::min<int64_t>(2 * spare * a.Hq / (64 * ct), 4096);
-  a.arrive = (unsigned long long*)(ws + pool->ws.waves + odma_plan::STREAM_MAX_LAUNCH_WG * 8 * sizeof(odma_plan::WaveDesc));
-  a.part_ml = (float2*)(ws + pool->ws.part_ml) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq;
-  a.part_o = (float*)(ws + pool->ws.part_o) + (int64_t)2 * odma_plan::STREAM_MAX_LAUNCH_WG * a.Hq * 128;
+  // There is one set of states of parts, for the null stream: its calls are ordered, whoever makes them.  A call on another
+  // stream, captured ones among them, may run beside it or beside its like, so it cuts nothing and keeps nothing in the
+  // workspace.
+  a.part_slots = s ? 0 : (int32_t)std::min<int64_t>(pool->ws.prompt_columns / (64 * ct), odma_plan::PROMPT_MAX_PARTS);
+  a.arrive = (unsigned long long*)(ws + pool->ws.prompt_arrive);
+  a.part_ml = (float2*)(ws + pool->ws.prompt_ml);
+  a.part_o = (float*)(ws + pool->ws.prompt_o);
   // Few items -- no more than work-groups, counted from the rows of q (rows that several requests share only make more of
   // them): planned in the attention launch.  With more, the work-groups balance through counters, which a planning launch
   // clears.

@@ -46,6 +46,9 @@ struct ReduceDesc {          // the segment cut by the boundary in front of work
 
 constexpr int STREAM_MAX_WG = 4096;  // work-groups the pool workspace is sized for
 constexpr int STREAM_MAX_LAUNCH_WG = 2048;   // most work-groups of one launch: eight waves per SIMD of 256 compute units
+// What the regions hold beyond a launch's most work-groups is prompt attention's: the states of items whose keys are cut into
+// parts, so that a plan for decode launches survives a prompt call (StreamLayout::prompt_*).  At most this many parts.
+constexpr int PROMPT_MAX_PARTS = 4096;
 // Work-groups of a pool served by the wide formats, whose partial states live in the workspace that the chunked scheme
 // sizes: one per compute unit, as many as fit.  In a small workspace the chunked kernel may spread further, one wave per
 // (chunk, KV head), up to eight per compute unit; it does G heads' arithmetic on the vector ALU, though, where the matrix
@@ -115,10 +118,16 @@ ODMA_HD inline StreamShares stream_shares(int total, int n_waves, int wpw, int q
   return s;
 }
 
+constexpr int STREAM_SPARE_WG = STREAM_MAX_WG - STREAM_MAX_LAUNCH_WG;
+static_assert(STREAM_SPARE_WG > 0 && (size_t)STREAM_SPARE_WG * 8 * sizeof(WaveDesc) >= (size_t)PROMPT_MAX_PARTS * sizeof(int64_t),
+              "an arrival counter for every part");
+
 // Byte offsets of the regions of a tile-stream workspace sized for max_requests requests, n_wg_cap attention
 // work-groups and n_q_heads query heads (partial states keep `channels` channels per head).
 struct StreamLayout {
   size_t header, req_info, items, waves, red, arrive, part_ml, part_o, end;   // (header and req_info: unused, kept so that the size stays)
+  size_t prompt_arrive, prompt_ml, prompt_o;   // with n_wg_cap = STREAM_MAX_WG, else 0
+  int64_t prompt_columns;                      // query columns (a reference, a sum and `channels` outputs) that fit there
 };
 ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int64_t n_wg_cap, int64_t n_q_heads,
                                           int64_t channels = 128) {
@@ -134,6 +143,11 @@ ODMA_HD inline StreamLayout stream_layout(size_t off, int64_t max_requests, int6
   w.part_ml = off;  off += up((size_t)2 * n_wg_cap * n_q_heads * 2 * sizeof(float));
   w.part_o = off;   off += up((size_t)2 * n_wg_cap * n_q_heads * channels * sizeof(float));
   w.end = off;
+  const bool spare = n_wg_cap == STREAM_MAX_WG;
+  w.prompt_arrive = spare ? w.waves + (size_t)STREAM_MAX_LAUNCH_WG * 8 * sizeof(WaveDesc) : 0;
+  w.prompt_ml = spare ? w.part_ml + (size_t)2 * STREAM_MAX_LAUNCH_WG * n_q_heads * 2 * sizeof(float) : 0;
+  w.prompt_o = spare ? w.part_o + (size_t)2 * STREAM_MAX_LAUNCH_WG * n_q_heads * channels * sizeof(float) : 0;
+  w.prompt_columns = spare ? (int64_t)2 * STREAM_SPARE_WG * n_q_heads : 0;
   return w;
 }
 

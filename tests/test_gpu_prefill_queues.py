@@ -130,6 +130,29 @@ def test_items_cut_into_parts_repeat_bit_for_bit():
         np.testing.assert_array_equal(H.prefill(dp, 0, q, np.array([0, 128]), n_q, lens, offsets=off), first)
 
 
+@pytest.mark.parametrize("waves_per_cu", [4, 32])
+def test_a_plan_for_decode_launches_survives_a_prompt_call(waves_per_cu):
+    """A planning decode call, a prompt call that cuts its items, a decode call that reuses the plan: the latter's output is what
+    it is without the prompt call between.  4: the usual launch; 32: as many work-groups as a launch can have."""
+    lens, n_q = np.array([5090, 3000, 700, 0, 33]), np.array([128, 40, 1, 0, 33])
+    w = small_workload(lens, hq=8, hkv=8, seed=102, bounds=(512, 8192), large_cap=8192, main=1 << 15)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_CU, waves_per_cu)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    off = H.assign_perfect(dp, lens)[0]
+    H.fill(dp, 0, kv, offsets=off)
+    rows, _ = wl.draw_values(np.random.default_rng(102), (int(n_q.sum()), 8, 128), 1.0, "bf16")
+    q = wl.queries(w, 0, sharp=True)
+    prompt = lambda: H.prefill(dp, 0, rows, np.concatenate([[0], np.cumsum(n_q)[:-1]]), n_q, lens, offsets=off)
+    decode = lambda flags: H.decode(dp, 0, q, lens, offsets=off, flags=flags)
+    planned = decode(0)
+    reused, cut = decode(B.REUSE_PLAN), prompt()
+    np.testing.assert_array_equal(reused, planned)
+    for _ in range(3):
+        np.testing.assert_array_equal(decode(B.REUSE_PLAN), reused)
+        np.testing.assert_array_equal(prompt(), cut)
+
+
 def test_calls_on_other_streams_are_independent():
     """Calls of few items on streams of their own leave the workspace alone, so they may overlap."""
     lens, n_q = np.array([5090, 3000]), np.array([128, 40])
