@@ -257,11 +257,17 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // 58 tokens 11.2 -> 8.3 us, 28 of 91 to 546 tokens 20.0 -> 17.5.
   __shared__ typename std::conditional<HERE, PrefillPlan, PrefillBounds>::type plan;   // (in LDS: read between runs only)
   int (&bound)[PREFILL_XCDS + 1] = plan.bound;
+  __shared__ int whole_runs[PREFILL_XCDS];                             // of each queue, in front of its singles
   const bool small = a.n <= PREFILL_LDS_REQ;
+  const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
+  int run = 1;
   if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
     prefill_plan(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
   } else {
+    run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(a.hdr->bound[PREFILL_XCDS] / ((int)gridDim.x * 8), 1));
     if (threadIdx.x <= PREFILL_XCDS) bound[threadIdx.x] = a.hdr->bound[threadIdx.x];
+    if (threadIdx.x < PREFILL_XCDS)
+      whole_runs[threadIdx.x] = max(a.hdr->bound[threadIdx.x + 1] - a.hdr->bound[threadIdx.x] - PREFILL_SINGLES * turns, 0) / run;
     if (small)
       for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
     __syncthreads();
@@ -271,14 +277,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // (fractions with a denominator of at most 512 are 1/512 apart or more; beyond 512 items the result is at most 1 all the same)
   const float part_room = (float)min(a.part_slots, (int)gridDim.x) * __builtin_amdgcn_rcpf((float)max(n_items, 1)) + 0x1p-10f;
   const int parts = CUT ? rfl(max(min((int)part_room, PREFILL_PARTS), 1)) : 1;
-  const int run = HERE ? 1 : min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(n_items / ((int)gridDim.x * 8), 1));
-  const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
-  // Run j of a queue of len items begins at its item run_at(len, j) and ends where the next one begins: the last
+  // Run j of a queue of len items begins at its item run_at(len, whole, j) and ends where the next one begins: the last
   // PREFILL_SINGLES items per work-group are runs of their own.
-  auto run_at = [&](int len, int j) {
-    const int whole = max(len - PREFILL_SINGLES * turns, 0) / run;
-    return min(min(j, whole) * run + max(j - whole, 0), len);
-  };
+  auto run_at = [&](int len, int whole, int j) { return min(min(j, whole) * run + max(j - whole, 0), len); };
   int queue = blockIdx.x % PREFILL_XCDS;                               // (work-group b runs on XCD b % 8)
   int ahead = 0;
   auto claim = [&]() {
@@ -288,19 +289,19 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   // work-group goes on with the fullest one that was longer than its work-groups' first runs.
   bool claimed = false;
   auto settle = [&]() {
-    const int x = lane % PREFILL_XCDS, at = bound[x], len = bound[x + 1] - at;   // lane x: queue x
-    const bool more = run_at(len, turns) < len;
+    const int x = lane % PREFILL_XCDS, at = bound[x], len = bound[x + 1] - at, whole = whole_runs[x];   // lane x: queue x
+    const bool more = run_at(len, whole, turns) < len;
     const unsigned longer = (unsigned)__builtin_amdgcn_ballot_w64(more);
     int start = 0, end = 0;
     auto take = [&]() {                                                // the run that `ahead` names
       const int j = turns + rfl(ahead);
-      start = __builtin_amdgcn_readlane(at + run_at(len, j), queue);
-      end = __builtin_amdgcn_readlane(at + run_at(len, j + 1), queue);
+      start = __builtin_amdgcn_readlane(at + run_at(len, whole, j), queue);
+      end = __builtin_amdgcn_readlane(at + run_at(len, whole, j + 1), queue);
     };
     if (claimed) take();
     while (start >= end && longer != 0) {
       const int taken = __hip_atomic_load(&a.hdr->next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int left = more ? len - run_at(len, turns + taken) : 0;
+      const int left = more ? len - run_at(len, whole, turns + taken) : 0;
       int most = left;
 #pragma unroll
       for (int o = 1; o < PREFILL_XCDS; o <<= 1) most = max(most, __shfl_xor(most, o));
@@ -333,10 +334,10 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       unit_end = n_of * parts;
     }
   } else {
-    const int at = rfl(bound[queue]), len = rfl(bound[queue + 1]) - at, turn = blockIdx.x / PREFILL_XCDS;
-    next = at + run_at(len, turn);
-    run_end = at + run_at(len, turn + 1);
-    if (wv == 0 && next < run_end && run_at(len, turns) < len) {
+    const int at = rfl(bound[queue]), len = rfl(bound[queue + 1]) - at, whole = rfl(whole_runs[queue]), turn = blockIdx.x / PREFILL_XCDS;
+    next = at + run_at(len, whole, turn);
+    run_end = at + run_at(len, whole, turn + 1);
+    if (wv == 0 && next < run_end && run_at(len, whole, turns) < len) {
       claimed = true;
       claim();
     }
