@@ -75,12 +75,15 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   // clears.
   const int64_t items = (total_q * a.G + 64 * ct - 1) / (64 * ct) * a.Hkv + (int64_t)n * a.Hkv;
   const bool here = n <= PREFILL_LDS_REQ && items <= (int64_t)grid.x;
-  // Items are cut on the null stream, and where a request can be long enough.  Such a launch has a work-group for every part that
-  // an item can have, counted from the longest request there can be, and none beyond: they would each scan the batch and hold
-  // up the end of the launch (a queue's first parts go to its first work-groups, which start first).
+  // Items are cut on the null stream, where a request can be long enough and there is room for two parts of every item.  How
+  // many items there are is known here to within a block per request and KV head: half of that is expected.  (With room for one
+  // part only, the kernel that can cut is the slower one: 30 prompts of 1 to 59 tokens, 28 / 4 heads, 10.1 -> 9.6 us, one of 1500
+  // and 50 short ones, 8 / 1 heads, 41.6 -> 40.4.)  Such a launch has a work-group for every part that
+  // an item can have, counted from the longest request there can be, and none beyond: they would each scan the batch and
+  // hold up the end of the launch (a queue's first parts go to its first work-groups, which start first).
   const int64_t longest = block_table ? (int64_t)bt_stride * BLK : std::max<int64_t>(c.large_cap, pool->boundaries.back());
   const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
-  const bool cut = here && a.part_slots && parts > 1;
+  const bool cut = here && a.part_slots && parts > 1 && 2 * items - (int64_t)n * a.Hkv <= (int64_t)grid.x;
   if (cut) grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
   if (!here)
     hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,

@@ -186,6 +186,8 @@ def test_prompt_calls_that_may_be_cut(runtime):
         check(prompt(p, paged=31), True, True, False)
         check(prompt(p, paged=1 << 30), True, True, True, 128)
         check(prompt(p, n=200), False, True, True)
+        check(prompt(p, n=254), False, True, True)           # 2 items of rows and one a request expected: 256, two parts of each
+        check(prompt(p, n=255), False, True, False)
         check(prompt(p, n=300), False, False, False)
         check(prompt(p, rows=1 << 20), False, False, False)
         check(prompt(p, rows=1 << 20, stream=77), False, False, False)
