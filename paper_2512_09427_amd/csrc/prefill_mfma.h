@@ -110,12 +110,13 @@ __device__ __forceinline__ int prefill_blocks(int rows, int G, int cols_item) {
 }
 
 // One work-group of PREFILL_PLAN_THREADS: exclusive prefix of items per request (item_start[0 .. n)), and in `pl` the bounds of
-// the eight queues of equal cost.  Ends with a barrier.
+// the eight queues of equal cost.  LONGEST: the most tokens of a request with items as well.  Ends with a barrier.
 struct PrefillPlan {
   double part_cost[PREFILL_PLAN_THREADS / 64];
-  int part_items[PREFILL_PLAN_THREADS / 64];
-  int bound[PREFILL_XCDS + 1], avg_pairs;
+  int part_items[PREFILL_PLAN_THREADS / 64], part_longest[PREFILL_PLAN_THREADS / 64];
+  int bound[PREFILL_XCDS + 1], avg_pairs, longest;
 };
+template <bool LONGEST>
 __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* lengths, const int64_t* q_start, int64_t total_q,
                                              int32_t n, int32_t Hkv, int32_t G, int32_t cols_item, PrefillPlan& pl,
                                              int32_t* item_start) {
@@ -123,7 +124,7 @@ __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* 
   const int per = (n + PREFILL_PLAN_THREADS - 1) / PREFILL_PLAN_THREADS;
   const int r0 = min(tid * per, n), r1 = min(r0 + per, n);
   double cost = 0;
-  int items = 0;
+  int items = 0, longest = 0;
   auto add = [&](int r, auto&& at) {                        // at(blocks of r, its cost rule), then past r
     const int rows = prefill_rows(n_q, lengths, q_start, total_q, r);
     const int nb = prefill_blocks(rows, G, cols_item);
@@ -131,6 +132,7 @@ __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* 
     at(nb, pc);
     cost += Hkv * pc.upto(nb);
     items += Hkv * nb;
+    if (LONGEST) longest = max(longest, nb ? lengths[r] : 0);
   };
   for (int r = r0; r < r1; ++r) add(r, [](int, const PrefillCost&) {});
   double inc_cost = cost;
@@ -139,6 +141,7 @@ __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* 
   for (int o = 1; o < 64; o <<= 1) {
     const double yc = __shfl_up(inc_cost, o);
     const int yi = __shfl_up(inc_items, o);
+    if (LONGEST) longest = max(longest, __shfl_up(longest, o));        // (a lane below o gets its own)
     if (lane >= o) {
       inc_cost += yc;
       inc_items += yi;
@@ -147,6 +150,7 @@ __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* 
   if (lane == 63) {
     pl.part_cost[wv] = inc_cost;
     pl.part_items[wv] = inc_items;
+    if (LONGEST) pl.part_longest[wv] = longest;
   }
   __syncthreads();
   double all_cost = 0;
@@ -160,10 +164,14 @@ __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* 
     }
     all_cost += pl.part_cost[i];
     all_items += pl.part_items[i];
+    if (LONGEST) longest = max(longest, pl.part_longest[i]);
   }
   // a boundary that rounding leaves to no thread keeps its share of the items
   if (tid <= PREFILL_XCDS) pl.bound[tid] = (int)((long long)all_items * tid / PREFILL_XCDS);
-  if (tid == 0) pl.avg_pairs = (int)(all_cost / max(all_items, 1));
+  if (tid == 0) {
+    pl.avg_pairs = (int)(all_cost / max(all_items, 1));
+    if (LONGEST) pl.longest = longest;
+  }
   __syncthreads();
   // boundary x lies at cost all_cost * x / 8, inside the request whose cost range holds it
   for (int r = r0; r < r1; ++r) {
@@ -197,7 +205,7 @@ __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(cons
                                                                            int32_t cols_item, PrefillHeader* hdr,
                                                                            int32_t* item_start) {
   __shared__ PrefillPlan pl;
-  prefill_plan(n_q, lengths, q_start, total_q, n, Hkv, G, cols_item, pl, item_start);
+  prefill_plan<false>(n_q, lengths, q_start, total_q, n, Hkv, G, cols_item, pl, item_start);
   const int tid = threadIdx.x;
   if (tid <= PREFILL_XCDS) hdr->bound[tid] = pl.bound[tid];
   if (tid < PREFILL_XCDS) hdr->next[tid] = 0;
@@ -262,7 +270,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   const int turns = gridDim.x / PREFILL_XCDS;                          // work-groups of an XCD
   int run = 1;
   if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
-    prefill_plan(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
+    prefill_plan<CUT>(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
   } else {
     run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(a.hdr->bound[PREFILL_XCDS] / ((int)gridDim.x * 8), 1));
     if (threadIdx.x <= PREFILL_XCDS) bound[threadIdx.x] = a.hdr->bound[threadIdx.x];
@@ -272,11 +280,14 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
     __syncthreads();
   }
-  // Most parts that an item is cut into; one that is too short for so many leaves its last ones empty.
+  // Most parts that an item is cut into: as many as there is room for, and no more than the longest request's items have (parts
+  // that nobody has are turns of a search, a round of loads and a barrier: five prompts of 50 tokens in a pool of slabs of
+  // 16 384 10.5 us with them, 9.9 without).  An item that is too short for so many leaves its last ones empty.
   const int n_items = rfl(bound[PREFILL_XCDS]);
   // (fractions with a denominator of at most 512 are 1/512 apart or more; beyond 512 items the result is at most 1 all the same)
   const float part_room = (float)min(a.part_slots, (int)gridDim.x) * __builtin_amdgcn_rcpf((float)max(n_items, 1)) + 0x1p-10f;
-  const int parts = CUT ? rfl(max(min((int)part_room, PREFILL_PARTS), 1)) : 1;
+  int parts = 1;
+  if constexpr (CUT) parts = rfl(max(min((int)part_room, prefill_parts((plan.longest + 2 * BLK - 1) / (2 * BLK))), 1));
   // Run j of a queue of len items begins at its item run_at(len, whole, j) and ends where the next one begins: the last
   // PREFILL_SINGLES items per work-group are runs of their own.
   auto run_at = [&](int len, int whole, int j) { return min(min(j, whole) * run + max(j - whole, 0), len); };

@@ -67,6 +67,8 @@ def test_runs_of_items_and_single_ones(n):
     ([1000, 31], [1000, 31], 7, 1),                          # late parts that some columns see nothing of; short items whole
     ([4000, 0, 2500, 17], [19, 0, 18, 17], 7, 1),            # empty request, a block that is just full, one column more
     ([9000, 3000], [20, 300], 1, 1),                         # fewer states than parts in the workspace
+    ([6000] + list(range(1, 41)), [128] + list(range(1, 41)), 7, 1),   # a long chunk beside many short prompts
+    (list(range(30, 60)), [5] * 30, 4, 4),                   # short ones alone
 ])
 def test_items_cut_into_parts(lens, n_q, hq, hkv, kvd, paged, column_tiles):
     for out_dtype in (B.F32, B.BF16):
