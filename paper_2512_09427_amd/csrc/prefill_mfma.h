@@ -30,16 +30,16 @@ constexpr int PREFILL_PLAN_THREADS = 256;
 constexpr int PREFILL_XCDS = 8;
 // A queue's last items go out one by one, this many per work-group: a work-group holds the run it is on and the one after
 // it, and with runs of four items to the end the last work-group of a call was busy 23 % longer than the mean one.  256
-// prompts around 256 tokens 715 -> 670 us, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 -> 632 (two singles: 677,
-// 664; eight: 675, 664).
+// prompts around 256 tokens 696 -> 659 us, the same in fp8 760 -> 687, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 ->
+// 632 (two singles 1 and 5 % longer, eight 0.7 and 5).
 constexpr int PREFILL_SINGLES = 4;
 // A call of few items (one chunk of a long prompt: a hundred, or eight) leaves most of the chip idle while each streams its
 // keys in one serial chain.  Such a call on the null stream cuts the keys of its items into parts, one per work-group, whose
-// states the last one to arrive merges.  A pair costs a lone work-group about 0.55 us and a merged state 1.2, so the best number of parts grows
-// with the square root of the pairs; at 16 pairs cutting is worth its fixed cost of 2.5 us.  One chunk of 128 tokens, 28 / 4 heads
-// (28 items): ending at 512 tokens 18.4 us both ways (at 384 16.2 whole, 17.0 cut), at 640 20.5 -> 18.8; two at 1024 28.0 ->
-// 23.5; chunks of 512 (112 items) at 2048 48.2 -> 37.9, at 8192 161 -> 86, at 32 768 612 -> 268; one of 128 at 5090 with 8 / 8
-// heads 102 -> 32.5.  With sqrt(0.75 pairs) parts two chunks at 1024 take 24.4, a whole prompt of 700 26.7 (whole 24.0, so 21.6).
+// states the last one to arrive merges.  A pair costs a lone work-group about 0.55 us and a merged state 1.2, so the best number of
+// parts grows with the square root of the pairs; at 16 pairs cutting is about even.  28 / 4 heads, whole -> cut: one chunk of 128
+// tokens (28 items) ending at 512 tokens 17.6 -> 17.6 to 18.3 us, at 640 20.0 -> 18.9 to 19.6; two at 1024 27.3 -> 23.3; chunks of
+// 512 (112 items) at 2048 45.9 -> 36.0, at 8192 158 -> 76, at 32 768 602 -> 237; one of 128 at 5090 with 8 / 8 heads 101 -> 32.2.
+// (With sqrt(0.75 pairs) parts two chunks at 1024 were 4 % longer, a whole prompt of 700 24 %.)
 constexpr int PREFILL_PARTS = 32;
 __host__ __device__ inline int prefill_parts(int pairs) {
   if (pairs < 16) return 1;
@@ -234,7 +234,7 @@ __device__ __forceinline__ unsigned fp8x2_to_bf16x2(unsigned w) {
 // HERE: the kernel plans for itself (a variant of its own: inside the other one the plan cost the pair loop registers, 254
 // for 242, and 2 to 7 % of every long call).
 // CUT: it cuts items into parts as well, where they are few and long (again a variant of its own, for calls that may: with the
-// code in them calls of few items took 0.3 to 0.4 us more, 41 prompts of 1 to 250 tokens 12.05 -> 12.45).
+// code in them calls of few items take 0.3 to 0.4 us more, 41 prompts of 1 to 250 tokens 12.05 -> 12.45).
 template <bool PAGED, int CT, bool FP8, bool HERE, bool CUT>
 __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillArgs a) {
   constexpr int TILE_BYTES = BLK * 128 * (FP8 ? 1 : 2);
