@@ -707,12 +707,15 @@ decode_stream_kernel(StreamArgs a) {
     // The tiles' registers are words, not vectors of bf16: where a branch changes 16-bit elements (the mask of a ragged tail,
     // the appended row), the compiler takes whole vectors apart over every branch they live across, the ones whose loads
     // are in flight too, and waits for those in every tile (bf16 with head_dim 96, 10 600 tokens: 18 us or 33, by luck).
-    uint4v kb[NBUF][NL], vb[NBUF][NL];
+    // (fp8 has no such branch.  There the appended row's block is a reference, which costs vectors of bf16 no scratch memory as it
+    // does words: 153 fused requests of 28 to 224 tokens, 20 / 4 heads, 18.7 us; words and selection by value 18.95.)
+    using Piece = typename std::conditional<FP8, bf16x8, uint4v>::type;
+    Piece kb[NBUF][NL], vb[NBUF][NL];
     // Loads of the prefetch cursor's tile.  They are issued in every step, so that the waits stay
     // static counts; once the whole range has been requested the surplus loads all read the first
     // block of the layer's pools, which stays in the L2 instead of costing HBM traffic.
     int to_issue = n_my;
-    auto issue = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
+    auto issue = [&](Piece (&kk)[NL], Piece (&vv)[NL]) {
       const int64_t off = to_issue > 0 ? tile_offset(pc) : 0;
       // two blocks per tile: the first half of the loads reads the first block, the rest the second one
       const int64_t off2 = !TWO ? 0 : (to_issue > 0 ? tile_offset2(pc) : 0);
@@ -722,14 +725,14 @@ decode_stream_kernel(StreamArgs a) {
         // streaming loads: K/V bytes are used once, and loads that do not allocate in the caches
         // read 9 % faster on this part (measured)
         const int64_t o = j < NP ? off + j * 1024 : off2 + (j - NP) * 1024;
-        kk[j] = __builtin_nontemporal_load((const uint4v*)(kbase + o));
+        kk[j] = __builtin_nontemporal_load((const Piece*)(kbase + o));
         if (F32) {
           // a lane's two fp32 pieces of 32 channels (c and 16 + c, four tokens each) are neighbours: the two loads that
           // take them share their cache lines
           const int64_t ov = j < NP ? off + (j >> 1) * 2048 + (j & 1) * 16 : off2 + ((j - NP) >> 1) * 2048 + (j & 1) * 16;
-          vv[j] = *(const uint4v*)(vbase + ov);
+          vv[j] = *(const Piece*)(vbase + ov);
         } else {
-          vv[j] = __builtin_nontemporal_load((const uint4v*)(vbase + o));
+          vv[j] = __builtin_nontemporal_load((const Piece*)(vbase + o));
         }
       }
     };
@@ -882,7 +885,7 @@ decode_stream_kernel(StreamArgs a) {
       w[2 * half] = lo;
       w[2 * half + 1] = hi;
     };
-    // Blocks of 2 KiB (fp8 storage, or bf16 with head_dim 64): the row's 128 K bytes and 128 V bytes are
+    // Blocks of 2 KiB (bf16 with head_dim 64; fp8 below): the row's 128 K bytes and 128 V bytes are
     // staged in the record's V area (overwritten by the patched pieces further down).  The pieces of the block that holds the
     // token, the tile's first or second, are selected by value: through a reference chosen at run time the tile's registers
     // live in scratch memory, in every tile (fused steps of 256 requests, 28 / 4 heads x 64 in bf16, config 3's lengths: 49 us
@@ -893,33 +896,15 @@ decode_stream_kernel(StreamArgs a) {
       const int rr = slot & 3;
       unsigned* stage = (unsigned*)(rec + REC_V);
       stage[lane] = newrow[0];
-      if (FP8) {
-        const uint2v* krow = (const uint2v*)stage;          // K[0..128) as 16 pieces of 8 bytes
-        const unsigned char* vrow = (const unsigned char*)(stage + 32);
-        if (col == slot) {                                   // K: per 64-channel half, 8 channels of each of its two k-steps
-          const uint2v a0 = krow[g4], b0 = krow[4 + g4], a1 = krow[8 + g4], b1 = krow[12 + g4];
-          k0 = uint4v{a0[0], a0[1], b0[0], b0[1]};
-          k1 = uint4v{a1[0], a1[1], b1[0], b1[1]};
-        }
-        if (g4 == (slot >> 2)) {                             // V: byte rr of every word is the new token's channel
-          const unsigned keep = ~(0xffu << (8 * rr));
+      const uint4v* krow = (const uint4v*)stage;          // K[0..64) as 8 pieces of 8 channels
+      const unsigned short* vrow = (const unsigned short*)(stage + 32);
+      if (col == slot) {                                   // K: 8 channels of the new token per k-step
+        k0 = krow[g4];
+        k1 = krow[4 + g4];
+      }
+      if (g4 == (slot >> 2)) {                             // V: this lane holds tokens 4*g4..+3 of 4 channels
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            v0[w] = (v0[w] & keep) | ((unsigned)vrow[16 * w + col] << (8 * rr));
-            v1[w] = (v1[w] & keep) | ((unsigned)vrow[64 + 16 * w + col] << (8 * rr));
-          }
-        }
-      } else {
-        const uint4v* krow = (const uint4v*)stage;          // K[0..64) as 8 pieces of 8 channels
-        const unsigned short* vrow = (const unsigned short*)(stage + 32);
-        if (col == slot) {                                   // K: 8 channels of the new token per k-step
-          k0 = krow[g4];
-          k1 = krow[4 + g4];
-        }
-        if (g4 == (slot >> 2)) {                             // V: this lane holds tokens 4*g4..+3 of 4 channels
-#pragma unroll
-          for (int k = 0; k < 4; ++k) insert_v_group(k < 2 ? v0 : v1, k & 1, rr, vrow[16 * k + col]);
-        }
+        for (int k = 0; k < 4; ++k) insert_v_group(k < 2 ? v0 : v1, k & 1, rr, vrow[16 * k + col]);
       }
       if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
         uint4v* kq = (uint4v*)(rec + 8);
@@ -939,6 +924,40 @@ decode_stream_kernel(StreamArgs a) {
       kk[NL / 2 + 1] = second ? k1 : kk[NL / 2 + 1];
       vv[NL / 2] = second ? v0 : vv[NL / 2];
       vv[NL / 2 + 1] = second ? v1 : vv[NL / 2 + 1];
+    };
+    // fp8: the same, through a reference; k0, k1 / v0, v1 are the pieces of the block that holds the token.
+    auto patch_fp8 = [&](int* rec, int slot, bf16x8& k0, bf16x8& k1, bf16x8& v0, bf16x8& v1) {
+      const int rr = slot & 3;
+      unsigned* stage = (unsigned*)(rec + REC_V);
+      stage[lane] = newrow[0];
+      const uint2v* krow = (const uint2v*)stage;            // K[0..128) as 16 pieces of 8 bytes
+      const unsigned char* vrow = (const unsigned char*)(stage + 32);
+      if (col == slot) {                                     // K: per 64-channel half, 8 channels of each of its two k-steps
+        const uint2v a0 = krow[g4], b0 = krow[4 + g4], a1 = krow[8 + g4], b1 = krow[12 + g4];
+        k0 = __builtin_bit_cast(bf16x8, uint4v{a0[0], a0[1], b0[0], b0[1]});
+        k1 = __builtin_bit_cast(bf16x8, uint4v{a1[0], a1[1], b1[0], b1[1]});
+      }
+      if (g4 == (slot >> 2)) {                               // V: byte rr of every word is the new token's channel
+        uint4v w0 = __builtin_bit_cast(uint4v, v0), w1 = __builtin_bit_cast(uint4v, v1);
+        const unsigned keep = ~(0xffu << (8 * rr));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          w0[w] = (w0[w] & keep) | ((unsigned)vrow[16 * w + col] << (8 * rr));
+          w1[w] = (w1[w] & keep) | ((unsigned)vrow[64 + 16 * w + col] << (8 * rr));
+        }
+        v0 = __builtin_bit_cast(bf16x8, w0);
+        v1 = __builtin_bit_cast(bf16x8, w1);
+      }
+      if ((col >> 1) == (slot >> 1)) {                       // K pieces of the token pair, patched
+        bf16x8* kq = (bf16x8*)(rec + 8);
+        kq[g4 * 2 + (col & 1)] = k0;
+        kq[(4 + g4) * 2 + (col & 1)] = k1;
+      }
+      if (g4 == (slot >> 2)) {                               // V pieces of the token quad, patched
+        bf16x8* vq = (bf16x8*)(rec + REC_V);
+        vq[col] = v0;
+        vq[16 + col] = v1;
+      }
     };
     // Wide formats: the same for a block of NP pieces.
     auto patch_wide = [&](int* rec, int slot, uint4v* kk, uint4v* vv) {
@@ -974,7 +993,7 @@ decode_stream_kernel(StreamArgs a) {
         for (int j = 0; j < NP; ++j) ((uint4v*)(rec + REC_V))[j * 16 + col] = vv[j];
       }
     };
-    auto patch_and_store = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
+    auto patch_and_store = [&](Piece (&kk)[NL], Piece (&vv)[NL]) {
       const int slot = (cc.len - 1) & (BLK - 1), rr = slot & 3;
       lookup_block(cc);                                      // the compute cursor looks its block up only here
       const bool second = TWO && (((cc.len - 1) / BLK) & 1);  // 32-token tiles: the token sits in the tile's second block
@@ -1006,6 +1025,9 @@ decode_stream_kernel(StreamArgs a) {
         } else {
           patch_wide(rec, slot, kk, vv);
         }
+      } else if constexpr (FP8) {
+        if (second) patch_fp8(rec, slot, kk[2], kk[3], vv[2], vv[3]);
+        else patch_fp8(rec, slot, kk[0], kk[1], vv[0], vv[1]);
       } else if constexpr (TWO) {
         patch_two(rec, slot, second, kk, vv);
       } else {
@@ -1040,7 +1062,7 @@ decode_stream_kernel(StreamArgs a) {
     // low E4M3 part as well; O^T += V^T P^T contracts over all 32 tokens in one mfma per d-tile and
     // part, the operand of lane (., g4) holding tokens 4 g4 .. 4 g4 + 3 of block 0, then of block 1,
     // which is the order the pool's V block format and the S^T accumulator layout both give.
-    auto compute_fp8 = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
+    auto compute_fp8 = [&](Piece (&kk)[NL], Piece (&vv)[NL]) {
       typedef long long2v __attribute__((ext_vector_type(2)));
       const int n_valid = cc.len - cc.t * TT;               // tokens of this tile in range (>= 32: all)
       const bool ragged = n_valid < TT;
@@ -1104,8 +1126,8 @@ decode_stream_kernel(StreamArgs a) {
       }
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) {
-        const unsigned w0 = vv[dt >> 2][dt & 3] & keep0;
-        const unsigned w1 = vv[2 + (dt >> 2)][dt & 3] & keep1;
+        const unsigned w0 = __builtin_bit_cast(uint4v, vv[dt >> 2])[dt & 3] & keep0;
+        const unsigned w1 = __builtin_bit_cast(uint4v, vv[2 + (dt >> 2)])[dt & 3] & keep1;
         const long av = (long)w0 | ((long)w1 << 32);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(av, phi, O[dt], 0, 0, 0);
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(av, plo, O[dt], 0, 0, 0);
@@ -1280,7 +1302,7 @@ decode_stream_kernel(StreamArgs a) {
       lsum += psum;
     };
 
-    auto compute = [&](uint4v (&kk)[NL], uint4v (&vv)[NL]) {
+    auto compute = [&](Piece (&kk)[NL], Piece (&vv)[NL]) {
       if constexpr (WIDE) {
         compute_wide(kk, vv);
       } else if constexpr (FP8) {
