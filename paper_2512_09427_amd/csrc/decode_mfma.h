@@ -215,9 +215,18 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
 // by a few microseconds instead.  A planning call, before and after: one request of 1 777 tokens 16.0 -> 12.7 us; 64
 // requests, 46 587 tokens 30.4 -> 25.9 us; 256 requests, 159 203 tokens 69.5 -> 64.6 us.  Beyond STREAM_INLINE_REQ requests
 // a thread would scan more than four of them and the table would pass 20 KiB of LDS: there the launch of its own stays.
+// With one wave per SIMD every instruction in front of the first tile costs 2 ns, so what the plan takes is its number of
+// instructions: only the wave's range stands in front of the loads, entries are 16-byte words, and the cuts (both boundaries
+// at once, one per half of the wave, work-groups found in closed form) follow under the first tile's latency, where they used
+// to stand behind the last tile.  The same three calls 12.4 -> 10.9, 23.8 -> 21.4, 63.4 -> 61.8; 1 000 requests 39.1 -> 34.5.
 // ---------------------------------------------------------------------------------
 constexpr int STREAM_INLINE_REQ = 1024;
 constexpr int STREAM_INLINE_WG = 512;
+// Up to this many requests every wave scans the batch by itself, two per lane, and writes the whole table (all waves the same
+// words): no barrier stands between the lengths' arrival and the wave's range.  Scanned by the work-group together -> by every
+// wave: one request of 1777 tokens 11.35 -> 11.1 us, 64 (46 587 tokens) 22.0 -> 21.6, 128 paged 65.2 -> 65.3; four per lane
+// is longer, 256 requests 62.0 -> 62.3, 153 in a fused fp8 step 16.9 -> 17.05.
+constexpr int STREAM_WAVE_REQ = 128;
 // A batch with no more (request, KV head) segments than work-groups is cut at its segments instead -- one work-group each,
 // whose waves heal the cuts between them in LDS -- if that gives no wave more than STREAM_MERGE_TILES tiles beyond an equal
 // share: nothing is left to merge through memory then (store, acknowledgement, counter, partial loads, all behind the last
@@ -225,39 +234,48 @@ constexpr int STREAM_INLINE_WG = 512;
 // tokens 13.3 -> 9.9 us, 60 of them 14.0 -> 10.4, 60 of 400 to 533 tokens 20.5 -> 16.2; but one of 900 tokens, where the
 // equal shares are a sixth of a segment's, 13.5 -> 16.0: it keeps equal shares.
 constexpr int STREAM_MERGE_TILES = 5;
-struct InlinePlan {          // LDS table: SoA over the non-empty requests, in batch order
-  int* wave_tot;             // [3 * waves]: tiles, entries, longest request per wave
-  int* info;                 // total tiles, entries, waves used, whether work-groups take whole segments
-  int* wg_pos;               // [n_wg + 1] first tile of every work-group
+typedef int int4v __attribute__((ext_vector_type(4)));
+struct InlinePlan {          // LDS table over the non-empty requests, in batch order; 16-byte aligned, a multiple of four ints
+  int4v* wave_tot;           // [waves]: tiles, entries, longest request of each wave's part of the batch
+  int4v* cuts;               // [2 * waves]: every wave's copy of the segments cut at the work-group's two boundaries (ReduceDesc)
+  int4v* entry;              // [n] request, tiles, tokens, base block
   int* first;                // [n] first tile of the entry
-  int* r;
-  int* tiles;
-  int* len;
-  int* base_block;
-  int* wave_desc;            // [waves][12]: the waves' descriptors, stored at the end
-  __device__ InlinePlan(float* lds, int at, int wpw, int n_wg, int n) {
-    wave_tot = (int*)lds + at;
-    info = wave_tot + 3 * wpw;
-    wave_desc = info + 4;
-    wg_pos = wave_desc + 12 * wpw;
-    first = wg_pos + n_wg + 1;
-    r = first + n;
-    tiles = r + n;
-    len = tiles + n;
-    base_block = len + n;
+  int* wg_pos;               // [n_wg] first tile of every work-group (unequal shares only)
+  __device__ InlinePlan(float* lds, int at, int wpw, int n) {
+    wave_tot = (int4v*)((int*)lds + at);
+    cuts = wave_tot + wpw;
+    entry = cuts + 2 * wpw;
+    first = (int*)(entry + n);
+    wg_pos = first + ((n + 3) & ~3);
   }
 };
-__host__ __device__ inline int stream_inline_ints(int wpw, int n_wg, int n) { return 15 * wpw + 4 + n_wg + 1 + 5 * n; }
+__host__ __device__ inline int stream_inline_ints(int wpw, int n_wg, int n) {
+  return 12 * wpw + 4 * n + ((n + 3) & ~3) + ((n_wg + 3) & ~3);
+}
+struct InlineTotals {        // what the scan gives every wave (wave-uniform)
+  int total, n_entries;      // tiles and non-empty requests of the batch
+  bool whole;                // work-group b takes segment b as a whole
+  odma_plan::StreamShares shares;   // otherwise: its range of the tile stream
+};
 
-// number of leading elements of the non-decreasing table tab[0 .. n) that are <= x (wave-uniform x)
+// Number of leading elements of the non-decreasing table tab[0 .. n) that are <= x, four per lane and round.  The lanes of a
+// group of LANES (64 or 32) ask for one x; every lane gets its group's answer.
+template <int LANES>
 __device__ __forceinline__ int count_le(const int* tab, int n, int x) {
   const int lane = threadIdx.x & 63;
   int cnt = 0;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const bool le = i0 + lane < n && tab[min(i0 + lane, n - 1)] <= x;
-    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
-    cnt += c;
-    if (c < 64) break;
+  for (int i0 = 0; i0 < n; i0 += 4 * LANES) {
+    const int i = i0 + 4 * (lane & (LANES - 1));
+    const int4v t = *(const int4v*)(tab + min(i, (n - 1) & ~3));
+    int lo = 0, hi = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned long long le = __builtin_amdgcn_ballot_w64(i + k < n && t[k] <= x);
+      lo += __builtin_popcount((unsigned)le);
+      hi += __builtin_popcount((unsigned)(le >> 32));
+    }
+    cnt += LANES == 64 ? lo + hi : lane < 32 ? lo : hi;
+    if ((LANES == 64 ? lo + hi : max(lo, hi)) < 4 * LANES) break;
   }
   return cnt;
 }
@@ -267,188 +285,185 @@ template <int CTRL, int ROWS>
 __device__ __forceinline__ int dpp_or_zero(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
 }
-// one step of a wave's inclusive scans of two sums and a maximum (>= 0): row shifts inside 16 lanes, then the last lane of
+// one step of a wave's inclusive scans of a sum and a maximum (>= 0): row shifts inside 16 lanes, then the last lane of
 // a row (0x142) or of two (0x143) to the rows behind it.  Six steps of vector arithmetic; through LDS permutes
 // (__shfl_up) each step is a dependent round trip, and the scan stands in front of the first tile of every launch: 0.3 us
 // of each (4 fp32 requests of 16 to 128 tokens 9.2 -> 8.9 us, one of 1777 tokens in bf16 13.3 -> 13.05, 60 of up to 500
 // 16.25 -> 15.9).
 template <int CTRL, int ROWS>
-__device__ __forceinline__ void scan_step(int& sum, int& cnt, int& top) {
+__device__ __forceinline__ void scan_step(int& sum, int& top) {
   sum += dpp_or_zero<CTRL, ROWS>(sum);
-  cnt += dpp_or_zero<CTRL, ROWS>(cnt);
   top = max(top, dpp_or_zero<CTRL, ROWS>(top));
 }
 
-template <int WPW, int TT>
-__device__ __forceinline__ void plan_in_block(const StreamArgs& a, const InlinePlan& pl) {
-  constexpr int T = 64 * WPW, PER = STREAM_INLINE_REQ / T;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n = a.n, n_wg = gridDim.x;
-  const int per = (n + T - 1) / T, r0 = min(tid * per, n), r1 = min(r0 + per, n);
+// One group of threads scans the batch into the table: the whole work-group (WAVES = WPW), or a wave for itself (WAVES = 1).
+struct InlineScan {
+  int sum_tiles, n_entries, top;
+};
+template <int WAVES, int PER, int TT>
+__device__ __forceinline__ InlineScan scan_batch(const StreamArgs& a, const InlinePlan& pl) {
+  constexpr int T = 64 * WAVES;
+  const int tid = threadIdx.x & (T - 1), lane = tid & 63, wv = tid >> 6;
+  const int n = a.n, per = (n + T - 1) / T, r0 = tid * per;   // (per: the same for every thread, rounds past it are branched over)
   int ln[PER], base[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const bool in = r0 + k < r1;
-    ln[k] = in ? a.lengths[r0 + k] : 0;
-    base[k] = in && a.offsets ? (int)(a.offsets[r0 + k] / BLK) : 0;
+    ln[k] = base[k] = 0;
+    if (k < per) {
+      const int r = min(r0 + k, n - 1);
+      ln[k] = a.lengths[r];
+      if (a.offsets) base[k] = (int)((unsigned long long)a.offsets[r] / BLK);
+    }
   }
-  int loc_tiles = 0, loc_cnt = 0, longest = 0;
+  int loc_tiles = 0, longest = 0, run_cnt = 0, wave_cnt = 0;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    ln[k] = max(ln[k], 0);
-    loc_tiles += (ln[k] + TT - 1) / TT;
-    loc_cnt += ln[k] > 0;
-    longest = max(longest, (ln[k] + TT - 1) / TT);
-  }
-  int inc_tiles = loc_tiles, inc_cnt = loc_cnt;
-  scan_step<0x111, 0xf>(inc_tiles, inc_cnt, longest);
-  scan_step<0x112, 0xf>(inc_tiles, inc_cnt, longest);
-  scan_step<0x114, 0xf>(inc_tiles, inc_cnt, longest);
-  scan_step<0x118, 0xf>(inc_tiles, inc_cnt, longest);
-  scan_step<0x142, 0xa>(inc_tiles, inc_cnt, longest);
-  scan_step<0x143, 0xc>(inc_tiles, inc_cnt, longest);
-  if (lane == 63) {                                        // (the wave's sums and maximum)
-    pl.wave_tot[3 * wv] = inc_tiles;
-    pl.wave_tot[3 * wv + 1] = inc_cnt;
-    pl.wave_tot[3 * wv + 2] = longest;
-  }
-  __syncthreads();
-  int run_tiles = inc_tiles - loc_tiles, run_cnt = inc_cnt - loc_cnt, sum_tiles = 0, n_entries = 0;
+  for (int k = 0; k < PER; ++k)
+    if (k < per) {
+      ln[k] = r0 + k < n ? max(ln[k], 0) : 0;
+      const int tiles = (int)((unsigned)(ln[k] + TT - 1) / TT);
+      loc_tiles += tiles;
+      longest = max(longest, tiles);
+      // entries of the lanes below, and of the wave
+      const unsigned long long held = __builtin_amdgcn_ballot_w64(ln[k] > 0);
+      run_cnt += __builtin_amdgcn_mbcnt_hi((unsigned)(held >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)held, 0u));
+      wave_cnt += __builtin_popcountll(held);
+    }
+  int inc_tiles = loc_tiles;
+  scan_step<0x111, 0xf>(inc_tiles, longest);
+  scan_step<0x112, 0xf>(inc_tiles, longest);
+  scan_step<0x114, 0xf>(inc_tiles, longest);
+  scan_step<0x118, 0xf>(inc_tiles, longest);
+  scan_step<0x142, 0xa>(inc_tiles, longest);
+  scan_step<0x143, 0xc>(inc_tiles, longest);
+  InlineScan sc = {__builtin_amdgcn_readlane(inc_tiles, 63), wave_cnt, __builtin_amdgcn_readlane(longest, 63)};
+  int run_tiles = inc_tiles - loc_tiles;
+  if constexpr (WAVES > 1) {
+    if (lane == 0) pl.wave_tot[wv] = int4v{sc.sum_tiles, sc.n_entries, sc.top, 0};
+    __syncthreads();
+    sc = InlineScan{0, 0, 0};
 #pragma unroll
-  for (int i = 0; i < WPW; ++i) {
-    const int t = pl.wave_tot[3 * i], c = pl.wave_tot[3 * i + 1];
-    longest = max(longest, pl.wave_tot[3 * i + 2]);
-    run_tiles += i < wv ? t : 0;
-    run_cnt += i < wv ? c : 0;
-    sum_tiles += t;
-    n_entries += c;
+    for (int i = 0; i < WAVES; ++i) {
+      const int4v t = pl.wave_tot[i];
+      sc.top = max(sc.top, rfl(t[2]));
+      run_tiles += i < wv ? t[0] : 0;
+      run_cnt += i < wv ? t[1] : 0;
+      sc.sum_tiles += rfl(t[0]);
+      sc.n_entries += rfl(t[1]);
+    }
   }
 #pragma unroll
   for (int k = 0; k < PER; ++k)
-    if (ln[k] > 0) {
-      const int tiles = (ln[k] + TT - 1) / TT;
+    if (k < per && ln[k] > 0) {
+      const int tiles = (int)((unsigned)(ln[k] + TT - 1) / TT);
       pl.first[run_cnt] = run_tiles * a.Hkv;
-      pl.r[run_cnt] = r0 + k;
-      pl.tiles[run_cnt] = tiles;
-      pl.len[run_cnt] = ln[k];
-      pl.base_block[run_cnt] = base[k];
+      pl.entry[run_cnt] = int4v{r0 + k, tiles, ln[k], base[k]};
       ++run_cnt;
       run_tiles += tiles;
     }
-  const int total = sum_tiles * a.Hkv;
-  const odma_plan::StreamShares shares =
-      odma_plan::stream_shares(total, n_wg * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
-  const int n_seg = n_entries * a.Hkv;
-  const bool whole = a.whole_extra >= 0 && n_seg <= n_wg &&
-                     (long long)longest * shares.used <= WPW * (total + (long long)a.whole_extra * shares.used);
-  if (!whole)
-    for (int b = tid; b <= n_wg; b += T) pl.wg_pos[b] = shares.start(b * WPW);
-  if (tid == 0) {
-    pl.info[0] = total;
-    pl.info[1] = n_entries;
-    pl.info[2] = whole ? n_seg * WPW : shares.used;
-    pl.info[3] = whole;
-  }
-  __syncthreads();
-  if (whole)                                               // (read in the epilogue, behind the next barrier)
-    for (int b = tid; b <= n_wg; b += T) {
-      const int e = b / a.Hkv;
-      pl.wg_pos[b] = b < n_seg ? pl.first[e] + (b - e * a.Hkv) * pl.tiles[e] : total;
-    }
+  return sc;
+}
+
+template <int WPW, int TT>
+__device__ __forceinline__ InlineTotals plan_in_block(const StreamArgs& a, const InlinePlan& pl) {
+  constexpr int T = 64 * WPW;
+  const int n_wg = gridDim.x;
+  const bool alone = a.n <= STREAM_WAVE_REQ;
+  const InlineScan sc = alone ? scan_batch<1, STREAM_WAVE_REQ / 64, TT>(a, pl) : scan_batch<WPW, STREAM_INLINE_REQ / T, TT>(a, pl);
+  InlineTotals t;
+  t.total = sc.sum_tiles * a.Hkv;
+  t.n_entries = sc.n_entries;
+  t.shares = odma_plan::stream_shares(t.total, n_wg * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
+  t.whole = a.whole_extra >= 0 && sc.n_entries * a.Hkv <= n_wg &&
+            (long long)sc.top * t.shares.used <= WPW * (t.total + (long long)a.whole_extra * t.shares.used);
+  if (__builtin_expect(!t.shares.equal(), 0))                // (read behind the barrier in front of the tile stream)
+    for (int b = threadIdx.x; b < n_wg; b += T) pl.wg_pos[b] = t.shares.start(b * WPW);
+  if (!alone) __syncthreads();
+  return t;
 }
 
 // this wave's range and its first entry
 template <int WPW>
-__device__ __forceinline__ WaveDesc inline_wave_desc(const StreamArgs& a, const InlinePlan& pl) {
+__device__ __forceinline__ WaveDesc inline_wave_desc(const StreamArgs& a, const InlinePlan& pl, const InlineTotals& t) {
   const int lane = threadIdx.x & 63, wv = rfl(threadIdx.x >> 6);
-  const int total = rfl(pl.info[0]), n_entries = rfl(pl.info[1]);
   WaveDesc wd;
   wd.entry0 = 0;
-  wd.n_entries = n_entries;
+  wd.n_entries = t.n_entries;
   wd.r = wd.tiles = wd.first_pos = wd.len = wd.base_block = wd.r_next = wd.pad1 = wd.pad2 = 0;
   int e = 0;
-  if (rfl(pl.info[3])) {
+  if (t.whole) {
     // segment b, its tiles in equal parts; with fewer tiles than waves the empty parts on the left (see StreamShares)
     const int seg = blockIdx.x;
-    wd.pos_start = wd.pos_end = total;
-    if (seg < n_entries * a.Hkv) {
+    wd.pos_start = wd.pos_end = t.total;
+    if (seg < t.n_entries * a.Hkv) {
       e = seg / a.Hkv;
-      const int t = rfl(pl.tiles[e]), at = rfl(pl.first[e]) + (seg - e * a.Hkv) * t;
-      wd.pos_start = at + (t < WPW ? max(t - (WPW - wv), 0) : t * wv / WPW);
-      wd.pos_end = at + (t < WPW ? max(t - (WPW - wv - 1), 0) : t * (wv + 1) / WPW);
+      const int n = rfl(pl.entry[e][1]), at = rfl(pl.first[e]) + (seg - e * a.Hkv) * n;
+      wd.pos_start = at + (n < WPW ? max(n - (WPW - wv), 0) : n * wv / WPW);
+      wd.pos_end = at + (n < WPW ? max(n - (WPW - wv - 1), 0) : n * (wv + 1) / WPW);
     }
   } else {
-    const odma_plan::StreamShares shares =
-        odma_plan::stream_shares(total, gridDim.x * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
-    const int at = shares.start(blockIdx.x * WPW + wv + (lane & 1));   // even lanes: the start, odd lanes: the end
+    const int at = t.shares.start(blockIdx.x * WPW + wv + (lane & 1));   // even lanes: the start, odd lanes: the end
     wd.pos_start = __builtin_amdgcn_readlane(at, 0);
     wd.pos_end = __builtin_amdgcn_readlane(at, 1);
-    if (wd.pos_start < wd.pos_end) e = count_le(pl.first, n_entries, wd.pos_start) - 1;
+    if (wd.pos_start < wd.pos_end) e = rfl(count_le<64>(pl.first, t.n_entries, wd.pos_start)) - 1;
   }
   if (wd.pos_start < wd.pos_end) {
+    const int4v en = pl.entry[e];
     wd.entry0 = e;
-    wd.r = rfl(pl.r[e]);
-    wd.tiles = rfl(pl.tiles[e]);
+    wd.r = rfl(en[0]);
+    wd.tiles = rfl(en[1]);
     wd.first_pos = rfl(pl.first[e]);
-    wd.len = rfl(pl.len[e]);
-    wd.base_block = rfl(pl.base_block[e]);
-    wd.r_next = rfl(pl.r[min(e + 1, n_entries - 1)]);
-  }
-  if (lane == 0) {
-    int* o = pl.wave_desc + 12 * wv;
-    o[0] = wd.pos_start;
-    o[1] = wd.pos_end;
-    o[2] = wd.entry0;
-    o[3] = wd.n_entries;
-    o[4] = wd.r;
-    o[5] = wd.tiles;
-    o[6] = wd.first_pos;
-    o[7] = wd.len;
-    o[8] = wd.base_block;
-    o[9] = wd.r_next;
-    o[10] = o[11] = 0;
+    wd.len = rfl(en[2]);
+    wd.base_block = rfl(en[3]);
+    wd.r_next = rfl(pl.entry[min(e + 1, t.n_entries - 1)][0]);
   }
   return wd;
 }
 
-// the segment cut by the boundary in front of work-group b (wave-uniform; the same rule as in stream_plan_kernel)
+// The segments cut by the boundaries in front of work-groups b (lanes 0 .. 31) and b + 1 (lanes 32 .. 63), the same rule as in
+// stream_plan_kernel: a wave has nothing to do beside it, so the two cost as much time as one.
 template <int WPW>
-__device__ __forceinline__ ReduceDesc inline_cut(const InlinePlan& pl, int b, int n_wg) {
-  ReduceDesc rd = {0, 0, 0, 0};
-  const int total = rfl(pl.info[0]), n_entries = rfl(pl.info[1]), used_wg = rfl(pl.info[2]) / WPW;
-  const int bpos = rfl(pl.wg_pos[b]);
-  if (b > 0 && b < n_wg && bpos < total) {
-    const int e = count_le(pl.first, n_entries, bpos) - 1;
-    const int first = rfl(pl.first[e]), tiles = rfl(pl.tiles[e]);
-    const int g = (bpos - first) / tiles, start = first + g * tiles;
-    if (start < bpos) {
-      rd.b0 = count_le(pl.wg_pos, used_wg, start) - 1;
-      rd.n_parts = count_le(pl.wg_pos, used_wg, start + tiles - 1) - rd.b0;
-      rd.r = rfl(pl.r[e]);
-      rd.g = g;
-    }
+__device__ __forceinline__ int4v inline_cuts(const InlinePlan& pl, const InlineTotals& t, int b, int n_wg) {
+  const int mine = b + ((threadIdx.x & 63) >> 5);
+  int4v rd = {0, 0, 0, 0};                                   // (a ReduceDesc)
+  if (t.whole || t.total == 0) return rd;
+  const bool inner = mine > 0 && mine < n_wg;
+  const int pos = t.shares.start(mine * WPW);
+  const bool in = inner && pos < t.total;
+  const int e = max(count_le<32>(pl.first, t.n_entries, in ? pos : 0) - 1, 0);
+  const int first = pl.first[e];
+  const int4v en = pl.entry[e];
+  const int g = (int)((unsigned)((in ? pos : 0) - first) / (unsigned)en[1]), start = first + g * en[1], last = start + en[1] - 1;
+  int b0, b1;
+  if (__builtin_expect(t.shares.equal(), 1)) {
+    b0 = t.shares.wave_of(start) / WPW;
+    b1 = t.shares.wave_of(last) / WPW;
+  } else {
+    b0 = count_le<32>(pl.wg_pos, t.shares.used / WPW, start) - 1;
+    b1 = count_le<32>(pl.wg_pos, t.shares.used / WPW, last) - 1;
   }
+  if (in && start < pos) rd = int4v{b1 - b0 + 1, en[0], g, b0};
   return rd;
 }
 
 // the records that stream_plan_kernel would have left, for calls that reuse the plan
 template <int WPW>
-__device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const InlinePlan& pl, const ReduceDesc& rd) {
+__device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const InlinePlan& pl, const WaveDesc& wd, int4v cut) {
   constexpr int T = 64 * WPW;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane < 12) ((int*)&a.waves[blockIdx.x * WPW + wv])[lane] = pl.wave_desc[12 * wv + lane];
+  if (lane == 0) a.waves[blockIdx.x * WPW + wv] = wd;
   if (threadIdx.x == 0) {
-    a.red[blockIdx.x] = rd;
+    *(int4v*)&a.red[blockIdx.x] = cut;
     if (blockIdx.x == gridDim.x - 1) a.red[gridDim.x] = ReduceDesc{0, 0, 0, 0};
   }
-  const int n_entries = pl.info[1];
+  const int n_entries = wd.n_entries;
   for (int i = blockIdx.x * T + threadIdx.x; i < n_entries; i += gridDim.x * T) {
+    const int4v en = pl.entry[i];
     StreamEntry e;
-    e.r = pl.r[i];
-    e.tiles = pl.tiles[i];
+    e.r = en[0];
+    e.tiles = en[1];
     e.first_pos = pl.first[i];
-    e.len = pl.len[i];
-    e.base_block = pl.base_block[i];
+    e.len = en[2];
+    e.base_block = en[3];
     e.pad0 = e.pad1 = e.pad2 = 0;
     a.entries[i] = e;
   }
@@ -587,14 +602,15 @@ decode_stream_kernel(StreamArgs a) {
   constexpr int BLOCK_BYTES = BLK * HD * F.eb;             // one pool block of K (or V)
 
   // the wave's range first: everything else waits for it
-  const InlinePlan pl(lds, a.plan_at, WPW, gridDim.x, a.n);
+  const InlinePlan pl(lds, a.plan_at, WPW, a.n);
+  InlineTotals totals;
   WaveDesc wd;
   // in-kernel merge: the segments cut at this work-group's two boundaries, requested now so that the
-  // epilogue does not wait for them (a launch that plans finds them in LDS while its last stores are under way)
+  // epilogue does not wait for them (a launch that plans derives them under its first tiles' loads)
   ReduceDesc rd_cut[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   if constexpr (PLAN) {
-    plan_in_block<WPW, TT>(a, pl);
-    wd = inline_wave_desc<WPW>(a, pl);
+    totals = plan_in_block<WPW, TT>(a, pl);
+    wd = inline_wave_desc<WPW>(a, pl, totals);
   } else {
     wd = a.waves[blockIdx.x * WPW + rfl(wv)];
     if (a.fuse_reduce) {
@@ -614,6 +630,15 @@ decode_stream_kernel(StreamArgs a) {
   if (lane == 0) flag_set(2 * wv, 0);
   __syncthreads();
 
+  // A launch that plans derives the cuts and leaves its records while the first tiles are on their way (behind the last tile,
+  // where everything waits for it, this was 1.5 to 2.5 us).  Every wave keeps the cuts in LDS until its end: eight scalar
+  // registers held over the tile loop would be spilled.
+  auto settle_plan = [&]() {
+    const int4v cut = inline_cuts<WPW>(pl, totals, blockIdx.x, gridDim.x);
+    if ((lane & 31) == 0) pl.cuts[2 * wv + (lane >> 5)] = cut;
+    store_inline_plan<WPW>(a, pl, wd, cut);
+  };
+  if (PLAN && n_my <= 0) settle_plan();
   if (n_my > 0) {
     const char* kbase = a.k + lane * 16;
     const char* vbase = a.v + lane * (F32 ? 32 : 16);
@@ -621,11 +646,12 @@ decode_stream_kernel(StreamArgs a) {
     auto load_window = [&](Window& w, int e_base) {
       const int idx = min(e_base + lane, n_entries - 1);
       if constexpr (PLAN) {
-        w.r = pl.r[idx];
-        w.tiles = pl.tiles[idx];
-        w.len = pl.len[idx];
-        w.base_block = pl.base_block[idx];
-        w.r_next = pl.r[min(idx + 1, n_entries - 1)];
+        const int4v en = pl.entry[idx];
+        w.r = en[0];
+        w.tiles = en[1];
+        w.len = en[2];
+        w.base_block = en[3];
+        w.r_next = pl.entry[min(idx + 1, n_entries - 1)][0];
         return;
       }
       const int4 lo = *(const int4*)&a.entries[idx];
@@ -765,6 +791,7 @@ decode_stream_kernel(StreamArgs a) {
         --p_left;
       }
     }
+    if constexpr (PLAN) settle_plan();
     // fp8 storage: the queries go to the matrix cores as fp8 too.  Each query row is scaled by a
     // power of two that brings its largest magnitude into [128, 256) and split into a high and a
     // low E4M3 part (together about 8 significant bits); the inverse scale joins the softmax scale.
@@ -1562,12 +1589,6 @@ decode_stream_kernel(StreamArgs a) {
 #endif
   }
 
-  if constexpr (PLAN) {
-    rd_cut[0] = inline_cut<WPW>(pl, blockIdx.x, gridDim.x);
-    rd_cut[1] = inline_cut<WPW>(pl, blockIdx.x + 1, gridDim.x);
-    store_inline_plan<WPW>(a, pl, rd_cut[0]);
-  }
-
   // Outputs of empty requests are zeros: thread i of the grid looks after request i, i + grid size, ...
   for (int r = r_mine; r < a.n; r += gridDim.x * (64 * WPW)) {
     if ((r == r_mine ? len_mine : a.lengths[r]) <= 0) {
@@ -1604,6 +1625,13 @@ decode_stream_kernel(StreamArgs a) {
   // barrier, and the merging work-group reads the partials with agent-scope loads after it has
   // seen the full count.
   const int b = blockIdx.x;
+  if constexpr (PLAN) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int4v c = pl.cuts[2 * wv + i];
+      rd_cut[i] = ReduceDesc{rfl(c[0]), rfl(c[1]), rfl(c[2]), rfl(c[3])};
+    }
+  }
   // a work-group whose range begins and ends on segment boundaries has written no partial and counts in nowhere:
   // its waves leave as they finish (the descriptors are the same for every wave, so all of them take this exit)
   if (rd_cut[0].n_parts == 0 && !(rd_cut[1].n_parts > 0 && rd_cut[1].b0 == b)) {

@@ -86,14 +86,22 @@ struct StreamShares {
     const long long in_wg = (long long)early * s_early + (long long)late * s_late;
     return ((long long)(b >> 3) * per8 + pre) * s_wg + ((x & 1) ? w_odd : w_even) * in_wg;
   }
+  ODMA_HD bool equal() const { return w_even == w_odd && s_early == s_late; }
   ODMA_HD int start(int W) const {
     if (W >= used) return total;
     if (total < used) return total - (used - W) > 0 ? total - (used - W) : 0;
     // Equal weights: floor(total * W / used).  The product is below 2^46 and exact in a double, and a quotient that is
     // not whole lies at least 1 / used > 2^-15 under the next whole number, which rounding to 53 bits cannot reach: the
     // division (which every wave waits for when it plans) need not be a 64-bit integer one.
-    if (w_even == w_odd && s_early == s_late) return (int)((double)((long long)total * W) / (double)used);
+    if (equal()) return (int)((double)((long long)total * W) / (double)used);
     return (int)((long long)total * cum(W) / cum_all);
+  }
+  // Equal weights: the wave that holds tile pos, 0 <= pos < total.  start(W) <= pos is total * W < (pos + 1) * used, so it is
+  // floor(((pos + 1) * used - 1) / total); with half a unit more above the line the quotient lies 1 / (2 total) > 2^-32 or more
+  // from the whole numbers, which the rounding of a double under 2^15 cannot reach.
+  ODMA_HD int wave_of(int pos) const {
+    if (total < used) return used - total + pos;
+    return (int)(((double)((long long)(pos + 1) * used) - 0.5) / (double)total);
   }
 };
 
@@ -113,8 +121,7 @@ ODMA_HD inline StreamShares stream_shares(int total, int n_waves, int wpw, int q
   s.w_odd = weighted ? odd_xcd_weight >> 2 : 64;
   s.s_early = 64;
   s.s_late = weighted ? late_wave_weight >> 2 : 64;
-  s.cum_all = 1;
-  s.cum_all = s.cum(used);
+  s.cum_all = s.equal() ? 1 : s.cum(used);   // (read with unequal weights alone)
   return s;
 }
 

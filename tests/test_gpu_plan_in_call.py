@@ -39,6 +39,21 @@ def test_batch_sizes_around_the_scan_width(n, wpw):
     np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
 
 
+@pytest.mark.parametrize("odd_xcd_weight", [256, 232])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 300])
+def test_scans_by_a_wave_and_by_a_work_group(n, odd_xcd_weight):
+    """Both ways to scan the batch, with equal shares (the work-group of a tile in closed form) and unequal ones (a table)."""
+    rng = np.random.default_rng(n)
+    lens = rng.integers(0, 60, n)
+    lens[[0, n // 2, n - 1]] = [700, 5000, 33]               # (the last entry's neighbours: none behind, empty ones in between)
+    lens[n // 3:n // 3 + n // 8] = 0
+    dp, q, lens, off, ref = make(lens, seed=74, main=n * 64 + 32768)
+    dp.pool.odma_pool_tune(B.TUNE_ODD_XCD_WEIGHT, odd_xcd_weight)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    H.check(got, ref, *TIGHT_F32, what=f"n={n}")
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
+
+
 @pytest.mark.parametrize("lens", [[0], [0, 0, 0], [1], [0, 16, 0, 17, 0]])
 def test_batches_with_next_to_no_tiles(lens):
     dp, q, lens, off, ref = make(lens, seed=72, main=16384)

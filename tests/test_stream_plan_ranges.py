@@ -7,6 +7,9 @@ empty range to its right among the used waves.  These tests pin that, and the pl
 over small totals, both work-group sizes, every tile minimum and the whole range of the share weights.
 """
 import itertools
+import os
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -85,3 +88,41 @@ def test_invalid_arguments_are_refused():
             B.odma_stream_plan_ranges(*args)
     with pytest.raises(B.OdmaError):
         B.odma_stream_plan_ranges(10, 8, 4, 4, 100, 256)
+
+
+WAVE_OF = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "plan_types.h"
+int check(int total, int n_waves, int wpw, int pos) {
+  const odma_plan::StreamShares s = odma_plan::stream_shares(total, n_waves, wpw, 4, 256, 256);
+  const int w = s.wave_of(pos);
+  if (s.equal() && w >= 0 && w < s.used && s.start(w) <= pos && pos < s.start(w + 1)) return 0;
+  std::printf("total %d n_waves %d wpw %d used %d pos %d: wave %d\n", total, n_waves, wpw, s.used, pos, w);
+  return 1;
+}
+int main() {
+  int bad = 0;
+  for (int wpw = 4; wpw <= 8; wpw += 4)
+    for (int n_waves : {wpw, 3 * wpw, 1024, 4096}) {
+      for (int total = 1; total < 300; ++total)                        // every tile, fewer tiles than waves among them
+        for (int pos = 0; pos < total; ++pos) bad += check(total, n_waves, wpw, pos);
+      for (int total : {1023, 1024, 1025, 4095, 4097, 11649, 26240, 1 << 20, 0x7ffffffe, 0x7fffffff}) {
+        const odma_plan::StreamShares s = odma_plan::stream_shares(total, n_waves, wpw, 4, 256, 256);
+        for (int w = 0; w < s.used; ++w)                                 // the first and the last tile of every wave
+          for (int pos : {s.start(w), s.start(w + 1) - 1}) if (pos >= s.start(w)) bad += check(total, n_waves, wpw, pos);
+      }
+    }
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_the_wave_that_holds_a_tile(tmp_path):
+    """StreamShares::wave_of is the inverse of StreamShares::start for equal shares."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_09427_amd", "csrc")
+    (tmp_path / "t.cpp").write_text(WAVE_OF)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True, timeout=120)
+    r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:]
