@@ -12,11 +12,14 @@
 // A (request, KV head) segment that lies inside one wave's range is finished by that wave
 // and written straight to `out`.  A segment cut by a range boundary leaves un-normalised
 // partial states (m, l, O).  The waves of a work-group (4 or 8) own consecutive ranges, so
-// a cut between two of them is healed inside the work-group: the right-hand wave parks the
-// state of its first piece in LDS as soon as that piece ends, and the left-hand wave, when
-// it reaches the end of its range, folds that state into its own registers and writes the
-// result.  Waves only ever wait for their right-hand neighbour, so the chain cannot
-// deadlock and needs no barrier.  Only pieces cut by a work-group boundary go to the HBM
+// a cut between two of them is healed inside the work-group: a wave parks the state of its
+// first piece in LDS as soon as that piece ends, and the wave that holds the segment's
+// beginning (or the work-group's first wave), when it reaches the end of its range, takes
+// the pieces to its right, in order, up to the one that ends inside a range, and writes the
+// result.  Waves only ever wait for waves to their right, and a wave whose whole range lies
+// inside the segment for nobody, so the chain cannot deadlock and needs no barrier (one
+// request of 1777 tokens, four waves a piece 10.9 -> 10.0 us; folded from neighbour to
+// neighbour every hop was 0.7 us behind the last tile).  Only pieces cut by a work-group boundary go to the HBM
 // workspace (at most two per work-group) and are merged by the last work-group to arrive
 // at the segment, or by stream_reduce_kernel when the pool asks for a launch of its own.
 //
@@ -474,7 +477,7 @@ __device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const Inl
 // ---------------------------------------------------------------------------------
 
 // LDS per work-group: one hand-off slot per wave (O[G][128], m[G], l[G], padded; slot 0 unused),
-// {ready, to_end} per wave, then per wave a queue of finished pieces waiting to be written to
+// how the parked piece ends per wave (as many ints again unused), then per wave a queue of finished pieces waiting to be written to
 // global memory (qs entries of slot + 8 ints) and of appended rows (aq records of STREAM_AQ_INTS).  The host sizes
 // the queues to the tiles a wave gets: a wave that runs out of queue has to write in mid-stream.
 constexpr int STREAM_MERGE_BATCH = 16;   // most partials whose loads are in flight together in the in-kernel merge
@@ -508,6 +511,9 @@ __device__ __forceinline__ float column_sum(float x) {
   return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 constexpr float LAZY_REF_LOG2 = 8.0f;
+// How a parked piece ends: cut by the work-group's end, with its segment, or at the end of its wave's range, the next wave's
+// first piece being the next of the segment
+constexpr int PIECE_CUT = 1, PIECE_ENDS = 2, PIECE_GOES_ON = 3;   // (0: not parked yet)
 constexpr float WIDE_LAZY_REF_LOG2 = 4.0f, WIDE_WEIGHT_SCALE = 0x1p-4f;   // wide formats: slack, and the factor 2^-slack of their weights
 
 // Development builds only (-DODMA_DEV_TIMELINE): wall-clock stamps (100 MHz) per wave, read back with
@@ -588,7 +594,7 @@ decode_stream_kernel(StreamArgs a) {
   const int col = lane & 15, g4 = lane >> 4;
   const int G = a.G, Hkv = a.Hkv;
   const int slot_floats = stream_slot_floats(G, CH);
-  // [wave]{ready, to_end}; read and written with work-group-scope atomics (plain LDS instructions:
+  // [wave]: 0, or how the parked piece ends; read and written with work-group-scope atomics (plain LDS instructions:
   // a volatile access would be compiled as a FLAT one, which also waits for the tile loads in flight)
   int* flags = (int*)(lds + WPW * slot_floats);
   auto flag_set = [&](int i, int v) { __hip_atomic_store(flags + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
@@ -627,7 +633,7 @@ decode_stream_kernel(StreamArgs a) {
   // ready flags must be clear before any neighbour can look at them: a wave clears its own
   // flag first thing, and its left neighbour reads it only at the end of a whole tile range,
   // so one work-group barrier at the top settles the order
-  if (lane == 0) flag_set(2 * wv, 0);
+  if (lane == 0) flag_set(wv, 0);
   __syncthreads();
 
   // A launch that plans derives the cuts and leaves its records while the first tiles are on their way (behind the last tile,
@@ -1394,44 +1400,53 @@ decode_stream_kernel(StreamArgs a) {
     float* qbase = lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq);
     const int qstride = slot_floats + 8;
     int qn = 0;
+    // A state in LDS: O[G][CH], m[G], l[G].  The 16-byte pieces of a head's row are permuted in groups of eight by the head, so that
+    // the lanes that hold the same channels of eight heads meet different banks (in rows as they are they all meet one, and a
+    // hand-off between waves, a store and a load of a whole state behind the last tile, took 0.4 us of it).
+    const int row = col < G ? col * CH : 0;
+    const int sw[2] = {row + 4 * (g4 ^ (col & 7)), row + 4 * ((4 + g4) ^ (col & 7))};
+    auto o_at = [&](float* state, int dt) -> float4v& { return *(float4v*)(state + sw[dt & 1] + 32 * (dt >> 1)); };
+    // a finished piece's outputs, or its un-normalised state, to global memory
+    auto put = [&](int kind, int r, int g, int gslot, const float4v (&o4)[CH / 16], float m_e, float l_e) {
+      if (col >= G) return;
+      if (kind == 0) {                                       // final: normalise and write to `out`
+        const float inv = a.out_scale / l_e;
+        const int64_t o_base = ((int64_t)r * a.Hq + g * G + col) * HD + 4 * g4;
+        if (a.out_bf16) {
+          unsigned short* o = (unsigned short*)a.out + o_base;
+#pragma unroll
+          for (int dt = 0; dt < HD / 16; ++dt) {
+            uint2v pk;
+            pk[0] = (unsigned)float_to_bf16_bits(o4[dt][0] * inv) | ((unsigned)float_to_bf16_bits(o4[dt][1] * inv) << 16);
+            pk[1] = (unsigned)float_to_bf16_bits(o4[dt][2] * inv) | ((unsigned)float_to_bf16_bits(o4[dt][3] * inv) << 16);
+            __builtin_nontemporal_store(pk, (uint2v*)(o + 16 * dt));
+          }
+        } else {
+          float* o = (float*)a.out + o_base;
+#pragma unroll
+          for (int dt = 0; dt < HD / 16; ++dt) __builtin_nontemporal_store(o4[dt] * inv, (float4v*)(o + 16 * dt));
+        }
+      } else {                                               // un-normalised state to the HBM workspace
+        const int64_t pi = (int64_t)gslot * a.Hq + g * G + col;
+        float* o = a.part_o + pi * CH + 4 * g4;
+#pragma unroll
+        for (int dt = 0; dt < CH / 16; ++dt) {
+          store_pair_agent(o + 16 * dt, o4[dt][0], o4[dt][1]);
+          store_pair_agent(o + 16 * dt + 2, o4[dt][2], o4[dt][3]);
+        }
+        if (g4 == 0) store_pair_agent((float*)&a.part_ml[pi], m_e, l_e);
+      }
+    };
     auto flush_outputs = [&]() {
       for (int i = 0; i < qn; ++i) {
-        const float* e = qbase + i * qstride;
+        float* e = qbase + i * qstride;
         const int* meta = (const int*)(e + slot_floats);
         const int kind = rfl(meta[0]), r = rfl(meta[1]), g = rfl(meta[2]), gslot = rfl(meta[3]);
-        if (col < G) {
-          float4v o4[CH / 16];
+        float4v o4[CH / 16];
 #pragma unroll
-          for (int dt = 0; dt < CH / 16; ++dt) o4[dt] = *(const float4v*)(e + col * CH + 16 * dt + 4 * g4);
-          const float m_e = e[G * CH + col], l_e = e[G * CH + G + col];
-          if (kind == 0) {                                   // final: normalise and write to `out`
-            const float inv = a.out_scale / l_e;
-            const int64_t o_base = ((int64_t)r * a.Hq + g * G + col) * HD + 4 * g4;
-            if (a.out_bf16) {
-              unsigned short* o = (unsigned short*)a.out + o_base;
-#pragma unroll
-              for (int dt = 0; dt < HD / 16; ++dt) {
-                uint2v pk;
-                pk[0] = (unsigned)float_to_bf16_bits(o4[dt][0] * inv) | ((unsigned)float_to_bf16_bits(o4[dt][1] * inv) << 16);
-                pk[1] = (unsigned)float_to_bf16_bits(o4[dt][2] * inv) | ((unsigned)float_to_bf16_bits(o4[dt][3] * inv) << 16);
-                __builtin_nontemporal_store(pk, (uint2v*)(o + 16 * dt));
-              }
-            } else {
-              float* o = (float*)a.out + o_base;
-#pragma unroll
-              for (int dt = 0; dt < HD / 16; ++dt) __builtin_nontemporal_store(o4[dt] * inv, (float4v*)(o + 16 * dt));
-            }
-          } else {                                           // un-normalised state to the HBM workspace
-            const int64_t pi = (int64_t)gslot * a.Hq + g * G + col;
-            float* o = a.part_o + pi * CH + 4 * g4;
-#pragma unroll
-            for (int dt = 0; dt < CH / 16; ++dt) {
-              store_pair_agent(o + 16 * dt, o4[dt][0], o4[dt][1]);
-              store_pair_agent(o + 16 * dt + 2, o4[dt][2], o4[dt][3]);
-            }
-            if (g4 == 0) store_pair_agent((float*)&a.part_ml[pi], m_e, l_e);
-          }
-        }
+        for (int dt = 0; dt < CH / 16; ++dt) o4[dt] = o_at(e, dt);
+        const int c = col < G ? col : 0;
+        put(kind, r, g, gslot, o4, e[G * CH + c], e[G * CH + G + c]);
       }
       qn = 0;
     };
@@ -1440,7 +1455,7 @@ decode_stream_kernel(StreamArgs a) {
       float* e = qbase + qn * qstride;
       if (col < G) {
 #pragma unroll
-        for (int dt = 0; dt < CH / 16; ++dt) *(float4v*)(e + col * CH + 16 * dt + 4 * g4) = O[dt];
+        for (int dt = 0; dt < CH / 16; ++dt) o_at(e, dt) = O[dt];
         if (g4 == 0) {
           e[G * CH + col] = m;
           e[G * CH + G + col] = l_all;
@@ -1455,13 +1470,11 @@ decode_stream_kernel(StreamArgs a) {
       }
       ++qn;
     };
-    auto write_out = [&](float l_all) { enqueue(0, 0, l_all); };
-    auto write_partial = [&](int gslot, float l_all) { enqueue(1, gslot, l_all); };
-    auto park = [&](float l_all, bool to_end) {               // hand this wave's first piece to its left neighbour
+    auto park = [&](float l_all, int ends) {                  // hand this wave's first piece to its left neighbour
       float* so = lds + wv * slot_floats;
       if (col < G) {
 #pragma unroll
-        for (int dt = 0; dt < CH / 16; ++dt) *(float4v*)(so + col * CH + 16 * dt + 4 * g4) = O[dt];
+        for (int dt = 0; dt < CH / 16; ++dt) o_at(so, dt) = O[dt];
         if (g4 == 0) {
           so[G * CH + col] = m;
           so[G * CH + G + col] = l_all;
@@ -1469,42 +1482,63 @@ decode_stream_kernel(StreamArgs a) {
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0) {
-        flag_set(2 * wv + 1, to_end);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        flag_set(2 * wv, 1);
+        flag_set(wv, ends);
       }
     };
 
-    // The piece [.., cc.t] of segment (cc.r, cc.g) is finished.  `last` = it is the last tile of
-    // this wave's range.  A piece that spans its whole segment is final; otherwise it is part
-    // of a chain of pieces of neighbouring waves (see the header comment).
-    auto emit = [&](bool to_end, bool last) {
+    // The last piece of segment (cc.r, cc.g) is finished, and the wave has more to stream.  A piece that spans its whole segment
+    // is final; otherwise it belongs to a chain of pieces of neighbouring waves (see the header comment), and the wave that
+    // began it (or, for wave 0, the work-group on the left through the workspace) takes it.
+    auto emit = [&]() {
+      const float l_all = column_sum(lsum);
+      if (from_start) enqueue(0, 0, l_all);
+      else if (wv == 0) enqueue(1, 2 * blockIdx.x, l_all);
+      else park(l_all, PIECE_ENDS);
+    };
+    // The last piece of the wave's range, whose state is still in registers.
+    auto finish = [&]() {
+      bool to_end = cc.t == cc.tiles - 1;
       float l_all = column_sum(lsum);
-      if (last && !to_end && wv < WPW - 1) {
-        // the segment continues in the right-hand neighbour's range: fold its first piece in
-        while (flag_get(2 * (wv + 1)) == 0) __builtin_amdgcn_s_sleep(2);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        to_end = flag_get(2 * (wv + 1) + 1) != 0;
-        const float* so = lds + (wv + 1) * slot_floats;
+      if (!to_end && wv < WPW - 1) {
+        // the segment continues in the right-hand neighbour's range
+        if (!from_start && wv > 0) {                           // and began to the left: whoever began it takes both pieces
+          park(l_all, PIECE_GOES_ON);
+          return;
+        }
+        // take the neighbours' first pieces, up to the one that does not fill its whole range: their references first, then
+        // the outputs, each scaled once
         const int c = col < G ? col : 0;
-        const float m2 = so[G * CH + c], l2 = so[G * CH + G + c];
-        const float m_new = fmaxf(m, m2);
-        const float a1 = __builtin_amdgcn_exp2f(m - m_new), a2 = __builtin_amdgcn_exp2f(m2 - m_new);
+        const int w0 = rfl(wv) + 1;
+        float m_new = m;
+        int ends, w1 = w0;
+#pragma nounroll
+        for (;; ++w1) {
+          while ((ends = rfl(flag_get(w1))) == 0) __builtin_amdgcn_s_sleep(1);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+          m_new = fmaxf(m_new, lds[w1 * slot_floats + G * CH + c]);
+          if (ends != PIECE_GOES_ON) break;
+        }
+        const float a1 = __builtin_amdgcn_exp2f(m - m_new);
+        l_all *= a1;
 #pragma unroll
-        for (int dt = 0; dt < CH / 16; ++dt) {
-          const float4v o2 = *(const float4v*)(so + c * CH + 16 * dt + 4 * g4);
-          O[dt] = O[dt] * a1 + o2 * a2;
+        for (int dt = 0; dt < CH / 16; ++dt) O[dt] *= a1;
+#pragma nounroll
+        for (int w = w0; w <= w1; ++w) {
+          float* so = lds + w * slot_floats;
+          const float a2 = __builtin_amdgcn_exp2f(so[G * CH + c] - m_new);
+          l_all = fmaf(so[G * CH + G + c], a2, l_all);
+#pragma unroll
+          for (int dt = 0; dt < CH / 16; ++dt) {
+            O[dt] += o_at(so, dt) * a2;
+            if (LATE_Q && (dt & 1)) __builtin_amdgcn_sched_barrier(0);   // (no registers for all of the piece at once)
+          }
         }
         m = m_new;
-        l_all = l_all * a1 + l2 * a2;
+        to_end = ends == PIECE_ENDS;
       }
-      if (from_start && to_end) write_out(l_all);
-      else if (!from_start) {
-        // began before this wave's range: the left neighbour (or, for wave 0, the work-group on
-        // the left through the workspace) continues the chain
-        if (wv == 0) write_partial(2 * blockIdx.x, l_all);
-        else park(l_all, to_end);
-      } else write_partial(2 * blockIdx.x + 1, l_all);       // starts here, ends in a later work-group
+      // (past the work-group's end: its slot of the segment that starts here and ends in a later one, or that began before it)
+      if (from_start || wv == 0) put(from_start && to_end ? 0 : 1, cc.r, cc.g, 2 * blockIdx.x + (from_start ? 1 : 0), O, m, l_all);
+      else park(l_all, to_end ? PIECE_ENDS : PIECE_CUT);
     };
 
     // main loop: NBUF tiles per trip so that buffer indices are compile-time constants.
@@ -1563,8 +1597,8 @@ decode_stream_kernel(StreamArgs a) {
           if (lane == 0 && qn == a.qs && (seg_end || !more)) tl_lds[wv][7] |= 1ll << (i + u);
 #endif
 
-          if (seg_end || !more) emit(seg_end, !more);
           if (more) {
+            if (seg_end) emit();
             advance(cc, wc);
             if (seg_end) {
               if constexpr (LATE_Q) load_q(qreg, cc.r, cc.g);
@@ -1580,6 +1614,7 @@ decode_stream_kernel(StreamArgs a) {
       }
     }
     // the range is streamed: write what was queued
+    finish();
     TL_STAMP(2);
     flush_outputs();
     if (FUSED) flush_appends();

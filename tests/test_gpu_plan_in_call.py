@@ -54,6 +54,19 @@ def test_scans_by_a_wave_and_by_a_work_group(n, odd_xcd_weight):
     np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
 
 
+@pytest.mark.parametrize("wpw", [4, 8])
+@pytest.mark.parametrize("lens", [[64], [130], [176], [250], [400], [641], [1000], [300, 900], [1100, 1300, 700], [2100, 90, 2500], [6000, 500]])
+def test_pieces_of_a_segment_over_waves_and_work_groups(lens, wpw):
+    """Segments over two to all waves of a work-group, cut at none, one or both of its ends, into two, four, eight and more parts."""
+    dp, q, lens, off, ref = make(lens, seed=75, main=32768)
+    dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_WG, wpw)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    H.check(got, ref, *TIGHT_F32, what=str(lens))
+    for _ in range(3):                                       # whoever arrives last, the same bits
+        np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off), got)
+        np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
+
+
 @pytest.mark.parametrize("lens", [[0], [0, 0, 0], [1], [0, 16, 0, 17, 0]])
 def test_batches_with_next_to_no_tiles(lens):
     dp, q, lens, off, ref = make(lens, seed=72, main=16384)
