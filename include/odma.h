@@ -390,9 +390,10 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
                                           each SIMD) relative to waves 0..3, in 1/256 (128..512, default 256) */
 #define ODMA_TUNE_FUSE_REDUCE      8   /* MFMA kernel: 1 (default) merges segments cut between work-groups inside the attention
                                           launch (last work-group to arrive), 0 in a reduction launch of its own */
-#define ODMA_TUNE_PREFILL_COLUMN_TILES 9 /* prefill kernel: 16-column tiles per wave.  2 (0 = default): 128-column work items, two
-                                          work-groups per CU.  4: 256-column items, one work-group per CU (more reuse per
-                                          K/V byte, measured slower on every prompt mix tried) */
+#define ODMA_TUNE_PREFILL_COLUMN_TILES 9 /* prefill kernel: 16-column tiles per wave.  0 (default): two; calls of long prompts run
+                                          256-column work items by eight waves, the others as 2.  2: 128-column items by four
+                                          waves, two work-groups per CU.  4: 256-column items by four waves, one work-group
+                                          per CU (more reuse per K/V byte, measured slower on every prompt mix tried) */
 int odma_pool_tune(odma_pool_t* pool, int32_t knob, int32_t value);
 
 /* Test aid, host only, needs no pool: the tile ranges the matrix-core plan gives its waves.  The batch's tiles

@@ -9,7 +9,8 @@
 // and O accumulators stay in registers, and share the K/V tiles the item can see through LDS.
 // CT = 4 (256-column items, one work-group per CU) has the most reuse per K/V byte.  CT = 2 halves the
 // registers so that two work-groups share a CU and one's LDS reads and item start run under the other's
-// matrix instructions: +12 to +25 % on every prompt mix measured, and the default.
+// matrix instructions: +12 to +25 % on every prompt mix measured, and the default.  Calls of long prompts run 256-column items by
+// eight waves of CT = 2 in two groups that take turns at the matrix cores (stream_eight).
 //
 // The items of a call, ordered by (request, KV head, column block from the heaviest down), are cut into eight queues
 // of equal cost, one per XCD (cost: the 32-token K/V pairs an item streams plus a constant for its start and end), and
@@ -28,6 +29,13 @@ namespace {
 constexpr int PREFILL_PLAN_THREADS = 256;
 
 constexpr int PREFILL_XCDS = 8;
+// Calls whose requests have this many query tokens on the average run items of 256 columns by eight waves, one work-group per CU
+// (stream_eight); the others items of 128 by four, two work-groups per CU.  Nothing hides the start of an item of the former,
+// so they have to be long, and how long the host knows from the rows of q alone.  Four -> eight waves, us, bf16: prompts of
+// 4096 tokens 1840 -> 1745, of 2048 1000 -> 974, one of 16 384 1895 -> 1750; but of 1500 with 8 / 1 heads 93 -> 98, of 512 400 ->
+// 418.  fp8, whose widening of a tile then serves twice the columns: chunks of 512 on 6000 to 9000 tokens 605 -> 500, prompts
+// of 4096 1078 -> 908, of 1024 340 -> 319, of 510 418 -> 420, of 256 307 -> 337.
+constexpr int PREFILL_EIGHT_ROWS_BF16 = 1792, PREFILL_EIGHT_ROWS_FP8 = 512;
 // A queue's last items go out one by one, this many per work-group: a work-group holds the run it is on and the one after
 // it, and with runs of four items to the end the last work-group of a call was busy 23 % longer than the mean one.  256
 // prompts around 256 tokens 696 -> 659 us, the same in fp8 760 -> 687, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 ->
@@ -235,12 +243,15 @@ __device__ __forceinline__ unsigned fp8x2_to_bf16x2(unsigned w) {
 // for 242, and 2 to 7 % of every long call).
 // CUT: it cuts items into parts as well, where they are few and long (again a variant of its own, for calls that may: with the
 // code in them calls of few items take 0.3 to 0.4 us more, 41 prompts of 1 to 250 tokens 12.05 -> 12.45).
-template <bool PAGED, int CT, bool FP8, bool HERE, bool CUT>
-__global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillArgs a) {
+template <bool PAGED, int CT, bool FP8, bool HERE, bool CUT, int WAVES = 4>
+__global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(PrefillArgs a) {
+  constexpr bool EIGHT = WAVES == 8;
+  static_assert(!EIGHT || (CT == 2 && !HERE && !CUT), "eight waves: long calls planned in front");
   constexpr int TILE_BYTES = BLK * 128 * (FP8 ? 1 : 2);
   constexpr int LOADS = TILE_BYTES / 1024;                         // 16-byte loads per lane and tile
-  constexpr int COLS_WAVE = 16 * CT, COLS_ITEM = 4 * COLS_WAVE;     // CT column tiles per wave, four waves per item
-  __shared__ __attribute__((aligned(16))) char stage_mem[PREFILL_STAGES * PREFILL_STAGE_BYTES];
+  constexpr int STAGES = EIGHT ? 4 : PREFILL_STAGES;
+  constexpr int COLS_WAVE = 16 * CT, COLS_ITEM = WAVES * COLS_WAVE;   // CT column tiles per wave
+  __shared__ __attribute__((aligned(16))) char stage_mem[STAGES * PREFILL_STAGE_BYTES];
   __shared__ int run_slot[2];
   __shared__ int item_start_lds[PREFILL_LDS_REQ];
   const int lane = threadIdx.x & 63, wv = rfl(threadIdx.x >> 6);
@@ -249,7 +260,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
   const float NEG_INF = -INFINITY;
   // loader role of this wave: waves 0, 1 bring the K tiles of a pair, waves 2, 3 the V tiles
   const bool loads_v = wv >= 2;
-  const int which = wv & 1;                                            // first or second tile of the pair
+  const int which = EIGHT ? wv >> 2 : wv & 1;                             // first or second tile of the pair
   const char* src_base = loads_v ? a.v : a.k;
   const unsigned lane16 = lane * 16;
 
@@ -278,7 +289,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     if (threadIdx.x < PREFILL_XCDS)
       whole_runs[threadIdx.x] = max(a.hdr->bound[threadIdx.x + 1] - a.hdr->bound[threadIdx.x] - PREFILL_SINGLES * turns, 0) / run;
     if (small)
-      for (int i = threadIdx.x; i < a.n; i += 256) item_start_lds[i] = a.item_start[i];
+      for (int i = threadIdx.x; i < a.n; i += 64 * WAVES) item_start_lds[i] = a.item_start[i];
     __syncthreads();
   }
   // Most parts that an item is cut into: as many as there is room for, and no more than the longest request's items have (parts
@@ -490,21 +501,22 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     auto lookup = [&](int pr) {
       if (PAGED) blk_next = bt_row[tile_of(pr)];
     };
-    auto issue = [&](uint4v (&rg)[4], int pr) {
+    auto issue = [&](uint4v (&rg)[LOADS], int pr) {
       const char* src = src_base + plane + (PAGED ? (int64_t)blk_next : base_block + tile_of(pr)) * TILE_BYTES;
 #pragma unroll
       for (int s = 0; s < LOADS; ++s) rg[s] = *(const uint4v*)(src + s * 1024 + lane16);
     };
-    auto write_stage = [&](uint4v (&rg)[4], int pr) {
-      char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES;
+    auto write_stage = [&](uint4v (&rg)[LOADS], int pr) {
+      char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES;
       const int t = tile_of(pr);
       if (FP8) {
         if (!loads_v) {
           // lane (t16, q) holds, per 64-channel half s, channels 64 s + 8 q .. +7 and 64 s + 32 + 8 q .. +7 of
           // token t16: two bf16 pieces, for channel octets 8 s + q and 8 s + 4 + q
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const uint4v w = rg[s];
+          for (int i = 0; i < LOADS; ++i) {
+            const uint4v w = rg[i];
+            const int s = i;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
               const uint4v o = {fp8x2_to_bf16x2<false>(w[2 * h]), fp8x2_to_bf16x2<true>(w[2 * h]),
@@ -517,8 +529,9 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
           const int tok0 = t * BLK + 4 * g4;
           const bool ragged = t * BLK + BLK > held;                      // (the same for the whole wave)
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const uint4v w = rg[s];
+          for (int j = 0; j < LOADS; ++j) {
+            const uint4v w = rg[j];
+            const int s = j;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               uint2v o = {fp8x2_to_bf16x2<false>(w[i]), fp8x2_to_bf16x2<true>(w[i])};
@@ -534,7 +547,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         }
       } else if (!loads_v) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
+        for (int s = 0; s < LOADS; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
       } else {
         // lane (c, q) holds, per piece s, tokens 4q .. 4q+3 of channel groups 2s (low 8 bytes) and 2s+1
         if (t * BLK + BLK > held) {                                      // some of the tile's tokens are not there
@@ -544,7 +557,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
             if (tok0 + i >= held) {
               const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
 #pragma unroll
-              for (int s = 0; s < 4; ++s) {
+              for (int s = 0; s < LOADS; ++s) {
                 rg[s][i >> 1] &= keep;
                 rg[s][2 + (i >> 1)] &= keep;
               }
@@ -552,7 +565,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         }
         char* dst = st + 8192 + lane * 16 + which * 8;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < LOADS; ++s) {
           *(uint2v*)(dst + (2 * s) * 1024) = uint2v{rg[s][0], rg[s][1]};
           *(uint2v*)(dst + (2 * s + 1) * 1024) = uint2v{rg[s][2], rg[s][3]};
         }
@@ -606,7 +619,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // the V operands of a pair: requested before the scores are computed, so that the LDS reads run under
     // the matrix instructions of S^T instead of in front of those of P V
     auto read_v = [&](bf16x8 (&av)[8], int pr) {
-      const char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES + lane * 16;
+      const char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES + lane * 16;
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) av[dt] = *(const bf16x8*)(st + 8192 + dt * 1024);
     };
@@ -631,24 +644,25 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         for (int ct = 0; ct < CT; ++ct)
           O[ct][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[dt], p8[ct], O[ct][dt], 0, 0, 0);
     };
+    auto references = [&](const float4v (&x)[CT][2]) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        float tmax = lane_max(x[ct]);
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+        m[ct] = tmax == NEG_INF ? 0.f : tmax;
+      }
+    };
     // fast pass: references fixed by the first pair.  m holds a finite value from then on (0 for a
     // column that does not exist).
     auto compute_fast = [&](int pr) {
       float4v x[CT][2];
       bf16x8 av[8];
       read_v(av, pr);
-      const char* st = stage_mem + (pr % PREFILL_STAGES) * PREFILL_STAGE_BYTES + lane * 16;
+      const char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES + lane * 16;
       scores_of(x, qreg, [&](int b, int s) { return *(const bf16x8*)(st + b * 4096 + s * 1024); });
       mask(x, pr);
-      if (pr == 0) {
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          float tmax = lane_max(x[ct]);
-          tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-          tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-          m[ct] = tmax == NEG_INF ? 0.f : tmax;
-        }
-      }
+      if (pr == 0) references(x);
       weights(x, av);
     };
     // the same zeroing in the operands
@@ -763,7 +777,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
     // registers until the computation of pair p is over, is written into the other stage, and one
     // work-group barrier per pair makes it visible (and tells that the stage of pair p is free again).
     auto stream = [&]() {
-      uint4v ra[4], rb[4];
+      uint4v ra[LOADS], rb[LOADS];
       lookup(0);
       issue(ra, 0);
       lookup(1);
@@ -771,7 +785,7 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       lookup(2);
       write_stage(ra, 0);
       __syncthreads();
-      auto step = [&](uint4v (&near)[4], uint4v (&far)[4], int pr) {     // near: pair pr + 1, far: free for pair pr + 2
+      auto step = [&](uint4v (&near)[LOADS], uint4v (&far)[LOADS], int pr) {     // near: pair pr + 1, far: free for pair pr + 2
         issue(far, pr + 2);
         lookup(pr + 3);
         if (active) compute_fast(pr);
@@ -785,6 +799,132 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
         if (++pr == n_pairs) break;
       }
     };
+    // ---- the eight-wave pipeline.  Two groups of four waves, a wave of each on every SIMD, take neighbouring columns of one
+    // item half a step apart: while one forms weights (step p's vector half), the other is in its matrix half, the scores of
+    // its next pair and P V of this one.  Two work-groups of four waves drift against each other as they like, and a SIMD's two
+    // waves took 967 cycles a pair each where either half alone needs 520 to 560; half a step is 930 here, of which the
+    // writes into the stages take 130 and the reads 70.  A barrier ends every half; group 1 starts a half later and group 0 waits
+    // for it once at the end, so both pass the same number of them.
+    //
+    // Halves h of a step are numbered by group 0's: it reads V of pair p and K of pair p + 1 in h = 2 p + 1 and writes pair p + 3 in
+    // h = 2 p + 2, group 1 each of them one later.  Pair p + 3 takes the stage of pair p - 1, read last by group 1 in h = 2 p, and is
+    // read first in h = 2 p + 5: four stages, and no read meets a write.
+    auto half_done = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto stream_eight = [&]() {
+      // Every wave brings an eighth of a pair's K and V: piece wv % 4 of its tile (fp8: half a piece, 8 bytes a lane).  The roles
+      // are the same, so the loop has no branch on them.
+      typedef typename std::conditional<FP8, uint2v, uint4v>::type Part;
+      struct Parts {
+        Part k, v;
+      };
+      const bool behind = wv >= 4;
+      const int ps = FP8 ? (wv >> 1) & 1 : wv & 3, ph = wv & 1;          // piece, and which half of its 16 bytes (fp8)
+      const unsigned part_at = ps * 1024 + lane16 + (FP8 ? ph * 8 : 0);
+      auto fetch = [&](Parts& to, int pr) {
+        const int64_t at = plane + (PAGED ? (int64_t)blk_next : base_block + tile_of(pr)) * TILE_BYTES;
+        to.k = *(const Part*)(a.k + at + part_at);
+        to.v = *(const Part*)(a.v + at + part_at);
+      };
+      uint2v keep = {0xffffffffu, 0xffffffffu};                          // which of this lane's four tokens have a V; once it is
+      auto keep_of = [&](int pr) {                                        // the last tile's it stays
+        const int t = tile_of(pr), tok0 = t * BLK + 4 * g4;
+        if (t * BLK + BLK > held) {
+#pragma unroll
+          for (int w = 0; w < 2; ++w)
+            keep[w] = (tok0 + 2 * w < held ? 0x0000ffffu : 0u) | (tok0 + 2 * w + 1 < held ? 0xffff0000u : 0u);
+        }
+      };
+      auto put = [&](const Parts& from, int pr) {                         // the layouts of write_stage
+        char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES;
+        uint2v lo, hi;                                                   // V of two channel groups
+        if constexpr (FP8) {
+          *(uint4v*)(st + which * 4096 + ((8 * ps + 4 * ph + g4) * 16 + col16) * 16) =
+              uint4v{fp8x2_to_bf16x2<false>(from.k[0]), fp8x2_to_bf16x2<true>(from.k[0]), fp8x2_to_bf16x2<false>(from.k[1]),
+                     fp8x2_to_bf16x2<true>(from.k[1])};
+          lo = uint2v{fp8x2_to_bf16x2<false>(from.v[0]), fp8x2_to_bf16x2<true>(from.v[0])};
+          hi = uint2v{fp8x2_to_bf16x2<false>(from.v[1]), fp8x2_to_bf16x2<true>(from.v[1])};
+        } else {
+          *(uint4v*)(st + which * 4096 + ps * 1024 + lane16) = from.k;
+          lo = uint2v{from.v[0], from.v[1]};
+          hi = uint2v{from.v[2], from.v[3]};
+        }
+        char* dst = st + 8192 + (FP8 ? 4 * ps + 2 * ph : 2 * ps) * 1024 + lane16 + which * 8;
+        *(uint2v*)dst = lo & keep;
+        *(uint2v*)(dst + 1024) = hi & keep;
+      };
+      Parts next, first[3];
+#pragma unroll
+      for (int pr = 0; pr < 3; ++pr) {
+        lookup(pr);
+        fetch(first[pr], pr);
+      }
+      lookup(3);
+#pragma unroll
+      for (int pr = 0; pr < 3; ++pr) {
+        keep_of(pr);
+        put(first[pr], pr);
+      }
+      fetch(next, 3);
+      lookup(4);
+      __syncthreads();
+      if (behind) half_done();
+      float4v x[CT][2];
+      bf16x8 p8[CT], kk[2][4], av[8];
+      auto read_k = [&](int pr) {
+        const char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES + lane16;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) kk[b][s] = *(const bf16x8*)(st + b * 4096 + s * 1024);
+      };
+      auto scores = [&]() { scores_of(x, qreg, [&](int b, int s) { return kk[b][s]; }); };
+      read_k(0);
+      scores();
+      // (A wave without columns computes as well, for nobody, as every wave does the scores behind its last pair.)
+      auto step = [&](int pr, auto is_first) {
+        half_done();
+        keep_of(pr + 3);
+        read_v(av, pr);
+        read_k(pr + 1);
+        mask(x, pr);
+        if (decltype(is_first)::value) references(x);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          float sum[2];
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float e[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[ct][b][i], a.scale_log2, -m[ct]));
+              p8[ct][4 * b + i] = (__bf16)e[i];
+            }
+            sum[b] = (e[0] + e[1]) + (e[2] + e[3]);
+          }
+          lsum[ct] += sum[0] + sum[1];
+        }
+        half_done();
+        // fp8: its conversions stand in the matrix half, which is then the longer one and goes first (chunks of 512 over paged pools
+        // 555 -> 495 us; bf16, whose vector half is the longer one, 1750 -> 1800 on 16 prompts of 4096)
+        if (FP8) __builtin_amdgcn_s_setprio(2);
+        scores();
+        put(next, pr + 3);
+        fetch(next, pr + 4);
+        lookup(pr + 5);
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) O[ct][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[dt], p8[ct], O[ct][dt], 0, 0, 0);
+        if (FP8) __builtin_amdgcn_s_setprio(0);
+      };
+      step(0, std::true_type{});
+      for (int pr = 1; pr < n_pairs; ++pr) step(pr, std::false_type{});
+      if (!behind) half_done();
+    };
     // each lane summed the weights of its own tokens: a column's total is the sum over g4
     auto column_sums = [&](float (&l)[CT]) {
 #pragma unroll
@@ -795,7 +935,8 @@ __global__ __launch_bounds__(256, CT == 4 ? 1 : 2) void prefill_kernel(PrefillAr
       }
     };
 
-    stream();
+    if constexpr (EIGHT) stream_eight();
+    else stream();
     if (!CUT && !active) continue;
     float l[CT];
     if (CUT)
