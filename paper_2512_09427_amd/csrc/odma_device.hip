@@ -304,7 +304,14 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     const int tile_tokens = f.blocks * BLK;
     // A plan bakes in the slab bases and the launch shape, so ODMA_REUSE_PLAN is honoured only while the library
     // knows of nothing that changed them; otherwise the call plans again.
-    const int q_min = pool->min_chunk ? (pool->min_chunk + tile_tokens - 1) / tile_tokens : 4;
+    // Fewest tiles of a wave.  A bf16 or fp8 tile of 128 or 64 channels takes a lone wave about as long as one more part
+    // takes a merge of up to eight; four tiles a wave keep most merges there (two: six requests around 4 000 tokens in fp8
+    // 15.0 -> 17.1 us, two around 1 000 in bf16 10.4 -> 12.5).  A tile of the wide formats has up to four times the matrix
+    // and vector instructions, and two is the better number where the two rules differ: one fp32 request of 512, 1 024 and
+    // 2 048 tokens 18.0 -> 11.6, 14.8 -> 12.0 and 15.3 -> 13.1 us, thirty bf16 requests around 300 with head_dim 96 and 256
+    // 10.7 -> 10.3 and 17.0 -> 15.7 (one tile: one fp32 request of 2 048 13.9).  With 32 channels the tile is a small one
+    // again (two tiles: six requests around 4 000 tokens in fp32 12.2 -> 14.2, in bf16 11.1 -> 12.7).
+    const int q_min = pool->min_chunk ? (pool->min_chunk + tile_tokens - 1) / tile_tokens : wide && c.head_dim > 32 ? 2 : 4;
     odma_pool::PlanStamp now;
     now.layout_gen = pool->layout_gen;
     now.owner = pool->serial;

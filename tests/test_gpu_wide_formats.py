@@ -134,3 +134,16 @@ def test_small_workspaces_by_either_kernel(hq, hkv, max_splits):
     H.check(H.decode(dp, 0, q, lens, **where), H.oracle_out(w, q, held), *TOL, what=f"max_splits={max_splits}")
     k_new, v_new = (np.stack([kv[r][i][lens[r]] for r in range(3)]) for i in (0, 1))
     H.check(H.decode_step(dp, 0, q, k_new, v_new, lens + 1, **where), H.oracle_out(w, q, kv), *TOL, what=f"max_splits={max_splits}")
+
+
+@pytest.mark.parametrize("lens", [[33], [63, 0, 1], [512], [1000, 24], [250, 260, 16, 1], [2040], [300] * 30])
+@pytest.mark.parametrize("kvd,d", [("f32", 32), ("f32", 64), ("f32", 256), ("bf16", 32), ("bf16", 96)])
+def test_fewest_tiles_of_a_wave(kvd, d, lens):
+    """Batches in which a wave's share lies around the fewest tiles it may get (two, or four with 32 channels)."""
+    w, dp, lens, _, kv, where = make(lens, kvd, d, 8, 2)
+    q = wl.queries(w, 0, sharp=True)
+    ref = H.oracle_out(w, q, kv)
+    ref[lens == 0] = 0.0
+    got = H.decode(dp, 0, q, lens, **where)
+    H.check(got, ref, *TOL, what=f"{kvd} {d} {lens}")
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, flags=B.REUSE_PLAN, **where), got)
