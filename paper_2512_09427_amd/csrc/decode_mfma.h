@@ -631,7 +631,7 @@ decode_stream_kernel(StreamArgs a) {
   const int n_my = pos_end - pos_start;
   TL_STAMP(1);
   // ready flags must be clear before any neighbour can look at them: a wave clears its own
-  // flag first thing, and its left neighbour reads it only at the end of a whole tile range,
+  // flag first thing, and a wave to its left reads it only at the end of a whole tile range,
   // so one work-group barrier at the top settles the order
   if (lane == 0) flag_set(wv, 0);
   __syncthreads();
@@ -1470,7 +1470,7 @@ decode_stream_kernel(StreamArgs a) {
       }
       ++qn;
     };
-    auto park = [&](float l_all, int ends) {                  // hand this wave's first piece to its left neighbour
+    auto park = [&](float l_all, int ends) {                  // leave this wave's first piece for the wave that begins the chain
       float* so = lds + wv * slot_floats;
       if (col < G) {
 #pragma unroll
