@@ -341,11 +341,11 @@ int odma_decode_attention_static(odma_pool_t* pool, int32_t layer, int32_t n,
  *   q_start    DEVICE int64[n]        n_q  DEVICE int32[n] (0: nothing to do; clamped to lengths[r])
  *   offsets, lengths, block_table, bt_stride as for odma_decode_attention (lengths include the chunk)
  * Launches the attention kernel on `stream`, for calls with many work items after a plan kernel, using the pool's workspace.
- * A work item is up to 128 (query token, head) columns of one request and KV head.  Calls with more items than two per compute
- * unit, or with more than 1024 requests, keep their plan in the workspace and must not overlap with each other on different
- * streams of one pool; calls of fewer are independent.  On the null stream the latter divide long requests among the compute
- * units, with partial results in the workspace (no decode call reads or writes them); on other streams every item is one
- * work-group's, so its rows may differ in rounding. */
+ * A work item is up to 128 (query token, head) columns of one request and KV head (256 in long calls, where the plan finds that
+ * this pays).  Calls with more items of 128 columns than two per compute unit, or with more than 1024 requests, keep their plan in
+ * the workspace and must not overlap with each other on different streams of one pool; calls of fewer are independent.  On the null
+ * stream the latter divide long requests among the compute units, with partial results in the workspace (no decode call reads or
+ * writes them); on other streams every item is one work-group's, so its rows may differ in rounding. */
 int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const void* q, int64_t total_q,
                            const int64_t* q_start, const int32_t* n_q, const int64_t* offsets,
                            const int32_t* lengths, const int32_t* block_table, int32_t bt_stride,
@@ -391,10 +391,11 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
                                           each SIMD) relative to waves 0..3, in 1/256 (128..512, default 256) */
 #define ODMA_TUNE_FUSE_REDUCE      8   /* MFMA kernel: 1 (default) merges segments cut between work-groups inside the attention
                                           launch (last work-group to arrive), 0 in a reduction launch of its own */
-#define ODMA_TUNE_PREFILL_COLUMN_TILES 9 /* prefill kernel: 16-column tiles per wave.  0 (default): two; calls of long prompts run
-                                          256-column work items by eight waves, the others as 2.  2: 128-column items by four
-                                          waves, two work-groups per CU.  4: 256-column items by four waves, one work-group
-                                          per CU (more reuse per K/V byte, measured slower on every prompt mix tried) */
+#define ODMA_TUNE_PREFILL_COLUMN_TILES 9 /* prefill kernel: 16-column tiles per wave.  0 (default): two; long calls run 256-column
+                                          work items by eight waves if the plan finds that this pays, the others as 2.
+                                          2: 128-column items by four waves, two work-groups per CU.  4: 256-column items
+                                          by four waves, one work-group per CU (more reuse per K/V byte, measured slower on
+                                          every prompt mix tried) */
 int odma_pool_tune(odma_pool_t* pool, int32_t knob, int32_t value);
 
 /* Test aid, host only, needs no pool: the tile ranges the matrix-core plan gives its waves.  The batch's tiles

@@ -85,14 +85,18 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   const int64_t parts = prefill_parts((int)std::min<int64_t>(longest / (2 * BLK), 1 << 20));
   const bool cut = here && a.part_slots && parts > 1 && 2 * items - (int64_t)n * a.Hkv <= (int64_t)grid.x;
   if (cut) grid.x = (unsigned)std::min<int64_t>(grid.x, (items * parts + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
-  // Long prompts: eight waves per item.  (A pool with a tuned number of column tiles keeps that, and rows that the requests
-  // cannot all have, no request having more queries than tokens, say nothing about their prompts.)
-  const bool eight = !here && !pool->prefill_ct && total_q >= (int64_t)n * (fp8 ? PREFILL_EIGHT_ROWS_FP8 : PREFILL_EIGHT_ROWS_BF16) &&
-                     total_q / n <= longest;
-  if (eight) grid.x = (unsigned)((pool->n_cu + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS);
+  // Long calls may be the eight-wave kernel's: the plan decides, and the other kernel ends at once.  (A pool with a tuned number of
+  // column tiles keeps that, and rows that the requests cannot all have, no request having more queries than tokens, say
+  // nothing about how long a call is.)
+  const double items_cu = (double)total_q * c.n_q_heads / (256.0 * pool->n_cu);   // items of 256 columns for each CU
+  const double least = items_cu * (total_q / n) / (4 * BLK), most = items_cu * longest / (2 * BLK);
+  const bool weigh = !here && !pool->prefill_ct && total_q / n <= longest &&
+                     (fp8 ? least >= PREFILL_WEIGH_FP8 || (least >= PREFILL_WEIGH_FP8_LEAST && most >= PREFILL_WEIGH_FP8_MOST) : least >= PREFILL_WEIGH_BF16);
+  PrefillRule rule = fp8 ? PREFILL_EIGHT_FP8 : block_table ? PREFILL_EIGHT_BF16_PAGED : PREFILL_EIGHT_BF16;
+  rule.n_cu = pool->n_cu;
   if (!here)
-    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths, q_start, total_q, n,
-                       c.n_kv_heads, a.G, eight ? 256 : 64 * ct, a.hdr, a.item_start);
+    hipLaunchKernelGGL(weigh ? prefill_plan_kernel<true> : prefill_plan_kernel<false>, dim3(1), dim3(PREFILL_PLAN_THREADS), 0, s, n_q, lengths,
+                       q_start, total_q, n, c.n_kv_heads, a.G, 64 * ct, a.hdr, a.item_start, rule);
   // [fp8][two column tiles][paged][planned in front, here, here and cut]
 #define ODMA_PREFILL(P, CT, F) {prefill_kernel<P, CT, F, false, false>, prefill_kernel<P, CT, F, true, false>, prefill_kernel<P, CT, F, true, true>}
 #define ODMA_PREFILL_F(F) {{ODMA_PREFILL(false, 4, F), ODMA_PREFILL(true, 4, F)}, {ODMA_PREFILL(false, 2, F), ODMA_PREFILL(true, 2, F)}}
@@ -100,8 +104,9 @@ int odma_prefill_attention(odma_pool_t* pool, int32_t layer, int32_t n, const vo
   static void (*const eight_kernels[2][2])(PrefillArgs) = {   // [fp8][paged]
       {prefill_kernel<false, 2, false, false, false, 8>, prefill_kernel<true, 2, false, false, false, 8>},
       {prefill_kernel<false, 2, true, false, false, 8>, prefill_kernel<true, 2, true, false, false, 8>}};
-  if (eight) hipLaunchKernelGGL(eight_kernels[fp8][block_table != nullptr], grid, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(kernels[fp8][ct == 2][block_table != nullptr][here + cut], grid, dim3(256), 0, s, a);
+  if (weigh)
+    hipLaunchKernelGGL(eight_kernels[fp8][block_table != nullptr], dim3((pool->n_cu + PREFILL_XCDS - 1) / PREFILL_XCDS * PREFILL_XCDS), dim3(512), 0, s, a);
+  hipLaunchKernelGGL(kernels[fp8][ct == 2][block_table != nullptr][here + cut], grid, dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(where, e);
   return ODMA_OK;

@@ -9,8 +9,8 @@
 // and O accumulators stay in registers, and share the K/V tiles the item can see through LDS.
 // CT = 4 (256-column items, one work-group per CU) has the most reuse per K/V byte.  CT = 2 halves the
 // registers so that two work-groups share a CU and one's LDS reads and item start run under the other's
-// matrix instructions: +12 to +25 % on every prompt mix measured, and the default.  Calls of long prompts run 256-column items by
-// eight waves of CT = 2 in two groups that take turns at the matrix cores (stream_eight).
+// matrix instructions: +12 to +25 % on every prompt mix measured, and the default.  Calls of long items run 256-column items by
+// eight waves of CT = 2 in two groups that take turns at the matrix cores (stream_eight), if the plan finds that this pays.
 //
 // The items of a call, ordered by (request, KV head, column block from the heaviest down), are cut into eight queues
 // of equal cost, one per XCD (cost: the 32-token K/V pairs an item streams plus a constant for its start and end), and
@@ -29,13 +29,28 @@ namespace {
 constexpr int PREFILL_PLAN_THREADS = 256;
 
 constexpr int PREFILL_XCDS = 8;
-// Calls whose requests have this many query tokens on the average run items of 256 columns by eight waves, one work-group per CU
-// (stream_eight); the others items of 128 by four, two work-groups per CU.  Nothing hides the start of an item of the former,
-// so they have to be long, and how long the host knows from the rows of q alone.  Four -> eight waves, us, bf16: prompts of
-// 4096 tokens 1840 -> 1745, of 2048 1000 -> 974, one of 16 384 1895 -> 1750; but of 1500 with 8 / 1 heads 93 -> 98, of 512 400 ->
-// 418.  fp8, whose widening of a tile then serves twice the columns: chunks of 512 on 6000 to 9000 tokens 605 -> 500, prompts
-// of 4096 1078 -> 908, of 1024 340 -> 319, of 510 418 -> 420, of 256 307 -> 337.
-constexpr int PREFILL_EIGHT_ROWS_BF16 = 1792, PREFILL_EIGHT_ROWS_FP8 = 512;
+// Two kernels serve the calls that are planned in front: items of 128 columns by four waves, two work-groups per CU, and items of
+// 256 by eight waves (stream_eight).  An item of the latter takes the time of two of the former less 4 % in bf16, 6 in paged bf16
+// and 16 in fp8, whose widening of a tile then serves twice the columns.  But nothing hides its start, the empty half of a last
+// block is computed for nobody, and the item that a call ends with takes up to half as long again as one of 128 columns that has
+// its CU to itself.  So the planning kernel, which knows every request, weighs them: the items must be long on the average,
+// next to none of it padding, and the longest one a part of what each CU streams.  Of 2022 calls of random heads, lengths and
+// chunks these rules give 420 to eight waves: the worst took 1.03 of its time with four (bf16; 0.996 in fp8), the mean 0.96 in bf16,
+// 0.94 in paged bf16, 0.85 in fp8.  Chosen by rows of q per request, all that the host knows, the worst took 1.46: one request of
+// many rows beside short ones, 8 / 8 heads and blocks of 256 columns with 4 in the last, 260 items on 256 CUs.
+struct PrefillRule {
+  float min_pairs, slope;    // mean pairs of an item of 256 columns: min_pairs and `slope` times the longest item's part (below)
+  float max_longest;         // pairs of the longest item, as a part of what each CU streams
+  float max_padding;         // pairs of the items of 256 columns relative to those of 128, two of these counted as one
+  int32_t n_cu;              // 0: four waves
+};
+constexpr PrefillRule PREFILL_EIGHT_BF16 = {28.f, 20.f, 0.8f, 1.03f, 0}, PREFILL_EIGHT_BF16_PAGED = {16.f, 20.f, 1.0f, 1.03f, 0},
+                      PREFILL_EIGHT_FP8 = {13.f, 0.f, 0.9f, 1.1f, 0};
+// A call that is weighed has one launch more, which finds the other kernel chosen and ends (2.4 us).  It has to be long for that, in
+// pairs that each CU streams (1 us or less): at least, with every row that of a whole prompt and all prompts of one length; or
+// at most, with every row the last of the longest request that there can be.  (fp8 chunks of 512 at 6000 to 9000 tokens: 14 and
+// 484, 605 -> 490 us.  Below 10 a call whose chunks do have little in front of them would notice the launch.)
+constexpr double PREFILL_WEIGH_BF16 = 200, PREFILL_WEIGH_FP8 = 100, PREFILL_WEIGH_FP8_LEAST = 10, PREFILL_WEIGH_FP8_MOST = 400;
 // A queue's last items go out one by one, this many per work-group: a work-group holds the run it is on and the one after
 // it, and with runs of four items to the end the last work-group of a call was busy 23 % longer than the mean one.  256
 // prompts around 256 tokens 696 -> 659 us, the same in fp8 760 -> 687, 29 of 816 tokens on the average (fp8, 56 / 8 heads) 728 ->
@@ -60,6 +75,7 @@ struct PrefillHeader {
   int32_t bound[PREFILL_XCDS + 1];          // items [bound[x], bound[x + 1]) are queue x
   int32_t next[PREFILL_XCDS];               // runs claimed of every queue beyond the first of each work-group, reset by the plan
   int32_t avg_pairs;                        // mean cost of an item
+  int32_t eight;                            // the call is the eight-wave kernel's
 };
 
 struct PrefillBounds {
@@ -118,106 +134,141 @@ __device__ __forceinline__ int prefill_blocks(int rows, int G, int cols_item) {
 }
 
 // One work-group of PREFILL_PLAN_THREADS: exclusive prefix of items per request (item_start[0 .. n)), and in `pl` the bounds of
-// the eight queues of equal cost.  LONGEST: the most tokens of a request with items as well.  Ends with a barrier.
+// the eight queues of equal cost.  LONGEST: the most tokens of a request with items as well.  WEIGH: items of cols_item or twice
+// the columns, by `rule`.  Ends with a barrier.
 struct PrefillPlan {
-  double part_cost[PREFILL_PLAN_THREADS / 64];
-  int part_items[PREFILL_PLAN_THREADS / 64], part_longest[PREFILL_PLAN_THREADS / 64];
-  int bound[PREFILL_XCDS + 1], avg_pairs, longest;
+  double part_cost[2][PREFILL_PLAN_THREADS / 64];
+  int part_items[2][PREFILL_PLAN_THREADS / 64], part_longest[PREFILL_PLAN_THREADS / 64];
+  int bound[PREFILL_XCDS + 1], avg_pairs, longest, eight;
 };
-template <bool LONGEST>
+template <bool LONGEST, bool WEIGH = false>
 __device__ __forceinline__ void prefill_plan(const int32_t* n_q, const int32_t* lengths, const int64_t* q_start, int64_t total_q,
                                              int32_t n, int32_t Hkv, int32_t G, int32_t cols_item, PrefillPlan& pl,
-                                             int32_t* item_start) {
+                                             int32_t* item_start, PrefillRule rule = {}) {
+  constexpr int SIZES = WEIGH ? 2 : 1;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (n + PREFILL_PLAN_THREADS - 1) / PREFILL_PLAN_THREADS;
   const int r0 = min(tid * per, n), r1 = min(r0 + per, n);
-  double cost = 0;
-  int items = 0, longest = 0;
-  auto add = [&](int r, auto&& at) {                        // at(blocks of r, its cost rule), then past r
+  double cost[SIZES] = {};
+  int items[SIZES] = {}, longest = 0;
+  for (int r = r0; r < r1; ++r) {
     const int rows = prefill_rows(n_q, lengths, q_start, total_q, r);
-    const int nb = prefill_blocks(rows, G, cols_item);
-    const PrefillCost pc(lengths[r] - rows, cols_item, G);
-    at(nb, pc);
-    cost += Hkv * pc.upto(nb);
-    items += Hkv * nb;
-    if (LONGEST) longest = max(longest, nb ? lengths[r] : 0);
-  };
-  for (int r = r0; r < r1; ++r) add(r, [](int, const PrefillCost&) {});
-  double inc_cost = cost;
-  int inc_items = items;
+#pragma unroll
+    for (int z = 0; z < SIZES; ++z) {
+      const int nb = prefill_blocks(rows, G, cols_item << z);
+      cost[z] += Hkv * PrefillCost(lengths[r] - rows, cols_item << z, G).upto(nb);
+      items[z] += Hkv * nb;
+    }
+    if (LONGEST || WEIGH) longest = max(longest, rows ? lengths[r] : 0);
+  }
+  double inc_cost[SIZES];
+  int inc_items[SIZES];
+#pragma unroll
+  for (int z = 0; z < SIZES; ++z) {
+    inc_cost[z] = cost[z];
+    inc_items[z] = items[z];
+  }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const double yc = __shfl_up(inc_cost, o);
-    const int yi = __shfl_up(inc_items, o);
-    if (LONGEST) longest = max(longest, __shfl_up(longest, o));        // (a lane below o gets its own)
-    if (lane >= o) {
-      inc_cost += yc;
-      inc_items += yi;
+    if (LONGEST || WEIGH) longest = max(longest, __shfl_up(longest, o));        // (a lane below o gets its own)
+#pragma unroll
+    for (int z = 0; z < SIZES; ++z) {
+      const double yc = __shfl_up(inc_cost[z], o);
+      const int yi = __shfl_up(inc_items[z], o);
+      if (lane >= o) {
+        inc_cost[z] += yc;
+        inc_items[z] += yi;
+      }
     }
   }
   if (lane == 63) {
-    pl.part_cost[wv] = inc_cost;
-    pl.part_items[wv] = inc_items;
-    if (LONGEST) pl.part_longest[wv] = longest;
-  }
-  __syncthreads();
-  double all_cost = 0;
-  int all_items = 0;
-  cost = inc_cost - cost;
-  items = inc_items - items;
-  for (int i = 0; i < PREFILL_PLAN_THREADS / 64; ++i) {
-    if (i < wv) {
-      cost += pl.part_cost[i];
-      items += pl.part_items[i];
+#pragma unroll
+    for (int z = 0; z < SIZES; ++z) {
+      pl.part_cost[z][wv] = inc_cost[z];
+      pl.part_items[z][wv] = inc_items[z];
     }
-    all_cost += pl.part_cost[i];
-    all_items += pl.part_items[i];
-    if (LONGEST) longest = max(longest, pl.part_longest[i]);
-  }
-  // a boundary that rounding leaves to no thread keeps its share of the items
-  if (tid <= PREFILL_XCDS) pl.bound[tid] = (int)((long long)all_items * tid / PREFILL_XCDS);
-  if (tid == 0) {
-    pl.avg_pairs = (int)(all_cost / max(all_items, 1));
-    if (LONGEST) pl.longest = longest;
+    if (LONGEST || WEIGH) pl.part_longest[wv] = longest;
   }
   __syncthreads();
-  // boundary x lies at cost all_cost * x / 8, inside the request whose cost range holds it
+  double all_cost[SIZES] = {};
+  int all_items[SIZES] = {};
+#pragma unroll
+  for (int z = 0; z < SIZES; ++z) {
+    cost[z] = inc_cost[z] - cost[z];
+    items[z] = inc_items[z] - items[z];
+    for (int i = 0; i < PREFILL_PLAN_THREADS / 64; ++i) {
+      if (i < wv) {
+        cost[z] += pl.part_cost[z][i];
+        items[z] += pl.part_items[z][i];
+      }
+      all_cost[z] += pl.part_cost[z][i];
+      all_items[z] += pl.part_items[z][i];
+    }
+  }
+  if (LONGEST || WEIGH)
+    for (int i = 0; i < PREFILL_PLAN_THREADS / 64; ++i) longest = max(longest, pl.part_longest[i]);
+  // the size of the items: everything below is about that one
+  bool eight = false;
+  if constexpr (WEIGH) {
+    const float pairs4 = (float)(all_cost[0] - PREFILL_ITEM_COST * all_items[0]), pairs8 = (float)(all_cost[1] - PREFILL_ITEM_COST * all_items[1]);
+    const float part = (float)longest * (1.f / (2 * BLK)) * (float)rule.n_cu / pairs8;
+    eight = pairs8 >= (rule.min_pairs + rule.slope * part) * (float)all_items[1] && part <= rule.max_longest &&
+            2.f * pairs8 <= rule.max_padding * pairs4;               // (a call without items: not a number, so four)
+  }
+  const int cols = cols_item << eight;
+  const double total = all_cost[eight];
+  const int n_items = all_items[eight];
+  double at = cost[eight];
+  int first = items[eight];
+  // a boundary that rounding leaves to no thread keeps its share of the items
+  if (tid <= PREFILL_XCDS) pl.bound[tid] = (int)((long long)n_items * tid / PREFILL_XCDS);
+  if (tid == 0) {
+    pl.avg_pairs = (int)(total / max(n_items, 1));
+    if (LONGEST) pl.longest = longest;
+    pl.eight = eight;
+  }
+  __syncthreads();
+  // boundary x lies at cost total * x / 8, inside the request whose cost range holds it
   for (int r = r0; r < r1; ++r) {
-    item_start[r] = items;
-    const double before = cost;
-    const int first = items;
-    add(r, [&](int nb, const PrefillCost& pc) {
-      if (nb == 0) return;
-      const double per_head = pc.upto(nb);
+    item_start[r] = first;
+    const int rows = prefill_rows(n_q, lengths, q_start, total_q, r), nb = prefill_blocks(rows, G, cols);
+    const PrefillCost pc(lengths[r] - rows, cols, G);
+    const double per_head = pc.upto(nb);
+    if (nb)
       for (int x = 1; x < PREFILL_XCDS; ++x) {
-        const double t = all_cost * x / PREFILL_XCDS - before;
+        const double t = total * x / PREFILL_XCDS - at;
         if (t < 0 || t >= Hkv * per_head) continue;
         const int g = min((int)(t / per_head), Hkv - 1);
         // blocks run from the last one (the dearest) down: those that cost t come after those that cost the rest
         const int left = min(max(pc.block_at(fmax(per_head - (t - g * per_head), 0.0)), 0), nb);
         pl.bound[x] = first + g * nb + nb - left;
       }
-    });
+    at += Hkv * per_head;
+    first += Hkv * nb;
   }
   __syncthreads();
   if (tid == 0)                                             // (two threads' ranges may meet an ulp apart)
-    for (int x = 1; x <= PREFILL_XCDS; ++x) pl.bound[x] = min(max(pl.bound[x], pl.bound[x - 1]), all_items);
+    for (int x = 1; x <= PREFILL_XCDS; ++x) pl.bound[x] = min(max(pl.bound[x], pl.bound[x - 1]), n_items);
   __syncthreads();
 }
 
 // the plan as a launch of its own: for calls with many items or requests
+template <bool WEIGH>
 __global__ __launch_bounds__(PREFILL_PLAN_THREADS) void prefill_plan_kernel(const int32_t* __restrict__ n_q,
                                                                            const int32_t* __restrict__ lengths,
                                                                            const int64_t* __restrict__ q_start,
                                                                            int64_t total_q, int32_t n, int32_t Hkv, int32_t G,
                                                                            int32_t cols_item, PrefillHeader* hdr,
-                                                                           int32_t* item_start) {
+                                                                           int32_t* item_start, PrefillRule rule) {
   __shared__ PrefillPlan pl;
-  prefill_plan<false>(n_q, lengths, q_start, total_q, n, Hkv, G, cols_item, pl, item_start);
+  prefill_plan<false, WEIGH>(n_q, lengths, q_start, total_q, n, Hkv, G, cols_item, pl, item_start, rule);
   const int tid = threadIdx.x;
   if (tid <= PREFILL_XCDS) hdr->bound[tid] = pl.bound[tid];
   if (tid < PREFILL_XCDS) hdr->next[tid] = 0;
-  if (tid == 0) hdr->avg_pairs = pl.avg_pairs;
+  if (tid == 0) {
+    hdr->avg_pairs = pl.avg_pairs;
+    hdr->eight = pl.eight;
+  }
 }
 
 // LDS stage of one pair of tiles (32 tokens): K of both tiles as loaded (the 16x16x32 A operands of
@@ -283,6 +334,7 @@ __global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(Pr
   if constexpr (HERE) {                                                // (n <= PREFILL_LDS_REQ)
     prefill_plan<CUT>(a.n_q, a.lengths, a.q_start, a.total_q, a.n, a.Hkv, a.G, COLS_ITEM, plan, item_start_lds);
   } else {
+    if (a.hdr->eight != EIGHT) return;                                 // the plan gave the call to the other kernel
     run = min(min(max(64 / max(a.hdr->avg_pairs, 1), 1), 16), max(a.hdr->bound[PREFILL_XCDS] / ((int)gridDim.x * 8), 1));
     if (threadIdx.x <= PREFILL_XCDS) bound[threadIdx.x] = a.hdr->bound[threadIdx.x];
     if (threadIdx.x == 0) run_items = run;

@@ -192,3 +192,43 @@ def test_prompt_calls_that_may_be_cut(runtime):
         check(prompt(p, rows=1 << 20), False, False, False)
         check(prompt(p, rows=1 << 20, stream=77), False, False, False)
     """)
+
+
+def test_prompt_calls_that_may_run_eight_waves(runtime):
+    """Calls that are long by what the host knows launch a plan that weighs them, the kernel of eight waves and the one of four; the
+    others, and those of a pool with a set number of column tiles, a plan that does not and the kernel of four."""
+    run(runtime, """
+        def prompt(p, n, rows, paged=None):
+            at = hip.fake_launches()
+            p.odma_prefill_attention(0, n, Q, rows, OFFS, NEW, None if paged else OFFS, LENS, TABLE if paged else None, paged or 0, OUT, 0)
+            return [(hip.fake_name(i).decode(), hip.fake_grid(i, 0)) for i in range(at, hip.fake_launches())]
+
+        def check(got, weighed, fp8, paged, ct=2):
+            kernel = lambda c, w: f"prefill_kernelILb{int(paged)}ELi{c}ELb{int(fp8)}ELb0ELb0ELi{w}E"
+            want = [(f"prefill_plan_kernelILb{int(weighed)}E", 1)] + [(kernel(2, 8), 256)] * weighed + [(kernel(ct, 4), 512 if ct == 2 else 256)]
+            assert len(got) == len(want) and all(w in g and x == y for (g, x), (w, y) in zip(got, want)), (got, want)
+
+        # 16 heads: a call of n * m rows has n * m / 4096 items of 256 columns for each of 256 CUs, of at least m / 64 pairs
+        for paged in (False, True):
+            stride = 256 if paged else None                  # (requests of up to 4096 tokens in both layouts)
+            p = make_pool(hq=16)
+            check(prompt(p, 16, 16 * 1792, stride), False, False, paged)
+            check(prompt(p, 16, 16 * 1811, stride), True, False, paged)          # 200.2 pairs: 16 * 1811^2 / 2^18
+            check(prompt(p, 14, 14 * 4096, stride), True, False, paged)
+            check(prompt(p, 14, 14 * 4097, stride), False, False, paged)         # rows that the requests cannot all have
+            for ct in (2, 4):
+                p.odma_pool_tune(B.TUNE_PREFILL_COLUMN_TILES, ct)
+                check(prompt(p, 14, 14 * 4096, stride), False, False, paged, ct)
+            p = make_pool(kv_dtype=B.FP8, hq=16)
+            check(prompt(p, 16, 16 * 404, stride), False, True, paged)
+            check(prompt(p, 16, 16 * 405, stride), False, True, paged)           # 10 pairs at least, 202 at most
+            check(prompt(p, 32, 32 * 404, stride), True, True, paged)            # 19.9 and 404
+            check(prompt(p, 31, 31 * 410, stride), False, True, paged)           # 19.9 and 397
+            check(prompt(p, 16, 16 * 1279, stride), True, True, paged)           # 99.8 and 639
+            check(prompt(p, 128, 128 * 142, stride), False, True, paged)         # 9.8 and 568
+            check(prompt(p, 128, 128 * 144, stride), True, True, paged)          # 10.1 and 576
+        # requests of up to 1024 tokens: the most is no more than four times the least
+        p = make_pool(kv_dtype=B.FP8, hq=16)
+        check(prompt(p, 32, 32 * 800, 64), False, True, True)    # 78 and 200
+        check(prompt(p, 32, 32 * 906, 64), True, True, True)     # 100.2
+    """)
