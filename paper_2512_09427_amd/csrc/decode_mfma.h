@@ -1717,10 +1717,10 @@ decode_stream_kernel(StreamArgs a) {
   const int n_a = do_a ? rd_cut[0].n_parts : 0, n_b = do_b ? rd_cut[1].n_parts : 0;
   // partials whose loads are in flight together: the usual cut has two parts, a long request spans tens of work-groups; loads
   // past the last part would only repeat it, so the batch fits the count
-  auto merge = [&](auto cuts_tag, auto batch_tag, int which) {
+  auto merge = [&](auto cuts_tag, auto batch_tag, int which, int wave, int waves) {
     constexpr int CUTS = decltype(cuts_tag)::value, BATCH = decltype(batch_tag)::value;
     // thread -> (head, four channels)
-    for (int idx = threadIdx.x; idx < G * (CH / 4); idx += 64 * WPW) {
+    for (int idx = 64 * wave + lane; idx < G * (CH / 4); idx += 64 * waves) {
       const int h = idx / (CH / 4), d4 = idx - h * (CH / 4);
       float m_run[CUTS], l_run[CUTS];
       float4v acc[CUTS];
@@ -1776,22 +1776,75 @@ decode_stream_kernel(StreamArgs a) {
       }
     }
   };
+  // More than eight parts: what bounds the merge are its load instructions, and a third of those brought every thread the same few
+  // references and sums.  Here a row of 16 lanes holds those of 16 parts of one head -- 64 threads of outputs belong to four heads at
+  // most, with 64 channels or more -- and the threads get the parts' weights from it.  Together with the halves below, launches that
+  // reuse a plan: 7 requests of 3 352 to 14 405 tokens, 14 / 2 heads 18.7 -> 16.6 us, two around 16 000, 6 / 3 heads 18.0 -> 13.9; in fp32,
+  // 64 channels, two of 6 633 and 5 210, 4 / 2 heads 18.4 -> 11.5.
+  auto merge_many = [&](int which, int wave, int waves) {
+    constexpr int BATCH = 16;
+    const ReduceDesc rd = which == 0 ? rd_cut[0] : rd_cut[1];
+    const int n = which == 0 ? n_a : n_b, size = G * (CH / 4);
+    auto over_row = [](float x, auto op) {
+      x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false)));   // (rotations by 8, 4, 2, 1)
+      x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false)));
+      x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false)));
+      return op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false)));
+    };
+    for (int t0 = 64 * wave; t0 < size; t0 += 64 * waves) {     // (every lane of a wave that has any: they hold the others' weights)
+      const int idx = min(t0 + lane, size - 1), h = idx / (CH / 4), d4 = idx - h * (CH / 4), h0 = t0 / (CH / 4);
+      const int row = 16 * (h - h0), row_h = min(h0 + (lane >> 4), G - 1);
+      float m_run = -INFINITY, l_run = 0.f;                     // of the row's head
+      float4v acc = float4v{0.f, 0.f, 0.f, 0.f};
+      for (int i0 = 0; i0 < n; i0 += BATCH) {
+        const bool held = i0 + (lane & 15) < n;
+        const float2 ml = load_pair_agent((const float*)&a.part_ml[part_at(rd, min(i0 + (lane & 15), n - 1)) + row_h]);
+        float4v ov[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const int64_t pi = part_at(rd, min(i0 + u, n - 1)) + h;
+          const float2 lo = load_pair_agent(a.part_o + pi * CH + 4 * d4);
+          const float2 hi = load_pair_agent(a.part_o + pi * CH + 4 * d4 + 2);
+          ov[u] = float4v{lo.x, lo.y, hi.x, hi.y};
+        }
+        asm volatile("" ::: "memory");                         // every load of the batch is issued before the first is waited for
+        const float m_new = fmaxf(m_run, over_row(held ? ml.x : -INFINITY, [](float x, float y) { return fmaxf(x, y); }));
+        const float keep = __builtin_amdgcn_exp2f(m_run - m_new), w = held ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
+        l_run = fmaf(l_run, keep, over_row(held ? w * ml.y : 0.f, [](float x, float y) { return x + y; }));
+        m_run = m_new;
+        acc *= __shfl(keep, row);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const float w_u = __shfl(w, row + u);
+          if (i0 + u < n) acc += ov[u] * w_u;
+        }
+      }
+      const float l = __shfl(l_run, row);
+      if (t0 + lane < size) write_merged(rd, h, d4, acc, l);
+    }
+  };
   // (One after the other, two cuts of a late work-group were two round trips: fp8, 64 requests 17.0 -> 16.2 us, 256 fused 115.8
   // -> 113.0 for four layers.  More than four parts of both cuts at once are slower again: 7 parts of one, 10.0 -> 10.6.)
   using std::integral_constant;
+  const int wave = rfl(wv);
   if (do_a && do_b && max(n_a, n_b) <= 2) {                    // the usual two cuts: their loads travel together
-    merge(integral_constant<int, 2>{}, integral_constant<int, 2>{}, 0);
+    merge(integral_constant<int, 2>{}, integral_constant<int, 2>{}, 0, wave, WPW);
   } else if (do_a && do_b && max(n_a, n_b) <= 4) {
-    merge(integral_constant<int, 2>{}, integral_constant<int, 4>{}, 0);
+    merge(integral_constant<int, 2>{}, integral_constant<int, 4>{}, 0, wave, WPW);
   } else {
+    // Half of the waves for each of two cuts, where that is threads enough; otherwise all of them for one after the other.  (Of a
+    // few long requests the work-group between two is often the last of both: it has two pieces to store.)
+    const bool halves = do_a && do_b && G * (CH / 4) <= 32 * WPW;
+    const int half = halves ? wave / (WPW / 2) : 0, waves = halves ? WPW / 2 : WPW, mine = wave - half * (WPW / 2);
 #pragma nounroll
-    for (int which = 0; which < 2; ++which) {
+    for (int which = half; which < (halves ? half + 1 : 2); ++which) {
       const int n = which == 0 ? n_a : n_b;
       if (n == 0) continue;
-      if (n <= 2) merge(integral_constant<int, 1>{}, integral_constant<int, 2>{}, which);
-      else if (n <= 4) merge(integral_constant<int, 1>{}, integral_constant<int, 4>{}, which);
-      else if (n <= 8) merge(integral_constant<int, 1>{}, integral_constant<int, 8>{}, which);
-      else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which);
+      if (n <= 2) merge(integral_constant<int, 1>{}, integral_constant<int, 2>{}, which, mine, waves);
+      else if (n <= 4) merge(integral_constant<int, 1>{}, integral_constant<int, 4>{}, which, mine, waves);
+      else if (n <= 8) merge(integral_constant<int, 1>{}, integral_constant<int, 8>{}, which, mine, waves);
+      else if constexpr (CH >= 64) merge_many(which, mine, waves);
+      else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which, mine, waves);
     }
   }
   tl_flush();

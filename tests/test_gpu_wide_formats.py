@@ -10,7 +10,8 @@ import pytest
 import workloads as wl
 from paper_2512_09427_amd import binding as B
 from tests import harness as H
-from tests.test_gpu_parity import small_workload
+from tests.test_gpu_fp8 import TIGHT_FP8
+from tests.test_gpu_parity import TIGHT_F32, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -147,3 +148,27 @@ def test_fewest_tiles_of_a_wave(kvd, d, lens):
     got = H.decode(dp, 0, q, lens, **where)
     H.check(got, ref, *TOL, what=f"{kvd} {d} {lens}")
     np.testing.assert_array_equal(H.decode(dp, 0, q, lens, flags=B.REUSE_PLAN, **where), got)
+
+
+@pytest.mark.parametrize("wpw", [4, 8])
+@pytest.mark.parametrize("lens", [[6100, 5900], [2300, 9000, 700, 4100]])
+@pytest.mark.parametrize("kvd,d", [("f32", 32), ("f32", 64), ("f32", 160), ("f32", 256), ("bf16", 96), ("bf16", 224), ("bf16", 64), ("bf16", 128),
+                                   ("fp8", 128)])
+def test_cuts_of_many_parts(kvd, d, lens, wpw):
+    """Segments over nine to tens of work-groups and next to each other, so that one work-group may merge the cuts at both of its
+    ends: batches of 16 parts and less, one to four heads in the threads of a wave, half of the waves and all of them."""
+    lens = np.array(lens)
+    for hq, hkv in [(1, 1), (5, 1), (14, 2), (16, 1)]:
+        w = small_workload(lens, kv_dtype=kvd, hq=hq, hkv=hkv, d=d, seed=d, bounds=(1024, 4096, 16384), large_cap=16384, main=65536)
+        dp = H.make_pool(w, out_dtype=B.F32)
+        dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_WG, wpw)
+        dp.pool.odma_pool_tune(B.TUNE_MIN_CHUNK, 64)
+        kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+        off, _ = H.assign_perfect(dp, lens)
+        H.fill(dp, 0, kv, offsets=off)
+        q = wl.queries(w, 0, sharp=True)
+        got = H.decode(dp, 0, q, lens, offsets=off)
+        tol = TIGHT_FP8 if kvd == "fp8" else TOL if kvd == "f32" or d not in (64, 128) else TIGHT_F32
+        H.check(got, H.oracle_out(w, q, kv), *tol, what=f"{kvd} {d} {hq}/{hkv}")
+        for _ in range(2):                                   # whoever arrives last, the same bits
+            np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
