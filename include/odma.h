@@ -382,7 +382,8 @@ int odma_block_read_probe(const void* k_plane, const void* v_plane, const int32_
                                           is 32 waves per compute unit in work-groups of four */
 #define ODMA_TUNE_ITEMS_PER_WAVE   2   /* VALU kernel: work items aimed at per wave, in sixteenths, 4..256 (default 32 = 2.0) */
 #define ODMA_TUNE_MIN_CHUNK        3   /* smallest range a wave is given, in tokens, multiple of 64 (default: four tiles of 16
-                                          or 32 tokens, two in wide formats of more than 32 channels; VALU kernel: 64) */
+                                          or 32 tokens, two for small batches in wide formats of more than 32 channels; VALU
+                                          kernel: 64) */
 #define ODMA_TUNE_PIPELINE_DEPTH   4   /* register tile buffers per wave in the MFMA kernel: 2 or 3 (default 2) */
 #define ODMA_TUNE_WAVES_PER_WG     5   /* MFMA kernel work-group size in waves: 4 or 8; 0 = default (4) */
 #define ODMA_TUNE_ODD_XCD_WEIGHT   6   /* MFMA kernel: tile share of work-groups on odd XCDs relative to even

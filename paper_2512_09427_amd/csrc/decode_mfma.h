@@ -61,7 +61,7 @@ struct StreamArgs {
   const int32_t* lengths;
   const int64_t* offsets;    // nullptr when paged
   int32_t plan_at;           // a launch that plans: float offset of the planning area in LDS
-  int32_t q_min, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (StreamShares)
+  int32_t q_min, q_long, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (stream_fewest, StreamShares)
   int32_t whole_extra;       // tiles beyond an equal share that a wave may get in order that no segment is cut (-1: never)
   unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
   int32_t fuse_reduce;       // 1: the last work-group to finish a cut segment merges it; 0: stream_reduce_kernel does
@@ -86,25 +86,28 @@ constexpr int STREAM_PLAN_LDS = 8192;
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
     const int32_t* __restrict__ lengths, const int64_t* __restrict__ offsets, int32_t n, int32_t Hkv,
-    int32_t tile_tokens, int32_t n_waves, int32_t wpw, int32_t q_min, int32_t odd_xcd_weight, int32_t late_wave_weight,
-    StreamEntry* entries, WaveDesc* waves, ReduceDesc* red) {
+    int32_t tile_tokens, int32_t n_waves, int32_t wpw, int32_t q_min, int32_t q_long, int32_t odd_xcd_weight,
+    int32_t late_wave_weight, StreamEntry* entries, WaveDesc* waves, ReduceDesc* red) {
   __shared__ int wave_tiles[STREAM_PLAN_THREADS / 64];
   __shared__ int wave_cnt[STREAM_PLAN_THREADS / 64];
+  __shared__ int wave_top[STREAM_PLAN_THREADS / 64];
   __shared__ int first_lds[STREAM_PLAN_LDS];
   __shared__ int wg_pos[STREAM_MAX_WG + 1];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int per = (n + STREAM_PLAN_THREADS - 1) / STREAM_PLAN_THREADS;
   const int r0 = min(tid * per, n), r1 = min(r0 + per, n);
-  int loc_tiles = 0, loc_cnt = 0;
+  int loc_tiles = 0, loc_cnt = 0, longest = 0;
   for (int r = r0; r < r1; ++r) {
-    const int len = max(lengths[r], 0);
-    loc_tiles += (len + tile_tokens - 1) / tile_tokens;
+    const int len = max(lengths[r], 0), tiles = (len + tile_tokens - 1) / tile_tokens;
+    loc_tiles += tiles;
     loc_cnt += len > 0;
+    longest = max(longest, tiles);
   }
   int inc_tiles = loc_tiles, inc_cnt = loc_cnt;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const int yt = __shfl_up(inc_tiles, o), yc = __shfl_up(inc_cnt, o);
+    longest = max(longest, __shfl_up(longest, o));           // (a lane below o gets its own)
     if (lane >= o) {
       inc_tiles += yt;
       inc_cnt += yc;
@@ -113,6 +116,7 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
   if (lane == 63) {
     wave_tiles[wv] = inc_tiles;
     wave_cnt[wv] = inc_cnt;
+    wave_top[wv] = longest;
   }
   __syncthreads();
   int base_tiles = 0, base_cnt = 0, sum_tiles = 0, n_entries = 0;
@@ -123,6 +127,7 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
     }
     sum_tiles += wave_tiles[i];
     n_entries += wave_cnt[i];
+    longest = max(longest, wave_top[i]);
   }
   int run_tiles = base_tiles + inc_tiles - loc_tiles, run_cnt = base_cnt + inc_cnt - loc_cnt;
   const bool use_lds = n <= STREAM_PLAN_LDS;
@@ -145,7 +150,8 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
   }
   const int total = sum_tiles * Hkv;
   // one contiguous tile range per wave (rule and weights: odma_plan::StreamShares)
-  const odma_plan::StreamShares shares = odma_plan::stream_shares(total, n_waves, wpw, q_min, odd_xcd_weight, late_wave_weight);
+  const odma_plan::StreamShares shares = odma_plan::stream_shares(
+      total, n_waves, wpw, odma_plan::stream_fewest(q_min, q_long, total, n_waves, wpw, longest), odd_xcd_weight, late_wave_weight);
   const int used = shares.used;
   auto pos_of = [&](int W) -> int { return shares.start(W); };
   const int n_wg = n_waves / wpw;
@@ -375,7 +381,8 @@ __device__ __forceinline__ InlineTotals plan_in_block(const StreamArgs& a, const
   InlineTotals t;
   t.total = sc.sum_tiles * a.Hkv;
   t.n_entries = sc.n_entries;
-  t.shares = odma_plan::stream_shares(t.total, n_wg * WPW, WPW, a.q_min, a.odd_xcd_weight, a.late_wave_weight);
+  t.shares = odma_plan::stream_shares(t.total, n_wg * WPW, WPW, odma_plan::stream_fewest(a.q_min, a.q_long, t.total, n_wg * WPW, WPW, sc.top),
+                                      a.odd_xcd_weight, a.late_wave_weight);
   t.whole = a.whole_extra >= 0 && sc.n_entries * a.Hkv <= n_wg &&
             (long long)sc.top * t.shares.used <= WPW * (t.total + (long long)a.whole_extra * t.shares.used);
   if (__builtin_expect(!t.shares.equal(), 0))                // (read behind the barrier in front of the tile stream)

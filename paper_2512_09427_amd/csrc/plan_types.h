@@ -105,6 +105,15 @@ struct StreamShares {
   }
 };
 
+// Fewest tiles of a wave, of the two numbers that the host allows.  The smaller one spreads a batch over more waves and cuts its
+// segments into more parts, which the last of their work-groups merges: it is for batches that leave a wave no more than 3.5 tiles
+// of their own, without a request of more than 64 parts.  1925 random batches of the wide formats under four tiles a wave, four -> two
+// by this rule: mean 0.913 of the time, two everywhere 0.915 with up to 1.45 beyond 64 parts (bf16, one request of 22 886 tokens, 8 / 1
+// heads of 96 channels 16.5 -> 23.1 us) and 0.97 to 1.02 beyond 3.5 tiles (fp32, three around 18 000, the same heads 24.3 -> 26.8).
+ODMA_HD inline int stream_fewest(int q_min, int q_long, int total, int n_waves, int wpw, int longest) {
+  return 2ll * total > 7ll * n_waves || longest > 64 * q_min * wpw ? q_long : q_min;
+}
+
 // Waves used: all of them unless that would leave less than q_min tiles per wave; a whole number of work-groups.
 ODMA_HD inline StreamShares stream_shares(int total, int n_waves, int wpw, int q_min, int odd_xcd_weight,
                                           int late_wave_weight) {

@@ -172,3 +172,21 @@ def test_cuts_of_many_parts(kvd, d, lens, wpw):
         H.check(got, H.oracle_out(w, q, kv), *tol, what=f"{kvd} {d} {hq}/{hkv}")
         for _ in range(2):                                   # whoever arrives last, the same bits
             np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
+
+
+@pytest.mark.parametrize("wpw", [4, 8])
+@pytest.mark.parametrize("lens", [[8192], [8193], [16384], [16385], [895] * 32, [897] * 32, [16] * 1030 + [8200], [16] * 200 + [8000]])
+@pytest.mark.parametrize("kvd,d", [("f32", 64), ("bf16", 96)])
+def test_fewest_tiles_where_the_rule_changes(kvd, d, lens, wpw):
+    """Longest requests of 64 parts and one tile more, shares of 3.5 tiles and a little more, planned in the launch and in front of it."""
+    lens = np.array(lens)
+    w = small_workload(lens, kv_dtype=kvd, hq=4, hkv=2, d=d, seed=d, bounds=(64, 1024, 16400), large_cap=16400, main=1 << 17)
+    dp = H.make_pool(w, out_dtype=B.F32)
+    dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_WG, wpw)
+    kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]
+    off, _ = H.assign_perfect(dp, lens)
+    H.fill(dp, 0, kv, offsets=off)
+    q = wl.queries(w, 0, sharp=True)
+    got = H.decode(dp, 0, q, lens, offsets=off)
+    H.check(got, H.oracle_out(w, q, kv), *TOL, what=f"{kvd} {d}")
+    np.testing.assert_array_equal(H.decode(dp, 0, q, lens, offsets=off, flags=B.REUSE_PLAN), got)
