@@ -1724,10 +1724,10 @@ decode_stream_kernel(StreamArgs a) {
   const int n_a = do_a ? rd_cut[0].n_parts : 0, n_b = do_b ? rd_cut[1].n_parts : 0;
   // partials whose loads are in flight together: the usual cut has two parts, a long request spans tens of work-groups; loads
   // past the last part would only repeat it, so the batch fits the count
-  auto merge = [&](auto cuts_tag, auto batch_tag, int which, int wave, int waves) {
+  auto merge = [&](auto cuts_tag, auto batch_tag, int which, int thread, int threads) {
     constexpr int CUTS = decltype(cuts_tag)::value, BATCH = decltype(batch_tag)::value;
     // thread -> (head, four channels)
-    for (int idx = 64 * wave + lane; idx < G * (CH / 4); idx += 64 * waves) {
+    for (int idx = thread; idx < G * (CH / 4); idx += threads) {
       const int h = idx / (CH / 4), d4 = idx - h * (CH / 4);
       float m_run[CUTS], l_run[CUTS];
       float4v acc[CUTS];
@@ -1833,25 +1833,25 @@ decode_stream_kernel(StreamArgs a) {
   // (One after the other, two cuts of a late work-group were two round trips: fp8, 64 requests 17.0 -> 16.2 us, 256 fused 115.8
   // -> 113.0 for four layers.  More than four parts of both cuts at once are slower again: 7 parts of one, 10.0 -> 10.6.)
   using std::integral_constant;
-  const int wave = rfl(wv);
+  const int t = threadIdx.x;
   if (do_a && do_b && max(n_a, n_b) <= 2) {                    // the usual two cuts: their loads travel together
-    merge(integral_constant<int, 2>{}, integral_constant<int, 2>{}, 0, wave, WPW);
+    merge(integral_constant<int, 2>{}, integral_constant<int, 2>{}, 0, t, 64 * WPW);
   } else if (do_a && do_b && max(n_a, n_b) <= 4) {
-    merge(integral_constant<int, 2>{}, integral_constant<int, 4>{}, 0, wave, WPW);
+    merge(integral_constant<int, 2>{}, integral_constant<int, 4>{}, 0, t, 64 * WPW);
   } else {
-    // Half of the waves for each of two cuts, where that is threads enough; otherwise all of them for one after the other.  (Of a
-    // few long requests the work-group between two is often the last of both: it has two pieces to store.)
-    const bool halves = do_a && do_b && G * (CH / 4) <= 32 * WPW;
-    const int half = halves ? wave / (WPW / 2) : 0, waves = halves ? WPW / 2 : WPW, mine = wave - half * (WPW / 2);
+    // Half of the waves for each of two cuts of many parts, where that is threads enough; otherwise all of them for one after the
+    // other.  (Of a few long requests the work-group between two is often the last of both: it has two pieces to store.)
+    const bool halves = min(n_a, n_b) > 8 && G * (CH / 4) <= 32 * WPW;
+    const int wave = rfl(wv), half = halves ? wave / (WPW / 2) : 0, waves = halves ? WPW / 2 : WPW, mine = wave - half * (WPW / 2);
 #pragma nounroll
     for (int which = half; which < (halves ? half + 1 : 2); ++which) {
       const int n = which == 0 ? n_a : n_b;
       if (n == 0) continue;
-      if (n <= 2) merge(integral_constant<int, 1>{}, integral_constant<int, 2>{}, which, mine, waves);
-      else if (n <= 4) merge(integral_constant<int, 1>{}, integral_constant<int, 4>{}, which, mine, waves);
-      else if (n <= 8) merge(integral_constant<int, 1>{}, integral_constant<int, 8>{}, which, mine, waves);
+      if (n <= 2) merge(integral_constant<int, 1>{}, integral_constant<int, 2>{}, which, t, 64 * WPW);
+      else if (n <= 4) merge(integral_constant<int, 1>{}, integral_constant<int, 4>{}, which, t, 64 * WPW);
+      else if (n <= 8) merge(integral_constant<int, 1>{}, integral_constant<int, 8>{}, which, t, 64 * WPW);
       else if constexpr (CH >= 64) merge_many(which, mine, waves);
-      else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which, mine, waves);
+      else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which, 64 * mine + lane, 64 * waves);
     }
   }
   tl_flush();
