@@ -61,7 +61,8 @@ struct StreamArgs {
   const int32_t* lengths;
   const int64_t* offsets;    // nullptr when paged
   int32_t plan_at;           // a launch that plans: float offset of the planning area in LDS
-  int32_t q_min, q_long, odd_xcd_weight, late_wave_weight;   // rule of the tile ranges (stream_fewest, StreamShares)
+  odma_plan::StreamFewest fewest;   // rule of the tile ranges, as the weights (StreamShares)
+  int32_t odd_xcd_weight, late_wave_weight;
   int32_t whole_extra;       // tiles beyond an equal share that a wave may get in order that no segment is cut (-1: never)
   unsigned long long* arrive;   // [n_workgroups + 1] arrival counters of the in-kernel merge (count_in)
   int32_t fuse_reduce;       // 1: the last work-group to finish a cut segment merges it; 0: stream_reduce_kernel does
@@ -86,7 +87,7 @@ constexpr int STREAM_PLAN_LDS = 8192;
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
     const int32_t* __restrict__ lengths, const int64_t* __restrict__ offsets, int32_t n, int32_t Hkv,
-    int32_t tile_tokens, int32_t n_waves, int32_t wpw, int32_t q_min, int32_t q_long, int32_t odd_xcd_weight,
+    int32_t tile_tokens, int32_t n_waves, int32_t wpw, odma_plan::StreamFewest fewest, int32_t odd_xcd_weight,
     int32_t late_wave_weight, StreamEntry* entries, WaveDesc* waves, ReduceDesc* red) {
   __shared__ int wave_tiles[STREAM_PLAN_THREADS / 64];
   __shared__ int wave_cnt[STREAM_PLAN_THREADS / 64];
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(STREAM_PLAN_THREADS) void stream_plan_kernel(
   const int total = sum_tiles * Hkv;
   // one contiguous tile range per wave (rule and weights: odma_plan::StreamShares)
   const odma_plan::StreamShares shares = odma_plan::stream_shares(
-      total, n_waves, wpw, odma_plan::stream_fewest(q_min, q_long, total, n_waves, wpw, longest), odd_xcd_weight, late_wave_weight);
+      total, n_waves, wpw, fewest.of(total, longest, n_entries * Hkv, n_waves, wpw), odd_xcd_weight, late_wave_weight);
   const int used = shares.used;
   auto pos_of = [&](int W) -> int { return shares.start(W); };
   const int n_wg = n_waves / wpw;
@@ -372,7 +373,8 @@ __device__ __forceinline__ InlineScan scan_batch(const StreamArgs& a, const Inli
   return sc;
 }
 
-template <int WPW, int TT>
+// CHOICE: formats with two numbers for the fewest tiles of a wave
+template <int WPW, int TT, bool CHOICE>
 __device__ __forceinline__ InlineTotals plan_in_block(const StreamArgs& a, const InlinePlan& pl) {
   constexpr int T = 64 * WPW;
   const int n_wg = gridDim.x;
@@ -381,8 +383,8 @@ __device__ __forceinline__ InlineTotals plan_in_block(const StreamArgs& a, const
   InlineTotals t;
   t.total = sc.sum_tiles * a.Hkv;
   t.n_entries = sc.n_entries;
-  t.shares = odma_plan::stream_shares(t.total, n_wg * WPW, WPW, odma_plan::stream_fewest(a.q_min, a.q_long, t.total, n_wg * WPW, WPW, sc.top),
-                                      a.odd_xcd_weight, a.late_wave_weight);
+  const int fewest = CHOICE ? a.fewest.of(t.total, sc.top, sc.n_entries * a.Hkv, n_wg * WPW, WPW) : a.fewest.q_long;
+  t.shares = odma_plan::stream_shares(t.total, n_wg * WPW, WPW, fewest, a.odd_xcd_weight, a.late_wave_weight);
   t.whole = a.whole_extra >= 0 && sc.n_entries * a.Hkv <= n_wg &&
             (long long)sc.top * t.shares.used <= WPW * (t.total + (long long)a.whole_extra * t.shares.used);
   if (__builtin_expect(!t.shares.equal(), 0))                // (read behind the barrier in front of the tile stream)
@@ -622,7 +624,7 @@ decode_stream_kernel(StreamArgs a) {
   // epilogue does not wait for them (a launch that plans derives them under its first tiles' loads)
   ReduceDesc rd_cut[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   if constexpr (PLAN) {
-    totals = plan_in_block<WPW, TT>(a, pl);
+    totals = plan_in_block<WPW, TT, WIDE && (HD > 32)>(a, pl);
     wd = inline_wave_desc<WPW>(a, pl, totals);
   } else {
     wd = a.waves[blockIdx.x * WPW + rfl(wv)];

@@ -304,15 +304,16 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     const int tile_tokens = f.blocks * BLK;
     // A plan bakes in the slab bases and the launch shape, so ODMA_REUSE_PLAN is honoured only while the library
     // knows of nothing that changed them; otherwise the call plans again.
-    // Fewest tiles of a wave (q_long: for batches of many or long pieces, stream_fewest).  A bf16 or fp8 tile of 128 or 64 channels takes a lone wave about as long as one more part
+    // Fewest tiles of a wave.  A bf16 or fp8 tile of 128 or 64 channels takes a lone wave about as long as one more part
     // takes a merge of up to eight; four tiles a wave keep most merges there (two: six requests around 4 000 tokens in fp8
     // 15.0 -> 17.1 us, two around 1 000 in bf16 10.4 -> 12.5).  A tile of the wide formats has up to four times the matrix
-    // and vector instructions, and two is the better number where the two rules differ: one fp32 request of 512, 1 024 and
+    // and vector instructions, and two is the better number for small batches (StreamFewest): one fp32 request of 512, 1 024 and
     // 2 048 tokens 18.0 -> 11.6, 14.8 -> 12.0 and 15.3 -> 13.1 us, thirty bf16 requests around 300 with head_dim 96 and 256
     // 10.7 -> 10.3 and 17.0 -> 15.7 (one tile: one fp32 request of 2 048 13.9).  With 32 channels the tile is a small one
     // again (two tiles: six requests around 4 000 tokens in fp32 12.2 -> 14.2, in bf16 11.1 -> 12.7).
-    const int q_min = pool->min_chunk ? (pool->min_chunk + tile_tokens - 1) / tile_tokens : wide && c.head_dim > 32 ? 2 : 4;
-    const int q_long = pool->min_chunk ? q_min : 4;
+    const int q_long = pool->min_chunk ? (pool->min_chunk + tile_tokens - 1) / tile_tokens : 4;
+    const int q_short = !pool->min_chunk && wide && c.head_dim > 32 ? 2 : q_long;   // (the kernels' CHOICE)
+    a.fewest = odma_plan::stream_fewest(q_short, q_long, n_wg * wpw, wpw, odma_plan::stream_few_parts(pool->elem_bytes == 4, c.head_dim, G));
     odma_pool::PlanStamp now;
     now.layout_gen = pool->layout_gen;
     now.owner = pool->serial;
@@ -320,21 +321,19 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
     now.paged = block_table ? 1 : 0;
     now.n_wg = n_wg;
     now.wpw = wpw;
-    now.q_min = q_min;
+    now.q_short = q_short;
     now.q_long = q_long;
     now.tile_tokens = tile_tokens;
     now.odd_w = pool->odd_xcd_weight;
     now.late_w = wpw == 8 ? pool->late_wave_weight : 256;
     const odma_pool::PlanStamp& was = stamp;
     const bool reuse = (flags & ODMA_REUSE_PLAN) && was.layout_gen == now.layout_gen && was.owner == now.owner && was.n == now.n &&
-                       was.paged == now.paged && was.n_wg == now.n_wg && was.wpw == now.wpw && was.q_min == now.q_min && was.q_long == now.q_long &&
-                       was.tile_tokens == now.tile_tokens && was.odd_w == now.odd_w && was.late_w == now.late_w;
+                       was.paged == now.paged && was.n_wg == now.n_wg && was.wpw == now.wpw && was.q_short == now.q_short &&
+                       was.q_long == now.q_long && was.tile_tokens == now.tile_tokens && was.odd_w == now.odd_w && was.late_w == now.late_w;
     // A call that plans does so inside the attention launch while the batch's table is small (STREAM_INLINE_REQ) and
     // fits beside the wave's queues; larger batches take a planning launch of their own.
     size_t lds_bytes = stream_lds_bytes(G, f.ch, f.np, wpw, qs, aq);
     a.plan_at = -1;
-    a.q_min = q_min;
-    a.q_long = q_long;
     a.whole_extra = pool->min_chunk ? -1 : STREAM_MERGE_TILES;   // (a pool with a tuned minimum keeps equal shares)
     a.odd_xcd_weight = now.odd_w;
     a.late_wave_weight = now.late_w;
@@ -345,7 +344,7 @@ int decode_impl(const char* where, odma_pool_t* pool, int32_t layer, int32_t n, 
         lds_bytes += plan_bytes;
       } else {
         hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(STREAM_PLAN_THREADS), 0, s, lengths, a.offsets, n, c.n_kv_heads,
-                           tile_tokens, n_wg * wpw, wpw, q_min, q_long, now.odd_w, now.late_w, a.entries, a.waves, a.red);
+                           tile_tokens, n_wg * wpw, wpw, a.fewest, now.odd_w, now.late_w, a.entries, a.waves, a.red);
       }
       // no plan until the launch that writes it has been accepted: a failed call must not leave one to reuse
       stamp = odma_pool::PlanStamp();

@@ -133,7 +133,7 @@ struct odma_pool {
   uint64_t layout_gen = 1;
   struct PlanStamp {
     uint64_t layout_gen = 0;               // 0: no plan yet
-    int32_t n = -1, paged = -1, n_wg = 0, wpw = 0, q_min = 0, q_long = 0, tile_tokens = 0, odd_w = 0, late_w = 0;
+    int32_t n = -1, paged = -1, n_wg = 0, wpw = 0, q_short = 0, q_long = 0, tile_tokens = 0, odd_w = 0, late_w = 0;
     uint64_t owner = 0;                    // serial of the pool that planned (the static scratch serves every pool)
   } plan_stamp;
   uint64_t serial = 0;                     // unique per pool ever created in this process

@@ -105,13 +105,34 @@ struct StreamShares {
   }
 };
 
-// Fewest tiles of a wave, of the two numbers that the host allows.  The smaller one spreads a batch over more waves and cuts its
-// segments into more parts, which the last of their work-groups merges: it is for batches that leave a wave no more than 3.5 tiles
-// of their own, without a request of more than 64 parts.  1925 random batches of the wide formats under four tiles a wave, four -> two
-// by this rule: mean 0.913 of the time, two everywhere 0.915 with up to 1.45 beyond 64 parts (bf16, one request of 22 886 tokens, 8 / 1
-// heads of 96 channels 16.5 -> 23.1 us) and 0.97 to 1.02 beyond 3.5 tiles (fp32, three around 18 000, the same heads 24.3 -> 26.8).
-ODMA_HD inline int stream_fewest(int q_min, int q_long, int total, int n_waves, int wpw, int longest) {
-  return 2ll * total > 7ll * n_waves || longest > 64 * q_min * wpw ? q_long : q_min;
+// Fewest tiles of a wave: q_short or q_long.  The smaller number spreads a batch over more waves and cuts its segments into more parts,
+// which the last of their work-groups merges.  It is for batches that leave a wave no more than three tiles of their own and whose
+// longest request has few parts.  Requests of one length that fill whole waves of q_long tiles and no more than one work-group
+// stay there: no segment is cut through memory then, and shares of two to three tiles would cut most of them.
+struct StreamFewest {
+  int q_short, q_long;              // the same: nothing to choose
+  int most_tiles, most_longest;     // of the batch and of its longest request
+  // (A launch that plans computes this in front of its first tile, where an instruction costs 2 ns: no division.  q_long * wpw is a
+  // power of two where there is a choice.)
+  ODMA_HD int of(int total, int longest, int segments, int n_waves, int wpw) const {
+    if (q_short == q_long || total > most_tiles || longest > most_longest) return q_long;
+    const int whole = q_long * wpw;
+    const bool even = longest > 1 && longest <= whole && (longest & (longest - 1)) == 0 && (total & (whole - 1)) == 0 &&
+                      longest * segments == total && total > q_short * n_waves;
+    return even ? q_long : q_short;
+  }
+};
+// The parts of a longest request that two tiles a wave still pay for.  fp32, whose tiles are the dearer ones: 64, with few channels less.
+// bf16: 24, and fewer where a merge is more than a turn of a work-group's threads (four channels each).  Of 3 577 random batches of
+// few tiles a wave and at most 64 parts, twos against fours, the mean of a planning call and of one that reuses the plan: bf16 0.964 of
+// the time, 25 of 1 482 above 1.04 (two always: 0.966 and 80, up to 1.33); fp32 0.918, 16 of 2 095 above 1.04 (0.918 and 27).
+ODMA_HD inline int stream_few_parts(bool f32, int head_dim, int G) {
+  if (f32) return head_dim < 128 ? 32 + head_dim / 4 : 64;
+  return G * head_dim > 1024 ? 24 * 1024 / (G * head_dim) : 24;
+}
+ODMA_HD inline StreamFewest stream_fewest(int q_short, int q_long, int n_waves, int wpw, int parts) {
+  if (q_short == q_long) return StreamFewest{q_short, q_long, 0, 0};
+  return StreamFewest{q_short, q_long, 3 * n_waves, parts * q_short * wpw};
 }
 
 // Waves used: all of them unless that would leave less than q_min tiles per wave; a whole number of work-groups.

@@ -175,12 +175,15 @@ def test_cuts_of_many_parts(kvd, d, lens, wpw):
 
 
 @pytest.mark.parametrize("wpw", [4, 8])
-@pytest.mark.parametrize("lens", [[8192], [8193], [16384], [16385], [895] * 32, [897] * 32, [16] * 1030 + [8200], [16] * 200 + [8000]])
+@pytest.mark.parametrize("lens", [[8192], [8193], [16384], [16385], [895] * 32, [897] * 32, [16] * 1030 + [8200], [16] * 200 + [8000],
+                                  [3072], [3073], [6144], [6145], [768] * 32, [769] * 32, [16] * 1030 + [3100], [64] * 300, [63] * 300, [128] * 140, [64] * 301,
+                                  [32] * 560, [256] * 72, [32] * 1040])
 @pytest.mark.parametrize("kvd,d", [("f32", 64), ("bf16", 96)])
 def test_fewest_tiles_where_the_rule_changes(kvd, d, lens, wpw):
-    """Longest requests of 64 parts and one tile more, shares of 3.5 tiles and a little more, planned in the launch and in front of it."""
+    """Longest requests of 24, 48 and 64 parts and one tile more, shares of 3 and 3.5 tiles and a little more, requests of one length
+    that fill waves of four tiles or do not, planned in the launch and in front of it."""
     lens = np.array(lens)
-    w = small_workload(lens, kv_dtype=kvd, hq=4, hkv=2, d=d, seed=d, bounds=(64, 1024, 16400), large_cap=16400, main=1 << 17)
+    w = small_workload(lens, kv_dtype=kvd, hq=4, hkv=2, d=d, seed=d, bounds=(64, 1024, 16400), large_cap=16400, main=1 << 18)
     dp = H.make_pool(w, out_dtype=B.F32)
     dp.pool.odma_pool_tune(B.TUNE_WAVES_PER_WG, wpw)
     kv = [wl.request_kv(w, 0, r, sharp=True) for r in range(len(lens))]

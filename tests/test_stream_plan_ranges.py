@@ -126,3 +126,64 @@ def test_the_wave_that_holds_a_tile(tmp_path):
     subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True, timeout=120)
     r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+FEWEST = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "plan_types.h"
+int bad = 0;
+void check(bool ok, const char* what, int wpw, int n_waves, int total, int longest, int segments, int got) {
+  if (ok) return;
+  std::printf("%s: wpw %d n_waves %d total %d longest %d segments %d: %d\n", what, wpw, n_waves, total, longest, segments, got);
+  ++bad;
+}
+int main() {
+  const int big = 0x7fffffff;
+  for (int wpw : {4, 8})
+    for (int n_waves : {3 * wpw, 1024, 4096}) {
+      // a tuned minimum, up to 2^31 - 64 tokens: nothing to choose, nothing to overflow
+      for (int q : {1, 4, big / 64 * 4})
+        for (int total : {0, 1, n_waves, big})
+          for (int longest : {0, 1, total}) {
+            const int got = odma_plan::stream_fewest(q, q, n_waves, wpw, 32).of(total, longest, 1, n_waves, wpw);
+            check(got == q, "tuned", wpw, n_waves, total, longest, 1, got);
+          }
+      for (int d : {32, 64, 96, 128, 256})
+        for (int G : {1, 5, 16}) {
+          const int parts = odma_plan::stream_few_parts(d == 64, d, G);
+          const auto f = odma_plan::stream_fewest(2, 4, n_waves, wpw, parts);
+          check(parts >= 6 && parts <= 64, "parts", wpw, n_waves, d, G, 0, parts);
+          // both lines, with segments of other lengths beside the longest one
+          const int line = 3 * n_waves, most = parts * 2 * wpw;
+          for (int total : {0, 1, line - 1, line, line + 1, big})
+            for (int longest : {0, 1, 7, most - 1, most, most + 1, big}) {
+              const int got = f.of(total, longest, 3, n_waves, wpw);
+              if ((long long)longest * 3 == total) continue;
+              check(got == (total > line || longest > most ? 4 : 2), "line", wpw, n_waves, total, longest, 3, got);
+            }
+          // segments of one length: four tiles where two would be cut to fractions and four end with the segments
+          for (int longest = 1; longest <= 4 * wpw + 1; ++longest)
+            for (int segments = 1; segments * longest <= line && segments < 5000; ++segments) {
+              const int total = segments * longest, got = f.of(total, longest, segments, n_waves, wpw);
+              const auto s = odma_plan::stream_shares(total, n_waves, wpw, 4, 256, 256);
+              bool uncut = total > 2 * n_waves && longest > 1;         // no segment reaches over a work-group's end, shares are whole
+              for (int w = 0; w < s.used && uncut; ++w) uncut = s.start(w + 1) - s.start(w) == 4 && (w % wpw || s.start(w) % longest == 0);
+              check(got == (uncut ? 4 : 2), "even", wpw, n_waves, total, longest, segments, got);
+            }
+        }
+    }
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_the_fewest_tiles_of_a_wave(tmp_path):
+    """StreamFewest on both sides of its lines and for segments of one length, without overflow at the largest tuned minimum."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_09427_amd", "csrc")
+    (tmp_path / "t.cpp").write_text(FEWEST)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", csrc, str(tmp_path / "t.cpp"),
+                    "-o", str(tmp_path / "t")], check=True, timeout=120)
+    r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-2000:]
