@@ -486,8 +486,8 @@ __device__ __forceinline__ void store_inline_plan(const StreamArgs& a, const Inl
 // ---------------------------------------------------------------------------------
 
 // LDS per work-group: one hand-off slot per wave (O[G][128], m[G], l[G], padded; slot 0 unused),
-// how the parked piece ends per wave (as many ints again unused), then per wave a queue of finished pieces waiting to be written to
-// global memory (qs entries of slot + 8 ints) and of appended rows (aq records of STREAM_AQ_INTS).  The host sizes
+// an int per wave that says how its parked piece ends (four or eight of them: what follows is 16-byte aligned), then per wave a
+// queue of finished pieces waiting to be written to global memory (qs entries of slot + 8 ints) and of appended rows (aq records of STREAM_AQ_INTS).  The host sizes
 // the queues to the tiles a wave gets: a wave that runs out of queue has to write in mid-stream.
 constexpr int STREAM_MERGE_BATCH = 16;   // most partials whose loads are in flight together in the in-kernel merge
 // (ch: channels a state keeps per head; np: 1 KiB pieces of a K block)
@@ -498,7 +498,7 @@ __host__ __device__ inline int stream_wave_queue_floats(int G, int ch, int np, i
   return qs * (stream_slot_floats(G, ch) + 8) + aq * stream_aq_ints(np);
 }
 __host__ inline size_t stream_lds_bytes(int G, int ch, int np, int wpw, int qs, int aq) {
-  return ((size_t)wpw * stream_slot_floats(G, ch) + 2 * wpw + (size_t)wpw * stream_wave_queue_floats(G, ch, np, qs, aq)) * 4;
+  return ((size_t)wpw * stream_slot_floats(G, ch) + wpw + (size_t)wpw * stream_wave_queue_floats(G, ch, np, qs, aq)) * 4;
 }
 
 // Maximum over the four lanes that hold one column (lanes l, l ^ 16, l ^ 32, l ^ 48), in every one of them: two
@@ -888,7 +888,7 @@ decode_stream_kernel(StreamArgs a) {
     // 256-byte runs).  The neighbours' bytes go back unchanged; slots past the end may get stale
     // bytes again, as before.  fp8 storage: the same with the 2 KiB block that holds the token (two
     // 1 KiB pieces of K and of V instead of four).
-    int* abase = (int*)(lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq) +
+    int* abase = (int*)(lds + WPW * slot_floats + WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq) +
                         a.qs * (slot_floats + 8));
     constexpr int REC_V = 8 + 32 * NP;                       // where a record's V pieces begin
     int an = 0;
@@ -1406,7 +1406,7 @@ decode_stream_kernel(StreamArgs a) {
     // vmcnt queue with the tile loads, and a store in the middle of the stream makes the next
     // tile wait for the store's acknowledgement.  They are queued in LDS (a separate counter)
     // and written when the wave has streamed its whole range (or when the queue is full).
-    float* qbase = lds + WPW * slot_floats + 2 * WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq);
+    float* qbase = lds + WPW * slot_floats + WPW + wv * stream_wave_queue_floats(G, CH, NP, a.qs, a.aq);
     const int qstride = slot_floats + 8;
     int qn = 0;
     // A state in LDS: O[G][CH], m[G], l[G].  The 16-byte pieces of a head's row are permuted in groups of eight by the head, so that
