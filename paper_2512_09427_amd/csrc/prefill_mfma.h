@@ -309,9 +309,10 @@ __global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(Pr
   const int col16 = lane & 15, g4 = lane >> 4;
   const int G = a.G;
   const float NEG_INF = -INFINITY;
-  // loader role of this wave: waves 0, 1 bring the K tiles of a pair, waves 2, 3 the V tiles
+  // Loader role of this wave, whose tile of a pair is the first or the second one.  Four waves: 0 and 1 bring its K, 2 and 3 its V
+  // (loads_v and src_base, issue and write_stage are theirs).  Eight: each brings a quarter of both (stream_eight).
   const bool loads_v = wv >= 2;
-  const int which = EIGHT ? wv >> 2 : wv & 1;                             // first or second tile of the pair
+  const int which = EIGHT ? wv >> 2 : wv & 1;
   const char* src_base = loads_v ? a.v : a.k;
   const unsigned lane16 = lane * 16;
 
@@ -538,7 +539,7 @@ __global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(Pr
 
     const int64_t plane = (int64_t)g * a.head_stride + (PAGED ? 0 : (int64_t)skipped * TILE_BYTES);
     const const_i32* bt_row = as_constant(PAGED ? a.bt + (int64_t)r * a.bt_stride + skipped : nullptr);
-    // ---- loading: this wave's tile of pair pr -> four 16-byte pieces per lane in registers -> LDS.  Pairs past the
+    // ---- loading: this wave's tile of pair pr -> registers, 16 bytes per lane and piece -> LDS.  Pairs past the
     // end and a second tile that does not exist re-read the last tile: every step issues its loads, so the waits on
     // them stay static counts (with conditional loads the wait before a stage was written covered the loads issued a
     // moment ago as well, and the whole memory latency was exposed in every pair).  V slots at or past `len` (stale bytes,
@@ -552,76 +553,6 @@ __global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(Pr
     int blk_next = 0;
     auto lookup = [&](int pr) {
       if (PAGED) blk_next = bt_row[tile_of(pr)];
-    };
-    auto issue = [&](uint4v (&rg)[LOADS], int pr) {
-      const char* src = src_base + plane + (PAGED ? (int64_t)blk_next : base_block + tile_of(pr)) * TILE_BYTES;
-#pragma unroll
-      for (int s = 0; s < LOADS; ++s) rg[s] = *(const uint4v*)(src + s * 1024 + lane16);
-    };
-    auto write_stage = [&](uint4v (&rg)[LOADS], int pr) {
-      char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES;
-      const int t = tile_of(pr);
-      if (FP8) {
-        if (!loads_v) {
-          // lane (t16, q) holds, per 64-channel half s, channels 64 s + 8 q .. +7 and 64 s + 32 + 8 q .. +7 of
-          // token t16: two bf16 pieces, for channel octets 8 s + q and 8 s + 4 + q
-#pragma unroll
-          for (int i = 0; i < LOADS; ++i) {
-            const uint4v w = rg[i];
-            const int s = i;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const uint4v o = {fp8x2_to_bf16x2<false>(w[2 * h]), fp8x2_to_bf16x2<true>(w[2 * h]),
-                                fp8x2_to_bf16x2<false>(w[2 * h + 1]), fp8x2_to_bf16x2<true>(w[2 * h + 1])};
-              *(uint4v*)(st + which * 4096 + (((8 * s + 4 * h + g4) * 16 + col16) * 16)) = o;
-            }
-          }
-        } else {
-          // lane (c, q) holds, per half s, one word per channel group 4 s + i: channel c of tokens 4q .. 4q+3
-          const int tok0 = t * BLK + 4 * g4;
-          const bool ragged = t * BLK + BLK > held;                      // (the same for the whole wave)
-#pragma unroll
-          for (int j = 0; j < LOADS; ++j) {
-            const uint4v w = rg[j];
-            const int s = j;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              uint2v o = {fp8x2_to_bf16x2<false>(w[i]), fp8x2_to_bf16x2<true>(w[i])};
-              if (ragged) {                                             // some of the tile's tokens are not there
-                if (tok0 + 0 >= held) o[0] &= 0xffff0000u;
-                if (tok0 + 1 >= held) o[0] &= 0x0000ffffu;
-                if (tok0 + 2 >= held) o[1] &= 0xffff0000u;
-                if (tok0 + 3 >= held) o[1] &= 0x0000ffffu;
-              }
-              *(uint2v*)(st + 8192 + (4 * s + i) * 1024 + lane * 16 + which * 8) = o;
-            }
-          }
-        }
-      } else if (!loads_v) {
-#pragma unroll
-        for (int s = 0; s < LOADS; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
-      } else {
-        // lane (c, q) holds, per piece s, tokens 4q .. 4q+3 of channel groups 2s (low 8 bytes) and 2s+1
-        if (t * BLK + BLK > held) {                                      // some of the tile's tokens are not there
-          const int tok0 = t * BLK + 4 * g4;
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (tok0 + i >= held) {
-              const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
-#pragma unroll
-              for (int s = 0; s < LOADS; ++s) {
-                rg[s][i >> 1] &= keep;
-                rg[s][2 + (i >> 1)] &= keep;
-              }
-            }
-        }
-        char* dst = st + 8192 + lane * 16 + which * 8;
-#pragma unroll
-        for (int s = 0; s < LOADS; ++s) {
-          *(uint2v*)(dst + (2 * s) * 1024) = uint2v{rg[s][0], rg[s][1]};
-          *(uint2v*)(dst + (2 * s + 1) * 1024) = uint2v{rg[s][2], rg[s][3]};
-        }
-      }
     };
 
     // One pair of tiles against the wave's 64 columns.  Scores: S^T = K Q^T per tile (16x16x32 over
@@ -829,6 +760,76 @@ __global__ __launch_bounds__(64 * WAVES, CT == 4 ? 1 : 2) void prefill_kernel(Pr
     // registers until the computation of pair p is over, is written into the other stage, and one
     // work-group barrier per pair makes it visible (and tells that the stage of pair p is free again).
     auto stream = [&]() {
+      auto issue = [&](uint4v (&rg)[LOADS], int pr) {
+        const char* src = src_base + plane + (PAGED ? (int64_t)blk_next : base_block + tile_of(pr)) * TILE_BYTES;
+#pragma unroll
+        for (int s = 0; s < LOADS; ++s) rg[s] = *(const uint4v*)(src + s * 1024 + lane16);
+      };
+      auto write_stage = [&](uint4v (&rg)[LOADS], int pr) {
+        char* st = stage_mem + (pr % STAGES) * PREFILL_STAGE_BYTES;
+        const int t = tile_of(pr);
+        if (FP8) {
+          if (!loads_v) {
+            // lane (t16, q) holds, per 64-channel half s, channels 64 s + 8 q .. +7 and 64 s + 32 + 8 q .. +7 of
+            // token t16: two bf16 pieces, for channel octets 8 s + q and 8 s + 4 + q
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+              const uint4v w = rg[i];
+              const int s = i;
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const uint4v o = {fp8x2_to_bf16x2<false>(w[2 * h]), fp8x2_to_bf16x2<true>(w[2 * h]),
+                                  fp8x2_to_bf16x2<false>(w[2 * h + 1]), fp8x2_to_bf16x2<true>(w[2 * h + 1])};
+                *(uint4v*)(st + which * 4096 + (((8 * s + 4 * h + g4) * 16 + col16) * 16)) = o;
+              }
+            }
+          } else {
+            // lane (c, q) holds, per half s, one word per channel group 4 s + i: channel c of tokens 4q .. 4q+3
+            const int tok0 = t * BLK + 4 * g4;
+            const bool ragged = t * BLK + BLK > held;                      // (the same for the whole wave)
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j) {
+              const uint4v w = rg[j];
+              const int s = j;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                uint2v o = {fp8x2_to_bf16x2<false>(w[i]), fp8x2_to_bf16x2<true>(w[i])};
+                if (ragged) {                                             // some of the tile's tokens are not there
+                  if (tok0 + 0 >= held) o[0] &= 0xffff0000u;
+                  if (tok0 + 1 >= held) o[0] &= 0x0000ffffu;
+                  if (tok0 + 2 >= held) o[1] &= 0xffff0000u;
+                  if (tok0 + 3 >= held) o[1] &= 0x0000ffffu;
+                }
+                *(uint2v*)(st + 8192 + (4 * s + i) * 1024 + lane * 16 + which * 8) = o;
+              }
+            }
+          }
+        } else if (!loads_v) {
+#pragma unroll
+          for (int s = 0; s < LOADS; ++s) *(uint4v*)(st + which * 4096 + s * 1024 + lane * 16) = rg[s];
+        } else {
+          // lane (c, q) holds, per piece s, tokens 4q .. 4q+3 of channel groups 2s (low 8 bytes) and 2s+1
+          if (t * BLK + BLK > held) {                                      // some of the tile's tokens are not there
+            const int tok0 = t * BLK + 4 * g4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (tok0 + i >= held) {
+                const unsigned keep = (i & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+                for (int s = 0; s < LOADS; ++s) {
+                  rg[s][i >> 1] &= keep;
+                  rg[s][2 + (i >> 1)] &= keep;
+                }
+              }
+          }
+          char* dst = st + 8192 + lane * 16 + which * 8;
+#pragma unroll
+          for (int s = 0; s < LOADS; ++s) {
+            *(uint2v*)(dst + (2 * s) * 1024) = uint2v{rg[s][0], rg[s][1]};
+            *(uint2v*)(dst + (2 * s + 1) * 1024) = uint2v{rg[s][2], rg[s][3]};
+          }
+        }
+      };
       uint4v ra[LOADS], rb[LOADS];
       lookup(0);
       issue(ra, 0);
