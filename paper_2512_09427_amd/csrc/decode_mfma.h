@@ -1841,19 +1841,23 @@ decode_stream_kernel(StreamArgs a) {
   } else if (do_a && do_b && max(n_a, n_b) <= 4) {
     merge(integral_constant<int, 2>{}, integral_constant<int, 4>{}, 0, t, 64 * WPW);
   } else {
-    // Half of the waves for each of two cuts of many parts, where that is threads enough; otherwise all of them for one after the
-    // other.  (Of a few long requests the work-group between two is often the last of both: it has two pieces to store.)
-    const bool halves = min(n_a, n_b) > 8 && G * (CH / 4) <= 32 * WPW;
-    const int wave = rfl(wv), half = halves ? wave / (WPW / 2) : 0, waves = halves ? WPW / 2 : WPW, mine = wave - half * (WPW / 2);
 #pragma nounroll
-    for (int which = half; which < (halves ? half + 1 : 2); ++which) {
+    for (int which = 0; which < 2; ++which) {
       const int n = which == 0 ? n_a : n_b;
       if (n == 0) continue;
       if (n <= 2) merge(integral_constant<int, 1>{}, integral_constant<int, 2>{}, which, t, 64 * WPW);
       else if (n <= 4) merge(integral_constant<int, 1>{}, integral_constant<int, 4>{}, which, t, 64 * WPW);
       else if (n <= 8) merge(integral_constant<int, 1>{}, integral_constant<int, 8>{}, which, t, 64 * WPW);
-      else if constexpr (CH >= 64) merge_many(which, mine, waves);
-      else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which, 64 * mine + lane, 64 * waves);
+      else {
+        // Two cuts of many parts, and half of the waves are threads enough: one half for each.  (Of a few long requests the work-group
+        // between two is often the last of both: it has two pieces to store.  Decided here: a number of waves that is a variable in
+        // front of the short merges costs every one of them 0.1 us, and so does a second copy of the long one.)
+        const bool halves = min(n_a, n_b) > 8 && G * (CH / 4) <= 32 * WPW;
+        const int waves = halves ? WPW / 2 : WPW, mine = rfl(wv) & (waves - 1);
+        if (halves && rfl(wv) / (WPW / 2) != which) continue;
+        if constexpr (CH >= 64) merge_many(which, mine, waves);
+        else merge(integral_constant<int, 1>{}, integral_constant<int, STREAM_MERGE_BATCH>{}, which, 64 * mine + lane, 64 * waves);
+      }
     }
   }
   tl_flush();
